@@ -401,18 +401,33 @@ int run_rows(flover_ctx* c, Lane& ln, const Row* rows, int n, bool want_tokens, 
                ss_v = (size_t)n * c->p_lm.ldc;
   HIPCHK(c, flk::embed(f.dtype, c->wte, c->wpe, d_tok, d_pos, ln.tok_out, ln.x, n, H, st));
   ++launches;
+  bool added = true;      // the residual stream already holds what the GEMM before the norm computed (or there was none)
   for (int l = 0; l < L; ++l) {
     const LayerW& w = c->lw[l];
-    const bool first = l == 0;
-    HIPCHK(c, flk::add_norm(f.dtype, !gpt, ln.x, first ? nullptr : ln.part, p_2.S, ss_h, p_2.ldc,
-                            first ? nullptr : c->lw[l - 1].b2,
+    HIPCHK(c, flk::add_norm(f.dtype, !gpt, ln.x, added ? nullptr : ln.part, p_2.S, ss_h, p_2.ldc,
+                            added ? nullptr : c->lw[l - 1].b2,
                             w.ln1_g, w.ln1_b, ln.h, n, H, f.norm_eps, mtt, st));
     char* kl = c->kv + (size_t)(2 * l) * c->plane_bytes;
     char* vl = kl + c->plane_bytes;
     const bool gs = gemm_iter && l == L / 2;
-    HIPCHK(c, timed_gemm(c, ln, FLOVER_PROF_GEMM_QKV, ln.h, w.wqkv, n, p_qkv, ss_qkv, mtt, gs));
-    HIPCHK(c, flk::qkv_post(f.dtype, ln.part, p_qkv.S, ss_qkv, p_qkv.ldc, w.bqkv, c->rope_cs, d_slot, d_pos, ln.q, kl, vl, n, H, nh,
-                            d, f.max_seq, st));
+    hipError_t err = hipSuccess;
+    flk::TileOut qo;
+    qo.bias = w.bqkv;
+    qo.rope = c->rope_cs;
+    qo.pos = d_pos;
+    qo.slot = d_slot;
+    qo.q = ln.q;
+    qo.kc = kl;
+    qo.vc = vl;
+    qo.d = d;
+    qo.Smax = f.max_seq;
+    if (context_pass && flk::context_qkv(f.dtype, ln.h, w.wqkv, n, p_qkv, qo, mtt, st, &err)) {
+      HIPCHK(c, err);
+    } else {
+      HIPCHK(c, timed_gemm(c, ln, FLOVER_PROF_GEMM_QKV, ln.h, w.wqkv, n, p_qkv, ss_qkv, mtt, gs));
+      HIPCHK(c, flk::qkv_post(f.dtype, ln.part, p_qkv.S, ss_qkv, p_qkv.ldc, w.bqkv, c->rope_cs, d_slot, d_pos, ln.q, kl, vl, n, H, nh,
+                              d, f.max_seq, st));
+    }
     if (context_pass && l == L - 1) {
       launches += 3;
       break;   // the pass exists to fill the cache: the last layer's K and V rows are written, nothing reads the rest
@@ -426,17 +441,24 @@ int run_rows(flover_ctx* c, Lane& ln, const Row* rows, int n, bool want_tokens, 
       HIPCHK(c, flk::decode_attention(f.dtype, d, ln.q, kl, vl, aw, n, nh, f.max_seq, ln.att, st,
                                       pi >= 0 ? c->ev[2 * pi] : nullptr, pi >= 0 ? c->ev[2 * pi + 1] : nullptr));
     }
-    HIPCHK(c, timed_gemm(c, ln, FLOVER_PROF_GEMM_OUT, ln.att, w.wo, n, p_o, ss_h, mtt, gs));
-    HIPCHK(c, flk::add_norm(f.dtype, !gpt, ln.x, ln.part, p_o.S, ss_h, p_o.ldc, w.bo, w.ln2_g, w.ln2_b, ln.h, n, H, f.norm_eps, mtt, st));
+    added = context_pass && flk::context_add(f.dtype, ln.att, w.wo, n, p_o, ln.x, w.bo, mtt, st, &err);
+    HIPCHK(c, err);
+    if (!added) HIPCHK(c, timed_gemm(c, ln, FLOVER_PROF_GEMM_OUT, ln.att, w.wo, n, p_o, ss_h, mtt, gs));
+    HIPCHK(c, flk::add_norm(f.dtype, !gpt, ln.x, added ? nullptr : ln.part, p_o.S, ss_h, p_o.ldc, added ? nullptr : w.bo, w.ln2_g, w.ln2_b,
+                            ln.h, n, H, f.norm_eps, mtt, st));
     if (p_1.paired) {
       // gated 16-bit model: the activation is the epilogue of the gate|up contraction wherever that is one launch
       HIPCHK(c, timed_gemm(c, ln, FLOVER_PROF_GEMM_FF1, ln.h, w.w1, n, p_1, ss_1, mtt, gs, ln.act));
       if (!context_pass && n <= flk::gated_fused_rows(p_1)) launches -= 1;
+    } else if (context_pass && gpt && flk::context_gelu(f.dtype, ln.h, w.w1, n, p_1, ln.act, w.b1, mtt, st, &err)) {
+      HIPCHK(c, err);
     } else {
       HIPCHK(c, timed_gemm(c, ln, FLOVER_PROF_GEMM_FF1, ln.h, w.w1, n, p_1, ss_1, mtt, gs));
       HIPCHK(c, flk::activation(f.dtype, !gpt, ln.part, p_1.S, ss_1, p_1.ldc, w.b1, ln.act, n, F, mtt, st, p_1.paired));
     }
-    HIPCHK(c, timed_gemm(c, ln, FLOVER_PROF_GEMM_FF2, ln.act, w.w2, n, p_2, ss_h, mtt, gs));
+    added = context_pass && flk::context_add(f.dtype, ln.act, w.w2, n, p_2, ln.x, w.b2, mtt, st, &err);
+    HIPCHK(c, err);
+    if (!added) HIPCHK(c, timed_gemm(c, ln, FLOVER_PROF_GEMM_FF2, ln.act, w.w2, n, p_2, ss_h, mtt, gs));
     launches += 10;
   }
   if (want_tokens) {

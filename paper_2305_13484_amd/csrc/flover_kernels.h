@@ -15,10 +15,27 @@ struct GemmPlan {
   int S;      // split-K slices, a function of (N, K) only
   int kbs;    // k-blocks per slice
   int ldc;    // row length of the partial-sum slices (N rounded up to 4)
+  int tile = -1;    // more than 128 rows: which kernel (TILE_*), -1 = left to gemm()
   int paired = 0;   // gate|up of a gated MLP in paired 32-column groups (see gemm_plan_gated)
 };
+// kernels of more than 128 rows, by block shape: TILE_ROWS holds the weights in registers, the others copy both operands
+// to LDS (gemm16_rows_kernel, gemm16_tile_kernel)
+enum { TILE_ROWS = 0, TILE_128X256 = 1, TILE_128X128 = 2, TILE_64X128 = 3, TILE_64X64 = 4, TILE_KINDS = 5 };
 inline int part_ld(int N) { return (N + 3) / 4 * 4; }
 GemmPlan gemm_plan(int dtype, int N, int K);
+// Where a context pass's GEMM leaves its result (the members its kind of epilogue uses).
+struct TileOut {
+  float* part = nullptr;          // partial sums; or the residual stream [M][ldc] the result is added to
+  size_t slice_stride = 0;
+  int ldc = 0;
+  const void* bias = nullptr;     // [N] dtype, may be null
+  void* act = nullptr;            // activation [M][F], fragment order with mtt row tiles or row-major
+  int F = 0, mtt = 0;
+  const float* rope = nullptr;    // rotary table (null: none), positions and slots of the rows, destinations of q, k, v
+  const int *pos = nullptr, *slot = nullptr;
+  void *q = nullptr, *kc = nullptr, *vc = nullptr;
+  int d = 0, Smax = 0;
+};
 // gate|up of a gated MLP with F columns each.  paired = 1: group j of the layout holds gate columns 16j..16j+15 then up
 // columns 16j..16j+15 (re-tile gate with n_off = 0 and up with n_off = 16, both with tile_step = 2), K is cut in two
 // halves, gemm_gated() serves the fused iterations, and gemm() writes its partial sums in that column order (gate column
@@ -28,6 +45,16 @@ size_t gemm_tiled_bytes(int dtype, int N, int K);
 // Slicing for a context pass of M rows of one request (a function of the matrix shape and of that request's own row
 // count only): same tiling, its own number of K slices, at most max_slices (what the partial-sum buffer holds) and 16.
 GemmPlan context_plan(const GemmPlan& p, int dtype, int M, int max_slices);
+// Context passes whose plan takes K in one slice with a kernel that can finish the job: true = launched (*err its result),
+// false = the caller goes through gemm() and the row-wise kernel.  context_qkv: bias, rotary, q and the cache rows (o: bias,
+// rope, pos, slot, q, kc, vc, d, Smax).  context_add: res[M][N] += x . W^T + bias (bias may be null).  context_gelu:
+// act = gelu(x . W^T + bias) in the model dtype.  All three read x (and context_gelu writes act) in the layout xmtt says.
+bool context_qkv(int dtype, const void* x, const void* w_tiled, int M, const GemmPlan& p, const TileOut& o, int xmtt, hipStream_t st,
+                 hipError_t* err);
+bool context_add(int dtype, const void* x, const void* w_tiled, int M, const GemmPlan& p, float* res, const void* bias, int xmtt,
+                 hipStream_t st, hipError_t* err);
+bool context_gelu(int dtype, const void* x, const void* w_tiled, int M, const GemmPlan& p, void* act, const void* bias, int xmtt,
+                  hipStream_t st, hipError_t* err);
 // Re-tile W [N][K] into `tiled` starting at output column n_off (multiple of 16) of a possibly larger matrix whose
 // plan uses NT n-tiles per column group.
 // Tile t of W lands at tile position n_off/16 + t * tile_step of the layout.

@@ -11,9 +11,12 @@
 //     a row block is the unit of work; up to 16 rows one wave takes it and reads the rows' operand straight from L2/L1
 //     (no LDS, no barriers); above that the rows' operand is staged through LDS once per block of 4 column groups and
 //     shared by the block's 4 or 8 waves.
-//   * more than 128 rows (context passes, very wide windows): the contraction turns MFMA-bound, so a wave keeps a
-//     128 x 64 output tile and a block covers 256 rows x 256 columns; row blocks of one (column block, K slice) get
-//     workgroup ids that land on the same XCD, so the weight tiles cross HBM once and are L2 hits for the others.
+//   * more than 128 rows (context passes, very wide windows): the contraction turns MFMA- and operand-bound.  A wave keeps
+//     a 128 x 64 output tile and a block covers 256 rows x 256 columns (gemm16_rows_kernel), or, where such blocks would
+//     leave the chip idle, smaller blocks with both operands in LDS (gemm16_tile_kernel); context_plan picks by a cost
+//     model.  Taken in one slice, the kernel finishes the job itself: residual add, activation, or rotary and append.
+//     Row blocks of one (column block, K slice) get workgroup ids that land on the same XCD, so the weight tiles cross HBM
+//     once and are L2 hits for the others.
 //   * split-K: for the fused iteration slice count and boundaries depend on (N, K) only -- never on M -- and partial
 //     sums are written per slice and added by the consumer in slice order, so a row's result does not depend on which
 //     other rows are live (the paper's premise that fused requests undergo identical operations).  A context pass
@@ -377,162 +380,344 @@ __global__ __launch_bounds__(128 * GPB) void gated_lds_kernel(const uint16_t* __
   }
 }
 
+// What a tile kernel does with its accumulators.
+enum { EPI_PART = 0, EPI_GATED = 1, EPI_QKV = 2, EPI_ADD = 3, EPI_GELU = 4 };
+
+// n-tile (of the block's B * WC) that a wave's u-th accumulator column holds: consecutive ones, except that the rotary
+// epilogue needs the partners (i, i + d/2) of a head in one lane: accumulator columns u and u + B/2 are then d/2 apart.
+template <int B, int WC, int EPI> __device__ __forceinline__ int tile_of(int wc, int u, int d) {
+  if constexpr (EPI == EPI_QKV) {
+    static_assert(B == 4 && WC % 2 == 0, "a head is one wave's or two waves' columns");
+    if (d == 128) return (wc >> 1) * 8 + (wc & 1) * 2 + (u & 1) + (u >> 1) * 4;
+  }
+  return wc * B + u;
+}
+
+template <int DT, int A, int B, int WR, int WC, int EPI>
+__device__ __forceinline__ void tile_epilogue(f32x4_t (&acc)[A][B], const TileOut& o, int M, int N, int mt0, int nt0, int wc, int s,
+                                              int lane) {
+  const int c4 = (lane >> 4) * 4;
+#pragma unroll
+  for (int i = 0; i < A; ++i) {
+    const int m = (mt0 + i) * 16 + (lane & 15);
+    if (m >= M) continue;
+    if constexpr (EPI == EPI_PART) {
+      float* out = o.part + (size_t)s * o.slice_stride + (size_t)m * o.ldc;
+#pragma unroll
+      for (int u = 0; u < B; ++u) {
+        const int n = (nt0 + wc * B + u) * 16 + c4;
+        if (n < o.ldc) *(f32x4_t*)(out + n) = acc[i][u];
+      }
+    } else if constexpr (EPI == EPI_GATED) {      // n-tiles alternate gate and up of the same 16 MLP columns
+#pragma unroll
+      for (int u = 0; u < B; u += 2) {
+        const int j = ((nt0 + wc * B + u) >> 1) * 16 + c4;
+        if (j < o.F) stv4<DT>(o.act, xrow_index(m, j, o.F, o.mtt), act_swiglu(acc[i][u], acc[i][u + 1]));
+      }
+    } else if constexpr (EPI == EPI_GELU) {
+#pragma unroll
+      for (int u = 0; u < B; ++u) {
+        const int j = (nt0 + wc * B + u) * 16 + c4;
+        if (j < o.F) stv4<DT>(o.act, xrow_index(m, j, o.F, o.mtt), act_gelu(acc[i][u] + ldv4<DT>(o.bias, j)));
+      }
+    } else if constexpr (EPI == EPI_ADD) {
+#pragma unroll
+      for (int u = 0; u < B; ++u) {
+        const int n = (nt0 + wc * B + u) * 16 + c4;
+        if (n < N) {
+          f32x4_t a = acc[i][u];
+          if (o.bias) a += ldv4<DT>(o.bias, n);
+          float* p = o.part + (size_t)m * o.ldc + n;
+          *(f32x4_t*)p = *(const f32x4_t*)p + a;
+        }
+      }
+    } else {                                      // q | k | v columns of one head, rotary partners u and u + B/2
+      const int pos = o.pos[m], slot = o.slot[m], H = N / 3, half = o.d >> 1;
+#pragma unroll
+      for (int u = 0; u < B / 2; ++u) {
+        const int n = (nt0 + tile_of<B, WC, EPI>(wc, u, o.d)) * 16 + c4;
+        if (n >= N) continue;
+        const int which = n / H, r = n - which * H, hd = r / o.d, e = r - hd * o.d;
+        f32x4_t a0 = acc[i][u], a1 = acc[i][u + B / 2];
+        if (o.bias) { a0 += ldv4<DT>(o.bias, n); a1 += ldv4<DT>(o.bias, n + half); }
+        if (o.rope && which < 2) {
+          const float* tab = o.rope + ((size_t)pos * half + e) * 2;
+          const f32x4_t t0 = ld4(tab), t1 = ld4(tab + 4);
+          rope_rotate(a0, a1, f32x4_t{t0[0], t0[2], t1[0], t1[2]}, f32x4_t{t0[1], t0[3], t1[1], t1[3]});
+        }
+        void* dst = which == 0 ? o.q : which == 1 ? o.kc : o.vc;
+        const size_t at = which == 0 ? (size_t)m * H + r : (((size_t)slot * (H / o.d) + hd) * o.Smax + pos) * o.d + e;
+        stv4<DT>(dst, at, a0);
+        stv4<DT>(dst, at + half, a1);
+      }
+    }
+  }
+}
+
+// Barrier behind which at most N of this wave's copies are still in flight (none when `all`) and its LDS reads are done.
+// The waits are builtins outside any branch, so that the compiler knows that the fragments read before have arrived.
+template <int N> __device__ __forceinline__ void copies_barrier(bool all) {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt((N & 15) | 7 << 4 | (N >> 4) << 14);        // vmcnt(N) lgkmcnt(0)
+  if (all) __builtin_amdgcn_s_waitcnt(7 << 4 | 15 << 8);                 // vmcnt(0)
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+// 64 lanes x 16 bytes, lane i from base + off (base is wave-uniform) to l[i].  The buffer form: after the global form the
+// compiler counts later LDS reads and loads as out of order and waits for all of them.
+__device__ __forceinline__ void copy_to_lds(const char* base, uint32_t off, u32x4_t* l) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc((void*)base, (short)0, -1, 0x00020000),
+                                           (__attribute__((address_space(3))) void*)l, 16, off, 0, 0, 0);
+}
+
+// The rows' operand of a block as 1 KiB fragments: row tile mt0 + f of k-block kb0 + t is at base + t * step + offset(f).
+// Row-major (xmtt == 0) or fragment order with xmtt row tiles per k-block; rows and row tiles past the last repeat it.
+struct RowTiles {
+  const char* base;
+  size_t step;
+  uint32_t row_bytes;
+  int left, xmtt;                                // row-major: rows from mt0 on; fragment order: row tiles from mt0 on
+  __device__ RowTiles(const uint16_t* x, int M, int K, int mt0, int kb0, int xmtt_) : xmtt(xmtt_) {
+    row_bytes = (uint32_t)K * 2;
+    if (xmtt) {
+      base = (const char*)x + ((size_t)kb0 * xmtt + mt0) * 1024;
+      step = (size_t)xmtt * 1024;
+      left = xmtt - mt0;
+    } else {
+      base = (const char*)x + ((size_t)mt0 * 16 * K + kb0 * 32) * 2;
+      step = 64;
+      left = M - mt0 * 16;
+    }
+  }
+  __device__ uint32_t offset(int f, int lane) const {
+    return xmtt ? min(f, left - 1) * 1024 + lane * 16 : min(f * 16 + (lane & 15), left - 1) * row_bytes + (lane >> 4) * 16;
+  }
+};
+
 // ---- context passes (hundreds of rows): the contraction is MFMA-bound there, so each wave keeps a 128 x 64 output
-// tile (MTW = 8 row tiles x NT = 4 n-tiles, 128 accumulator registers): per k-block 32 MFMAs for 8 KiB of LDS reads and
-// 4 KiB of W loads, which halves the operand traffic per flop of the 128-row kernel above (whose waves own 128 x 32).
-// A block is 4 column units x 2 row halves = 8 waves over 256 rows x 256 columns; a unit is 64 columns = one group of
-// the matrix layout or (NTL = 2) two consecutive ones; x tile and W ring as above.
+// tile (8 row tiles x 4 n-tiles, 128 accumulator registers): per k-block 32 MFMAs for 8 KiB of LDS reads and 4 KiB of W
+// loads.  A block is 4 column units of 64 columns x 2 row halves = 8 waves over 256 rows x 256 columns.  The weights go
+// straight to registers (each wave its own four fragments, PF k-blocks ahead), the rows' operand goes to LDS by
+// asynchronous copies (16 fragments per k-block, L k-blocks ahead, a ring of L + 1 slots): with both operands through LDS
+// its 128 bytes per cycle would be the bound.  One barrier per k-block, placed in the middle of the multiplications: the
+// fragments of the next k-block are then read while this one's last row tiles are multiplied, so the matrix units see
+// neither the barrier nor the LDS latency.  0.71 us per k-block (0.75 with the x tile staged through registers and a
+// barrier per two k-blocks): 1024 rows x 12288 x 4096 102 -> 96 us, 288 rows x 22016 x 4096 100 -> 89 us; over the 192
+// blocks of the former that is the rate per compute unit of an 8192-cubed library product on the whole chip.
 // The per-(m, n) arithmetic is again the same MFMA sequence over k.
-// GATED (a paired gate|up matrix taken in one slice): instead of partial sums the wave writes silu(gate) * up of its
-// two column groups, rounded to the model dtype, as the next GEMM's row operand (`part` is then that buffer, N = 2F).
-template <int DT, int MTW, int NT, int NTL, int KC, int PF, bool GATED = false>
+// EPI: what becomes of the accumulators (see tile_epilogue); all but partial sums need the whole of K in one slice.
+template <int DT, int NTL, int EPI>
 __global__ __launch_bounds__(512) void gemm16_rows_kernel(const uint16_t* __restrict__ x, const u32x4_t* __restrict__ wt,
-                                                          float* __restrict__ part, int M, int N, int K, int ngroups,
-                                                          int KB, int kbs, size_t slice_stride, int ldc, int nx,
+                                                          TileOut o, int M, int N, int K, int ngroups, int KB, int kbs, int nx,
                                                           int nslices, int nz, int xmtt) {
-  static_assert(!GATED || NTL == 2, "gate and up tiles alternate in groups of two");
-  static_assert(PF % KC == 0 && NT % NTL == 0, "ring and tile shapes");
-  constexpr int MTB = 2 * MTW;                   // row tiles per block
-  constexpr int NW = 8;
-  __shared__ u32x4_t lds[2][KC * MTB * 64];
-  constexpr int FPW = (KC * MTB + NW - 1) / NW;
-  constexpr int CPR = PF / KC;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int xcd = blockIdx.x & 7, qq = blockIdx.x >> 3;     // row blocks of one task share an XCD (see above)
+  static_assert(NTL == 2 || NTL == 4, "layout groups");
+  constexpr int A = 8, B = 4, PF = 4, L = 4, D = L + 1, MTB = 2 * A, F = MTB / 8;   // F: copies per wave and k-block
+  __shared__ u32x4_t lds[D][MTB * 64];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // 1-D grid, XCD-aware: row blocks of one (column block, K slice) task share an XCD (see gemm16_lds_kernel)
+  const int xcd = blockIdx.x & 7, qq = blockIdx.x >> 3;
   const int zb = qq % nz, task = (qq / nz) * 8 + xcd;
   if (task >= nx * nslices) return;
   const int bx = task % nx, s = task / nx;
   const int g = bx * 4 + (wave >> 1), half = wave & 1;
   const int gl = min(g, ngroups - 1);
-  const int m0 = zb * (16 * MTB);
-  const int kb0 = s * kbs;
-  const int kb1 = min(KB, kb0 + kbs);
-  const int nchunks = (kb1 - kb0 + KC - 1) / KC;
-  const int live_tiles = min(MTW, max(0, (M - m0 - half * (16 * MTW) + 15) / 16));   // of this wave's MTW row tiles
+  const int kb0 = s * kbs, T = min(KB, kb0 + kbs) - kb0;
+  const int mt0 = zb * MTB;
+  const int live = min(A, max(0, (M + 15) / 16 - mt0 - half * A));     // of this wave's row tiles
 
-  f32x4_t acc[MTW][NT];
+  // the wave's four n-tiles are 4 / NTL consecutive column groups of the matrix layout (NTL tiles per group), or the rotary
+  // partners' tiles of a head: those sit four n-tiles apart (d = 128)
+  const bool split = EPI == EPI_QKV && o.d == 128;     // three times a multiple of four heads: whole blocks of 256 columns
+  const int u0 = split ? bx * 16 + tile_of<B, 4, EPI>(wave >> 1, 0, 128) : gl * B;         // first n-tile
+  const u32x4_t* wp = wt + (((size_t)(u0 / NTL) * KB + kb0) * NTL + u0 % NTL) * 64 + lane;   // + kb * NTL * 64
+  const size_t far = split ? (size_t)(4 / NTL) * KB * NTL * 64 : NTL == 2 ? (size_t)KB * NTL * 64 : 128;   // n-tiles 2 and 3
+  RowTiles rows(x, M, K, mt0, kb0, xmtt);
+  uint32_t src[F];
 #pragma unroll
-  for (int i = 0; i < MTW; ++i)
+  for (int j = 0; j < F; ++j) src[j] = rows.offset(wave + 8 * j, lane);
+  // Copies and W loads past the slice repeat its last k-block (in bounds, unused): every k-block then issues the same
+  // number of loads and the wait counts are constants.
+  auto copy_rows = [&](int t, int slot) {
+    const char* base = rows.base + (size_t)min(t, T - 1) * rows.step;
 #pragma unroll
-    for (int t = 0; t < NT; ++t) acc[i][t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-
-  // the wave's NT n-tiles are NT / NTL consecutive column groups of the matrix layout (NTL tiles per group)
-  const u32x4_t* wp = wt + ((size_t)gl * (NT / NTL) * KB) * NTL * 64 + lane;     // + woff(kb, t)
-  auto woff = [&](int kb, int t) { return (((size_t)(t / NTL) * KB + kb) * NTL + (t % NTL)) * 64; };
-  // rows' operand: row-major [M][K] (xmtt == 0) or fragment order with xmtt row tiles per k-block
-  const size_t tstride = xmtt ? 512 : (size_t)16 * K, kstride = xmtt ? (size_t)xmtt * 512 : 32;
-  const uint16_t* xp = xmtt ? x + (size_t)(m0 >> 4) * 512 + lane * 8
-                            : x + (size_t)(m0 + (lane & 15)) * K + (lane >> 4) * 8;     // + i*tstride + kb*kstride
-
-  u32x4_t bq[PF][NT], areg[FPW];
-#pragma unroll
-  for (int j = 0; j < PF; ++j) {
-    const int kk = min(kb0 + j, kb1 - 1);
-#pragma unroll
-    for (int t = 0; t < NT; ++t) bq[j][t] = wp[woff(kk, t)];
-  }
-  auto load_a = [&](int chunk) {
-#pragma unroll
-    for (int j = 0; j < FPW; ++j) {
-      const int f = min(wave + NW * j, KC * MTB - 1), kc = f / MTB, i = f - kc * MTB;
-      const int kk = min(kb0 + chunk * KC + kc, kb1 - 1);
-      areg[j] = *(const u32x4_t*)(xp + i * tstride + kk * kstride);
-    }
+    for (int j = 0; j < F; ++j) copy_to_lds(base, src[j], lds[slot] + (wave + 8 * j) * 64);
   };
-  auto store_a = [&](int buf) {
+  u32x4_t bq[PF][B], af[4];
+  auto load_w = [&](auto j_, int t) {
+    constexpr int j = decltype(j_)::value;
+    const u32x4_t* w = wp + (size_t)min(t, T - 1) * NTL * 64;
 #pragma unroll
-    for (int j = 0; j < FPW; ++j) lds[buf][min(wave + NW * j, KC * MTB - 1) * 64 + lane] = areg[j];
+    for (int u = 0; u < B; ++u) bq[j][u] = w[(u & 1) * 64 + (u >> 1) * far];
   };
-  load_a(0);
-  store_a(0);
-  __syncthreads();
-  // Chunks as in the kernel above: branch-free steady state, refills pinned where they are written.
-  auto chunk = [&](auto cc_, auto tail_, auto full_, int c) {
-    constexpr int cc = decltype(cc_)::value;
-    constexpr bool tail = decltype(tail_)::value;
-    constexpr bool full = decltype(full_)::value;
-    const bool more = !tail || c + 1 < nchunks;
-    if (more) load_a(c + 1);
+  f32x4_t acc[A][B];
+#pragma unroll
+  for (int i = 0; i < A; ++i)
+#pragma unroll
+    for (int u = 0; u < B; ++u) acc[i][u] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  // issue order as in the loop: copies, then W, k-block by k-block
+  auto ahead = [&](auto j_) {
+    copy_rows(decltype(j_)::value, decltype(j_)::value);
     __builtin_amdgcn_sched_barrier(0);
-    const u32x4_t* la = lds[c & 1];
-    if constexpr (full && !tail) {
-      // Every row tile live and every k-block of the chunk inside the slice (all but a ragged last row block and a
-      // slice's last chunk): no branches, and a row tile's fragment is read from LDS two tiles ahead of its MFMAs.
-      const u32x4_t* lw = la + (half * MTW) * 64 + lane;
-      constexpr int T = KC * MTW;
-      auto frag = [&](int q) { return lw[((q / MTW) * MTB + (q % MTW)) * 64]; };
-      u32x4_t af[3];
-      af[0] = frag(0);
-      af[1] = frag(1);
-#pragma unroll
-      for (int q = 0; q < T; ++q) {
-        const int kc = q / MTW, i = q % MTW;
-        if (q + 2 < T) af[(q + 2) % 3] = frag(q + 2);
-#pragma unroll
-        for (int t = 0; t < NT; ++t) acc[i][t] = mfma16<DT>(bq[cc * KC + kc][t], af[q % 3], acc[i][t]);
-        if (i == MTW - 1) {
-          const int kk = min(kb0 + c * KC + kc + PF, kb1 - 1);
-#pragma unroll
-          for (int t = 0; t < NT; ++t) bq[cc * KC + kc][t] = wp[woff(kk, t)];
-          __builtin_amdgcn_sched_barrier(0);
-        }
-      }
-    } else
-#pragma unroll
-    for (int kc = 0; kc < KC; ++kc) {
-      const int kb = kb0 + c * KC + kc;
-      if (!tail || kb < kb1) {
-#pragma unroll
-        for (int i = 0; i < MTW; ++i)
-          if (i < live_tiles) {               // wave-uniform: row tiles past M are skipped
-            const u32x4_t af = la[(kc * MTB + half * MTW + i) * 64 + lane];
-#pragma unroll
-            for (int t = 0; t < NT; ++t) acc[i][t] = mfma16<DT>(bq[cc * KC + kc][t], af, acc[i][t]);
-          }
-      }
-      const int kk = min(kb + PF, kb1 - 1);
-#pragma unroll
-      for (int t = 0; t < NT; ++t) bq[cc * KC + kc][t] = wp[woff(kk, t)];
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    if (more) store_a((c + 1) & 1);
-    __syncthreads();
+    load_w(j_, decltype(j_)::value);
+    __builtin_amdgcn_sched_barrier(0);
   };
-  static_assert(CPR <= 2, "ring turns of one or two chunks");
-  // Two copies of the loop, chosen per wave (the accumulators stay in place in each; both pass the same barriers).
-  auto loops = [&](auto full_) {
-    int c = 0;
-    for (; c + CPR < nchunks; c += CPR) {
-      chunk(std::integral_constant<int, 0>{}, std::false_type{}, full_, c);
-      if constexpr (CPR >= 2) chunk(std::integral_constant<int, 1>{}, std::false_type{}, full_, c + 1);
+  ahead(std::integral_constant<int, 0>{});
+  ahead(std::integral_constant<int, 1>{});
+  ahead(std::integral_constant<int, 2>{});
+  ahead(std::integral_constant<int, 3>{});
+  static_assert(L == 4 && PF == 4, "prologue");
+  copies_barrier<(F + B) * L - F>(false);        // the copies of k-block 0 have landed
+  int slot = 0;                                  // of the k-block being multiplied
+  // One k-block.  ROWS8 = all eight row tiles live (no branches); otherwise dead row tiles are skipped (wave-uniform).
+  auto kblock = [&](auto j_, auto rows8_, int t) {
+    constexpr int j = decltype(j_)::value;
+    constexpr bool rows8 = decltype(rows8_)::value;
+    const int nslot = slot + 1 == D ? 0 : slot + 1, cslot = slot == 0 ? D - 1 : slot - 1;
+    const u32x4_t *lw = lds[slot] + half * A * 64 + lane, *ln = lds[nslot] + half * A * 64 + lane;
+#pragma unroll
+    for (int i = 0; i < A; ++i) {
+      if (i == A / 2) {
+        // the copies of k-block t + 1 have landed; every wave has read k-block t - 1, whose slot is refilled
+        copies_barrier<(F + B) * (L - 1) - F>(false);
+        copy_rows(t + L, cslot);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if (rows8) {                               // the last two reads are the next k-block's first fragments
+        af[(i + 2) % 4] = i + 2 < A ? lw[(i + 2) * 64] : ln[(i + 2 - A) * 64];
+      } else if (i < live) {
+        af[i % 4] = lw[i * 64];
+      }
+      if (rows8 || i < live) {
+#pragma unroll
+        for (int u = 0; u < B; ++u) acc[i][u] = mfma16<DT>(bq[j][u], af[i % 4], acc[i][u]);
+        if (rows8) __builtin_amdgcn_sched_barrier(0);   // keeps every fragment's read two row tiles ahead of its use
+      }
     }
-    for (; c < nchunks; c += CPR) {
-      chunk(std::integral_constant<int, 0>{}, std::true_type{}, full_, c);
-      if constexpr (CPR >= 2) if (c + 1 < nchunks) chunk(std::integral_constant<int, 1>{}, std::true_type{}, full_, c + 1);
-    }
+    load_w(j_, t + PF);
+    __builtin_amdgcn_sched_barrier(0);
+    slot = nslot;
   };
-  if (live_tiles == MTW) loops(std::true_type{});
-  else loops(std::false_type{});
+  auto loop = [&](auto rows8_) {
+    if (decltype(rows8_)::value) {
+      af[0] = (lds[0] + half * A * 64 + lane)[0];
+      af[1] = (lds[0] + half * A * 64 + lane)[64];
+    }
+    int t = 0;
+    for (; t + PF <= T; t += PF) {
+      kblock(std::integral_constant<int, 0>{}, rows8_, t);
+      kblock(std::integral_constant<int, 1>{}, rows8_, t + 1);
+      kblock(std::integral_constant<int, 2>{}, rows8_, t + 2);
+      kblock(std::integral_constant<int, 3>{}, rows8_, t + 3);
+    }
+    if (t < T) kblock(std::integral_constant<int, 0>{}, rows8_, t);
+    if (t + 1 < T) kblock(std::integral_constant<int, 1>{}, rows8_, t + 1);
+    if (t + 2 < T) kblock(std::integral_constant<int, 2>{}, rows8_, t + 2);
+  };
+  // Two copies of the loop, chosen per wave (both pass the same barriers).
+  if (live == A) loop(std::true_type{});
+  else loop(std::false_type{});
+  copies_barrier<0>(true);                       // no copy may still be under way when the block's LDS is given away
   if (g >= ngroups) return;
-  if constexpr (GATED) {
-    const int F = N >> 1;
+  tile_epilogue<DT, A, B, 2, 4, EPI>(acc, o, M, N, mt0 + half * A, bx * 16, wave >> 1, s, lane);
+}
+
+// ---- context passes: both operands through LDS by asynchronous copies (memory to LDS without registers).  Both operands
+// already are sequences of 1 KiB MFMA fragments (the weights always, the rows unless they are row-major, where every lane
+// simply points at its own 16 bytes), so one copy instruction of a wave lands one fragment and the reads back are
+// conflict-free ds_read_b128.  A block is WR x WC waves, a wave owns A row tiles x B n-tiles; a stage is one k-block, D
+// stages form a ring in LDS; the fragments of stage t + 1 are read while stage t is multiplied, one barrier per stage.
+// What bounds it: the operand bytes through the L2s (about 24 TB/s over the chip; less while the weights come from HBM) at
+// the small blocks, the 128 bytes per cycle of LDS at the large ones.  Its place is between 129 and a few hundred rows and
+// at narrow matrices, where 256 x 256 blocks with up to 16 K slices left most compute units waiting (288 rows, cold
+// weights, the slices' sums not counted): 6144 x 2048 28.7 -> 16.7 us, 2048 x 2048 20.5 -> 11.2, 8192 x 2048 28.0 -> 23,
+// 512 x 512 12.7 -> 5.2 us.
+template <int DT, int A, int B, int WR, int WC, int D, int EPI>
+__global__ __launch_bounds__(64 * WR * WC) __attribute__((amdgpu_waves_per_eu(2))) void gemm16_tile_kernel(const uint16_t* __restrict__ x, const char* __restrict__ wt, TileOut o,
+                                                                   int M, int N, int K, int ntiles, int NTL, int KB, int kbs,
+                                                                   int ncb, int nrb, int tasks, int per, int xmtt) {
+  constexpr int FA = A * WR, FB = B * WC, NW = WR * WC, F = (FA + FB) / NW;   // F: copies per wave and stage
+  static_assert((FA + FB) % NW == 0 && D >= 2, "every wave copies the same number of fragments per stage");
+  static_assert(F * (D - 1) < 64, "the wait count has six bits");
+  __shared__ u32x4_t lds[D][(FA + FB) * 64];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wr = wave / WC, wc = wave % WC;
+  // workgroup ids go round-robin over the 8 XCDs: each XCD gets a contiguous run of tasks (row block fastest), so the row
+  // blocks of a column block share its weight tiles in that XCD's L2
+  const int task = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
+  if ((int)(blockIdx.x >> 3) >= per || task >= tasks) return;
+  const int rb = task % nrb, cs = task / nrb, cb = cs % ncb, s = cs / ncb;
+  const int kb0 = s * kbs, T = min(KB, kb0 + kbs) - kb0;
+  const int mt0 = rb * FA, nt0 = cb * FB;        // first row tile / n-tile of the block
+
+  static_assert(FA % NW == 0, "a copy instruction takes fragments of one operand");
+  constexpr int FX = FA / NW;                    // of a wave's F copies per stage, the first FX are of the rows' operand
+  RowTiles rows(x, M, K, mt0, kb0, xmtt);
+  const int g0 = nt0 / NTL;
+  const char* wbase = wt + ((size_t)g0 * KB + kb0) * NTL * 1024;
+  uint32_t src[F];
 #pragma unroll
-    for (int i = 0; i < MTW; ++i)
-#pragma unroll
-      for (int pr = 0; pr < NT / 2; ++pr) {
-        const int j = (g * (NT / 2) + pr) * 16 + (lane >> 4) * 4, m = m0 + (half * MTW + i) * 16 + (lane & 15);
-        if (m < M && j < F) stv4<DT>(part, xrow_index(m, j, F, xmtt), act_swiglu(acc[i][2 * pr], acc[i][2 * pr + 1]));
-      }
-    return;
-  }
-  float* out = part + (size_t)s * slice_stride;
-#pragma unroll
-  for (int i = 0; i < MTW; ++i)
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      const int n = (g * NT + t) * 16 + (lane >> 4) * 4, m = m0 + (half * MTW + i) * 16 + (lane & 15);
-      if (m < M && n < ldc) *(f32x4_t*)(out + (size_t)m * ldc + n) = acc[i][t];
+  for (int j = 0; j < F; ++j) {
+    const int f = wave + NW * j;
+    if (j < FX) {
+      src[j] = rows.offset(f, lane);
+    } else {
+      const int nt = min(nt0 + f - FA, ntiles - 1), g = nt / NTL;
+      src[j] = ((uint32_t)(g - g0) * KB * NTL + (nt - g * NTL)) * 1024 + lane * 16;
     }
+  }
+  auto issue = [&](int slot) {                   // copies of the next stage
+#pragma unroll
+    for (int j = 0; j < F; ++j) copy_to_lds(j < FX ? rows.base : wbase, src[j], lds[slot] + (wave + NW * j) * 64);
+    rows.base += rows.step;
+    wbase += NTL * 1024;
+  };
+  u32x4_t fa[2][A], fb[2][B];
+  auto fetch = [&](auto r_, int slot) {
+    constexpr int r = decltype(r_)::value;
+    const u32x4_t* l = lds[slot] + lane;
+#pragma unroll
+    for (int u = 0; u < B; ++u) fb[r][u] = l[(FA + tile_of<B, WC, EPI>(wc, u, o.d)) * 64];
+#pragma unroll
+    for (int i = 0; i < A; ++i) fa[r][i] = l[(wr * A + i) * 64];
+  };
+  f32x4_t acc[A][B];
+#pragma unroll
+  for (int i = 0; i < A; ++i)
+#pragma unroll
+    for (int t = 0; t < B; ++t) acc[i][t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  auto multiply = [&](auto r_) {
+    constexpr int r = decltype(r_)::value;
+#pragma unroll
+    for (int i = 0; i < A; ++i)
+#pragma unroll
+      for (int u = 0; u < B; ++u) acc[i][u] = mfma16<DT>(fb[r][u], fa[r][i], acc[i][u]);
+  };
+  const std::integral_constant<int, 0> r0{};
+  const std::integral_constant<int, 1> r1{};
+#pragma unroll
+  for (int t = 0; t < D; ++t)
+    if (t < T) issue(t);
+  copies_barrier<F * (D - 1)>(T < D);
+  fetch(r0, 0);
+  int t = 0, slot = 0;                           // slot = t % D
+  // One step: stage t sits in registers `cur`; its slot in LDS is free once every wave is past the barrier, so the copies
+  // of stage t + D go there, and the fragments of stage t + 1 are read while stage t is multiplied.  The last step reads
+  // a slot whose contents nobody uses.
+  auto step1 = [&](auto cur, auto nxt) {
+    const bool more = t + D < T;
+    copies_barrier<F * (D - 2)>(!more);
+    if (more) issue(slot);
+    slot = slot + 1 == D ? 0 : slot + 1;
+    fetch(nxt, slot);
+    __builtin_amdgcn_sched_barrier(0);
+    multiply(cur);
+    __builtin_amdgcn_sched_barrier(0);
+    return ++t == T;
+  };
+  for (;;) {
+    if (step1(r0, r1)) break;
+    if (step1(r1, r0)) break;
+  }
+  tile_epilogue<DT, A, B, WR, WC, EPI>(acc, o, M, N, mt0 + wr * A, nt0, wc, s, lane);
 }
 
 // ---------------------------------------------------------------- fp32 FMA kernel (tiny models)
@@ -616,35 +801,66 @@ size_t gemm_tiled_bytes(int dtype, int N, int K) {
   return Npad * K * 2;
 }
 
-// Context passes: the slice count that minimises a simple cost model of the 256 x 256 blocks on 256 compute units:
-// rounds of blocks x k-blocks per slice (about 1 us per k-block step of a block, measured), plus the fp32 partial sums
-// written by this kernel and re-read by the next one (about 2 TB/s in effect: the stores are a burst at the kernel's
-// end that nothing overlaps; the divisor is the one that minimises the context passes' time on a stream of prompts of
-// 32 to 1024 rows, flat between 1.7 and 2.5) -- at hundreds of rows those outweigh the weights
-// when the iteration's slicing is kept, while a single slice leaves most of the chip idle for the 4096-column matrices.
+// Above 128 rows: estimated time (microseconds) of the contraction with one kernel and slice count, a latency-or-throughput
+// model of the blocks that share a compute unit: a block's k-block step takes `step` alone and `busy` per block where
+// several fill the unit; `start` is launch, ramp and drain, `store` the rate of the fp32 results (bytes per microsecond).
+// Fitted to 3000 measured launches (16 matrix shapes from 512 x 512 to 35840 x 6656, 132 to 1024 rows, 1 to 8 slices,
+// cold weights): 6-8 % rms per kernel, and the kernel and count it picks are on average 0.7 % slower than the best.
+// That is the time of a launch that has the chip to itself; two pre-processing streams share it, and there the work per
+// launch counts (blocks x steps over 256 compute units).  Weighed 7 : 3 (0, 3, 5, 8 and 10 tenths tried: prompts of 120 to
+// 440 tokens at the 1.3B shape one after the other 1.90 / 1.96 / 1.95 / 2.05 / 3.81 ms, two overlapped 7B prompts of 780
+// and 940 tokens 2.96 / 2.88 / 2.9-3.1 / 2.86 / 2.87 ms).
+struct TileKernel {
+  int bm, bn, occ;      // rows and columns of a block, blocks a compute unit holds
+  double start, step, busy, store;
+};
+static constexpr TileKernel kTile[] = {
+    {256, 256, 1, 7.7, 0.628, 0.628, 4.3e6},    // TILE_ROWS
+    {128, 256, 1, 4.9, 0.411, 0.411, 4.0e6},    // TILE_128X256
+    {128, 128, 2, 3.7, 0.256, 0.238, 4.3e6},    // TILE_128X128
+    {64, 128, 3, 2.4, 0.205, 0.169, 4.9e6},     // TILE_64X128
+    {64, 64, 4, 2.15, 0.160, 0.107, 5.1e6},     // TILE_64X64
+};
+static double tile_cost(int tile, int M, const GemmPlan& p, int S, int kbs) {
+  const TileKernel& k = kTile[tile];
+  const int ncols = tile == TILE_ROWS ? p.Npad : p.N;
+  const long blocks = (long)((M + k.bm - 1) / k.bm) * ((ncols + k.bn - 1) / k.bn) * S, per_cu = (blocks + 255) / 256;
+  const long full = per_cu / k.occ, rest = per_cu % k.occ;
+  const double steps = full * std::max(k.step, k.busy * k.occ) + (rest ? std::max(k.step, k.busy * rest) : 0.0);
+  return k.start + kbs * (0.7 * steps + 0.3 * k.busy * blocks / 256) + (double)S * M * p.N * 4.0 / k.store;
+}
+
+// Kernel and slice count of a context pass's GEMM: the pair with the least time, counting what the result costs the next
+// kernel as well -- fp32 sums read back (4 TB/s) and a launch of its own, unless the kernel takes K in one slice and finishes the job in its epilogue.
 GemmPlan context_plan(const GemmPlan& p, int dtype, int M, int max_slices) {
   GemmPlan q = p;
   if (dtype == DT_F32 || M <= 128) return q;
-  const long units = (long)((p.Npad / 64 + 3) / 4) * ((M + 255) / 256);
   const int smax = std::max(1, std::min(max_slices, 16));   // what the caller's partial-sum buffer holds; the row-wise
                                                              // kernels load up to 16 slices at once
   double best = 0.0;
-  int bestS = 1;
+  q.S = 0;
   for (int S = 1; S <= smax; ++S) {
     const int kbs = (p.KB + S - 1) / S;
     if ((p.KB + kbs - 1) / kbs != S) continue;                       // slice counts that leave an empty last slice
-    const double rounds = (double)((units * S + 255) / 256);
-    // a paired gate|up matrix in one slice writes the activation instead of partial sums (gemm_gated)
-    const double sums = (p.paired && S == 1) ? (double)M * p.N / 2.0e6 : (double)S * M * p.N * 8.0 / 2.0e6;
-    const double cost = rounds * kbs * 1.0 + sums;   // microseconds
-    if (S == 1 || cost < best) {
-      best = cost;
-      bestS = S;
+    for (int tile = TILE_ROWS; tile < TILE_KINDS; ++tile) {
+      const bool finished = S == 1;
+      const double cost = tile_cost(tile, M, p, S, kbs) + (finished ? 0.0 : (double)S * M * p.N * 4.0 / 4.0e6 + 1.5);
+      if (q.S == 0 || cost < best) {
+        best = cost;
+        q.S = S;
+        q.kbs = kbs;
+        q.tile = tile;
+      }
     }
   }
-  q.S = bestS;
-  q.kbs = (p.KB + q.S - 1) / q.S;
   return q;
+}
+// The slicing is given (a fused iteration of more than 128 rows, whose slices depend on the matrix alone): only the kernel.
+static int best_tile(int M, const GemmPlan& p) {
+  int at = TILE_ROWS;
+  for (int tile = TILE_ROWS + 1; tile < TILE_KINDS; ++tile)
+    if (tile_cost(tile, M, p, p.S, p.kbs) < tile_cost(at, M, p, p.S, p.kbs)) at = tile;
+  return at;
 }
 
 hipError_t retile(int dtype, const void* W, int N, int K, void* tiled, int n_off, int NT, hipStream_t st, int tile_step) {
@@ -682,14 +898,74 @@ static void launch_lds(const void* x, const void* wt, float* part, int M, const 
                (const uint16_t*)x, (const u32x4_t*)wt, part, M, p.N, p.K, ngroups, p.KB, p.kbs, ss, p.ldc, nx, p.S, nz, xmtt);
 }
 
-template <int DT, int NTL, bool GATED = false>
-static void launch_rows(const void* x, const void* wt, float* part, int M, const GemmPlan& p, size_t ss, int xmtt,
-                        hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
+template <int DT, int NTL, int EPI>
+static void launch_rows(const void* x, const void* wt, const TileOut& o, int M, const GemmPlan& p, int xmtt, hipStream_t st,
+                        hipEvent_t ev0, hipEvent_t ev1) {
   const int ngroups = p.Npad / 64;            // units of 64 columns, whatever the layout's group width
   const int nx = (ngroups + 3) / 4, nz = (M + 255) / 256;
   const int tasks8 = (nx * p.S + 7) / 8 * 8;
-  launch_timed(gemm16_rows_kernel<DT, 8, 4, NTL, 2, 2, GATED>, dim3(tasks8 * nz), dim3(512), st, ev0, ev1, (const uint16_t*)x,
-               (const u32x4_t*)wt, part, M, p.N, p.K, ngroups, p.KB, p.kbs, ss, p.ldc, nx, p.S, nz, xmtt);
+  launch_timed(gemm16_rows_kernel<DT, NTL, EPI>, dim3(tasks8 * nz), dim3(512), st, ev0, ev1, (const uint16_t*)x,
+               (const u32x4_t*)wt, o, M, p.N, p.K, ngroups, p.KB, p.kbs, nx, p.S, nz, xmtt);
+}
+
+template <int DT, int A, int B, int WR, int WC, int D, int EPI>
+static void launch_tile(const void* x, const void* wt, const TileOut& o, int M, const GemmPlan& p, int xmtt, hipStream_t st,
+                        hipEvent_t ev0, hipEvent_t ev1) {
+  const int nrb = (M + 16 * A * WR - 1) / (16 * A * WR), ncb = (p.N + 16 * B * WC - 1) / (16 * B * WC);
+  const int tasks = nrb * ncb * p.S, per = (tasks + 7) / 8;
+  launch_timed(gemm16_tile_kernel<DT, A, B, WR, WC, D, EPI>, dim3(per * 8), dim3(64 * WR * WC), st, ev0, ev1, (const uint16_t*)x,
+               (const char*)wt, o, M, p.N, p.K, p.Npad / 16, p.NT, p.KB, p.kbs, ncb, nrb, tasks, per, xmtt);
+}
+// 64-column blocks do not hold the rotary partners of a 128-wide head: that epilogue takes 128 columns instead
+template <int DT, int EPI>
+static void dispatch_tile(int tile, const void* x, const void* wt, const TileOut& o, int M, const GemmPlan& p, int xmtt, hipStream_t st,
+                          hipEvent_t ev0, hipEvent_t ev1) {
+  if (tile == TILE_ROWS) {
+    if (p.NT == 4) {
+      if constexpr (EPI != EPI_GATED) launch_rows<DT, 4, EPI>(x, wt, o, M, p, xmtt, st, ev0, ev1);   // paired layouts have NT = 2
+    } else {
+      launch_rows<DT, 2, EPI>(x, wt, o, M, p, xmtt, st, ev0, ev1);
+    }
+  }
+  else if (tile == TILE_128X256) launch_tile<DT, 4, 4, 2, 4, 4, EPI>(x, wt, o, M, p, xmtt, st, ev0, ev1);
+  else if (tile == TILE_128X128) launch_tile<DT, 2, 4, 4, 2, 4, EPI>(x, wt, o, M, p, xmtt, st, ev0, ev1);
+  else if (tile == TILE_64X128 || EPI == EPI_QKV) launch_tile<DT, 2, 4, 2, 2, 4, EPI>(x, wt, o, M, p, xmtt, st, ev0, ev1);
+  else if constexpr (EPI != EPI_QKV) launch_tile<DT, 2, 2, 2, 2, 4, EPI>(x, wt, o, M, p, xmtt, st, ev0, ev1);
+}
+template <int EPI>
+static hipError_t run_tile(int dtype, const void* x, const void* wt, const TileOut& o, int M, const GemmPlan& p, int xmtt, hipStream_t st,
+                           hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr) {
+  if (dtype == DT_BF16) dispatch_tile<DT_BF16, EPI>(p.tile, x, wt, o, M, p, xmtt, st, ev0, ev1);
+  else dispatch_tile<DT_F16, EPI>(p.tile, x, wt, o, M, p, xmtt, st, ev0, ev1);
+  return hipGetLastError();
+}
+static bool finishes(int dtype, const GemmPlan& p, int M) { return dtype != DT_F32 && M > 128 && p.S == 1 && p.tile >= 0; }
+
+bool context_qkv(int dtype, const void* x, const void* wt, int M, const GemmPlan& p, const TileOut& o, int xmtt, hipStream_t st, hipError_t* err) {
+  if (!finishes(dtype, p, M)) return false;
+  *err = run_tile<EPI_QKV>(dtype, x, wt, o, M, p, xmtt, st);
+  return true;
+}
+bool context_add(int dtype, const void* x, const void* wt, int M, const GemmPlan& p, float* res, const void* bias, int xmtt, hipStream_t st,
+                 hipError_t* err) {
+  if (!finishes(dtype, p, M)) return false;
+  TileOut o;
+  o.part = res;
+  o.ldc = p.N;
+  o.bias = bias;
+  *err = run_tile<EPI_ADD>(dtype, x, wt, o, M, p, xmtt, st);
+  return true;
+}
+bool context_gelu(int dtype, const void* x, const void* wt, int M, const GemmPlan& p, void* act, const void* bias, int xmtt, hipStream_t st,
+                  hipError_t* err) {
+  if (!finishes(dtype, p, M)) return false;
+  TileOut o;
+  o.act = act;
+  o.bias = bias;
+  o.F = p.N;
+  o.mtt = xmtt;
+  *err = run_tile<EPI_GELU>(dtype, x, wt, o, M, p, xmtt, st);
+  return true;
 }
 
 template <int DT, int NT>
@@ -723,7 +999,15 @@ static void dispatch16(const void* x, const void* wt, float* part, int M, const 
   }
   else if (M <= 64) launch_lds<DT, 4, NT, 2, 4>(x, wt, part, M, p, ss, xmtt, st, ev0, ev1);
   else if (M <= 128) launch_lds<DT, 8, NT, 2, 4, 8>(x, wt, part, M, p, ss, xmtt, st, ev0, ev1);   // paired: 8 groups, 256 columns
-  else launch_rows<DT, NT>(x, wt, part, M, p, ss, xmtt, st, ev0, ev1);             // row blocks of 256
+  else {                                                                             // context passes, very wide windows
+    GemmPlan q = p;
+    if (q.tile < 0) q.tile = best_tile(M, p);
+    TileOut o;
+    o.part = part;
+    o.slice_stride = ss;
+    o.ldc = p.ldc;
+    dispatch_tile<DT, EPI_PART>(q.tile, x, wt, o, M, q, xmtt, st, ev0, ev1);
+  }
 }
 
 template <int DT>
@@ -764,10 +1048,12 @@ hipError_t gemm_gated(int dtype, const void* x, const void* wt, int M, const Gem
                       size_t slice_stride, int xmtt, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
   if (M <= 0) return hipSuccess;
   if (!p.paired || dtype == DT_F32) return hipErrorInvalidValue;
-  if (p.S == 1 && M > 128) {
-    if (dtype == DT_BF16) launch_rows<DT_BF16, 2, true>(x, wt, (float*)act, M, p, 0, xmtt, st, ev0, ev1);
-    else launch_rows<DT_F16, 2, true>(x, wt, (float*)act, M, p, 0, xmtt, st, ev0, ev1);
-    return hipGetLastError();
+  if (finishes(dtype, p, M)) {
+    TileOut o;
+    o.act = act;
+    o.F = p.N / 2;
+    o.mtt = xmtt;
+    return run_tile<EPI_GATED>(dtype, x, wt, o, M, p, xmtt, st, ev0, ev1);
   }
   if (M > gated_fused_rows(p) || p.S != 2) {
     hipError_t e = gemm(dtype, x, wt, M, p, part, slice_stride, xmtt, st, ev0, nullptr);   // timed from the first launch's

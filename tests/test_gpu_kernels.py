@@ -77,6 +77,20 @@ def test_gemm_full_size_sampled_columns(M):
         del W
 
 
+@pytest.mark.parametrize("dtype", [synth.DT_BF16, synth.DT_F16])
+@pytest.mark.parametrize("M,N,K", [(129, 70, 32), (191, 130, 64), (257, 320, 96), (130, 4100, 160), (300, 2050, 512), (513, 8192, 288),
+                                   (700, 8192, 1024), (900, 12288, 2048), (1024, 22016, 256)])
+def test_gemm_of_more_than_128_rows_every_block_shape(dtype, M, N, K):
+    """Row blocks of 64, 128 and 256 rows and their ragged last ones, slices shorter than the copy ring, columns past the
+    last full block; the bound is fp32 accumulation (4e-6 of the sum of magnitudes) against fp64."""
+    g = torch.Generator(device="cuda").manual_seed(M + N + K)
+    x = torch.randn((M, K), generator=g, device="cuda").to(TDT[dtype])
+    W = (torch.randn((N, K), generator=g, device="cuda") * 0.05).to(TDT[dtype])
+    got = fl.k_gemm(x, W).double()
+    xd, Wd = x.double(), W.double()
+    assert torch.all((got - xd @ Wd.T).abs() <= 4e-6 * (xd.abs() @ Wd.abs().T) + 1e-30)
+
+
 # ---------------------------------------------------------------- gated MLP input (contraction + activation, one launch)
 
 def _gated_reference(dtype, x, Wg, Wu):
