@@ -338,6 +338,7 @@ int run_rows(flover_ctx* c, Lane& ln, const Row* rows, int n, bool want_tokens, 
     len[i] = rows[i].pos + 1;
     const int nc = (len[i] + flk::attn_chunk() - 1) / flk::attn_chunk();
     nchunk[i] = nc;
+    if (context_pass) continue;         // its attention takes the rows as they are, or (fp32) the blocks below
     for (int ch = 0; ch < nc; ++ch) {
       items[4 * n_items] = i;
       items[4 * n_items + 1] = ch;
@@ -346,14 +347,13 @@ int run_rows(flover_ctx* c, Lane& ln, const Row* rows, int n, bool want_tokens, 
       ++n_items;
     }
   }
-  // context pass: runs of consecutive positions of one slot are served several query rows per wave
-  const int qb = flk::prefill_rows_per_block(f.dtype);
+  // context pass of an fp32 model: runs of consecutive positions of one slot are served several query rows per wave
   int n_blocks = 0;
   int* blk = items + 4 * n_items;
-  if (context_pass) {
+  if (context_pass && f.dtype == FLOVER_F32) {
     for (int i = 0; i < n;) {
       int nr = 1;
-      while (nr < qb && i + nr < n && rows[i + nr].slot == rows[i].slot && rows[i + nr].pos == rows[i].pos + nr)
+      while (nr < flk::kPrefillQB && i + nr < n && rows[i + nr].slot == rows[i].slot && rows[i + nr].pos == rows[i].pos + nr)
         ++nr;
       for (int ch = 0; ch < nchunk[i + nr - 1]; ++ch) {
         blk[4 * n_blocks] = i;

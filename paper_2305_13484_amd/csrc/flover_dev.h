@@ -142,6 +142,31 @@ __device__ __forceinline__ f32x4_t act_gelu(const f32x4_t& t) {                 
   return o;
 }
 
+// ---- matrix core: D[16][16] += A[16][32] . B[32][16]
+template <int DT> __device__ __forceinline__ f32x4_t mfma16(const u32x4_t& a, const u32x4_t& b, f32x4_t c) {
+  if constexpr (DT == DT_BF16)
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
+  else
+    return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8_t, a), __builtin_bit_cast(f16x8_t, b), c, 0, 0, 0);
+}
+
+// ---- asynchronous copies to LDS
+// Barrier behind which at most N of this wave's copies are still in flight (none when `all`) and its LDS reads are done.
+// The waits are builtins outside any branch, so that the compiler knows that the fragments read before have arrived.
+template <int N> __device__ __forceinline__ void copies_barrier(bool all) {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt((N & 15) | 7 << 4 | (N >> 4) << 14);        // vmcnt(N) lgkmcnt(0)
+  if (all) __builtin_amdgcn_s_waitcnt(7 << 4 | 15 << 8);                 // vmcnt(0)
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+// 64 lanes x 16 bytes, lane i from base + off (base is wave-uniform) to l[i].  The buffer form: after the global form the
+// compiler counts later LDS reads and loads as out of order and waits for all of them.
+__device__ __forceinline__ void copy_to_lds(const char* base, uint32_t off, u32x4_t* l) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc((void*)base, (short)0, -1, 0x00020000),
+                                           (__attribute__((address_space(3))) void*)l, 16, off, 0, 0, 0);
+}
+
 // ---- cross-lane: DPP within a row of 16 lanes, LDS-permute beyond.  Every step is a fixed butterfly,
 // so a reduction's result does not depend on anything but the values reduced.
 template <int CTRL> __device__ __forceinline__ float dpp_f(float v) {

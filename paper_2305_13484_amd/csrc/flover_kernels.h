@@ -109,19 +109,19 @@ struct AttnWork {          // all device pointers
   int n_items;
   int chunk;
   int maxch;               // chunk slots per row in pml / po: at least ceil(longest row / chunk)
-  const int4* blocks = nullptr;   // pre-processing passes: (first row, rows <= prefill_rows_per_block, chunk, -)
+  const int4* blocks = nullptr;   // pre-processing passes of fp32 models: (first row, rows <= kPrefillQB, chunk, -)
   int n_blocks = 0;
   int out_mtt = 0;                // layout of the attention output: 0 row-major, else fragment order (see add_norm)
 };
-constexpr int kPrefillQB = 8;     // query rows one wave serves in a pre-processing pass (fp32 models)
-int prefill_rows_per_block(int dtype);   // rows per entry of AttnWork::blocks: 8 for fp32, 32 for the 16-bit (MFMA) kernel
+constexpr int kPrefillQB = 8;     // query rows one wave serves in a pre-processing pass of an fp32 model (an entry of blocks)
 int attn_chunk();   // positions per wave task; fixed for the process, so chunking depends on a request's own length only
 // ev0 / ev1 (optional) take the start / end time stamps of the streaming kernel's dispatch (the merge kernel follows).
 hipError_t decode_attention(int dtype, int d, const void* q, const void* kc, const void* vc, const AttnWork& w, int M,
                             int nh, int Smax, void* out, hipStream_t st, hipEvent_t ev0 = nullptr,
                             hipEvent_t ev1 = nullptr);
 
-// Attention of a pre-processing pass: rows listed in w.blocks are runs of consecutive positions of one slot.
+// Attention of a pre-processing pass: all M rows are consecutive positions of one slot (fp32: as listed in w.blocks, through
+// the partial results; 16-bit: w.items, blocks, pml and po are not used).
 hipError_t prefill_attention(int dtype, int d, const void* q, const void* kc, const void* vc, const AttnWork& w, int M,
                              int nh, int Smax, void* out, hipStream_t st);
 

@@ -332,190 +332,183 @@ __global__ __launch_bounds__(256) void attn_prefill_kernel(const void* __restric
   }
 }
 
-// ---------------------------------------------------------------- pre-processing variant on the matrix cores
-// 16-bit models: a wave serves 32 consecutive query rows (two tiles of 16) and walks its chunk 32 keys at a time.
-//   scores   S^T[key][query] = K . Q^T   : A = K rows (a lane's 16 bytes of a cache row are 8 consecutive d of one
-//                                          key), B = Q^T (8 consecutive d of one query) -- both straight from memory;
+// ---------------------------------------------------------------- context passes on the matrix cores
+// 16-bit models.  The rows of a pass are consecutive positions of ONE slot; a block serves 64 of them for one
+// head, a wave 16, and walks all the keys they may see, 32 at a time, so nothing is left to merge.  K and V of the
+// next three steps are on their way to LDS by asynchronous copies (a ring of four steps), shared by the block's waves.
+//   scores   S^T[key][query] = K . Q^T   : A = K rows (a lane's 16 bytes are 8 consecutive d of one key; copied in that
+//                                          order), B = Q^T (8 consecutive d of one query);
 //   softmax  per query = per output column: 8 values in the lane, then the 4 lane groups (2 shuffles);
 //   output   O^T[d][query] += V^T . P^T  : B = P^T is what the lane already holds from S^T (keys 4g..4g+3 of both
-//            16-key tiles = its 8 k-slots), A = V^T needs 8 keys of one d per lane: the V rows are staged in LDS
-//            (wave-private, row stride D + 8 elements: 16-byte aligned and conflict-free) and read back transposed.
+//            16-key tiles = its 8 k-slots), A = V^T by transposing LDS reads (ds_read_b64_tr_b16: 16 lanes give the
+//            addresses of 4 keys x 16 d and get 4 keys of one d each).  V rows lie in LDS with their 16-byte pieces
+//            permuted by key, so that the 16 keys of a read spread over the banks.
 // P enters the second product as two 16-bit terms (value + rounding remainder), i.e. with 16 or more significant bits;
-// m, l and the accumulators stay fp32.  Same chunking, partial layout and merge kernel as the other variants.     grid = (n_blocks, n_head / 4), block = 256 (a wave per head).
-constexpr int kPrefillMfmaQB = 32;
+// m, l and the accumulators stay fp32.
+// What bounds it: the chain of a step (LDS read, product, softmax, LDS read, product) at the few wavefronts a pass offers,
+// hence 16 queries per wave: 32 halve the LDS reads per multiplication but also the blocks (943 rows x 32 heads: 75 us
+// against 43; key chunks per wave with a merge launch, V through 2-byte LDS reads: 38 + 15).  290 rows x 16 heads: 16.4 us
+// and a merge of 5.2 -> 11.9 us.
 template <int DT> __device__ __forceinline__ uint32_t pack2(float a, float b) {
   if constexpr (DT == DT_BF16) return (uint32_t)f32_to_bf16(a) | ((uint32_t)f32_to_bf16(b) << 16);
   else return (uint32_t)f32_to_f16(a) | ((uint32_t)f32_to_f16(b) << 16);
 }
-template <int DT> __device__ __forceinline__ f32x4_t mfma_kq(const u32x4_t& a, const u32x4_t& b, f32x4_t c) {
-  if constexpr (DT == DT_BF16)
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
-  else
-    return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8_t, a), __builtin_bit_cast(f16x8_t, b), c, 0, 0, 0);
+// Four V^T operands (8 keys of 16 d each) by transposing reads; a[i]: this lane's LDS address of operand i, the second
+// 16 keys lie HI bytes further.  Written out with its own wait: after the builtin's form the compiler waits for every copy
+// to LDS in flight.
+template <int HI> __device__ __forceinline__ void read_transposed4(const uint32_t (&a)[4], u32x4_t (&v)[4]) {
+  uint2 x[4], y[4];
+  asm volatile("ds_read_b64_tr_b16 %0, %8\n\tds_read_b64_tr_b16 %4, %8 offset:%12\n\t"
+               "ds_read_b64_tr_b16 %1, %9\n\tds_read_b64_tr_b16 %5, %9 offset:%12\n\t"
+               "ds_read_b64_tr_b16 %2, %10\n\tds_read_b64_tr_b16 %6, %10 offset:%12\n\t"
+               "ds_read_b64_tr_b16 %3, %11\n\tds_read_b64_tr_b16 %7, %11 offset:%12\n\t"
+               "s_waitcnt lgkmcnt(0)"
+               : "=&v"(x[0]), "=&v"(x[1]), "=&v"(x[2]), "=&v"(x[3]), "=&v"(y[0]), "=&v"(y[1]), "=&v"(y[2]), "=&v"(y[3])
+               : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "n"(HI)
+               : "memory");
+#pragma unroll
+  for (int i = 0; i < 4; ++i) v[i] = u32x4_t{x[i].x, x[i].y, y[i].x, y[i].y};
 }
 
+// permutation of a V row's 16-byte pieces (pairs stay together): 8 consecutive keys put the same pair in 8 places
+template <int D> __device__ __forceinline__ int swizzle(int key) { return D == 128 ? (key & 7) * 2 : ((key >> 1) & 3) * 2; }
+
 template <int DT, int D>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_prefill_mfma_kernel(const void* __restrict__ q, const void* __restrict__ kc,
-                                                                const void* __restrict__ vc,
-                                                                const int4* __restrict__ blocks,
-                                                                const int* __restrict__ row_slot,
-                                                                const int* __restrict__ row_len, int nh, int Smax,
-                                                                int chunk, int maxch, float scale,
-                                                                float* __restrict__ pml, float* __restrict__ po) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void attn_context_kernel(
+    const uint16_t* __restrict__ q, const char* __restrict__ kc, const char* __restrict__ vc, const int* __restrict__ row_slot,
+    const int* __restrict__ row_len, int M, int nh, int Smax, int nrb, float scale, void* __restrict__ out, int mtt) {
   static_assert(DT != DT_F32, "16-bit models only");
-  constexpr int QT = kPrefillMfmaQB / 16;   // query tiles per wave
   constexpr int KS = D / 32;                // MFMA steps over the head dimension
   constexpr int DTL = D / 16;               // output tiles over the head dimension
-  constexpr int VSTR = D + 8;               // LDS row stride (elements)
-  constexpr int LPRV = D / 8;               // lanes per V row when staging (16 bytes each)
-  constexpr int RPL = 64 / LPRV;            // V rows per wave load
-  __shared__ __attribute__((aligned(16))) uint16_t vlds[4][32 * VSTR];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  constexpr int SEG = D / 8;                // 16-byte pieces of a row
+  constexpr int RING = 4, F = D / 32;       // copies per wave and step: 2 * KS fragments of K and as many KiB of V by 4 waves
+  __shared__ __attribute__((aligned(1024))) u32x4_t lds[RING][2][32 * SEG];   // [step][K fragments | V rows]
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int g = lane >> 4, n = lane & 15;
-  const int4 bk = blocks[blockIdx.x];
-  const int first = bk.x, nr = bk.y, ch = bk.z;
-  const int hd = blockIdx.y * 4 + wave;
-  const int slot = row_slot[first];
-  const int len0 = row_len[first];                          // rows are consecutive positions: len_i = len0 + i
-  const int j0 = ch * chunk, j1 = min(len0 + nr - 1, j0 + chunk);
-  uint16_t* vl = vlds[wave];
+  // heads go round the XCDs, so that a head's K and V stay in one L2; the blocks with the most keys start first
+  const int qq = blockIdx.x >> 3, hd = (qq / nrb) * 8 + (blockIdx.x & 7), rb = nrb - 1 - qq % nrb;
+  if (hd >= nh) return;
+  const int slot = row_slot[0], len0 = row_len[0];         // row r attends to keys 0 .. len0 + r - 1
+  const int first = rb * 64 + wave * 16;                   // the wave's rows
+  const int klen = len0 + min(M, (rb + 1) * 64) - 1;   // keys of the block's last row
+  const int wlen = first < M ? len0 + min(M, first + 16) - 1 : 0;   // of the wave's last row
+  const int T = (klen + 31) >> 5;
+  const size_t head_off = ((size_t)slot * nh + hd) * Smax * D * 2;
+  const char *kb = kc + head_off, *vb = vc + head_off;
 
-  u32x4_t qf[QT][KS];
+  auto issue = [&](int t) {                                 // rows past the last key repeat it (masked below)
+    u32x4_t(*buf)[32 * SEG] = lds[t % RING];
 #pragma unroll
-  for (int t = 0; t < QT; ++t) {
-    const int r = first + min(t * 16 + n, nr - 1);
-    const uint16_t* qr = (const uint16_t*)q + (size_t)(r * nh + hd) * D + g * 8;
+    for (int j = 0; j < F / 2; ++j) {
+      const int f = wave + 4 * j;                           // K fragment: 16 keys x 32 d
+      const int key = min(t * 32 + (f / KS) * 16 + n, klen - 1);
+      copy_to_lds(kb, (uint32_t)key * D * 2 + (f % KS) * 64 + g * 16, buf[0] + f * 64);
+    }
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) qf[t][ks] = *(const u32x4_t*)(qr + ks * 32);
-  }
-  const size_t head_off = ((size_t)slot * nh + hd) * Smax * D;
-  const uint16_t* kb = (const uint16_t*)kc + head_off;
-  const uint16_t* vb = (const uint16_t*)vc + head_off;
-
-  f32x4_t oacc[DTL][QT];
-  float m[QT], l[QT];
+    for (int j = 0; j < F / 2; ++j) {
+      const int u = (wave + 4 * j) * 64 + lane, kr = u / SEG;   // V piece: key kr of the step, place u % SEG
+      const int seg = (u % SEG) ^ swizzle<D>(kr);
+      copy_to_lds(vb, (uint32_t)min(t * 32 + kr, klen - 1) * D * 2 + seg * 16, buf[1] + (wave + 4 * j) * 64);
+    }
+  };
+  // the 8 bytes of V this lane addresses for the first operand: key 4g + n/4, d 4 * (n % 4); 16 d further is a flip of the
+  // piece's bits above bit 0 (the places of a row's pieces are permuted by an exclusive or as well)
+  const int vk = 4 * g + (n >> 2);
+  const uint32_t vaddr = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds[0][1] +
+                         (uint32_t)((vk * SEG + (((n & 3) >> 1) ^ swizzle<D>(vk))) * 16 + (n & 1) * 8);
+  u32x4_t qf[KS];
+  const uint16_t* qr = q + ((size_t)min(first + n, M - 1) * nh + hd) * D + g * 8;
 #pragma unroll
-  for (int t = 0; t < QT; ++t) {
-    m[t] = -INFINITY;
-    l[t] = 0.f;
+  for (int ks = 0; ks < KS; ++ks) qf[ks] = *(const u32x4_t*)(qr + ks * 32);
+  f32x4_t oacc[DTL];
+  float m = -INFINITY, l = 0.f;
+  const int lim = first + n < M ? len0 + first + n : 0;     // causal: key < lim
 #pragma unroll
-    for (int dt = 0; dt < DTL; ++dt) oacc[dt][t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-  }
-
-  for (int jb = j0; jb < j1; jb += 32) {
-    // K rows as the A operand, V rows to LDS (rows past the chunk repeat its last row; they are masked below)
-    u32x4_t kf[2][KS], vr[32 / RPL];
+  for (int dt = 0; dt < DTL; ++dt) oacc[dt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int t = 0; t < RING - 1; ++t)
+    if (t < T) issue(t);
+  for (int t = 0; t < T; ++t) {
+    copies_barrier<F * (RING - 2)>(t + RING - 2 >= T);      // step t has landed; every wave is done with step t - 1
+    if (t + RING - 1 < T) issue(t + RING - 1);
+    const int jb = t * 32;
+    if (jb >= wlen) continue;                               // wave-uniform: none of its rows sees these keys
+    const u32x4_t* kl = lds[t % RING][0] + lane;
+    u32x4_t kf[2][KS];
+#pragma unroll
+    for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) kf[kt][ks] = kl[(kt * KS + ks) * 64];
+    // scores: rows = keys kt*16 + 4g + r, column = query n
+    f32x4_t sacc[2];
 #pragma unroll
     for (int kt = 0; kt < 2; ++kt) {
-      const uint16_t* kr = kb + (size_t)min(jb + kt * 16 + n, j1 - 1) * D + g * 8;
+      sacc[kt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) kf[kt][ks] = *(const u32x4_t*)(kr + ks * 32);
+      for (int ks = 0; ks < KS; ++ks) sacc[kt] = mfma16<DT>(kf[kt][ks], qf[ks], sacc[kt]);
     }
+    float sc[8];
+    float tmax = -INFINITY;
 #pragma unroll
-    for (int i = 0; i < 32 / RPL; ++i) {
-      const int row = i * RPL + lane / LPRV;
-      vr[i] = *(const u32x4_t*)(vb + (size_t)min(jb + row, j1 - 1) * D + (lane % LPRV) * 8);
-    }
-    __builtin_amdgcn_wave_barrier();          // the previous block's transposed reads come before these writes
+    for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
-    for (int i = 0; i < 32 / RPL; ++i) {
-      const int row = i * RPL + lane / LPRV;
-      *(u32x4_t*)(vl + row * VSTR + (lane % LPRV) * 8) = vr[i];
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-
-    // scores: rows = keys kt*16 + 4g + r, column = query n of tile t
-    u32x4_t pb[QT], pl[QT];
-#pragma unroll
-    for (int t = 0; t < QT; ++t) {
-      f32x4_t sacc[2];
-#pragma unroll
-      for (int kt = 0; kt < 2; ++kt) {
-        sacc[kt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) sacc[kt] = mfma_kq<DT>(kf[kt][ks], qf[t][ks], sacc[kt]);
+      for (int r = 0; r < 4; ++r) {
+        const int key = jb + kt * 16 + 4 * g + r;
+        const float v = (key < lim) ? sacc[kt][r] * scale : -INFINITY;
+        sc[kt * 4 + r] = v;
+        tmax = fmaxf(tmax, v);
       }
-      const int qi = t * 16 + n;
-      const int lim = (qi < nr) ? min(len0 + qi, j1) : 0;        // causal: key < len_i, and inside the chunk
-      float sc[8];
-      float tmax = -INFINITY;
+    tmax = fmaxf(tmax, __shfl_xor(tmax, 16, 64));
+    tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
+    const float mn = fmaxf(m, tmax);
+    const float ms = (mn == -INFINITY) ? 0.f : mn;
+    const float alpha = __expf(m - ms);
+    float p[8], ps = 0.f;
 #pragma unroll
-      for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int key = jb + kt * 16 + 4 * g + r;
-          const float v = (key < lim) ? sacc[kt][r] * scale : -INFINITY;
-          sc[kt * 4 + r] = v;
-          tmax = fmaxf(tmax, v);
-        }
-      tmax = fmaxf(tmax, __shfl_xor(tmax, 16, 64));
-      tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
-      const float mn = fmaxf(m[t], tmax);
-      const float ms = (mn == -INFINITY) ? 0.f : mn;
-      const float alpha = __expf(m[t] - ms);
-      float p[8], ps = 0.f;
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        p[j] = __expf(sc[j] - ms);
-        ps += p[j];
-      }
-      l[t] = l[t] * alpha + ps;                                   // per-lane share; the lane groups are added at the end
-      m[t] = mn;
-#pragma unroll
-      for (int dt = 0; dt < DTL; ++dt) oacc[dt][t] *= alpha;
-      // The probabilities enter the second product as two 16-bit terms, p = hi + lo with hi = p rounded to the model
-      // dtype and lo = (p - hi) rounded: 16 significant bits for bf16 (more for fp16), so that this kernel weighs the V
-      // rows as accurately as the decode kernel's fp32 probabilities do (one term alone would add a rounding point
-      // that the decode path does not have).
-      float q_[8];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) q_[j] = p[j] - rdt<DT>(p[j]);
-      pb[t] = u32x4_t{pack2<DT>(p[0], p[1]), pack2<DT>(p[2], p[3]), pack2<DT>(p[4], p[5]), pack2<DT>(p[6], p[7])};
-      pl[t] = u32x4_t{pack2<DT>(q_[0], q_[1]), pack2<DT>(q_[2], q_[3]), pack2<DT>(q_[4], q_[5]), pack2<DT>(q_[6], q_[7])};
+    for (int j = 0; j < 8; ++j) {
+      p[j] = __expf(sc[j] - ms);
+      ps += p[j];
     }
+    l = l * alpha + ps;                                     // per-lane share; the lane groups are added at the end
+    m = mn;
+#pragma unroll
+    for (int dt = 0; dt < DTL; ++dt) oacc[dt] *= alpha;
+    // The probabilities enter the second product as two 16-bit terms, p = hi + lo with hi = p rounded to the model
+    // dtype and lo = (p - hi) rounded: 16 significant bits for bf16 (more for fp16), so that this kernel weighs the V
+    // rows as accurately as the decode kernel's fp32 probabilities do (one term alone would add a rounding point
+    // that the decode path does not have).
+    float q_[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) q_[j] = p[j] - rdt<DT>(p[j]);
+    const u32x4_t pb = u32x4_t{pack2<DT>(p[0], p[1]), pack2<DT>(p[2], p[3]), pack2<DT>(p[4], p[5]), pack2<DT>(p[6], p[7])};
+    const u32x4_t pl = u32x4_t{pack2<DT>(q_[0], q_[1]), pack2<DT>(q_[2], q_[3]), pack2<DT>(q_[4], q_[5]), pack2<DT>(q_[6], q_[7])};
     // output: A = V^T, k-slot j of lane group g <-> key 4g + j (j < 4) or 16 + 4g + (j - 4), as in pb
 #pragma unroll
-    for (int dt = 0; dt < DTL; ++dt) {
-      const uint16_t* vcol = vl + dt * 16 + n;
-      uint32_t w[4];
+    for (int d4 = 0; d4 < DTL; d4 += 4) {
+      uint32_t at[4];
 #pragma unroll
-      for (int jj = 0; jj < 4; ++jj) {
-        const int ka = (jj < 2) ? 4 * g + 2 * jj : 16 + 4 * g + 2 * (jj - 2);
-        w[jj] = (uint32_t)vcol[ka * VSTR] | ((uint32_t)vcol[(ka + 1) * VSTR] << 16);
-      }
-      const u32x4_t va = u32x4_t{w[0], w[1], w[2], w[3]};
+      for (int i = 0; i < 4; ++i) at[i] = (vaddr + (t % RING) * (uint32_t)sizeof(lds[0])) ^ ((d4 + i) * 32);
+      u32x4_t va[4];
+      read_transposed4<16 * D * 2>(at, va);
 #pragma unroll
-      for (int t = 0; t < QT; ++t) {
-        oacc[dt][t] = mfma_kq<DT>(va, pl[t], oacc[dt][t]);
-        oacc[dt][t] = mfma_kq<DT>(va, pb[t], oacc[dt][t]);
+      for (int i = 0; i < 4; ++i) {
+        oacc[d4 + i] = mfma16<DT>(va[i], pl, oacc[d4 + i]);
+        oacc[d4 + i] = mfma16<DT>(va[i], pb, oacc[d4 + i]);
       }
     }
   }
-  // partial results: lane (n, g) owns O[query n][d = dt*16 + 4g .. +3]
+  // lane (n, g) owns O[query n][d = dt*16 + 4g .. +3]
+  l += __shfl_xor(l, 16, 64);
+  l += __shfl_xor(l, 32, 64);
+  if (first + n < M) {
 #pragma unroll
-  for (int t = 0; t < QT; ++t) {
-    float lv = l[t];
-    lv += __shfl_xor(lv, 16, 64);
-    lv += __shfl_xor(lv, 32, 64);
-    const int qi = t * 16 + n;
-    const int r = first + min(qi, nr - 1);
-    if (qi < nr && ch * chunk < len0 + qi) {                     // this chunk holds keys this query may see
-      const size_t pi = ((size_t)r * maxch + ch) * nh + hd;
-#pragma unroll
-      for (int dt = 0; dt < DTL; ++dt) *(f32x4_t*)(po + pi * D + dt * 16 + 4 * g) = oacc[dt][t];
-      if (g == 0) {
-        pml[pi * 2] = m[t];
-        pml[pi * 2 + 1] = lv;
-      }
-    }
+    for (int dt = 0; dt < DTL; ++dt) stv4<DT>(out, xrow_index(first + n, hd * D + dt * 16 + 4 * g, nh * D, mtt), oacc[dt] / l);
   }
 }
 
 // ---------------------------------------------------------------- host side
 
 int attn_chunk() { return 256; }
-int prefill_rows_per_block(int dtype) { return dtype == DT_F32 ? kPrefillQB : kPrefillMfmaQB; }
 
 template <int DT, int D>
 static void launch_attn(const void* q, const void* kc, const void* vc, const AttnWork& w, int M, int nh, int Smax,
@@ -545,18 +538,20 @@ template <int DT, int D>
 static void launch_prefill(const void* q, const void* kc, const void* vc, const AttnWork& w, int M, int nh, int Smax,
                            void* out, hipStream_t st) {
   const float scale = 1.0f / sqrtf((float)D);
-  if constexpr (DT == DT_F32)
+  if constexpr (DT == DT_F32) {
     attn_prefill_kernel<DT, D, kPrefillQB><<<dim3(w.n_blocks, nh / 4), 256, 0, st>>>(
         q, kc, vc, w.blocks, w.row_slot, w.row_len, nh, Smax, w.chunk, w.maxch, scale, w.pml, w.po);
-  else
-    attn_prefill_mfma_kernel<DT, D><<<dim3(w.n_blocks, nh / 4), 256, 0, st>>>(
-        q, kc, vc, w.blocks, w.row_slot, w.row_len, nh, Smax, w.chunk, w.maxch, scale, w.pml, w.po);
-  attn_merge_kernel<DT, D><<<dim3(M, (nh * D + 1023) / 1024), 256, 0, st>>>(w.pml, w.po, w.row_len, w.chunk, w.maxch, nh, out, w.out_mtt);
+    attn_merge_kernel<DT, D><<<dim3(M, (nh * D + 1023) / 1024), 256, 0, st>>>(w.pml, w.po, w.row_len, w.chunk, w.maxch, nh, out, w.out_mtt);
+  } else {
+    const int nrb = (M + 63) / 64;
+    attn_context_kernel<DT, D><<<(nh + 7) / 8 * 8 * nrb, 256, 0, st>>>((const uint16_t*)q, (const char*)kc, (const char*)vc, w.row_slot,
+                                                                      w.row_len, M, nh, Smax, nrb, scale, out, w.out_mtt);
+  }
 }
 
 hipError_t prefill_attention(int dtype, int d, const void* q, const void* kc, const void* vc, const AttnWork& w, int M,
                              int nh, int Smax, void* out, hipStream_t st) {
-  if (M <= 0 || w.n_blocks <= 0) return hipSuccess;
+  if (M <= 0) return hipSuccess;
   if (d == 128) {
     if (dtype == DT_F32) launch_prefill<DT_F32, 128>(q, kc, vc, w, M, nh, Smax, out, st);
     else if (dtype == DT_F16) launch_prefill<DT_F16, 128>(q, kc, vc, w, M, nh, Smax, out, st);

@@ -530,6 +530,23 @@ def test_long_prompts_through_the_context_pass(make):
     ls.close()
 
 
+@pytest.mark.parametrize("make", [lambda: synth.tiny_llama(synth.DT_BF16, C=11, S=320), lambda: synth.small_llama16(synth.DT_BF16, C=11, S=320),
+                                  lambda: synth.small_gpt16(synth.DT_F16, C=11, S=320)])
+def test_context_passes_at_the_edges_of_their_blocks(make):
+    """Context rows (prompt length - 1) around the 16-row tiles, the 32-key steps and 64-row blocks of the attention and the
+    64- and 128-row blocks of the GEMMs, both head widths; first generated token against the oracle."""
+    cfg = make()
+    w = synth.make_weights(cfg, 71)
+    rng = np.random.default_rng(72)
+    rows = [1, 15, 16, 32, 33, 64, 65, 128, 129, 192, 257]
+    reqs = [synth.Request(i, 0, rng.integers(0, cfg.V, size=n + 1).astype(np.int32), 2) for i, n in enumerate(rows)]
+    ls = Lockstep(cfg, w)
+    ls.run(reqs)
+    print(cfg.name, "max rel err", ls.max_err, "ties", ls.ties)
+    assert ls.max_err <= TOL[cfg.dtype]
+    ls.close()
+
+
 def test_more_than_128_live_rows():
     """max_concurrency above one GEMM row block: 150 requests live at once (two row blocks, XCD-mapped), against the
     oracle on a tiny model, and the window bookkeeping with a large burst."""
