@@ -262,7 +262,8 @@ int32_t flover_k_attention_workspace_bytes(int32_t M, int32_t n_head, int32_t he
  * fp32 scores, softmax and accumulation, result rounded to dtype.
  * q, out [device][M][n_head][head_dim]; kcache, vcache [device][C][n_head][S][head_dim]; slot, len [host][M]
  * (1 <= len[m] <= S, 0 <= slot[m] < C); workspace [device].  The host arrays are consumed before return
- * (this call waits for its small host-to-device copy, not for the kernels). */
+ * (up to 256 rows they travel as a kernel argument; above that this call waits for its small host-to-device copy, not for
+ * the kernels). */
 int32_t flover_k_decode_attention(int32_t dtype, const void* q, const void* kcache, const void* vcache,
                                   const int32_t* slot, const int32_t* len, int32_t M, int32_t C, int32_t n_head,
                                   int32_t head_dim, int32_t S, void* out, void* workspace, uint64_t workspace_bytes,
@@ -295,8 +296,7 @@ int32_t flover_k_compact(void* cache, int32_t L, int32_t C, int32_t n_head, int3
 
 /* Weight GEMM of the fused rows: y[M][N] (fp32) = x[M][K] . W[N][K]^T, fp32 accumulation (MFMA for the 16-bit
  * dtypes).  W is first re-tiled into `w_tiled` (flover_k_gemm_tiled_bytes bytes, [device]) by flover_k_gemm_retile;
- * flover_k_gemm then streams the tiled copy.  x [device][Mpad][K]: rows up to M rounded up to a multiple of 128 (of 256 when
- * M > 128) must be readable (their contents do not matter);
+ * flover_k_gemm then streams the tiled copy.  x [device][M][K], 16-byte aligned;
  * workspace holds the split-K partial sums.  K % 32 == 0.  y == NULL leaves the result as partial sums in the
  * workspace (timing the streaming kernel alone). */
 int32_t flover_k_gemm_tiled_bytes(int32_t dtype, int32_t N, int32_t K, uint64_t* out);
@@ -318,7 +318,7 @@ int32_t flover_k_gemm(int32_t dtype, const void* x, const void* w_tiled, int32_t
  * K % 512 == 0, INVAL otherwise (the step then uses flover_k_gemm's kernels and a separate activation).
  * flover_k_gated_retile writes both matrices ([device][F][K] each) into w_tiled ([device],
  * flover_k_gemm_tiled_bytes(dtype, 2F, K) bytes) with gate and up columns interleaved in tiles of 16;
- * flover_k_gated_mlp streams that copy.  x [device][Mpad][K] row-major with the rows flover_k_gemm asks for readable;
+ * flover_k_gated_mlp streams that copy.  x [device][M][K] row-major, 16-byte aligned;
  * act [device][M][F] row-major, model dtype.
  * context_pass == 0, the fused iteration: a row's result depends on that row of x alone, not on M.  Up to 128 rows (64
  * when F > 16384) it is one launch; above that the two halves of K go through `workspace` as partial sums and the

@@ -384,16 +384,18 @@ class TiledWeight:
                                                    _stream_ptr()))
 
 
+def _aligned_rows(x: torch.Tensor) -> torch.Tensor:
+    """x itself, or a copy where its rows are strided or do not start on the 16 bytes that the kernels load at a time."""
+    x = x.contiguous()
+    return x if x.data_ptr() % 16 == 0 else x.clone()
+
+
 def k_gemm(x: torch.Tensor, W, out: Optional[torch.Tensor] = None, workspace: Optional[torch.Tensor] = None):
     """y[M][N] fp32 = x[M][K] . W[N][K]^T; W a device tensor or a TiledWeight."""
     tw = W if isinstance(W, TiledWeight) else TiledWeight(W)
     M, K = x.shape
     assert K == tw.K and _DT_OF[x.dtype] == tw.dtype
-    rows = (M + 127) // 128 * 128 if M <= 128 else (M + 255) // 256 * 256
-    xp = x
-    if M != rows:
-        xp = torch.zeros((rows, K), dtype=x.dtype, device=x.device)
-        xp[:M] = x
+    xp = _aligned_rows(x)
     if out is None:
         out = torch.empty((M, tw.N), dtype=torch.float32, device=x.device)
     if workspace is None:
@@ -426,11 +428,7 @@ def k_gated_mlp(x: torch.Tensor, gw: GatedWeight, out: Optional[torch.Tensor] = 
     context pass."""
     M, K = x.shape
     assert K == gw.K and _DT_OF[x.dtype] == gw.dtype
-    rows = (M + 127) // 128 * 128 if M <= 128 else (M + 255) // 256 * 256
-    xp = x
-    if M != rows:
-        xp = torch.zeros((rows, K), dtype=x.dtype, device=x.device)
-        xp[:M] = x
+    xp = _aligned_rows(x)
     if out is None:
         out = torch.empty((M, gw.F), dtype=x.dtype, device=x.device)
     n = C.c_uint64()

@@ -459,7 +459,7 @@ int run_rows(flover_ctx* c, Lane& ln, const Row* rows, int n, bool want_tokens, 
     added = context_pass && flk::context_add(f.dtype, ln.act, w.w2, n, p_2, ln.x, w.b2, mtt, st, &err);
     HIPCHK(c, err);
     if (!added) HIPCHK(c, timed_gemm(c, ln, FLOVER_PROF_GEMM_FF2, ln.act, w.w2, n, p_2, ss_h, mtt, gs));
-    launches += 10;
+    launches += 10 - (!context_pass && n_items == n ? 1 : 0);     // one chunk per row: nothing to merge
   }
   if (want_tokens) {
     HIPCHK(c, flk::add_norm(f.dtype, !gpt, ln.x, ln.part, c->p_2.S, ss_h, c->p_2.ldc, c->lw[L - 1].b2, c->lnf_g, c->lnf_b, ln.h, n, H,
@@ -1100,7 +1100,7 @@ int32_t flover_reorder_evict(flover_ctx* c, flover_reorder_out* out) {
         c->moves_busy[mi] = true;
         const int pi = prof_begin(c, FLOVER_PROF_COMPACT, bytes);
         if (pi >= 0) (void)hipEventRecord(c->ev[2 * pi], c->st);
-        HIPCHK(c, flk::compact(c->kv, 2 * f.n_layer, C, f.n_head, c->slot_bytes, c->d_moves, n_dev, blocks,
+        HIPCHK(c, flk::compact(c->kv, C, f.n_head, c->slot_bytes, c->d_moves, nullptr, n_dev, blocks,
                                flk::kCompactPiece, c->st));
         if (pi >= 0) (void)hipEventRecord(c->ev[2 * pi + 1], c->st);
         if (!piped) {
@@ -1217,6 +1217,18 @@ int32_t flover_k_attention_workspace_bytes(int32_t M, int32_t nh, int32_t d, int
   return FLOVER_OK;
 }
 
+// Row descriptors for the kernels' argument; returns the number of chunks.
+static int attn_rows(const int32_t* slot, const int32_t* len, int M, flk::AttnRows* r) {
+  int n_items = 0;
+  for (int i = 0; i < M; ++i) {
+    r->slot[i] = slot[i];
+    r->len[i] = len[i];
+    n_items += (len[i] + flk::attn_chunk() - 1) / flk::attn_chunk();
+  }
+  for (int i = M; i < flk::kAttnRows; ++i) r->slot[i] = r->len[i] = 0;
+  return n_items;
+}
+
 int32_t flover_k_decode_attention(int32_t dtype, const void* q, const void* kcache, const void* vcache,
                                   const int32_t* slot, const int32_t* len, int32_t M, int32_t C, int32_t nh, int32_t d,
                                   int32_t S, void* out, void* workspace, uint64_t workspace_bytes, void* stream) {
@@ -1232,27 +1244,34 @@ int32_t flover_k_decode_attention(int32_t dtype, const void* q, const void* kcac
   size_t o_items, o_pml, o_po;
   const size_t need = attn_ws_layout(M, nh, d, max_len, &o_items, &o_pml, &o_po);
   if (need > workspace_bytes) return fail(nullptr, FLOVER_E_NOMEM, "attention workspace too small");
-  std::vector<int> hs((size_t)2 * M);       // slot[M] | len[M]
-  std::vector<int> items;
-  for (int i = 0; i < M; ++i) {
-    hs[i] = slot[i];
-    hs[M + i] = len[i];
-    const int nc = (len[i] + flk::attn_chunk() - 1) / flk::attn_chunk();
-    for (int ch = 0; ch < nc; ++ch) {
-      items.push_back(i);
-      items.push_back(ch);
-      items.push_back(slot[i]);
-      items.push_back(len[i]);
-    }
-  }
   hipStream_t st = (hipStream_t)stream;
   char* ws = (char*)workspace;
-  HIPCHK(nullptr, hipMemcpyAsync(ws, hs.data(), (size_t)2 * M * 4, hipMemcpyHostToDevice, st));
-  HIPCHK(nullptr, hipMemcpyAsync(ws + o_items, items.data(), items.size() * 4, hipMemcpyHostToDevice, st));
-  HIPCHK(nullptr, hipStreamSynchronize(st));
-  int* ds = (int*)ws;
-  flk::AttnWork aw{(const int4*)(ws + o_items), ds, ds + M, (float*)(ws + o_pml), (float*)(ws + o_po),
-                   (int)items.size() / 4, flk::attn_chunk(), (max_len + flk::attn_chunk() - 1) / flk::attn_chunk()};
+  const int maxch = (max_len + flk::attn_chunk() - 1) / flk::attn_chunk();
+  flk::AttnWork aw{(const int4*)(ws + o_items), (const int*)ws, (const int*)ws + M, (float*)(ws + o_pml), (float*)(ws + o_po), 0,
+                   flk::attn_chunk(), maxch};
+  flk::AttnRows rows;
+  std::vector<int> hs, items;
+  if (M <= flk::kAttnRows) {
+    aw.n_items = attn_rows(slot, len, M, &rows);
+    aw.rows = &rows;
+  } else {                                  // slot[M] | len[M] and the (row, chunk, slot, len) work list
+    hs.resize((size_t)2 * M);
+    for (int i = 0; i < M; ++i) {
+      hs[i] = slot[i];
+      hs[M + i] = len[i];
+      const int nc = (len[i] + flk::attn_chunk() - 1) / flk::attn_chunk();
+      for (int ch = 0; ch < nc; ++ch) {
+        items.push_back(i);
+        items.push_back(ch);
+        items.push_back(slot[i]);
+        items.push_back(len[i]);
+      }
+    }
+    HIPCHK(nullptr, hipMemcpyAsync(ws, hs.data(), (size_t)2 * M * 4, hipMemcpyHostToDevice, st));
+    HIPCHK(nullptr, hipMemcpyAsync(ws + o_items, items.data(), items.size() * 4, hipMemcpyHostToDevice, st));
+    HIPCHK(nullptr, hipStreamSynchronize(st));
+    aw.n_items = (int)items.size() / 4;
+  }
   HIPCHK(nullptr, flk::decode_attention(dtype, d, q, kcache, vcache, aw, M, nh, S, out, st));
   return FLOVER_OK;
 }
@@ -1290,33 +1309,7 @@ int scratch_of_current_device(void** out) {
 }
 
 // Row descriptors travel as a kernel argument (2 KiB), so the call needs no host-to-device copy either.
-struct NoallocRows {
-  int32_t slot[kNoallocMaxRows];
-  int32_t len[kNoallocMaxRows];
-};
-
-// One block of kNoallocMaxRows threads: thread t owns row t, writes its descriptors and its (row, chunk, slot, len)
-// work items; first-item indices are an exclusive scan of the rows' chunk counts.
-__global__ __launch_bounds__(kNoallocMaxRows) void noalloc_rows_kernel(NoallocRows r, int M, int chunk, int* __restrict__ row_slot,
-                                                                       int* __restrict__ row_len, int4* __restrict__ items) {
-  __shared__ int scan[kNoallocMaxRows];
-  const int t = threadIdx.x;
-  const int slot = t < M ? r.slot[t] : 0, len = t < M ? r.len[t] : 0;
-  const int nc = (len + chunk - 1) / chunk;
-  scan[t] = nc;
-  __syncthreads();
-  for (int dlt = 1; dlt < kNoallocMaxRows; dlt <<= 1) {     // inclusive scan, log steps
-    const int v = t >= dlt ? scan[t - dlt] : 0;
-    __syncthreads();
-    scan[t] += v;
-    __syncthreads();
-  }
-  if (t >= M) return;
-  const int first = scan[t] - nc;
-  row_slot[t] = slot;
-  row_len[t] = len;
-  for (int ch = 0; ch < nc; ++ch) items[first + ch] = make_int4(t, ch, slot, len);
-}
+static_assert(kNoallocMaxRows == flk::kAttnRows, "rows of one call");
 
 }  // namespace
 
@@ -1332,16 +1325,13 @@ int32_t flover_k_decode_attention_noalloc(int32_t dtype, const void* q, const vo
   if (M > kNoallocMaxRows)
     return fail(nullptr, FLOVER_E_NOMEM, "flover_k_decode_attention_noalloc serves at most " + std::to_string(kNoallocMaxRows) +
                                              " rows per call; got " + std::to_string(M));
-  NoallocRows rows;
-  int max_len = 0, n_items = 0;
+  int max_len = 0;
   for (int i = 0; i < M; ++i) {
     if (len[i] < 1 || len[i] > S || slot[i] < 0 || slot[i] >= C) return fail(nullptr, FLOVER_E_INVAL, "slot / len out of range");
-    rows.slot[i] = slot[i];
-    rows.len[i] = len[i];
     max_len = std::max(max_len, len[i]);
-    n_items += (len[i] + flk::attn_chunk() - 1) / flk::attn_chunk();
   }
-  for (int i = M; i < kNoallocMaxRows; ++i) rows.slot[i] = rows.len[i] = 0;
+  flk::AttnRows rows;
+  const int n_items = attn_rows(slot, len, M, &rows);
   size_t o_items, o_pml, o_po;
   const size_t need = attn_ws_layout(M, nh, d, max_len, &o_items, &o_pml, &o_po);
   if (need > kNoallocScratchBytes)
@@ -1351,14 +1341,12 @@ int32_t flover_k_decode_attention_noalloc(int32_t dtype, const void* q, const vo
   int rc = scratch_of_current_device(&base);
   if (rc != FLOVER_OK) return rc;
   char* ws = (char*)base;
-  int* ds = (int*)ws;
-  hipStream_t st = (hipStream_t)stream;
   // every part of the scratch this call reads is written first by this call's own kernels: nothing has to start at zero
-  noalloc_rows_kernel<<<1, kNoallocMaxRows, 0, st>>>(rows, M, flk::attn_chunk(), ds, ds + M, (int4*)(ws + o_items));
-  HIPCHK(nullptr, hipGetLastError());
-  flk::AttnWork aw{(const int4*)(ws + o_items), ds, ds + M, (float*)(ws + o_pml), (float*)(ws + o_po),
-                   n_items, flk::attn_chunk(), (max_len + flk::attn_chunk() - 1) / flk::attn_chunk()};
-  HIPCHK(nullptr, flk::decode_attention(dtype, d, q, kcache, vcache, aw, M, nh, S, out, st));
+  flk::AttnWork aw{(const int4*)(ws + o_items), (const int*)ws, (const int*)ws + M, (float*)(ws + o_pml), (float*)(ws + o_po), n_items,
+                   flk::attn_chunk(),
+                   (max_len + flk::attn_chunk() - 1) / flk::attn_chunk()};
+  aw.rows = &rows;
+  HIPCHK(nullptr, flk::decode_attention(dtype, d, q, kcache, vcache, aw, M, nh, S, out, (hipStream_t)stream));
   return FLOVER_OK;
 }
 
@@ -1397,9 +1385,15 @@ int32_t flover_k_compact(void* cache, int32_t L, int32_t C, int32_t nh, int32_t 
   }
   if (mv.empty()) return FLOVER_OK;
   hipStream_t st = (hipStream_t)stream;
-  HIPCHK(nullptr, hipMemcpyAsync(workspace, mv.data(), mv.size() * sizeof(int4), hipMemcpyHostToDevice, st));
-  HIPCHK(nullptr, hipStreamSynchronize(st));
-  HIPCHK(nullptr, flk::compact(cache, 2 * L, C, nh, (size_t)nh * S * d * eb, workspace, (int)mv.size(), blocks,
+  flk::CompactMoves few;
+  const bool by_value = mv.size() <= (size_t)flk::CompactMoves::kMost;
+  if (by_value) {
+    std::fill(std::copy(mv.begin(), mv.end(), few.move), few.move + flk::CompactMoves::kMost, make_int4(0, 0, 0, 0));
+  } else {
+    HIPCHK(nullptr, hipMemcpyAsync(workspace, mv.data(), mv.size() * sizeof(int4), hipMemcpyHostToDevice, st));
+    HIPCHK(nullptr, hipStreamSynchronize(st));
+  }
+  HIPCHK(nullptr, flk::compact(cache, C, nh, (size_t)nh * S * d * eb, workspace, by_value ? &few : nullptr, (int)mv.size(), blocks,
                                flk::kCompactPiece, st));
   return FLOVER_OK;
 }
@@ -1443,17 +1437,31 @@ extern "C" int32_t flover_k_copy_probe(void* dst, const void* src, uint64_t byte
   return FLOVER_OK;
 }
 
-// y = sum of the split-K slices, in slice order (same order the step's consumers use)
+// y = sum of the split-K slices, in slice order (same order the step's consumers use).  grid = (ceil(N / 1024), M): four
+// consecutive columns per thread; the slices' rows are 16-byte aligned, those of y only when N is a multiple of 4.
 namespace flk {
-__global__ void slice_sum_kernel(const float* __restrict__ part, int S, size_t stride, int ldc, float* __restrict__ y, int M,
-                                 int N) {
-  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= (size_t)M * N) return;
-  const size_t m = i / N, n = i - m * N;
-  const size_t idx = m * ldc + n;
-  float v = part[idx];
-  for (int s = 1; s < S; ++s) v += part[(size_t)s * stride + idx];
-  y[i] = v;
+__global__ __launch_bounds__(256) void slice_sum_kernel(const float* __restrict__ part, int S, size_t stride, int ldc, float* __restrict__ y,
+                                                        int N) {
+  const int n = (blockIdx.x * 256 + threadIdx.x) * 4;
+  if (n >= N) return;
+  const float* p = part + (size_t)blockIdx.y * ldc + n;
+  float4 v = *(const float4*)p;
+  for (int s = 1; s < S; ++s) {
+    const float4 w = *(const float4*)(p + (size_t)s * stride);
+    v.x += w.x;
+    v.y += w.y;
+    v.z += w.z;
+    v.w += w.w;
+  }
+  float* o = y + (size_t)blockIdx.y * N + n;
+  if ((N & 3) == 0) {
+    *(float4*)o = v;
+  } else {
+    o[0] = v.x;
+    if (n + 1 < N) o[1] = v.y;
+    if (n + 2 < N) o[2] = v.z;
+    if (n + 3 < N) o[3] = v.w;
+  }
 }
 }  // namespace flk
 
@@ -1479,10 +1487,16 @@ extern "C" int32_t flover_k_gemm(int32_t dtype, const void* x, const void* w_til
   const size_t stride = (size_t)M * p.ldc;
   if ((size_t)p.S * stride * 4 > workspace_bytes) return fail(nullptr, FLOVER_E_NOMEM, "gemm workspace too small");
   hipStream_t st = (hipStream_t)stream;
-  HIPCHK(nullptr, flk::gemm(dtype, x, w_tiled, M, p, (float*)workspace, stride, 0, st));
-  if (y) {
-    const size_t total = (size_t)M * N;
-    flk::slice_sum_kernel<<<(unsigned)((total + 255) / 256), 256, 0, st>>>((const float*)workspace, p.S, stride, p.ldc, y, M, N);
+  // one slice and 16-byte aligned rows: the contraction's own stores are the result
+  const bool direct = y && p.S == 1 && N % 4 == 0 && ((uintptr_t)y & 15) == 0;
+  HIPCHK(nullptr, flk::gemm(dtype, x, w_tiled, M, p, direct ? y : (float*)workspace, stride, 0, st));
+  if (y && !direct) {
+    // grid.y is the row: at most 65535 of them per launch
+    for (int m = 0; m < M; m += 65535) {
+      const int n = std::min(M - m, 65535);
+      flk::slice_sum_kernel<<<dim3((unsigned)((N + 1023) / 1024), (unsigned)n), 256, 0, st>>>((const float*)workspace + (size_t)m * p.ldc, p.S,
+                                                                                         stride, p.ldc, y + (size_t)m * N, N);
+    }
     HIPCHK(nullptr, hipGetLastError());
   }
   return FLOVER_OK;

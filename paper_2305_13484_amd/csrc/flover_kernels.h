@@ -62,7 +62,7 @@ hipError_t retile(int dtype, const void* W, int N, int K, void* tiled, int n_off
                   int tile_step = 1);
 hipError_t zero_fill(void* p, size_t bytes, hipStream_t st);
 // part[s][m][p.ldc] (slice stride in floats) = x[M][K] . W^T over slice s of K.
-// xmtt == 0: x is row-major [gemm_rows_read(M)][K]; xmtt = ceil(M/16) (16-bit dtypes only): x is in fragment order
+// xmtt == 0: x is row-major [M][K]; xmtt = ceil(M/16) (16-bit dtypes only): x is in fragment order
 // (tiles of 16 rows x 32 k, [k-block][row tile], see xrow_index) and the buffer holds K/32 * gemm_rows_read(M)/16 tiles.
 // ev0 / ev1 (optional, here and below): take the start / end time stamps of the call's first / last dispatch.
 hipError_t gemm(int dtype, const void* x, const void* w_tiled, int M, const GemmPlan& p, float* part,
@@ -76,7 +76,7 @@ hipError_t gemm(int dtype, const void* x, const void* w_tiled, int M, const Gemm
 inline int gated_fused_rows(const GemmPlan& p) { return (p.N / 2 / 16 + 3) / 4 > 256 ? 64 : 128; }
 hipError_t gemm_gated(int dtype, const void* x, const void* w_tiled, int M, const GemmPlan& p, void* act, float* part,
                       size_t slice_stride, int xmtt, hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
-// rows of x that gemm() may read for M live rows
+// rows that a fragment-order x of M live rows must have room for (row tiles past the last may be read)
 inline int gemm_rows_read(int M) {
   return M <= 16 ? 16 : M <= 32 ? 32 : M <= 64 ? 64 : M <= 128 ? 128 : (M + 255) / 256 * 256;
 }
@@ -100,7 +100,11 @@ hipError_t logits_argmax(const float* part, int S, size_t stride, int ldp, float
                          hipStream_t st);
 
 // ---- ragged decode attention
-struct AttnWork {          // all device pointers
+constexpr int kAttnRows = 256;
+struct AttnRows {          // row descriptors of an operation-level call, passed to the kernels by value
+  int32_t slot[kAttnRows], len[kAttnRows];
+};
+struct AttnWork {          // device pointers unless stated
   const int4* items;       // [n_items] (row, chunk, slot of the row, cache rows of the row)
   const int* row_slot;     // [M]
   const int* row_len;      // [M] rows of cache attended to (>= 1)
@@ -111,6 +115,8 @@ struct AttnWork {          // all device pointers
   int maxch;               // chunk slots per row in pml / po: at least ceil(longest row / chunk)
   const int4* blocks = nullptr;   // pre-processing passes of fp32 models: (first row, rows <= kPrefillQB, chunk, -)
   int n_blocks = 0;
+  const AttnRows* rows = nullptr;   // [host] set: the rows' descriptors (at most kAttnRows rows); items and row_len are then
+                                    // room for them, n_items is the number of chunks and maxch that of the longest row
   int out_mtt = 0;                // layout of the attention output: 0 row-major, else fragment order (see add_norm)
 };
 constexpr int kPrefillQB = 8;     // query rows one wave serves in a pre-processing pass of an fp32 model (an entry of blocks)
@@ -127,7 +133,12 @@ hipError_t prefill_attention(int dtype, int d, const void* q, const void* kc, co
 
 // ---- memory shuffle copy
 constexpr int kCompactPiece = 16384;   // bytes per block
-hipError_t compact(void* cache, int planes, int C, int nh, size_t slot_bytes, const void* moves_dev, int n_moves,
+struct CompactMoves {                  // a short list passed to the kernel by value
+  static constexpr int kMost = 64;
+  int4 move[kMost];
+};
+// moves (source slot, destination slot, bytes per segment, first block) from moves_host when set, else from moves_dev
+hipError_t compact(void* cache, int C, int nh, size_t slot_bytes, const void* moves_dev, const CompactMoves* moves_host, int n_moves,
                    int total_blocks, int piece, hipStream_t st);
 
 }  // namespace flk

@@ -18,15 +18,61 @@
 
 namespace flk {
 
-// grid = (n_items, n_head / 4), block = 256: wave w handles head blockIdx.y * 4 + w of item blockIdx.x.
-// items[i] = (row, chunk, slot, len).  Writes the unnormalised partial (m, l, o[D]) of (row, chunk, head) at index
-// (row * maxch + chunk) * n_head + head: the place depends on the row and the chunk alone, so the merge kernel finds a
-// row's partials without looking anything up.
-template <int DT, int D, int U>
+// Where a launch's work comes from: a list in device memory (the fused iteration; one entry per chunk), or row
+// descriptors that travel as a kernel argument (operation-level calls of up to 256 rows: no copy to the device, no wait,
+// one launch less), where block i is chunk i / M of row i % M and rows with fewer chunks leave blocks without work (row by
+// row instead, the chunks that every row has would all meet on the same XCDs: 256 rows of up to 16 chunks 1588 us).  That
+// is for small calls: with thousands of blocks it also costs locality (the same 256 rows: 1395 us against 1350 from a
+// list), so above 1024 possible chunks a one-block kernel turns the argument into the list (3 us).
+struct ItemList {
+  const int4* items;
+  const int* row_len;
+  __device__ int4 at(int i) const { return items[i]; }
+  __device__ int len(int row) const { return row_len[row]; }
+};
+struct RowList {
+  AttnRows r;
+  int M;
+  __device__ int4 at(int i) const {
+    const int ch = i / M, row = i - ch * M;
+    return make_int4(row, ch, r.slot[row], r.len[row]);
+  }
+  __device__ int len(int row) const { return r.len[row]; }
+};
+
+// One block of kAttnRows threads: thread t owns row t, writes its length and its (row, chunk, slot, len) work items;
+// first-item indices are an exclusive scan of the rows' chunk counts.
+__global__ __launch_bounds__(kAttnRows) void attn_items_kernel(AttnRows r, int M, int chunk, int* __restrict__ row_len,
+                                                               int4* __restrict__ items) {
+  __shared__ int scan[kAttnRows];
+  const int t = threadIdx.x;
+  const int slot = t < M ? r.slot[t] : 0, len = t < M ? r.len[t] : 0;
+  const int nc = (len + chunk - 1) / chunk;
+  scan[t] = nc;
+  __syncthreads();
+  for (int dlt = 1; dlt < kAttnRows; dlt <<= 1) {     // inclusive scan, log steps
+    const int v = t >= dlt ? scan[t - dlt] : 0;
+    __syncthreads();
+    scan[t] += v;
+    __syncthreads();
+  }
+  if (t >= M) return;
+  const int first = scan[t] - nc;
+  row_len[t] = len;
+  for (int ch = 0; ch < nc; ++ch) items[first + ch] = make_int4(t, ch, slot, len);
+}
+
+// grid = (items, n_head / 4), block = 256: wave w handles head blockIdx.y * 4 + w of item blockIdx.x = (row, chunk, slot,
+// len).  Writes the unnormalised partial (m, l, o[D]) of (row, chunk, head) at index (row * maxch + chunk) * n_head + head:
+// the place depends on the row and the chunk alone, so the merge kernel finds a row's partials without looking anything up.
+// ONE: no row of the launch has a second chunk, so the wave normalises and writes the output itself (what the merge kernel
+// does with one chunk, bit for bit) and there is no merge launch.
+template <int DT, int D, int U, bool ONE, class Src>
 __global__ __launch_bounds__(256) void attn_partial_kernel(const void* __restrict__ q, const void* __restrict__ kc,
-                                                           const void* __restrict__ vc, const int4* __restrict__ items, int nh,
+                                                           const void* __restrict__ vc, Src src, int nh,
                                                            int Smax, int chunk, int maxch,
-                                                           float scale, float* __restrict__ pml, float* __restrict__ po) {
+                                                           float scale, float* __restrict__ pml, float* __restrict__ po,
+                                                           void* __restrict__ out, int mtt) {
   constexpr int EB = (DT == DT_F32) ? 4 : 2;
   constexpr int EPL = 16 / EB;          // elements per lane
   constexpr int LPR = D / EPL;          // lanes per row
@@ -34,10 +80,12 @@ __global__ __launch_bounds__(256) void attn_partial_kernel(const void* __restric
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int item = blockIdx.x;
   const int hd = blockIdx.y * 4 + wave;
-  const int4 it = items[item];          // one load: the cache addresses below depend on nothing else
+  const int4 it = src.at(item);         // one load: the cache addresses below depend on nothing else
   const int row = it.x, ch = it.y, slot = it.z, len = it.w;
   // the row's ceil(len / chunk) chunks are made equally long, so that no wave task of a row is a short remainder
-  const int nch = (len + chunk - 1) / chunk, cr = (len + nch - 1) / nch;
+  const int nch = (len + chunk - 1) / chunk;
+  if (ch >= nch) return;
+  const int cr = (len + nch - 1) / nch;
   const int j0 = ch * cr, j1 = min(len, j0 + cr);
   const int grp = lane / LPR, li = lane % LPR;
 
@@ -134,7 +182,14 @@ __global__ __launch_bounds__(256) void attn_partial_kernel(const void* __restric
     }
     m = mt;
   }
-  if (grp == 0) {
+  if (grp != 0) return;
+  if constexpr (ONE) {
+#pragma unroll
+    for (int e = 0; e < EPL; e += 4) {
+      const f32x4_t v = f32x4_t{o[e], o[e + 1], o[e + 2], o[e + 3]} + 0.f;      // the merge adds to zero (-0 becomes +0)
+      stv4<DT>(out, xrow_index(row, hd * D + li * EPL + e, nh * D, mtt), v / l);
+    }
+  } else {
     const size_t pi = ((size_t)row * maxch + ch) * nh + hd;
     float* op = po + pi * D + li * EPL;
 #pragma unroll
@@ -152,9 +207,9 @@ __global__ __launch_bounds__(256) void attn_partial_kernel(const void* __restric
 // The partials of a row sit at a place known from the row index alone, so the loads of the first four chunks go out
 // together with the load of the row's length (one memory round trip for rows of up to 4 chunks; slots of chunks the row
 // does not have are read and never used); longer rows fetch the rest in a second round.
-template <int DT, int D>
+template <int DT, int D, class Src>
 __global__ __launch_bounds__(256) void attn_merge_kernel(const float* __restrict__ pml, const float* __restrict__ po,
-                                                         const int* __restrict__ row_len, int chunk, int maxch, int nh,
+                                                         Src src, int chunk, int maxch, int nh,
                                                          void* __restrict__ out, int mtt) {
   constexpr int FIRST = 4;
   constexpr int TPH = D / 4, HPB = 256 / TPH;
@@ -171,7 +226,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const float* __restrict
     lc[j] = ml.y;
     oc[j] = ld4(po + pi * D + i);
   }
-  const int nc = (row_len[row] + chunk - 1) / chunk;
+  const int nc = (src.len(row) + chunk - 1) / chunk;
   float red_m = -INFINITY;                                    // the global maximum needs the m of every chunk
 #pragma unroll
   for (int j = 0; j < FIRST; ++j)
@@ -510,13 +565,29 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
 
 int attn_chunk() { return 256; }
 
-template <int DT, int D>
-static void launch_attn(const void* q, const void* kc, const void* vc, const AttnWork& w, int M, int nh, int Smax,
+template <int DT, int D, class Src>
+static void launch_attn(const void* q, const void* kc, const void* vc, const AttnWork& w, const Src& src, int items, int M, int nh, int Smax,
                         void* out, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
   const float scale = 1.0f / sqrtf((float)D);
-  launch_timed(attn_partial_kernel<DT, D, 4>, dim3(w.n_items, nh / 4), dim3(256), st, ev0, ev1, q, kc, vc, w.items, nh, Smax,
-               w.chunk, w.maxch, scale, w.pml, w.po);
-  attn_merge_kernel<DT, D><<<dim3(M, (nh * D + 1023) / 1024), 256, 0, st>>>(w.pml, w.po, w.row_len, w.chunk, w.maxch, nh, out, w.out_mtt);
+  const dim3 grid(items, nh / 4);
+  if (w.n_items == M) {        // one chunk per row
+    launch_timed(attn_partial_kernel<DT, D, 4, true, Src>, grid, dim3(256), st, ev0, ev1, q, kc, vc, src, nh, Smax, w.chunk, w.maxch,
+                 scale, w.pml, w.po, out, w.out_mtt);
+    return;
+  }
+  launch_timed(attn_partial_kernel<DT, D, 4, false, Src>, grid, dim3(256), st, ev0, ev1, q, kc, vc, src, nh, Smax, w.chunk, w.maxch, scale,
+               w.pml, w.po, out, w.out_mtt);
+  attn_merge_kernel<DT, D, Src><<<dim3(M, (nh * D + 1023) / 1024), 256, 0, st>>>(w.pml, w.po, src, w.chunk, w.maxch, nh, out, w.out_mtt);
+}
+template <int DT, int D>
+static void launch_attn(const void* q, const void* kc, const void* vc, const AttnWork& w, int M, int nh, int Smax, void* out,
+                        hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
+  if (w.rows && M * w.maxch <= 1024) {
+    launch_attn<DT, D>(q, kc, vc, w, RowList{*w.rows, M}, M * w.maxch, M, nh, Smax, out, st, ev0, ev1);
+    return;
+  }
+  if (w.rows) attn_items_kernel<<<1, kAttnRows, 0, st>>>(*w.rows, M, w.chunk, (int*)w.row_len, (int4*)w.items);
+  launch_attn<DT, D>(q, kc, vc, w, ItemList{w.items, w.row_len}, w.n_items, M, nh, Smax, out, st, ev0, ev1);
 }
 
 hipError_t decode_attention(int dtype, int d, const void* q, const void* kc, const void* vc, const AttnWork& w, int M,
@@ -541,7 +612,8 @@ static void launch_prefill(const void* q, const void* kc, const void* vc, const 
   if constexpr (DT == DT_F32) {
     attn_prefill_kernel<DT, D, kPrefillQB><<<dim3(w.n_blocks, nh / 4), 256, 0, st>>>(
         q, kc, vc, w.blocks, w.row_slot, w.row_len, nh, Smax, w.chunk, w.maxch, scale, w.pml, w.po);
-    attn_merge_kernel<DT, D><<<dim3(M, (nh * D + 1023) / 1024), 256, 0, st>>>(w.pml, w.po, w.row_len, w.chunk, w.maxch, nh, out, w.out_mtt);
+    attn_merge_kernel<DT, D, ItemList><<<dim3(M, (nh * D + 1023) / 1024), 256, 0, st>>>(w.pml, w.po, ItemList{w.items, w.row_len}, w.chunk, w.maxch,
+                                                                                     nh, out, w.out_mtt);
   } else {
     const int nrb = (M + 63) / 64;
     attn_context_kernel<DT, D><<<(nh + 7) / 8 * 8 * nrb, 256, 0, st>>>((const uint16_t*)q, (const char*)kc, (const char*)vc, w.row_slot,
@@ -569,16 +641,25 @@ hipError_t prefill_attention(int dtype, int d, const void* q, const void* kc, co
 // moves[i] = (src slot, dst slot, bytes per segment = len * d * elem, first block index).
 // Sources lie outside the chosen window and destinations are holes inside it, so the two sets are disjoint and
 // the copies can run in any order.
-__global__ __launch_bounds__(256) void compact_kernel(char* __restrict__ cache, const int4* __restrict__ moves, int n_moves,
-                                                      int nseg_per_slot, int C, size_t slot_bytes, int piece) {
+// The list is in device memory, or (operation-level calls of up to 64 moves) a kernel argument: no copy and no wait for it.
+struct MoveList {
+  const int4* moves;
+  __device__ int4 at(int i) const { return moves[i]; }
+};
+struct MoveArgs {
+  CompactMoves m;
+  __device__ int4 at(int i) const { return m.move[i]; }
+};
+template <class Src>
+__global__ __launch_bounds__(256) void compact_kernel(char* __restrict__ cache, Src moves, int n_moves, int nseg_per_slot, int C, size_t slot_bytes, int piece) {
   // binary search: last move whose first block <= blockIdx.x
   int lo = 0, hi = n_moves - 1;
   const int b = blockIdx.x;
   while (lo < hi) {
     const int mid = (lo + hi + 1) >> 1;
-    if (moves[mid].w <= b) lo = mid; else hi = mid - 1;
+    if (moves.at(mid).w <= b) lo = mid; else hi = mid - 1;
   }
-  const int4 mv = moves[lo];
+  const int4 mv = moves.at(lo);
   const int bytes = mv.z;
   const int ppseg = (bytes + piece - 1) / piece;
   const int rel = b - mv.w;
@@ -597,11 +678,11 @@ __global__ __launch_bounds__(256) void compact_kernel(char* __restrict__ cache, 
   }
 }
 
-hipError_t compact(void* cache, int planes, int C, int nh, size_t slot_bytes, const void* moves_dev, int n_moves,
+hipError_t compact(void* cache, int C, int nh, size_t slot_bytes, const void* moves_dev, const CompactMoves* moves_host, int n_moves,
                    int total_blocks, int piece, hipStream_t st) {
   if (n_moves <= 0 || total_blocks <= 0) return hipSuccess;
-  (void)planes;
-  compact_kernel<<<total_blocks, 256, 0, st>>>((char*)cache, (const int4*)moves_dev, n_moves, nh, C, slot_bytes, piece);
+  if (moves_host) compact_kernel<<<total_blocks, 256, 0, st>>>((char*)cache, MoveArgs{*moves_host}, n_moves, nh, C, slot_bytes, piece);
+  else compact_kernel<<<total_blocks, 256, 0, st>>>((char*)cache, MoveList{(const int4*)moves_dev}, n_moves, nh, C, slot_bytes, piece);
   return hipGetLastError();
 }
 

@@ -82,8 +82,9 @@ __global__ __launch_bounds__(256) void gemm16_direct_kernel(const uint16_t* __re
   const u32x4_t* wp = wt + ((size_t)g * KB) * NT * 64 + lane;                    // + (kb*NT + t)*64
   // rows' operand: row-major [M][K] (xmtt == 0) or fragment order with xmtt row tiles per k-block
   const size_t tstride = xmtt ? 512 : (size_t)16 * K, kstride = xmtt ? (size_t)xmtt * 512 : 32;
+  static_assert(MT == 1, "row-major rows past M repeat the last one, here for one tile");
   const uint16_t* xp = xmtt ? x + (size_t)(m0 >> 4) * 512 + lane * 8
-                            : x + (size_t)(m0 + (lane & 15)) * K + (lane >> 4) * 8;     // + i*tstride + kb*kstride
+                            : x + (size_t)min(m0 + (lane & 15), M - 1) * K + (lane >> 4) * 8;     // + i*tstride + kb*kstride
 
   u32x4_t bq[PFW][NT], aq[PFA][MT];
   static_assert(PFW == PFA, "both rings turn together");
@@ -176,10 +177,16 @@ __global__ __launch_bounds__(64 * GPB * (NT / NTW)) void gemm16_lds_kernel(const
     for (int t = 0; t < NTW; ++t) acc[i][t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
   const u32x4_t* wp = wt + (((size_t)gl * KB) * NT + sub * NTW) * 64 + lane;     // + (kb*NT + t)*64
-  // rows' operand: row-major [M][K] (xmtt == 0) or fragment order with xmtt row tiles per k-block
-  const size_t tstride = xmtt ? 512 : (size_t)16 * K, kstride = xmtt ? (size_t)xmtt * 512 : 32;
-  const uint16_t* xp = xmtt ? x + (size_t)(m0 >> 4) * 512 + lane * 8
-                            : x + (size_t)(m0 + (lane & 15)) * K + (lane >> 4) * 8;     // + i*tstride + kb*kstride
+  // rows' operand: row-major [M][K] (xmtt == 0; rows past M repeat the last one) or fragment order with xmtt row tiles per
+  // k-block; xo: where the wave's j-th fragment of a chunk is, relative to the block's rows
+  const size_t kstride = xmtt ? (size_t)xmtt * 512 : 32;
+  const uint16_t* xp = x + (xmtt ? (size_t)(m0 >> 4) * 512 : (size_t)m0 * K);
+  uint32_t xo[FPW];
+#pragma unroll
+  for (int j = 0; j < FPW; ++j) {
+    const int i = min(wave + NW * j, KC * MT - 1) % MT;
+    xo[j] = xmtt ? (uint32_t)(i * 512 + lane * 8) : (uint32_t)min(i * 16 + (lane & 15), M - 1 - m0) * K + (lane >> 4) * 8;
+  }
 
   u32x4_t bq[PF][NTW], areg[FPW];
 #pragma unroll
@@ -191,9 +198,9 @@ __global__ __launch_bounds__(64 * GPB * (NT / NTW)) void gemm16_lds_kernel(const
   auto load_a = [&](int chunk) {      // one fragment = 16 rows x 64 B per wave load
 #pragma unroll
     for (int j = 0; j < FPW; ++j) {
-      const int f = min(wave + NW * j, KC * MT - 1), kc = f / MT, i = f - kc * MT;
+      const int kc = min(wave + NW * j, KC * MT - 1) / MT;
       const int kk = min(kb0 + chunk * KC + kc, kb1 - 1);
-      areg[j] = *(const u32x4_t*)(xp + i * tstride + kk * kstride);
+      areg[j] = *(const u32x4_t*)(xp + xo[j] + kk * kstride);
     }
   };
   auto store_a = [&](int buf) {      // surplus waves store the last fragment once more (same data, no branch)
@@ -294,8 +301,13 @@ __global__ __launch_bounds__(128 * GPB) void gated_lds_kernel(const uint16_t* __
     for (int t = 0; t < 2; ++t) acc[i][t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
   const u32x4_t* wp = wt + ((size_t)gl * KB) * 2 * 64 + lane;                    // + (kb*2 + t)*64
-  const size_t tstride = xmtt ? 512 : (size_t)16 * K, kstride = xmtt ? (size_t)xmtt * 512 : 32;
-  const uint16_t* xp = xmtt ? x + lane * 8 : x + (size_t)(lane & 15) * K + (lane >> 4) * 8;   // + i*tstride + kb*kstride
+  const size_t kstride = xmtt ? (size_t)xmtt * 512 : 32;
+  uint32_t xo[FPW];                              // where the wave's j-th fragment of a chunk is; row-major rows past M repeat the last one
+#pragma unroll
+  for (int j = 0; j < FPW; ++j) {
+    const int i = min(gw + GPB * j, KC * MT - 1) % MT;
+    xo[j] = xmtt ? (uint32_t)(i * 512 + lane * 8) : (uint32_t)min(i * 16 + (lane & 15), M - 1) * K + (lane >> 4) * 8;
+  }
 
   u32x4_t bq[PF][2], areg[FPW];
 #pragma unroll
@@ -305,8 +317,8 @@ __global__ __launch_bounds__(128 * GPB) void gated_lds_kernel(const uint16_t* __
   auto load_a = [&](int chunk) {
 #pragma unroll
     for (int j = 0; j < FPW; ++j) {
-      const int f = min(gw + GPB * j, KC * MT - 1), kc = f / MT, i = f - kc * MT;
-      areg[j] = *(const u32x4_t*)(xp + i * tstride + (kb0 + chunk * KC + kc) * kstride);
+      const int kc = min(gw + GPB * j, KC * MT - 1) / MT;
+      areg[j] = *(const u32x4_t*)(x + xo[j] + (kb0 + chunk * KC + kc) * kstride);
     }
   };
   auto store_a = [&](int buf) {      // surplus fragments store the last one once more (same data, no branch)

@@ -91,6 +91,23 @@ def test_gemm_of_more_than_128_rows_every_block_shape(dtype, M, N, K):
     assert torch.all((got - xd @ Wd.T).abs() <= 4e-6 * (xd.abs() @ Wd.abs().T) + 1e-30)
 
 
+@pytest.mark.parametrize("dtype", [synth.DT_BF16, synth.DT_F32])
+@pytest.mark.parametrize("M,N", [(5, 96), (20, 98), (100, 128), (140, 100)])
+def test_gemm_takes_rows_as_they_are(dtype, M, N):
+    """Rows that end with the allocation, that are a strided view, and that start off the 16-byte grid give the same bits."""
+    K = 256
+    g = torch.Generator(device="cuda").manual_seed(M)
+    x = torch.randn((M, K), generator=g, device="cuda").to(TDT[dtype])
+    tw = fl.binding.TiledWeight(torch.randn((N, K), generator=g, device="cuda").to(TDT[dtype]))
+    ref = fl.k_gemm(x, tw)
+    wide = torch.zeros((M, 2 * K), dtype=x.dtype, device="cuda")
+    wide[:, :K] = x
+    flat = torch.zeros(M * K + 1, dtype=x.dtype, device="cuda")
+    flat[1:] = x.reshape(-1)
+    for other in (wide[:, :K], flat[1:].view(M, K)):
+        assert torch.equal(fl.k_gemm(other, tw), ref)
+
+
 # ---------------------------------------------------------------- gated MLP input (contraction + activation, one launch)
 
 def _gated_reference(dtype, x, Wg, Wu):
@@ -240,6 +257,21 @@ def test_attention_row_result_does_not_depend_on_other_rows():
         assert torch.equal(one[0], full[m])
 
 
+@pytest.mark.parametrize("dtype,d", [(synth.DT_BF16, 128), (synth.DT_F16, 64), (synth.DT_F32, 64)])
+def test_attention_rows_by_argument_by_list_and_by_copy_give_the_same_bits(dtype, d):
+    """300 rows take a work list copied from the host, 256 one built on the device, 20 come as a kernel argument, and rows
+    without a second chunk skip the merge: a row's result is the same in all of them."""
+    M, Cn, nh, S = 300, 301, 4, 1100
+    q, k, v, slots, lens = synth.attention_case(31, M, Cn, nh, d, S, dtype, 1, S)
+    lens[:4] = [1, 256, 257, S]
+    lens[4:20] = np.minimum(lens[4:20], 256)
+    qd, kd, vd = q.cuda(), k.cuda(), v.cuda()
+    full = fl.k_decode_attention(qd, kd, vd, slots, lens)
+    for lo, hi in ((0, 256), (0, 20), (4, 20), (3, 4), (0, 1)):
+        part = fl.k_decode_attention(qd[lo:hi].contiguous(), kd, vd, slots[lo:hi], lens[lo:hi])
+        assert torch.equal(part, full[lo:hi]), (lo, hi)
+
+
 def test_attention_benchmark_shape_sampled_pairs():
     """Config 2's shape (256 live, 32 heads, head_dim 128, lengths U{1..4096}, bf16): sampled (row, head) outputs."""
     dtype, M, Cn, nh, d, S = synth.DT_BF16, 256, 256, 32, 128, 4096
@@ -291,6 +323,21 @@ def test_compact_is_bit_exact(dtype):
     # rows >= len of the destination and all other slots stay untouched
     assert torch.equal(dev.cpu()[:, :, 3, :, 1:], cache[:, :, 3, :, 1:])
     assert torch.equal(dev.cpu()[:, :, 1], cache[:, :, 1])
+
+
+@pytest.mark.parametrize("n", [1, 64, 65])
+def test_compact_moves_by_argument_and_by_copy(n):
+    L, Cn, nh, S, d = 1, 140, 4, 24, 64
+    cache = torch.randn((L, 2, Cn, nh, S, d), generator=torch.Generator().manual_seed(n)).to(torch.bfloat16)
+    rng = np.random.default_rng(n)
+    perm = rng.permutation(Cn)
+    src, dst, ln = perm[:n].tolist(), perm[n:2 * n].tolist(), rng.integers(0, S + 1, size=n).tolist()
+    ref = cache.clone()
+    for a, b, m in zip(src, dst, ln):
+        ref[:, :, b, :, :m] = cache[:, :, a, :, :m]
+    dev = cache.cuda()
+    fl.k_compact(dev, src, dst, ln)
+    assert torch.equal(dev.cpu().view(torch.uint8), ref.view(torch.uint8))
 
 
 def test_compact_rejects_overlapping_sets_and_empty_list():
