@@ -56,7 +56,7 @@ struct Lane {
   float* x = nullptr;
   void *h = nullptr, *q = nullptr, *att = nullptr, *act = nullptr;
   float* part = nullptr;
-  int* tok_out = nullptr;
+  flk::Choice* choice = nullptr;   // [rows][parts]
   int* d_stage = nullptr;   // tok | pos | slot | len | (2 host-only arrays) | items(4x) | context-pass blocks(4x)
   float *pml = nullptr, *po = nullptr;
   // pinned host staging; a ring so that passes can be queued without waiting for the previous copy
@@ -65,8 +65,8 @@ struct Lane {
   bool staged_busy[kStageRing] = {false, false, false, false};
   int ring = 1, next = 0;
   int tok_next = 0;         // ring of token buffers: advanced only by passes that return tokens
-  int* h_tok = nullptr;     // [kStageRing][rows_cap]
-  hipEvent_t done[kStageRing] = {nullptr, nullptr, nullptr, nullptr};     // submitted iteration's tokens are in h_tok
+  flk::Choice* h_choice = nullptr;   // [kStageRing][rows_cap][parts]
+  hipEvent_t done[kStageRing] = {nullptr, nullptr, nullptr, nullptr};     // submitted iteration's choices are in h_choice
 };
 
 size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
@@ -243,7 +243,7 @@ size_t layout(flover_ctx* c, char* base) {
     ln->act = b.take((size_t)R * F * e);
     ln->part = (float*)b.take(pw * R * 4);
     c->part_floats = pw * R;
-    ln->tok_out = (int*)b.take((size_t)R * 4);
+    ln->choice = (flk::Choice*)b.take((size_t)R * flk::argmax_parts(V) * sizeof(flk::Choice));
     ln->d_stage = (int*)b.take(c->stage_ints * 4);
     ln->pml = (float*)b.take((size_t)c->max_items * f.n_head * 2 * 4);
     ln->po = (float*)b.take((size_t)c->max_items * f.n_head * f.head_dim * 4);
@@ -309,7 +309,7 @@ hipError_t timed_gemm(flover_ctx* c, Lane& ln, int kind, const void* x, const vo
 }
 
 // One pass of the decoder over n rows on lane `ln`: a single launch per operation covers all of them.
-// With want_tokens the final norm, output projection and argmax run and ln.h_tok (host) holds the choices.
+// With want_tokens the final norm, output projection and argmax run and ln.h_choice (host) holds the choices.
 // With wait the call returns after the lane's stream has drained; otherwise the pass is only enqueued.
 int run_rows(flover_ctx* c, Lane& ln, const Row* rows, int n, bool want_tokens, float* logits_out, bool context_pass,
              bool wait, int* ring_used = nullptr) {
@@ -399,14 +399,15 @@ int run_rows(flover_ctx* c, Lane& ln, const Row* rows, int n, bool want_tokens, 
   const flk::GemmPlan p_2 = context_pass ? ctx_plan(c->p_2) : c->p_2;
   const size_t ss_qkv = (size_t)n * p_qkv.ldc, ss_h = (size_t)n * p_o.ldc, ss_1 = (size_t)n * p_1.ldc,
                ss_v = (size_t)n * c->p_lm.ldc;
-  HIPCHK(c, flk::embed(f.dtype, c->wte, c->wpe, d_tok, d_pos, ln.tok_out, ln.x, n, H, st));
-  ++launches;
-  bool added = true;      // the residual stream already holds what the GEMM before the norm computed (or there was none)
+  const int parts = flk::argmax_parts(V);
+  HIPCHK(c, flk::embed_norm(f.dtype, !gpt, c->wte, c->wpe, d_tok, d_pos, ln.choice, parts, ln.x, c->lw[0].ln1_g, c->lw[0].ln1_b, ln.h, n, H,
+                            f.norm_eps, mtt, st));
+  bool added = true;      // the residual stream already holds what the GEMM before the norm computed
   for (int l = 0; l < L; ++l) {
     const LayerW& w = c->lw[l];
-    HIPCHK(c, flk::add_norm(f.dtype, !gpt, ln.x, added ? nullptr : ln.part, p_2.S, ss_h, p_2.ldc,
-                            added ? nullptr : c->lw[l - 1].b2,
-                            w.ln1_g, w.ln1_b, ln.h, n, H, f.norm_eps, mtt, st));
+    if (l > 0)
+      HIPCHK(c, flk::add_norm(f.dtype, !gpt, ln.x, added ? nullptr : ln.part, p_2.S, ss_h, p_2.ldc, added ? nullptr : c->lw[l - 1].b2,
+                              w.ln1_g, w.ln1_b, ln.h, n, H, f.norm_eps, mtt, st));
     char* kl = c->kv + (size_t)(2 * l) * c->plane_bytes;
     char* vl = kl + c->plane_bytes;
     const bool gs = gemm_iter && l == L / 2;
@@ -465,11 +466,12 @@ int run_rows(flover_ctx* c, Lane& ln, const Row* rows, int n, bool want_tokens, 
     HIPCHK(c, flk::add_norm(f.dtype, !gpt, ln.x, ln.part, c->p_2.S, ss_h, c->p_2.ldc, c->lw[L - 1].b2, c->lnf_g, c->lnf_b, ln.h, n, H,
                             f.norm_eps, mtt, st));
     HIPCHK(c, timed_gemm(c, ln, FLOVER_PROF_GEMM_LM, ln.h, c->wlm, n, c->p_lm, ss_v, mtt, gemm_iter));
-    HIPCHK(c, flk::logits_argmax(ln.part, c->p_lm.S, ss_v, c->p_lm.ldc, logits_out, ln.tok_out, n, V, st));
+    HIPCHK(c, flk::logits_argmax(ln.part, c->p_lm.S, ss_v, c->p_lm.ldc, logits_out, ln.choice, n, V, st));
     const int ti = ln.tok_next;       // at most kStageRing - 1 iterations are outstanding, so this entry is free
     ln.tok_next = (ln.tok_next + 1) % kStageRing;
     if (ring_used) *ring_used = ti;
-    HIPCHK(c, hipMemcpyAsync(ln.h_tok + (size_t)ti * R, ln.tok_out, (size_t)n * 4, hipMemcpyDeviceToHost, st));
+    HIPCHK(c, hipMemcpyAsync(ln.h_choice + (size_t)ti * R * parts, ln.choice, (size_t)n * parts * sizeof(flk::Choice), hipMemcpyDeviceToHost,
+                             st));
     if (!wait) HIPCHK(c, hipEventRecord(ln.done[ti], st));
     launches += 3;
   }
@@ -479,6 +481,12 @@ int run_rows(flover_ctx* c, Lane& ln, const Row* rows, int n, bool want_tokens, 
   }
   if (&ln == &c->step_lane) c->launches += launches;
   return FLOVER_OK;
+}
+
+// Row `row`'s token of the iteration whose choices are in ring entry `ring`.
+int token_of(const flover_ctx* c, int ring, int row) {
+  const int parts = flk::argmax_parts(c->cfg.vocab);
+  return flk::best_choice(c->step_lane.h_choice + ((size_t)ring * c->rows_cap + row) * parts, parts);
 }
 
 // Pre-processing (Section V-B): the context decoder caches K/V of prompt positions 0..P-2 in the assigned slot.
@@ -622,7 +630,7 @@ void release(flover_ctx* c) {
       if (ln->staged[i]) (void)hipEventDestroy(ln->staged[i]);
       if (ln->done[i]) (void)hipEventDestroy(ln->done[i]);
     }
-    if (ln->h_tok) (void)hipHostFree(ln->h_tok);
+    if (ln->h_choice) (void)hipHostFree(ln->h_choice);
   }
   for (int i = 0; i < kStageRing; ++i) {
     if (c->h_moves_ring[i]) (void)hipHostFree(c->h_moves_ring[i]);
@@ -708,7 +716,8 @@ int32_t flover_init(const flover_config* cfg, const flover_weights* w, flover_ct
     HIPTRY(hipHostMalloc((void**)&c->h_moves_ring[i], (size_t)cfg->max_concurrency * sizeof(int4), hipHostMallocDefault));
     HIPTRY(hipEventCreateWithFlags(&c->moves_ev[i], hipEventDisableTiming));
   }
-  HIPTRY(hipHostMalloc((void**)&c->step_lane.h_tok, (size_t)kStageRing * c->rows_cap * 4, hipHostMallocDefault));
+  HIPTRY(hipHostMalloc((void**)&c->step_lane.h_choice,
+                       (size_t)kStageRing * c->rows_cap * flk::argmax_parts(cfg->vocab) * sizeof(flk::Choice), hipHostMallocDefault));
   if (cfg->async_preprocess) {
     for (Lane& pl : c->prep_lanes) {
       HIPTRY(hipStreamCreateWithFlags(&pl.st, hipStreamNonBlocking));   // default priority
@@ -895,7 +904,7 @@ int32_t flover_step(flover_ctx* c, flover_step_out* out) {
   c->last_launches = c->launches;
   for (int j = 0; j < n; ++j) {
     Slot& s = c->slots[live[j]];
-    const int t = c->step_lane.h_tok[(size_t)ring * c->rows_cap + j];
+    const int t = token_of(c, ring, j);
     s.len += 1;
     s.generated += 1;
     s.next_token = t;
@@ -984,19 +993,18 @@ int32_t flover_step_collect(flover_ctx* c, flover_step_out* out) {
   HIPCHK(c, hipEventSynchronize(done));
   lock.lock();
   prof_collect(c, fl.ev_end);
-  const int* tok = c->step_lane.h_tok + (size_t)fl.ring * c->rows_cap;
   out->n_live = fl.n;
   for (int j = 0; j < fl.n; ++j) {
     if (out->req_id) out->req_id[j] = fl.req_id[j];
     if (out->slot) out->slot[j] = fl.slot[j];
-    if (out->token) out->token[j] = tok[j];
+    if (out->token) out->token[j] = token_of(c, fl.ring, j);
     if (out->finished) out->finished[j] = fl.fin[j];
   }
   // the host copy of each request's last token; a slot whose device-resident token was this iteration's is back on
   // host tokens (the request may have been moved by a shuffle since: found by id)
   for (Slot& s : c->slots)
     if (s.state != FLOVER_SLOT_EMPTY && s.dev_step == fl.id && s.dev_row >= 0) {
-      s.next_token = tok[s.dev_row];
+      s.next_token = token_of(c, fl.ring, s.dev_row);
       s.dev_row = -1;
     }
   c->inflight.pop_front();

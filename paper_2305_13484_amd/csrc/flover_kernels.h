@@ -82,9 +82,24 @@ inline int gemm_rows_read(int M) {
 }
 
 // ---- row-wise kernels
-// tok[m] < 0: the token is tok_prev[-1 - tok[m]] (device-resident choice of the previous iteration).
-hipError_t embed(int dtype, const void* wte, const void* wpe, const int* tok, const int* pos, const int* tok_prev,
-                 float* x, int M, int H, hipStream_t st);
+// A row's greedy choice is left in parts: the best logit of each part of the vocabulary and its column (kNoToken: none, a part
+// of NaNs); best_choice gives the token, the lowest column on ties, 0 when there is none.
+constexpr int kNoToken = 0x7fffffff;
+struct Choice {
+  float value;
+  int token;
+};
+__host__ __device__ inline int best_choice(const Choice* c, int parts) {
+  Choice b = c[0];
+  for (int p = 1; p < parts; ++p)
+    if (c[p].value > b.value || (c[p].value == b.value && c[p].token < b.token)) b = c[p];
+  return b.token == kNoToken ? 0 : b.token;
+}
+int argmax_parts(int V);
+// x = embedding of the rows (wpe: learned positions, may be null), h = the norm of it.  tok[m] < 0: the token is the best of
+// the previous iteration's choices for its row -1 - tok[m].
+hipError_t embed_norm(int dtype, bool rms, const void* wte, const void* wpe, const int* tok, const int* pos, const Choice* prev, int parts,
+                      float* x, const void* g, const void* b, void* h, int M, int H, float eps, int mtt, hipStream_t st);
 // `part` is the preceding GEMM's split-K output: S slices, `stride` floats apart, rows of `ldp` floats (ldp % 4 == 0).
 // h (and the outputs of activation and of the attention calls below) feed a GEMM: with mtt = ceil(M/16) they are
 // written in fragment order (16-bit dtypes; see gemm), with mtt == 0 row-major.
@@ -96,8 +111,7 @@ hipError_t qkv_post(int dtype, const float* part, int S, size_t stride, int ldp,
 // paired: gate and up columns of `part` interleaved in tiles of 16 (see gemm_plan_gated); gated activation only.
 hipError_t activation(int dtype, bool swiglu, const float* part, int S, size_t stride, int ldp, const void* bias, void* a,
                       int M, int F, int mtt, hipStream_t st, bool paired = false, hipEvent_t ev1 = nullptr);
-hipError_t logits_argmax(const float* part, int S, size_t stride, int ldp, float* logits, int* tok, int M, int V,
-                         hipStream_t st);
+hipError_t logits_argmax(const float* part, int S, size_t stride, int ldp, float* logits, Choice* choice, int M, int V, hipStream_t st);
 
 // ---- ragged decode attention
 constexpr int kAttnRows = 256;

@@ -4,6 +4,8 @@
 // Each consumes the split-K partial sums of the GEMM before it (added in slice order, then bias), so a GEMM's
 // epilogue lives in the next launch and nothing depends on how many rows are live.  All are HBM/L2 streaming
 // kernels: one block (or wave) per row, coalesced 4-byte-per-lane accesses, fixed reduction trees.
+#include <algorithm>
+
 #include "flover_dev.h"
 #include "flover_kernels.h"
 
@@ -47,25 +49,6 @@ __device__ __forceinline__ f32x4_t psum4(const float* __restrict__ part, int S, 
   for (int s = 16; s < S; ++s) v += ld4(p + (size_t)s * stride);
   return v;
 }
-// ---------------------------------------------------------------- embedding
-// x[m][i] = wte[tok[m]][i] (+ wpe[pos[m]][i])            grid = M, block = 256
-// tok[m] < 0 feeds the token the previous iteration chose for its row -1 - tok[m] (still on the device).
-template <int DT>
-__global__ __launch_bounds__(256) void embed_kernel(const void* __restrict__ wte, const void* __restrict__ wpe,
-                                                    const int* __restrict__ tok, const int* __restrict__ pos,
-                                                    const int* __restrict__ tok_prev, float* __restrict__ x, int H) {
-  const int m = blockIdx.x;
-  int tk = tok[m];
-  if (tk < 0) tk = tok_prev[-1 - tk];
-  const size_t t = (size_t)tk * H;
-  const size_t p = wpe ? (size_t)pos[m] * H : 0;
-  for (int i = threadIdx.x * 4; i < H; i += 1024) {
-    f32x4_t v = ldv4<DT>(wte, t + i);
-    if (wpe) v += ldv4<DT>(wpe, p + i);
-    *(f32x4_t*)(x + (size_t)m * H + i) = v;
-  }
-}
-
 // ---------------------------------------------------------------- residual add + norm
 // x[m] += sum_s part[s][m] + bias   (skipped when part == nullptr), then
 // h[m] = LayerNorm(x[m]) * g + b   (RMS == 0)   or   x[m] / rms(x[m]) * g   (RMS == 1), rounded to dtype.
@@ -76,13 +59,12 @@ __global__ __launch_bounds__(256) void embed_kernel(const void* __restrict__ wte
 // (256 threads: 3 % of the 7B stream's tokens/s less; 290 rows of 2048 columns 6.8 us against 7.8); VW = 4 above 512 rows,
 // where the rows in flight count: a compute unit holds eight of them instead of two, and the blocks fit beside another
 // stream's GEMM (940 rows of 4096 beside a second context pass: 43.7 us -> 33.8).
-template <int DT, int RMS, int VW>
-__global__ __launch_bounds__(1024 / VW) void add_norm_kernel(float* __restrict__ x, const float* __restrict__ part, int S,
-                                                             size_t stride, int ldp, const void* __restrict__ bias,
-                                                             const void* __restrict__ g, const void* __restrict__ b,
-                                                             void* __restrict__ h, int H, float eps, int mtt) {
+// update(i): the row's new elements i..i+3, stored to x where they changed.
+template <int DT, int RMS, int VW, class Update>
+__device__ __forceinline__ void norm_row(Update update, int m, const void* __restrict__ g, const void* __restrict__ b,
+                                         void* __restrict__ h, int H, float eps, int mtt) {
   __shared__ float red[2][16];
-  const int m = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   constexpr int PER = 2;
   auto column = [&](int w, int c) { return ((wave * VW + w) * 64 + lane + c * 1024) * 4; };
   // sum of one value per virtual wave and lane over the row, in an order that is the same for every VW
@@ -113,13 +95,7 @@ __global__ __launch_bounds__(1024 / VW) void add_norm_kernel(float* __restrict__
       if (i < H) {
         gv[w][c] = ldv4<DT>(g, i);                     // issued early: needed only after the reductions
         if (!RMS) bv[w][c] = ldv4<DT>(b, i);
-        f32x4_t t = *(const f32x4_t*)(x + (size_t)m * H + i);
-        if (part) {
-          f32x4_t a = psum4(part, S, stride, (size_t)m * ldp + i);
-          if (bias) a += ldv4<DT>(bias, i);
-          t += a;
-          *(f32x4_t*)(x + (size_t)m * H + i) = t;
-        }
+        const f32x4_t t = update(i);
         v[w][c] = t;
         sum[w] += RMS ? (t[0] * t[0] + t[1] * t[1]) + (t[2] * t[2] + t[3] * t[3]) : (t[0] + t[1]) + (t[2] + t[3]);
       }
@@ -155,6 +131,46 @@ __global__ __launch_bounds__(1024 / VW) void add_norm_kernel(float* __restrict__
         stv4<DT>(h, xrow_index(m, i, H, mtt), o);
       }
     }
+}
+
+template <int DT, int RMS, int VW>
+__global__ __launch_bounds__(1024 / VW) void add_norm_kernel(float* __restrict__ x, const float* __restrict__ part, int S,
+                                                             size_t stride, int ldp, const void* __restrict__ bias,
+                                                             const void* __restrict__ g, const void* __restrict__ b,
+                                                             void* __restrict__ h, int H, float eps, int mtt) {
+  const int m = blockIdx.x;
+  norm_row<DT, RMS, VW>([&](int i) {
+    f32x4_t t = *(const f32x4_t*)(x + (size_t)m * H + i);
+    if (part) {
+      f32x4_t a = psum4(part, S, stride, (size_t)m * ldp + i);
+      if (bias) a += ldv4<DT>(bias, i);
+      t += a;
+      *(f32x4_t*)(x + (size_t)m * H + i) = t;
+    }
+    return t;
+  }, m, g, b, h, H, eps, mtt);
+}
+
+// ---------------------------------------------------------------- embedding + first norm
+// x[m][i] = wte[tok[m]][i] (+ wpe[pos[m]][i]), then the norm above of that row: one launch for both (the embedding alone
+// took 4 to 5 us of every pass, nearly all of it the launch and one round trip to memory).
+// tok[m] < 0 feeds the token the previous iteration chose for its row -1 - tok[m]: the best of that row's `parts` choices.
+template <int DT, int RMS, int VW>
+__global__ __launch_bounds__(1024 / VW) void embed_norm_kernel(const void* __restrict__ wte, const void* __restrict__ wpe,
+                                                               const int* __restrict__ tok, const int* __restrict__ pos,
+                                                               const Choice* __restrict__ prev, int parts, float* __restrict__ x,
+                                                               const void* __restrict__ g, const void* __restrict__ b,
+                                                               void* __restrict__ h, int H, float eps, int mtt) {
+  const int m = blockIdx.x;
+  int tk = tok[m];
+  if (tk < 0) tk = best_choice(prev + (size_t)(-1 - tk) * parts, parts);
+  const size_t t = (size_t)tk * H, p = wpe ? (size_t)pos[m] * H : 0;
+  norm_row<DT, RMS, VW>([&](int i) {
+    f32x4_t v = ldv4<DT>(wte, t + i);
+    if (wpe) v += ldv4<DT>(wpe, p + i);
+    *(f32x4_t*)(x + (size_t)m * H + i) = v;
+    return v;
+  }, m, g, b, h, H, eps, mtt);
 }
 
 // ---------------------------------------------------------------- QKV epilogue: bias, rotary, KV append
@@ -249,40 +265,52 @@ __global__ __launch_bounds__(256) void act_kernel(const float* __restrict__ part
 }
 
 // ---------------------------------------------------------------- logits + greedy token
-// logits[m][j] = sum_s part[s][m][j] (fp32, optionally stored, row length V); tok[m] = argmax_j, lowest j on ties.
-// grid = M, block = 1024; part rows have length ldp (multiple of 4, >= V).
-__global__ __launch_bounds__(1024) void argmax_kernel(const float* __restrict__ part, int S, size_t stride, int ldp,
-                                                      float* __restrict__ logits, int* __restrict__ tok, int V) {
-  __shared__ float bv[16];
-  __shared__ int bi[16];
-  const int m = blockIdx.x;
+// logits[m][j] = sum_s part[s][m][j] (fp32, optionally stored, row length V); choice[m][p] = the largest of part p's columns,
+// lowest j on ties.  grid = (M, parts), block = 512; part rows have length ldp (multiple of 4, >= V).  A block per row left
+// the launch to one compute unit's latency and store rate (18.4 us at 23 rows x 50257, 13.0 us at 6 rows x 32000); whoever
+// needs the token picks the best of the few parts (the host, and the next iteration's embedding).
+// VEC: rows of logits are 16-byte aligned; otherwise lanes take single columns side by side.
+template <bool VEC>
+__global__ __launch_bounds__(512) void argmax_kernel(const float* __restrict__ part, int S, size_t stride, int ldp,
+                                                     float* __restrict__ logits, Choice* __restrict__ choice, int V, int per) {
+  __shared__ float bv[8];
+  __shared__ int bi[8];
+  const int m = blockIdx.x, first = blockIdx.y * per, last = min(V, first + per);
+  const float* row = part + (size_t)m * ldp;
   float best = -INFINITY;
-  int arg = 0x7fffffff;
-  for (int j0 = threadIdx.x * 4; j0 < V; j0 += 4 * 4096) {      // four strides at a time: their loads go out together
-    f32x4_t v[4];
-    if (S == 2) {          // the output projection's usual slicing: straight-line, all eight loads in flight at once
-      f32x4_t w[4];
+  int arg = kNoToken;
+  auto take = [&](float v, int j) {                            // ascending j in a thread: the first maximum stays
+    if (v > best) { best = v; arg = j; }
+  };
+  if constexpr (VEC) {
+    for (int j0 = first + threadIdx.x * 4; j0 < last; j0 += 2 * 2048) {
+      f32x4_t v[2];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const float* p = part + (size_t)m * ldp + min(j0 + u * 4096, ldp - 4);
-        v[u] = ld4(p);
-        w[u] = ld4(p + stride);
+      for (int u = 0; u < 2; ++u) v[u] = psum4(part, S, stride, (size_t)m * ldp + min(j0 + u * 2048, ldp - 4));
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const int j = j0 + u * 2048;
+        if (j >= last) continue;
+        if (logits) *(f32x4_t*)(logits + (size_t)m * V + j) = v[u];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) take(v[u][e], j + e);
       }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) v[u] += w[u];
-    } else {
-#pragma unroll
-      for (int u = 0; u < 4; ++u) v[u] = psum4(part, S, stride, (size_t)m * ldp + min(j0 + u * 4096, ldp - 4));
     }
+  } else {
+    for (int j0 = first + threadIdx.x; j0 < last; j0 += 8 * 512) {
+      float v[8];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int j = j0 + u * 4096;
+      for (int u = 0; u < 8; ++u) v[u] = row[min(j0 + u * 512, last - 1)];
+      for (int s = 1; s < S; ++s)
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if (j + e < V) {
-          if (logits) logits[(size_t)m * V + j + e] = v[u][e];
-          if (v[u][e] > best) { best = v[u][e]; arg = j + e; }      // ascending j: the first maximum stays
-        }
+        for (int u = 0; u < 8; ++u) v[u] += row[(size_t)s * stride + min(j0 + u * 512, last - 1)];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int j = j0 + u * 512;
+        if (j >= last) continue;
+        if (logits) logits[(size_t)m * V + j] = v[u];
+        take(v[u], j);
+      }
     }
   }
 #pragma unroll
@@ -294,9 +322,9 @@ __global__ __launch_bounds__(1024) void argmax_kernel(const float* __restrict__ 
   if ((threadIdx.x & 63) == 0) { bv[threadIdx.x >> 6] = best; bi[threadIdx.x >> 6] = arg; }
   __syncthreads();
   if (threadIdx.x == 0) {
-    for (int w = 1; w < 16; ++w)
+    for (int w = 1; w < 8; ++w)
       if (bv[w] > best || (bv[w] == best && bi[w] < arg)) { best = bv[w]; arg = bi[w]; }
-    tok[m] = (arg == 0x7fffffff) ? 0 : arg;       // a row of NaNs has no maximum
+    choice[(size_t)m * gridDim.y + blockIdx.y] = Choice{best, arg};
   }
 }
 
@@ -309,10 +337,17 @@ __global__ __launch_bounds__(1024) void argmax_kernel(const float* __restrict__ 
     default: { constexpr int DT = DT_BF16; CALL; } break;     \
   }
 
-hipError_t embed(int dtype, const void* wte, const void* wpe, const int* tok, const int* pos, const int* tok_prev,
-                 float* x, int M, int H, hipStream_t st) {
+hipError_t embed_norm(int dtype, bool rms, const void* wte, const void* wpe, const int* tok, const int* pos, const Choice* prev, int parts,
+                      float* x, const void* g, const void* b, void* h, int M, int H, float eps, int mtt, hipStream_t st) {
   if (M <= 0) return hipSuccess;
-  FLK_DT_SWITCH(dtype, (embed_kernel<DT><<<M, 256, 0, st>>>(wte, wpe, tok, pos, tok_prev, x, H)));
+#define FLK_EMBED(RMS, VW) \
+  FLK_DT_SWITCH(dtype, (embed_norm_kernel<DT, RMS, VW><<<M, 1024 / VW, 0, st>>>(wte, wpe, tok, pos, prev, parts, x, g, b, h, H, eps, mtt)))
+  if (M > 512) {         // as for add_norm
+    if (rms) FLK_EMBED(1, 4) else FLK_EMBED(0, 4)
+  } else {
+    if (rms) FLK_EMBED(1, 1) else FLK_EMBED(0, 1)
+  }
+#undef FLK_EMBED
   return hipGetLastError();
 }
 
@@ -354,10 +389,15 @@ hipError_t activation(int dtype, bool swiglu, const float* part, int S, size_t s
   return hipGetLastError();
 }
 
-hipError_t logits_argmax(const float* part, int S, size_t stride, int ldp, float* logits, int* tok, int M, int V,
-                         hipStream_t st) {
+// as many blocks per row as 2048 columns each, at most 8
+int argmax_parts(int V) { return std::max(1, std::min(8, (V + 2047) / 2048)); }
+
+hipError_t logits_argmax(const float* part, int S, size_t stride, int ldp, float* logits, Choice* choice, int M, int V, hipStream_t st) {
   if (M <= 0) return hipSuccess;
-  argmax_kernel<<<M, 1024, 0, st>>>(part, S, stride, ldp, logits, tok, V);
+  const int parts = argmax_parts(V), per = ((V + parts - 1) / parts + 3) / 4 * 4;
+  const dim3 grid(M, parts);
+  if (V % 4 == 0 && ((uintptr_t)logits & 15) == 0) argmax_kernel<true><<<grid, 512, 0, st>>>(part, S, stride, ldp, logits, choice, V, per);
+  else argmax_kernel<false><<<grid, 512, 0, st>>>(part, S, stride, ldp, logits, choice, V, per);
   return hipGetLastError();
 }
 

@@ -53,7 +53,7 @@ def iterations(db_path: str) -> str:
         "select name, start, end from kernels where name like '%flk%' order by start").fetchall()
     its, cur = [], []
     for n, s, e in rows:
-        if "embed_kernel" in n and cur:
+        if "embed_" in n and cur:
             its.append(cur)
             cur = []
         cur.append((n, s, e))
