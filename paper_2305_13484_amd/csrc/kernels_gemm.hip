@@ -7,7 +7,7 @@
 //     lane l holds W[n0 + l%16][k0 + 8*(l/16) .. +8], so every wave load is one contiguous, fully used 1 KiB;
 //     tiles are ordered [column group of NT n-tiles][k-block][n-tile in group], so the K slice a wave streams is
 //     one contiguous run of memory (NT KiB per k-block).
-//   * a column group (NT n-tiles: 64 columns, or 32 for matrices of at most 4096 columns) x one K slice x all rows of
+//   * a column group (NT n-tiles: 32 columns, or 64 for very wide matrices) x one K slice x all rows of
 //     a row block is the unit of work; up to 16 rows one wave takes it and reads the rows' operand straight from L2/L1
 //     (no LDS, no barriers); above that the rows' operand is staged through LDS once per block of 4 column groups and
 //     shared by the block's 4 or 8 waves.
@@ -29,6 +29,7 @@
 //     the layout so that a lane holds both; above 128 rows the same halves go through memory as two slices.
 // fp32 models (tiny configurations only) use a plain FMA kernel on the untiled matrix.
 #include <algorithm>
+#include <cmath>
 #include <type_traits>
 
 #include "flover_dev.h"
@@ -754,21 +755,33 @@ GemmPlan gemm_plan(int dtype, int N, int K) {
   }
   p.Npad = (N + 63) / 64 * 64;
   p.KB = K / 32;
-  // Everything below is a function of (N, K) only, never of the number of live rows.  A wave owns 64 columns -- 32 for
-  // matrices of at most 4096 columns, which would otherwise need 13 K slices to fill the chip -- and K is split just
-  // enough for about 800 waves (3 per CU, each streaming a contiguous run of W with a deep prefetch ring): more slices
-  // only add partial-sum traffic, for this kernel's stores and for the row-wise kernel that adds the slices up
-  // (measured on the 7B stream: 32-column waves for out-proj and FFN-down + 2 % tokens/s, for the wider matrices - 2 %).
-  p.NT = p.Npad / 64 <= 64 ? 2 : 4;
-  const int ngroups = p.Npad / (16 * p.NT);
-  const int target = 800;
-  int S = (target + ngroups / 2) / ngroups;
-  int maxS = std::min(16, p.KB / 8);
-  if (maxS < 1) maxS = 1;
-  if (S > maxS) S = maxS;
-  if (S < 1) S = 1;
-  p.kbs = (p.KB + S - 1) / S;
-  p.S = (p.KB + p.kbs - 1) / p.kbs;
+  // Everything below is a function of (N, K) only, never of the number of live rows.  Column groups of 32 (NT = 2) or 64
+  // columns and S slices of K are chosen together, for the least time of a launch and of the kernel that reads the slices
+  // back, averaged over row counts of 6 to 100 (mean 47): a block of four groups walks its k-blocks at one latency each
+  // and all blocks share the memory rate, so more slices shorten the walk, cost their sums once to write and once to
+  // read, and must not start a second round on the 256 compute units; slices that begin at the same power of two meet in
+  // the same memory channels.  Fitted to 900 launches (16 shapes from 512 x 512 to 50257 x 2048 and 6656 x 17920, cold
+  // weights, both widths, 1 to 16 slices; 11-13 % rms).  Against a fixed count of 800 wavefronts and 64-column groups above
+  // 4096 columns, sums counted, at 6 / 23 / 60 / 100 rows: 6144 x 2048 (8 slices -> 3, 32 columns) 8.1 / 9.6 / 14.2 / 18.7 ->
+  // 6.7 / 8.3 / 10.4 / 13.6 us, 12288 x 4096 (4 -> 2, 32 columns) 18.7 / 20.3 / 25.1 / 30.0 -> 17.9 / 18.8 / 22.1 / 27.5.
+  double best = 0.0;
+  for (int NT = 2; NT <= 4; NT += 2) {
+    const int per_slice = (p.Npad / (16 * NT) + 3) / 4;
+    for (int S = 1; S <= 16; ++S) {
+      const int kbs = (p.KB + S - 1) / S;
+      if (S > 1 && (kbs < 4 || (p.KB + kbs - 1) / kbs != S || per_slice * S > 256)) continue;
+      const double walk = (NT == 2 ? 0.195 : 0.338) * kbs * ((per_slice * S + 255) / 256);
+      const double stream = (NT == 2 ? 0.111 : 0.153) * p.Npad * K * 2e-6 * (S > 1 && kbs % 16 == 0 ? 1.1 : 1.0);
+      const double cost = (NT == 2 ? 2.6 + std::sqrt(walk * walk + stream * stream) : 3.35 + std::max(walk, stream)) +
+                          (0.4 + 0.25) * S * 47 * p.ldc * 4e-6;
+      if (p.S == 0 || cost < best) {
+        best = cost;
+        p.NT = NT;
+        p.S = S;
+        p.kbs = kbs;
+      }
+    }
+  }
   return p;
 }
 
