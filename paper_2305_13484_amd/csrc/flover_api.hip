@@ -297,16 +297,18 @@ void prof_collect(flover_ctx* c, size_t upto = (size_t)-1) {
     c->ev_base += 1;
   }
 }
-// `sampled`: this launch is one of those level 1 times (level 2 times every launch).
-// gated_out: the plan is a paired gate|up plan and the launch is the fused one that writes the activation there.
-hipError_t timed_gemm(flover_ctx* c, Lane& ln, int kind, const void* x, const void* w, int n, const flk::GemmPlan& p,
-                      size_t ss, int mtt, bool sampled, void* gated_out = nullptr) {
-  const int64_t bytes = (int64_t)flk::gemm_tiled_bytes(c->cfg.dtype, p.N, p.K);
-  const int pi = (&ln == &c->step_lane && c->prof_now && (sampled || c->profile >= 2)) ? prof_begin(c, kind, bytes) : -1;
-  hipEvent_t ev0 = pi >= 0 ? c->ev[2 * pi] : nullptr, ev1 = pi >= 0 ? c->ev[2 * pi + 1] : nullptr;
-  return gated_out ? flk::gemm_gated(c->cfg.dtype, x, w, n, p, gated_out, ln.part, ss, mtt, ln.st, ev0, ev1)
-                   : flk::gemm(c->cfg.dtype, x, w, n, p, ln.part, ss, mtt, ln.st, ev0, ev1);
-}
+// Event pair for a weight GEMM's launch on lane `ln` (null: not timed).  `sampled`: this launch is one of those level 1 times
+// (level 2 times every launch).
+struct GemmTimer {
+  hipEvent_t ev0 = nullptr, ev1 = nullptr;
+  GemmTimer(flover_ctx* c, const Lane& ln, int kind, const flk::GemmPlan& p, bool sampled) {
+    if (&ln != &c->step_lane || !c->prof_now || !(sampled || c->profile >= 2)) return;
+    const int pi = prof_begin(c, kind, (int64_t)flk::gemm_tiled_bytes(c->cfg.dtype, p.N, p.K));
+    if (pi < 0) return;
+    ev0 = c->ev[2 * pi];
+    ev1 = c->ev[2 * pi + 1];
+  }
+};
 
 // One pass of the decoder over n rows on lane `ln`: a single launch per operation covers all of them.
 // With want_tokens the final norm, output projection and argmax run and ln.h_choice (host) holds the choices.
@@ -411,23 +413,28 @@ int run_rows(flover_ctx* c, Lane& ln, const Row* rows, int n, bool want_tokens, 
     char* kl = c->kv + (size_t)(2 * l) * c->plane_bytes;
     char* vl = kl + c->plane_bytes;
     const bool gs = gemm_iter && l == L / 2;
-    hipError_t err = hipSuccess;
-    flk::TileOut qo;
-    qo.bias = w.bqkv;
-    qo.rope = c->rope_cs;
-    qo.pos = d_pos;
-    qo.slot = d_slot;
-    qo.q = ln.q;
-    qo.kc = kl;
-    qo.vc = vl;
-    qo.d = d;
-    qo.Smax = f.max_seq;
-    if (context_pass && flk::context_qkv(f.dtype, ln.h, w.wqkv, n, p_qkv, qo, mtt, st, &err)) {
-      HIPCHK(c, err);
-    } else {
-      HIPCHK(c, timed_gemm(c, ln, FLOVER_PROF_GEMM_QKV, ln.h, w.wqkv, n, p_qkv, ss_qkv, mtt, gs));
-      HIPCHK(c, flk::qkv_post(f.dtype, ln.part, p_qkv.S, ss_qkv, p_qkv.ldc, w.bqkv, c->rope_cs, d_slot, d_pos, ln.q, kl, vl, n, H, nh,
-                              d, f.max_seq, st));
+    // a GEMM whose kernel finishes the job leaves nothing to the row-wise kernel behind it (in a fused iteration: fp32 models)
+    auto finishes = [&](const flk::GemmPlan& p) { return (context_pass || f.dtype == FLOVER_F32) && flk::gemm_finishes(f.dtype, p, n); };
+    {
+      const GemmTimer t(c, ln, FLOVER_PROF_GEMM_QKV, p_qkv, gs);
+      if (finishes(p_qkv)) {
+        flk::TileOut qo;
+        qo.bias = w.bqkv;
+        qo.rope = c->rope_cs;
+        qo.pos = d_pos;
+        qo.slot = d_slot;
+        qo.q = ln.q;
+        qo.kc = kl;
+        qo.vc = vl;
+        qo.d = d;
+        qo.Smax = f.max_seq;
+        HIPCHK(c, flk::gemm_qkv(f.dtype, ln.h, w.wqkv, n, p_qkv, qo, mtt, st, t.ev0, t.ev1));
+        launches -= 1;
+      } else {
+        HIPCHK(c, flk::gemm(f.dtype, ln.h, w.wqkv, n, p_qkv, ln.part, ss_qkv, mtt, st, t.ev0, t.ev1));
+        HIPCHK(c, flk::qkv_post(f.dtype, ln.part, p_qkv.S, ss_qkv, p_qkv.ldc, w.bqkv, c->rope_cs, d_slot, d_pos, ln.q, kl, vl, n, H, nh, d,
+                                f.max_seq, st));
+      }
     }
     if (context_pass && l == L - 1) {
       launches += 3;
@@ -442,30 +449,41 @@ int run_rows(flover_ctx* c, Lane& ln, const Row* rows, int n, bool want_tokens, 
       HIPCHK(c, flk::decode_attention(f.dtype, d, ln.q, kl, vl, aw, n, nh, f.max_seq, ln.att, st,
                                       pi >= 0 ? c->ev[2 * pi] : nullptr, pi >= 0 ? c->ev[2 * pi + 1] : nullptr));
     }
-    added = context_pass && flk::context_add(f.dtype, ln.att, w.wo, n, p_o, ln.x, w.bo, mtt, st, &err);
-    HIPCHK(c, err);
-    if (!added) HIPCHK(c, timed_gemm(c, ln, FLOVER_PROF_GEMM_OUT, ln.att, w.wo, n, p_o, ss_h, mtt, gs));
+    {
+      const GemmTimer t(c, ln, FLOVER_PROF_GEMM_OUT, p_o, gs);
+      added = finishes(p_o);
+      HIPCHK(c, added ? flk::gemm_add(f.dtype, ln.att, w.wo, n, p_o, ln.x, w.bo, mtt, st, t.ev0, t.ev1)
+                      : flk::gemm(f.dtype, ln.att, w.wo, n, p_o, ln.part, ss_h, mtt, st, t.ev0, t.ev1));
+    }
     HIPCHK(c, flk::add_norm(f.dtype, !gpt, ln.x, added ? nullptr : ln.part, p_o.S, ss_h, p_o.ldc, added ? nullptr : w.bo, w.ln2_g, w.ln2_b,
                             ln.h, n, H, f.norm_eps, mtt, st));
-    if (p_1.paired) {
-      // gated 16-bit model: the activation is the epilogue of the gate|up contraction wherever that is one launch
-      HIPCHK(c, timed_gemm(c, ln, FLOVER_PROF_GEMM_FF1, ln.h, w.w1, n, p_1, ss_1, mtt, gs, ln.act));
-      if (!context_pass && n <= flk::gated_fused_rows(p_1)) launches -= 1;
-    } else if (context_pass && gpt && flk::context_gelu(f.dtype, ln.h, w.w1, n, p_1, ln.act, w.b1, mtt, st, &err)) {
-      HIPCHK(c, err);
-    } else {
-      HIPCHK(c, timed_gemm(c, ln, FLOVER_PROF_GEMM_FF1, ln.h, w.w1, n, p_1, ss_1, mtt, gs));
-      HIPCHK(c, flk::activation(f.dtype, !gpt, ln.part, p_1.S, ss_1, p_1.ldc, w.b1, ln.act, n, F, mtt, st, p_1.paired));
+    {
+      const GemmTimer t(c, ln, FLOVER_PROF_GEMM_FF1, p_1, gs);
+      if (p_1.paired) {
+        // gated 16-bit model: the activation is the epilogue of the gate|up contraction wherever that is one launch
+        HIPCHK(c, flk::gemm_gated(f.dtype, ln.h, w.w1, n, p_1, ln.act, ln.part, ss_1, mtt, st, t.ev0, t.ev1));
+        if (!context_pass && n <= flk::gated_fused_rows(p_1)) launches -= 1;
+      } else if (finishes(p_1) && (gpt || f.dtype == FLOVER_F32)) {     // an unpaired 16-bit gated layout has up far from gate
+        HIPCHK(c, flk::gemm_act(f.dtype, !gpt, ln.h, w.w1, n, p_1, ln.act, w.b1, mtt, st, t.ev0, t.ev1));
+        launches -= 1;
+      } else {
+        HIPCHK(c, flk::gemm(f.dtype, ln.h, w.w1, n, p_1, ln.part, ss_1, mtt, st, t.ev0, t.ev1));
+        HIPCHK(c, flk::activation(f.dtype, !gpt, ln.part, p_1.S, ss_1, p_1.ldc, w.b1, ln.act, n, F, mtt, st, p_1.paired));
+      }
     }
-    added = context_pass && flk::context_add(f.dtype, ln.act, w.w2, n, p_2, ln.x, w.b2, mtt, st, &err);
-    HIPCHK(c, err);
-    if (!added) HIPCHK(c, timed_gemm(c, ln, FLOVER_PROF_GEMM_FF2, ln.act, w.w2, n, p_2, ss_h, mtt, gs));
+    {
+      const GemmTimer t(c, ln, FLOVER_PROF_GEMM_FF2, p_2, gs);
+      added = finishes(p_2);
+      HIPCHK(c, added ? flk::gemm_add(f.dtype, ln.act, w.w2, n, p_2, ln.x, w.b2, mtt, st, t.ev0, t.ev1)
+                      : flk::gemm(f.dtype, ln.act, w.w2, n, p_2, ln.part, ss_h, mtt, st, t.ev0, t.ev1));
+    }
     launches += 10 - (!context_pass && n_items == n ? 1 : 0);     // one chunk per row: nothing to merge
   }
   if (want_tokens) {
-    HIPCHK(c, flk::add_norm(f.dtype, !gpt, ln.x, ln.part, c->p_2.S, ss_h, c->p_2.ldc, c->lw[L - 1].b2, c->lnf_g, c->lnf_b, ln.h, n, H,
-                            f.norm_eps, mtt, st));
-    HIPCHK(c, timed_gemm(c, ln, FLOVER_PROF_GEMM_LM, ln.h, c->wlm, n, c->p_lm, ss_v, mtt, gemm_iter));
+    HIPCHK(c, flk::add_norm(f.dtype, !gpt, ln.x, added ? nullptr : ln.part, c->p_2.S, ss_h, c->p_2.ldc, added ? nullptr : c->lw[L - 1].b2,
+                            c->lnf_g, c->lnf_b, ln.h, n, H, f.norm_eps, mtt, st));
+    const GemmTimer t(c, ln, FLOVER_PROF_GEMM_LM, c->p_lm, gemm_iter);
+    HIPCHK(c, flk::gemm(f.dtype, ln.h, c->wlm, n, c->p_lm, ln.part, ss_v, mtt, st, t.ev0, t.ev1));
     HIPCHK(c, flk::logits_argmax(ln.part, c->p_lm.S, ss_v, c->p_lm.ldc, logits_out, ln.choice, n, V, st));
     const int ti = ln.tok_next;       // at most kStageRing - 1 iterations are outstanding, so this entry is free
     ln.tok_next = (ln.tok_next + 1) % kStageRing;

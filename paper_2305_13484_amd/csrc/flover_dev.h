@@ -181,37 +181,35 @@ template <int DIST> __device__ __forceinline__ float partner(float v) {
   else if constexpr (DIST == 8) return dpp_f<0x140>(v);  // row_mirror
   else return __shfl_xor(v, DIST, 64);
 }
+// v + its partner, and the larger of the two; at distances 16 and 32 the lane swaps give both sides of the pair without a
+// round through LDS (sums are the same bits: a + b = b + a).
+template <int DIST> __device__ __forceinline__ float sum_partner(float v) {
+  if constexpr (DIST < 16) {
+    return v + partner<DIST>(v);
+  } else {
+    const auto r = DIST == 16 ? __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false)
+                              : __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  }
+}
+template <int DIST> __device__ __forceinline__ float max_partner(float v) {
+  if constexpr (DIST < 16) {
+    return fmaxf(v, partner<DIST>(v));
+  } else {
+    const auto r = DIST == 16 ? __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false)
+                              : __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  }
+}
 // all-reduce sum over aligned groups of W lanes (W = 2..64), every lane gets the total
 template <int W> __device__ __forceinline__ float group_sum(float v) {
-  if constexpr (W >= 2) v += partner<1>(v);
-  if constexpr (W >= 4) v += partner<2>(v);
-  if constexpr (W >= 8) v += partner<4>(v);
-  if constexpr (W >= 16) v += partner<8>(v);
-  if constexpr (W >= 32) v += partner<16>(v);
-  if constexpr (W >= 64) v += partner<32>(v);
+  if constexpr (W >= 2) v = sum_partner<1>(v);
+  if constexpr (W >= 4) v = sum_partner<2>(v);
+  if constexpr (W >= 8) v = sum_partner<4>(v);
+  if constexpr (W >= 16) v = sum_partner<8>(v);
+  if constexpr (W >= 32) v = sum_partner<16>(v);
+  if constexpr (W >= 64) v = sum_partner<32>(v);
   return v;
-}
-template <int W> __device__ __forceinline__ float group_max(float v) {
-  if constexpr (W >= 2) v = fmaxf(v, partner<1>(v));
-  if constexpr (W >= 4) v = fmaxf(v, partner<2>(v));
-  if constexpr (W >= 8) v = fmaxf(v, partner<4>(v));
-  if constexpr (W >= 16) v = fmaxf(v, partner<8>(v));
-  if constexpr (W >= 32) v = fmaxf(v, partner<16>(v));
-  if constexpr (W >= 64) v = fmaxf(v, partner<32>(v));
-  return v;
-}
-
-// block-wide sum for blocks of NW waves; `red` is NW floats of LDS.  Fixed order.
-template <int NW> __device__ __forceinline__ float block_sum(float v, float* red) {
-  v = group_sum<64>(v);
-  if constexpr (NW == 1) return v;
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-  __syncthreads();
-  float t = red[0];
-#pragma unroll
-  for (int i = 1; i < NW; ++i) t += red[i];
-  return t;
 }
 
 }  // namespace flk

@@ -23,7 +23,7 @@ struct GemmPlan {
 enum { TILE_ROWS = 0, TILE_128X256 = 1, TILE_128X128 = 2, TILE_64X128 = 3, TILE_64X64 = 4, TILE_KINDS = 5 };
 inline int part_ld(int N) { return (N + 3) / 4 * 4; }
 GemmPlan gemm_plan(int dtype, int N, int K);
-// Where a context pass's GEMM leaves its result (the members its kind of epilogue uses).
+// Where a GEMM that finishes the job leaves its result (the members its kind of epilogue uses).
 struct TileOut {
   float* part = nullptr;          // partial sums; or the residual stream [M][ldc] the result is added to
   size_t slice_stride = 0;
@@ -45,16 +45,18 @@ size_t gemm_tiled_bytes(int dtype, int N, int K);
 // Slicing for a context pass of M rows of one request (a function of the matrix shape and of that request's own row
 // count only): same tiling, its own number of K slices, at most max_slices (what the partial-sum buffer holds) and 16.
 GemmPlan context_plan(const GemmPlan& p, int dtype, int M, int max_slices);
-// Context passes whose plan takes K in one slice with a kernel that can finish the job: true = launched (*err its result),
-// false = the caller goes through gemm() and the row-wise kernel.  context_qkv: bias, rotary, q and the cache rows (o: bias,
-// rope, pos, slot, q, kc, vc, d, Smax).  context_add: res[M][N] += x . W^T + bias (bias may be null).  context_gelu:
-// act = gelu(x . W^T + bias) in the model dtype.  All three read x (and context_gelu writes act) in the layout xmtt says.
-bool context_qkv(int dtype, const void* x, const void* w_tiled, int M, const GemmPlan& p, const TileOut& o, int xmtt, hipStream_t st,
-                 hipError_t* err);
-bool context_add(int dtype, const void* x, const void* w_tiled, int M, const GemmPlan& p, float* res, const void* bias, int xmtt,
-                 hipStream_t st, hipError_t* err);
-bool context_gelu(int dtype, const void* x, const void* w_tiled, int M, const GemmPlan& p, void* act, const void* bias, int xmtt,
-                  hipStream_t st, hipError_t* err);
+// The contraction and what follows it in one launch: fp32 models always, 16-bit models in a context pass whose plan takes K in
+// one slice (gemm_finishes); otherwise the caller goes through gemm() and the row-wise kernel.  gemm_qkv: bias, rotary, q and
+// the cache rows (o: bias, rope, pos, slot, q, kc, vc, d, Smax).  gemm_add: res[M][N] += x . W^T + bias (bias may be null).
+// gemm_act: GELU of x . W^T + bias, or SwiGLU (16-bit: paired layout; fp32: up after gate).  x is read and the activation written
+// in the layout xmtt says.
+bool gemm_finishes(int dtype, const GemmPlan& p, int M);
+hipError_t gemm_qkv(int dtype, const void* x, const void* w_tiled, int M, const GemmPlan& p, const TileOut& o, int xmtt, hipStream_t st,
+                    hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+hipError_t gemm_add(int dtype, const void* x, const void* w_tiled, int M, const GemmPlan& p, float* res, const void* bias, int xmtt,
+                    hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+hipError_t gemm_act(int dtype, bool swiglu, const void* x, const void* w_tiled, int M, const GemmPlan& p, void* act, const void* bias, int xmtt,
+                    hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 // Re-tile W [N][K] into `tiled` starting at output column n_off (multiple of 16) of a possibly larger matrix whose
 // plan uses NT n-tiles per column group.
 // Tile t of W lands at tile position n_off/16 + t * tile_step of the layout.

@@ -18,6 +18,10 @@
 
 namespace flk {
 
+// the pair at distance d (8, 16 or 32; a constant once the loops below are unrolled) added, or the larger of it
+__device__ __forceinline__ float sum_over(float v, int d) { return d == 8 ? v + __shfl_xor(v, 8, 64) : d == 16 ? sum_partner<16>(v) : sum_partner<32>(v); }
+__device__ __forceinline__ float max_over(float v, int d) { return d == 8 ? fmaxf(v, __shfl_xor(v, 8, 64)) : d == 16 ? max_partner<16>(v) : max_partner<32>(v); }
+
 // Where a launch's work comes from: a list in device memory (the fused iteration; one entry per chunk), or row
 // descriptors that travel as a kernel argument (operation-level calls of up to 256 rows: no copy to the device, no wait,
 // one launch less), where block i is chunk i / M of row i % M and rows with fewer chunks leave blocks without work (row by
@@ -169,16 +173,16 @@ __global__ __launch_bounds__(256) void attn_partial_kernel(const void* __restric
   if constexpr (RPW > 1) {
     float mt = m;
 #pragma unroll
-    for (int dlt = LPR; dlt < 64; dlt <<= 1) mt = fmaxf(mt, __shfl_xor(mt, dlt, 64));
+    for (int dlt = LPR; dlt < 64; dlt <<= 1) mt = max_over(mt, dlt);
     const float w = (m == -INFINITY) ? 0.f : __expf(m - mt);
     l *= w;
 #pragma unroll
     for (int e = 0; e < EPL; ++e) o[e] *= w;
 #pragma unroll
     for (int dlt = LPR; dlt < 64; dlt <<= 1) {
-      l += __shfl_xor(l, dlt, 64);
+      l = sum_over(l, dlt);
 #pragma unroll
-      for (int e = 0; e < EPL; ++e) o[e] += __shfl_xor(o[e], dlt, 64);
+      for (int e = 0; e < EPL; ++e) o[e] = sum_over(o[e], dlt);
     }
     m = mt;
   }
@@ -360,16 +364,16 @@ __global__ __launch_bounds__(256) void attn_prefill_kernel(const void* __restric
     if constexpr (RPW > 1) {
       float mt = mi;
 #pragma unroll
-      for (int dlt = LPR; dlt < 64; dlt <<= 1) mt = fmaxf(mt, __shfl_xor(mt, dlt, 64));
+      for (int dlt = LPR; dlt < 64; dlt <<= 1) mt = max_over(mt, dlt);
       const float w = (mi == -INFINITY) ? 0.f : __expf(mi - mt);
       lv *= w;
 #pragma unroll
       for (int e = 0; e < EPL; ++e) o[i][e] *= w;
 #pragma unroll
       for (int dlt = LPR; dlt < 64; dlt <<= 1) {
-        lv += __shfl_xor(lv, dlt, 64);
+        lv = sum_over(lv, dlt);
 #pragma unroll
-        for (int e = 0; e < EPL; ++e) o[i][e] += __shfl_xor(o[i][e], dlt, 64);
+        for (int e = 0; e < EPL; ++e) o[i][e] = sum_over(o[i][e], dlt);
       }
       mi = mt;
     }
@@ -513,8 +517,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
         sc[kt * 4 + r] = v;
         tmax = fmaxf(tmax, v);
       }
-    tmax = fmaxf(tmax, __shfl_xor(tmax, 16, 64));
-    tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
+    tmax = max_partner<32>(max_partner<16>(tmax));
     const float mn = fmaxf(m, tmax);
     const float ms = (mn == -INFINITY) ? 0.f : mn;
     const float alpha = __expf(m - ms);
@@ -553,8 +556,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
     }
   }
   // lane (n, g) owns O[query n][d = dt*16 + 4g .. +3]
-  l += __shfl_xor(l, 16, 64);
-  l += __shfl_xor(l, 32, 64);
+  l = sum_partner<32>(sum_partner<16>(l));
   if (first + n < M) {
 #pragma unroll
     for (int dt = 0; dt < DTL; ++dt) stv4<DT>(out, xrow_index(first + n, hd * D + dt * 16 + 4 * g, nh * D, mtt), oacc[dt] / l);

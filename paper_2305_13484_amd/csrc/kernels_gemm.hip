@@ -712,29 +712,100 @@ __global__ __launch_bounds__(64 * WR * WC) __attribute__((amdgpu_waves_per_eu(2)
 
 // ---------------------------------------------------------------- fp32 FMA kernel (tiny models)
 
-// one wave per output column, 8 rows at a time; lanes stride K, fixed butterfly reduction.
-__global__ __launch_bounds__(256) void gemm32_kernel(const float* __restrict__ x, const float* __restrict__ W,
-                                                     float* __restrict__ out, int M, int N, int K, int ldc) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int n = blockIdx.x * 4 + wave;
-  if (n >= N) return;
-  const int m0 = blockIdx.y * 8;
-  float acc[8];
+// Lane l ends with the sum over the wave of v[l >> 2]: halves of the values are exchanged at distances 32, 16, 8 and 4 (15
+// exchanges instead of 6 for each of the 16 values; all within the vector unit), then the last four lanes are added.
+// Fixed order.
+__device__ __forceinline__ float wave_sums16(float (&v)[16], int lane) {
 #pragma unroll
-  for (int r = 0; r < 8; ++r) acc[r] = 0.f;
-  const float* wr = W + (size_t)n * K;
-  for (int k = lane; k < K; k += 64) {
-    const float w = wr[k];
-#pragma unroll
-    for (int r = 0; r < 8; ++r) {
-      const int m = min(m0 + r, M - 1);
-      acc[r] = fmaf(x[(size_t)m * K + k], w, acc[r]);
-    }
+  for (int i = 0; i < 8; ++i) {                  // lower half of the wave: both halves of v[i], upper half: of v[i + 8]
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[i]), __float_as_uint(v[i + 8]), false, false);
+    v[i] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
   }
 #pragma unroll
-  for (int r = 0; r < 8; ++r) {
-    const float v = group_sum<64>(acc[r]);
-    if (lane == 0 && m0 + r < M) out[(size_t)(m0 + r) * ldc + n] = v;
+  for (int i = 0; i < 4; ++i) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v[i]), __float_as_uint(v[i + 4]), false, false);
+    v[i] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  }
+  const bool up8 = lane & 8, up4 = lane & 4;
+#pragma unroll
+  for (int i = 0; i < 2; ++i) v[i] = (up8 ? v[i + 2] : v[i]) + dpp_f<0x128>(up8 ? v[i] : v[i + 2]);      // row_ror:8
+  float r = (up4 ? v[1] : v[0]) + dpp_f<0x141>(up4 ? v[0] : v[1]);     // row_half_mirror: the other four lanes, in reverse
+  return sum_partner<2>(sum_partner<1>(r));
+}
+
+// A wave takes two output columns and 8 rows: lanes stride K four elements at a time, so that a row of up to 256 elements is
+// one round of loads (3.1 us per launch at 7 rows x 256 x 256, 4.8 at 256 x 1024; one column and four bytes per lane and
+// load: 5.2 on average, up to 10.5; the time is the launch and the round trips).  The second column is the next one, or the one that
+// the epilogue needs beside it: the rotary partner, or up beside gate.  Every model of this type finishes in the epilogue
+// (see tile_epilogue): tiny models are bound by their count of launches.
+template <int EPI, int U>
+__global__ __launch_bounds__(256) void gemm32_kernel(const float* __restrict__ x, const float* __restrict__ W, TileOut o, int M, int N,
+                                                     int K) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int pair = blockIdx.x * 4 + wave, half = o.d >> 1;
+  const int c0 = EPI == EPI_QKV ? pair / half * o.d + pair % half : EPI == EPI_GATED ? pair : 2 * pair;
+  const int c1 = EPI == EPI_QKV ? c0 + half : EPI == EPI_GATED ? pair + o.F : 2 * pair + 1;
+  if (c0 >= (EPI == EPI_GATED ? o.F : N)) return;
+  const int m0 = blockIdx.y * 8;
+  // lanes 8r .. 8r+3 end with column c0 of row m0 + r, the next four with c1; what the epilogue reads goes out first
+  const int m = m0 + (lane >> 3), mr = min(m, M - 1), c = min((lane & 4) ? c1 : c0, N - 1);
+  float bias = 0.f, old = 0.f;
+  int pos = 0, slot = 0;
+  if (EPI != EPI_PART && EPI != EPI_GATED && o.bias) bias = ((const float*)o.bias)[c];
+  if constexpr (EPI == EPI_ADD) old = o.part[(size_t)mr * o.ldc + c];
+  if constexpr (EPI == EPI_QKV) {
+    pos = o.pos[mr];
+    slot = o.slot[mr];
+  }
+  float acc[16];
+#pragma unroll
+  for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+  const float *w0 = W + (size_t)c0 * K, *w1 = W + (size_t)min(c1, N - 1) * K;
+  for (int k0 = lane * 4; k0 < K; k0 += U * 256) {             // U rounds of loads in flight; those past K count as zero
+    f32x4_t a[U], b[U], v[U][8];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int k = min(k0 + u * 256, K - 4);
+      a[u] = ld4(w0 + k);
+      b[u] = ld4(w1 + k);
+#pragma unroll
+      for (int r = 0; r < 8; ++r) v[u][r] = ld4(x + (size_t)min(m0 + r, M - 1) * K + k);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (k0 + u * 256 >= K) continue;
+#pragma unroll
+      for (int r = 0; r < 8; ++r)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          acc[2 * r] = fmaf(v[u][r][e], a[u][e], acc[2 * r]);
+          acc[2 * r + 1] = fmaf(v[u][r][e], b[u][e], acc[2 * r + 1]);
+        }
+    }
+  }
+  const float sum = wave_sums16(acc, lane) + (EPI == EPI_PART || EPI == EPI_GATED ? 0.f : bias), other = __shfl_xor(sum, 4, 64);
+  if (m >= M || (lane & 3)) return;
+  if constexpr (EPI == EPI_QKV) {
+    if (lane & 4) return;
+    const int H = N / 3, which = c0 / H, r = c0 - which * H, hd = r / o.d, e = r - hd * o.d;
+    f32x4_t a0 = {sum, 0.f, 0.f, 0.f}, a1 = {other, 0.f, 0.f, 0.f};
+    if (o.rope && which < 2) {
+      const float* tab = o.rope + ((size_t)pos * half + e) * 2;
+      rope_rotate(a0, a1, f32x4_t{tab[0], 0.f, 0.f, 0.f}, f32x4_t{tab[1], 0.f, 0.f, 0.f});
+    }
+    float* dst = (float*)(which == 0 ? o.q : which == 1 ? o.kc : o.vc);
+    const size_t at = which == 0 ? (size_t)m * H + r : (((size_t)slot * (H / o.d) + hd) * o.Smax + pos) * o.d + e;
+    dst[at] = a0[0];
+    dst[at + half] = a1[0];
+  } else if constexpr (EPI == EPI_GATED) {
+    if (lane & 4) return;
+    ((float*)o.act)[(size_t)m * o.F + c0] = act_swiglu(f32x4_t{sum, 0.f, 0.f, 0.f}, f32x4_t{other, 0.f, 0.f, 0.f})[0];
+  } else {
+    if (((lane & 4) ? c1 : c0) >= N) return;
+    if constexpr (EPI == EPI_PART) o.part[(size_t)m * o.ldc + c] = sum;
+    else if constexpr (EPI == EPI_ADD) o.part[(size_t)m * o.ldc + c] = old + sum;
+    else ((float*)o.act)[(size_t)m * o.F + c] = act_gelu(f32x4_t{sum, 0.f, 0.f, 0.f})[0];
   }
 }
 
@@ -935,39 +1006,42 @@ static void dispatch_tile(int tile, const void* x, const void* wt, const TileOut
   else if constexpr (EPI != EPI_QKV) launch_tile<DT, 2, 2, 2, 2, 4, EPI>(x, wt, o, M, p, xmtt, st, ev0, ev1);
 }
 template <int EPI>
-static hipError_t run_tile(int dtype, const void* x, const void* wt, const TileOut& o, int M, const GemmPlan& p, int xmtt, hipStream_t st,
-                           hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr) {
-  if (dtype == DT_BF16) dispatch_tile<DT_BF16, EPI>(p.tile, x, wt, o, M, p, xmtt, st, ev0, ev1);
-  else dispatch_tile<DT_F16, EPI>(p.tile, x, wt, o, M, p, xmtt, st, ev0, ev1);
+static hipError_t finish(int dtype, const void* x, const void* wt, const TileOut& o, int M, const GemmPlan& p, int xmtt, hipStream_t st,
+                         hipEvent_t ev0, hipEvent_t ev1) {
+  if (dtype == DT_F32) {
+    const int pairs = EPI == EPI_GATED ? o.F : (p.N + 1) / 2;
+    const dim3 grid((pairs + 3) / 4, (M + 7) / 8);
+    if (p.K <= 256) launch_timed(gemm32_kernel<EPI, 1>, grid, dim3(256), st, ev0, ev1, (const float*)x, (const float*)wt, o, M, p.N, p.K);
+    else launch_timed(gemm32_kernel<EPI, 4>, grid, dim3(256), st, ev0, ev1, (const float*)x, (const float*)wt, o, M, p.N, p.K);
+  } else if (dtype == DT_BF16) {
+    dispatch_tile<DT_BF16, EPI>(p.tile, x, wt, o, M, p, xmtt, st, ev0, ev1);
+  } else {
+    dispatch_tile<DT_F16, EPI>(p.tile, x, wt, o, M, p, xmtt, st, ev0, ev1);
+  }
   return hipGetLastError();
 }
-static bool finishes(int dtype, const GemmPlan& p, int M) { return dtype != DT_F32 && M > 128 && p.S == 1 && p.tile >= 0; }
+bool gemm_finishes(int dtype, const GemmPlan& p, int M) { return dtype == DT_F32 || (M > 128 && p.S == 1 && p.tile >= 0); }
 
-bool context_qkv(int dtype, const void* x, const void* wt, int M, const GemmPlan& p, const TileOut& o, int xmtt, hipStream_t st, hipError_t* err) {
-  if (!finishes(dtype, p, M)) return false;
-  *err = run_tile<EPI_QKV>(dtype, x, wt, o, M, p, xmtt, st);
-  return true;
+hipError_t gemm_qkv(int dtype, const void* x, const void* wt, int M, const GemmPlan& p, const TileOut& o, int xmtt, hipStream_t st,
+                    hipEvent_t ev0, hipEvent_t ev1) {
+  return finish<EPI_QKV>(dtype, x, wt, o, M, p, xmtt, st, ev0, ev1);
 }
-bool context_add(int dtype, const void* x, const void* wt, int M, const GemmPlan& p, float* res, const void* bias, int xmtt, hipStream_t st,
-                 hipError_t* err) {
-  if (!finishes(dtype, p, M)) return false;
+hipError_t gemm_add(int dtype, const void* x, const void* wt, int M, const GemmPlan& p, float* res, const void* bias, int xmtt, hipStream_t st,
+                    hipEvent_t ev0, hipEvent_t ev1) {
   TileOut o;
   o.part = res;
   o.ldc = p.N;
   o.bias = bias;
-  *err = run_tile<EPI_ADD>(dtype, x, wt, o, M, p, xmtt, st);
-  return true;
+  return finish<EPI_ADD>(dtype, x, wt, o, M, p, xmtt, st, ev0, ev1);
 }
-bool context_gelu(int dtype, const void* x, const void* wt, int M, const GemmPlan& p, void* act, const void* bias, int xmtt, hipStream_t st,
-                  hipError_t* err) {
-  if (!finishes(dtype, p, M)) return false;
+hipError_t gemm_act(int dtype, bool swiglu, const void* x, const void* wt, int M, const GemmPlan& p, void* act, const void* bias, int xmtt,
+                    hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
   TileOut o;
   o.act = act;
   o.bias = bias;
-  o.F = p.N;
+  o.F = swiglu ? p.N / 2 : p.N;
   o.mtt = xmtt;
-  *err = run_tile<EPI_GELU>(dtype, x, wt, o, M, p, xmtt, st);
-  return true;
+  return swiglu ? finish<EPI_GATED>(dtype, x, wt, o, M, p, xmtt, st, ev0, ev1) : finish<EPI_GELU>(dtype, x, wt, o, M, p, xmtt, st, ev0, ev1);
 }
 
 template <int DT, int NT>
@@ -1050,13 +1124,7 @@ hipError_t gemm_gated(int dtype, const void* x, const void* wt, int M, const Gem
                       size_t slice_stride, int xmtt, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
   if (M <= 0) return hipSuccess;
   if (!p.paired || dtype == DT_F32) return hipErrorInvalidValue;
-  if (finishes(dtype, p, M)) {
-    TileOut o;
-    o.act = act;
-    o.F = p.N / 2;
-    o.mtt = xmtt;
-    return run_tile<EPI_GATED>(dtype, x, wt, o, M, p, xmtt, st, ev0, ev1);
-  }
+  if (gemm_finishes(dtype, p, M)) return gemm_act(dtype, true, x, wt, M, p, act, nullptr, xmtt, st, ev0, ev1);
   if (M > gated_fused_rows(p) || p.S != 2) {
     hipError_t e = gemm(dtype, x, wt, M, p, part, slice_stride, xmtt, st, ev0, nullptr);   // timed from the first launch's
     if (e != hipSuccess) return e;                                                       // start to the second's end
@@ -1072,8 +1140,10 @@ hipError_t gemm(int dtype, const void* x, const void* wt, int M, const GemmPlan&
   if (M <= 0) return hipSuccess;
   if (dtype == DT_F32) {
     if (xmtt) return hipErrorInvalidValue;   // fp32 rows are always row-major
-    dim3 grid((p.N + 3) / 4, (M + 7) / 8);
-    launch_timed(gemm32_kernel, grid, dim3(256), st, ev0, ev1, (const float*)x, (const float*)wt, part, M, p.N, p.K, p.ldc);
+    TileOut o;
+    o.part = part;
+    o.ldc = p.ldc;
+    return finish<EPI_PART>(dtype, x, wt, o, M, p, 0, st, ev0, ev1);
   } else if (dtype == DT_BF16) {
     if (p.NT == 4) dispatch16<DT_BF16, 4>(x, wt, part, M, p, slice_stride, xmtt, st, ev0, ev1);
     else dispatch16<DT_BF16, 2>(x, wt, part, M, p, slice_stride, xmtt, st, ev0, ev1);
