@@ -12,7 +12,8 @@
 //     lengths are: a row of len positions has ceil(len / CHUNK) chunks of equal length (no short remainder task, which
 //     would leave the memory system under-used while the full-length tasks finish); chunking depends on the
 //     request's own length only, and a second tiny kernel merges a row's chunks in chunk order (results never depend
-//     on other rows).
+//     on other rows); where every row of a launch has one chunk, the first kernel writes the output itself.
+// Context passes of 16-bit models take the matrix cores instead (attn_context_kernel).
 #include "flover_dev.h"
 #include "flover_kernels.h"
 

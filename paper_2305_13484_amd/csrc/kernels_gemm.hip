@@ -27,7 +27,8 @@
 //   * gate|up of a gated MLP, up to 128 fused rows: no partial sums at all -- the two K halves are the two wave sets of
 //     a block and the activation is the kernel's epilogue (gated_lds_kernel), with gate and up columns interleaved in
 //     the layout so that a lane holds both; above 128 rows the same halves go through memory as two slices.
-// fp32 models (tiny configurations only) use a plain FMA kernel on the untiled matrix.
+// fp32 models (tiny configurations only) use a plain FMA kernel on the untiled matrix, with what follows the contraction as
+// its epilogue.
 #include <algorithm>
 #include <cmath>
 #include <type_traits>
