@@ -59,7 +59,6 @@ template <int DT> __device__ __forceinline__ float rdt(float v) {
 }
 
 // 16 bytes of storage -> fp32 lanes (8 values for the 16-bit dtypes, 4 for fp32)
-template <int DT> struct Vec16 { static constexpr int N = (DT == DT_F32) ? 4 : 8; };
 template <int DT> __device__ __forceinline__ void unpack16(const u32x4_t& r, float* f) {
   if constexpr (DT == DT_F32) {
     f[0] = __uint_as_float(r.x); f[1] = __uint_as_float(r.y); f[2] = __uint_as_float(r.z); f[3] = __uint_as_float(r.w);

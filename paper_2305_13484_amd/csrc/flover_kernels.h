@@ -65,7 +65,8 @@ hipError_t retile(int dtype, const void* W, int N, int K, void* tiled, int n_off
 hipError_t zero_fill(void* p, size_t bytes, hipStream_t st);
 // part[s][m][p.ldc] (slice stride in floats) = x[M][K] . W^T over slice s of K.
 // xmtt == 0: x is row-major [M][K]; xmtt = ceil(M/16) (16-bit dtypes only): x is in fragment order
-// (tiles of 16 rows x 32 k, [k-block][row tile], see xrow_index) and the buffer holds K/32 * gemm_rows_read(M)/16 tiles.
+// (tiles of 16 rows x 32 k, [k-block][row tile], see xrow_index) and the buffer has room for M
+// rounded up to 16, 32, 64, 128 or a multiple of 256 rows (row tiles past the last may be read).
 // ev0 / ev1 (optional, here and below): take the start / end time stamps of the call's first / last dispatch.
 hipError_t gemm(int dtype, const void* x, const void* w_tiled, int M, const GemmPlan& p, float* part,
                 size_t slice_stride, int xmtt, hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
@@ -78,10 +79,6 @@ hipError_t gemm(int dtype, const void* x, const void* w_tiled, int M, const Gemm
 inline int gated_fused_rows(const GemmPlan& p) { return (p.N / 2 / 16 + 3) / 4 > 256 ? 64 : 128; }
 hipError_t gemm_gated(int dtype, const void* x, const void* w_tiled, int M, const GemmPlan& p, void* act, float* part,
                       size_t slice_stride, int xmtt, hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
-// rows that a fragment-order x of M live rows must have room for (row tiles past the last may be read)
-inline int gemm_rows_read(int M) {
-  return M <= 16 ? 16 : M <= 32 ? 32 : M <= 64 ? 64 : M <= 128 ? 128 : (M + 255) / 256 * 256;
-}
 
 // ---- row-wise kernels
 // A row's greedy choice is left in parts: the best logit of each part of the vocabulary and its column (kNoToken: none, a part
