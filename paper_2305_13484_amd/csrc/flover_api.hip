@@ -226,7 +226,7 @@ size_t layout(flover_ctx* c, char* base) {
   c->kv = (char*)b.take(c->kv_bytes);
   const int R = (std::max(C, 1024) + 255) / 256 * 256;   // rows per pass: live rows of an iteration, or a chunk of a prompt
   c->rows_cap = R;
-  const int chunks = (S + flk::attn_chunk() - 1) / flk::attn_chunk();
+  const int chunks = (S + flk::kAttnChunk - 1) / flk::kAttnChunk;
   c->max_items = R * chunks;
   size_t pw = 0;
   for (const flk::GemmPlan* p : {&c->p_qkv, &c->p_o, &c->p_1, &c->p_2, &c->p_lm}) pw = std::max(pw, (size_t)p->S * p->ldc);
@@ -338,7 +338,7 @@ int run_rows(flover_ctx* c, Lane& ln, const Row* rows, int n, bool want_tokens, 
     pos[i] = rows[i].pos;
     slot[i] = rows[i].slot;
     len[i] = rows[i].pos + 1;
-    const int nc = (len[i] + flk::attn_chunk() - 1) / flk::attn_chunk();
+    const int nc = (len[i] + flk::kAttnChunk - 1) / flk::kAttnChunk;
     nchunk[i] = nc;
     if (context_pass) continue;         // its attention takes the rows as they are, or (fp32) the blocks below
     for (int ch = 0; ch < nc; ++ch) {
@@ -375,8 +375,8 @@ int run_rows(flover_ctx* c, Lane& ln, const Row* rows, int n, bool want_tokens, 
   }
   int* ds = ln.d_stage;
   const int *d_tok = ds, *d_pos = ds + R, *d_slot = ds + 2 * R, *d_len = ds + 3 * R;
-  flk::AttnWork aw{(const int4*)(ds + 6 * R), d_slot, d_len, ln.pml, ln.po, n_items, flk::attn_chunk(),
-                   (f.max_seq + flk::attn_chunk() - 1) / flk::attn_chunk()};
+  flk::AttnWork aw{(const int4*)(ds + 6 * R), d_slot, d_len, ln.pml, ln.po, n_items,
+                   (f.max_seq + flk::kAttnChunk - 1) / flk::kAttnChunk};
   aw.blocks = (const int4*)(ds + 6 * R + 4 * n_items);
   aw.n_blocks = n_blocks;
   // what feeds a GEMM (norm output, attention output, MLP activation) is written in the order the GEMM's MFMA reads
@@ -1224,7 +1224,7 @@ int32_t flover_k_find_window(const int32_t* arr, int32_t n, int32_t* mem_offset,
 }
 
 static size_t attn_ws_layout(int M, int nh, int d, int max_len, size_t* o_items, size_t* o_pml, size_t* o_po) {
-  const int chunks = (max_len + flk::attn_chunk() - 1) / flk::attn_chunk();
+  const int chunks = (max_len + flk::kAttnChunk - 1) / flk::kAttnChunk;
   const size_t items = (size_t)M * chunks;
   size_t off = align_up((size_t)4 * M * 4, 256);
   *o_items = off;
@@ -1249,7 +1249,7 @@ static int attn_rows(const int32_t* slot, const int32_t* len, int M, flk::AttnRo
   for (int i = 0; i < M; ++i) {
     r->slot[i] = slot[i];
     r->len[i] = len[i];
-    n_items += (len[i] + flk::attn_chunk() - 1) / flk::attn_chunk();
+    n_items += (len[i] + flk::kAttnChunk - 1) / flk::kAttnChunk;
   }
   for (int i = M; i < flk::kAttnRows; ++i) r->slot[i] = r->len[i] = 0;
   return n_items;
@@ -1272,9 +1272,9 @@ int32_t flover_k_decode_attention(int32_t dtype, const void* q, const void* kcac
   if (need > workspace_bytes) return fail(nullptr, FLOVER_E_NOMEM, "attention workspace too small");
   hipStream_t st = (hipStream_t)stream;
   char* ws = (char*)workspace;
-  const int maxch = (max_len + flk::attn_chunk() - 1) / flk::attn_chunk();
+  const int maxch = (max_len + flk::kAttnChunk - 1) / flk::kAttnChunk;
   flk::AttnWork aw{(const int4*)(ws + o_items), (const int*)ws, (const int*)ws + M, (float*)(ws + o_pml), (float*)(ws + o_po), 0,
-                   flk::attn_chunk(), maxch};
+                   maxch};
   flk::AttnRows rows;
   std::vector<int> hs, items;
   if (M <= flk::kAttnRows) {
@@ -1285,7 +1285,7 @@ int32_t flover_k_decode_attention(int32_t dtype, const void* q, const void* kcac
     for (int i = 0; i < M; ++i) {
       hs[i] = slot[i];
       hs[M + i] = len[i];
-      const int nc = (len[i] + flk::attn_chunk() - 1) / flk::attn_chunk();
+      const int nc = (len[i] + flk::kAttnChunk - 1) / flk::kAttnChunk;
       for (int ch = 0; ch < nc; ++ch) {
         items.push_back(i);
         items.push_back(ch);
@@ -1368,9 +1368,8 @@ int32_t flover_k_decode_attention_noalloc(int32_t dtype, const void* q, const vo
   if (rc != FLOVER_OK) return rc;
   char* ws = (char*)base;
   // every part of the scratch this call reads is written first by this call's own kernels: nothing has to start at zero
-  flk::AttnWork aw{(const int4*)(ws + o_items), (const int*)ws, (const int*)ws + M, (float*)(ws + o_pml), (float*)(ws + o_po), n_items,
-                   flk::attn_chunk(),
-                   (max_len + flk::attn_chunk() - 1) / flk::attn_chunk()};
+  flk::AttnWork aw{nullptr, nullptr, nullptr, (float*)(ws + o_pml), (float*)(ws + o_po), n_items,
+                   (max_len + flk::kAttnChunk - 1) / flk::kAttnChunk};
   aw.rows = &rows;
   HIPCHK(nullptr, flk::decode_attention(dtype, d, q, kcache, vcache, aw, M, nh, S, out, (hipStream_t)stream));
   return FLOVER_OK;

@@ -113,8 +113,9 @@ hipError_t activation(int dtype, bool swiglu, const float* part, int S, size_t s
 hipError_t logits_argmax(const float* part, int S, size_t stride, int ldp, float* logits, Choice* choice, int M, int V, hipStream_t st);
 
 // ---- ragged decode attention
+constexpr int kAttnChunk = 256;   // most positions of a wave task; fixed, so chunking depends on a request's own length only
 constexpr int kAttnRows = 256;
-struct AttnRows {          // row descriptors of an operation-level call, passed to the kernels by value
+struct alignas(16) AttnRows {   // row descriptors of an operation-level call, passed to the kernels by value; no rows: length 0
   int32_t slot[kAttnRows], len[kAttnRows];
 };
 struct AttnWork {          // device pointers unless stated
@@ -124,16 +125,13 @@ struct AttnWork {          // device pointers unless stated
   float* pml;              // [M][maxch][nh][2]: (m, l) of chunk ch of row r at ((r * maxch + ch) * nh + head)
   float* po;               // [M][maxch][nh][d]
   int n_items;
-  int chunk;
-  int maxch;               // chunk slots per row in pml / po: at least ceil(longest row / chunk)
+  int maxch;               // chunk slots per row in pml / po: at least ceil(longest row / kAttnChunk)
   const int4* blocks = nullptr;   // pre-processing passes of fp32 models: (first row, rows <= kPrefillQB, chunk, -)
   int n_blocks = 0;
-  const AttnRows* rows = nullptr;   // [host] set: the rows' descriptors (at most kAttnRows rows); items and row_len are then
-                                    // room for them, n_items is the number of chunks and maxch that of the longest row
+  const AttnRows* rows = nullptr;   // [host] set: the rows' descriptors (at most kAttnRows rows), instead of items and row_len
   int out_mtt = 0;                // layout of the attention output: 0 row-major, else fragment order (see add_norm)
 };
 constexpr int kPrefillQB = 8;     // query rows one wave serves in a pre-processing pass of an fp32 model (an entry of blocks)
-int attn_chunk();   // positions per wave task; fixed for the process, so chunking depends on a request's own length only
 // ev0 / ev1 (optional) take the start / end time stamps of the streaming kernel's dispatch (the merge kernel follows).
 hipError_t decode_attention(int dtype, int d, const void* q, const void* kc, const void* vc, const AttnWork& w, int M,
                             int nh, int Smax, void* out, hipStream_t st, hipEvent_t ev0 = nullptr,

@@ -23,49 +23,53 @@ namespace flk {
 __device__ __forceinline__ float sum_over(float v, int d) { return d == 8 ? v + __shfl_xor(v, 8, 64) : d == 16 ? sum_partner<16>(v) : sum_partner<32>(v); }
 __device__ __forceinline__ float max_over(float v, int d) { return d == 8 ? fmaxf(v, __shfl_xor(v, 8, 64)) : d == 16 ? max_partner<16>(v) : max_partner<32>(v); }
 
-// Where a launch's work comes from: a list in device memory (the fused iteration; one entry per chunk), or row
-// descriptors that travel as a kernel argument (operation-level calls of up to 256 rows: no copy to the device, no wait,
-// one launch less), where block i is chunk i / M of row i % M and rows with fewer chunks leave blocks without work (row by
-// row instead, the chunks that every row has would all meet on the same XCDs: 256 rows of up to 16 chunks 1588 us).  That
-// is for small calls: with thousands of blocks it also costs locality (the same 256 rows: 1395 us against 1350 from a
-// list), so above 1024 possible chunks a one-block kernel turns the argument into the list (3 us).
+__device__ __forceinline__ int chunks_of(int len) { return ((unsigned)len + kAttnChunk - 1) / kAttnChunk; }
+
+// Where a launch's work comes from, in either case row by row, one item per chunk: a list in device memory (the fused
+// iteration, and operation-level calls of more than 256 rows), or the rows' descriptors as a kernel argument (no copy to the
+// device, no wait, no launch before this one).  There every wave finds item i by itself: lane t holds rows 4t .. 4t+3 and the
+// wave adds up their chunk counts -- one round of loads and a handful of lane operations, no longer than a list's round of
+// loads (both 67 us at 48 rows x 32 heads of up to 1000 positions, 128 wide, bf16; 31 us at 64 rows x 4 heads of up to 2000).
+// A grid of rows x most chunks with block i = chunk i / M of row i % M needs no search, but leaves blocks without work and
+// puts all chunks of a row on one XCD where M is a multiple of 8: 78 and 30 us.
 struct ItemList {
   const int4* items;
   const int* row_len;
   __device__ int4 at(int i) const { return items[i]; }
   __device__ int len(int row) const { return row_len[row]; }
 };
+template <int CTRL, int ROWS> __device__ __forceinline__ int add_dpp(int v) {     // lanes without a source add zero
+  return v + __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xf, false);
+}
 struct RowList {
   AttnRows r;
   int M;
   __device__ int4 at(int i) const {
-    const int ch = i / M, row = i - ch * M;
-    return make_int4(row, ch, r.slot[row], r.len[row]);
+    static_assert(kAttnRows == 4 * 64, "four rows per lane");
+    const int lane = threadIdx.x & 63;
+    int4 slot = {0, 0, 0, 0}, len = {0, 0, 0, 0};
+    if (4 * lane < M) {                          // a few rows are a few of the argument's cache lines
+      slot = *(const int4*)(r.slot + 4 * lane);
+      len = *(const int4*)(r.len + 4 * lane);
+    }
+    const int n0 = chunks_of(len.x), n1 = n0 + chunks_of(len.y), n2 = n1 + chunks_of(len.z), n3 = n2 + chunks_of(len.w);
+    int sum = n3;                                // inclusive scan over the wave
+    sum = add_dpp<0x111, 0xf>(sum);              // row_shr 1, 2, 4, 8: within rows of 16 lanes
+    sum = add_dpp<0x112, 0xf>(sum);
+    sum = add_dpp<0x114, 0xf>(sum);
+    sum = add_dpp<0x118, 0xf>(sum);
+    sum = add_dpp<0x142, 0xa>(sum);              // lane 15 of rows 0 and 2 to rows 1 and 3
+    sum = add_dpp<0x143, 0xc>(sum);              // lane 31 to rows 2 and 3
+    const int own = __builtin_ctzll(__ballot(i < sum));      // the lane whose rows hold item i
+    const int rel = i - (sum - n3);              // of that lane: the item within its four rows
+    const int k = (rel >= n0) + (rel >= n1) + (rel >= n2);
+    const int ch = rel - (k == 0 ? 0 : k == 1 ? n0 : k == 2 ? n1 : n2);
+    return make_int4(__builtin_amdgcn_readlane(4 * lane + k, own), __builtin_amdgcn_readlane(ch, own),
+                     __builtin_amdgcn_readlane(k == 0 ? slot.x : k == 1 ? slot.y : k == 2 ? slot.z : slot.w, own),
+                     __builtin_amdgcn_readlane(k == 0 ? len.x : k == 1 ? len.y : k == 2 ? len.z : len.w, own));
   }
   __device__ int len(int row) const { return r.len[row]; }
 };
-
-// One block of kAttnRows threads: thread t owns row t, writes its length and its (row, chunk, slot, len) work items;
-// first-item indices are an exclusive scan of the rows' chunk counts.
-__global__ __launch_bounds__(kAttnRows) void attn_items_kernel(AttnRows r, int M, int chunk, int* __restrict__ row_len,
-                                                               int4* __restrict__ items) {
-  __shared__ int scan[kAttnRows];
-  const int t = threadIdx.x;
-  const int slot = t < M ? r.slot[t] : 0, len = t < M ? r.len[t] : 0;
-  const int nc = (len + chunk - 1) / chunk;
-  scan[t] = nc;
-  __syncthreads();
-  for (int dlt = 1; dlt < kAttnRows; dlt <<= 1) {     // inclusive scan, log steps
-    const int v = t >= dlt ? scan[t - dlt] : 0;
-    __syncthreads();
-    scan[t] += v;
-    __syncthreads();
-  }
-  if (t >= M) return;
-  const int first = scan[t] - nc;
-  row_len[t] = len;
-  for (int ch = 0; ch < nc; ++ch) items[first + ch] = make_int4(t, ch, slot, len);
-}
 
 // grid = (items, n_head / 4), block = 256: wave w handles head blockIdx.y * 4 + w of item blockIdx.x = (row, chunk, slot,
 // len).  Writes the unnormalised partial (m, l, o[D]) of (row, chunk, head) at index (row * maxch + chunk) * n_head + head:
@@ -75,7 +79,7 @@ __global__ __launch_bounds__(kAttnRows) void attn_items_kernel(AttnRows r, int M
 template <int DT, int D, int U, bool ONE, class Src>
 __global__ __launch_bounds__(256) void attn_partial_kernel(const void* __restrict__ q, const void* __restrict__ kc,
                                                            const void* __restrict__ vc, Src src, int nh,
-                                                           int Smax, int chunk, int maxch,
+                                                           int Smax, int maxch,
                                                            float scale, float* __restrict__ pml, float* __restrict__ po,
                                                            void* __restrict__ out, int mtt) {
   constexpr int EB = (DT == DT_F32) ? 4 : 2;
@@ -87,9 +91,8 @@ __global__ __launch_bounds__(256) void attn_partial_kernel(const void* __restric
   const int hd = blockIdx.y * 4 + wave;
   const int4 it = src.at(item);         // one load: the cache addresses below depend on nothing else
   const int row = it.x, ch = it.y, slot = it.z, len = it.w;
-  // the row's ceil(len / chunk) chunks are made equally long, so that no wave task of a row is a short remainder
-  const int nch = (len + chunk - 1) / chunk;
-  if (ch >= nch) return;
+  // the row's ceil(len / kAttnChunk) chunks are made equally long, so that no wave task of a row is a short remainder
+  const int nch = chunks_of(len);
   const int cr = (len + nch - 1) / nch;
   const int j0 = ch * cr, j1 = min(len, j0 + cr);
   const int grp = lane / LPR, li = lane % LPR;
@@ -214,7 +217,7 @@ __global__ __launch_bounds__(256) void attn_partial_kernel(const void* __restric
 // does not have are read and never used); longer rows fetch the rest in a second round.
 template <int DT, int D, class Src>
 __global__ __launch_bounds__(256) void attn_merge_kernel(const float* __restrict__ pml, const float* __restrict__ po,
-                                                         Src src, int chunk, int maxch, int nh,
+                                                         Src src, int maxch, int nh,
                                                          void* __restrict__ out, int mtt) {
   constexpr int FIRST = 4;
   constexpr int TPH = D / 4, HPB = 256 / TPH;
@@ -231,7 +234,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const float* __restrict
     lc[j] = ml.y;
     oc[j] = ld4(po + pi * D + i);
   }
-  const int nc = (src.len(row) + chunk - 1) / chunk;
+  const int nc = chunks_of(src.len(row));
   float red_m = -INFINITY;                                    // the global maximum needs the m of every chunk
 #pragma unroll
   for (int j = 0; j < FIRST; ++j)
@@ -278,7 +281,7 @@ template <int DT, int D, int QB>
 __global__ __launch_bounds__(256) void attn_prefill_kernel(const void* __restrict__ q, const void* __restrict__ kc,
                                                            const void* __restrict__ vc, const int4* __restrict__ blocks,
                                                            const int* __restrict__ row_slot,
-                                                           const int* __restrict__ row_len, int nh, int Smax, int chunk,
+                                                           const int* __restrict__ row_len, int nh, int Smax,
                                                            int maxch, float scale, float* __restrict__ pml,
                                                            float* __restrict__ po) {
   constexpr int EB = (DT == DT_F32) ? 4 : 2;
@@ -292,7 +295,7 @@ __global__ __launch_bounds__(256) void attn_prefill_kernel(const void* __restric
   const int hd = blockIdx.y * 4 + wave;
   const int slot = row_slot[first];
   const int len0 = row_len[first];                          // rows are consecutive positions: len_i = len0 + i
-  const int j0 = ch * chunk, j1 = min(len0 + nr - 1, j0 + chunk);
+  const int j0 = ch * kAttnChunk, j1 = min(len0 + nr - 1, j0 + kAttnChunk);
   const int grp = lane / LPR, li = lane % LPR;
 
   float qf[QB][EPL];
@@ -379,7 +382,7 @@ __global__ __launch_bounds__(256) void attn_prefill_kernel(const void* __restric
       mi = mt;
     }
     const int r = first + i;
-    if (i < nr && ch * chunk < len0 + i && grp == 0) {       // this chunk holds keys this query may see
+    if (i < nr && ch * kAttnChunk < len0 + i && grp == 0) {       // this chunk holds keys this query may see
       const size_t pi = ((size_t)r * maxch + ch) * nh + hd;
       float* op = po + pi * D + li * EPL;
 #pragma unroll
@@ -566,31 +569,25 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
 
 // ---------------------------------------------------------------- host side
 
-int attn_chunk() { return 256; }
-
 template <int DT, int D, class Src>
-static void launch_attn(const void* q, const void* kc, const void* vc, const AttnWork& w, const Src& src, int items, int M, int nh, int Smax,
+static void launch_attn(const void* q, const void* kc, const void* vc, const AttnWork& w, const Src& src, int M, int nh, int Smax,
                         void* out, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
   const float scale = 1.0f / sqrtf((float)D);
-  const dim3 grid(items, nh / 4);
+  const dim3 grid(w.n_items, nh / 4);
   if (w.n_items == M) {        // one chunk per row
-    launch_timed(attn_partial_kernel<DT, D, 4, true, Src>, grid, dim3(256), st, ev0, ev1, q, kc, vc, src, nh, Smax, w.chunk, w.maxch,
+    launch_timed(attn_partial_kernel<DT, D, 4, true, Src>, grid, dim3(256), st, ev0, ev1, q, kc, vc, src, nh, Smax, w.maxch,
                  scale, w.pml, w.po, out, w.out_mtt);
     return;
   }
-  launch_timed(attn_partial_kernel<DT, D, 4, false, Src>, grid, dim3(256), st, ev0, ev1, q, kc, vc, src, nh, Smax, w.chunk, w.maxch, scale,
+  launch_timed(attn_partial_kernel<DT, D, 4, false, Src>, grid, dim3(256), st, ev0, ev1, q, kc, vc, src, nh, Smax, w.maxch, scale,
                w.pml, w.po, out, w.out_mtt);
-  attn_merge_kernel<DT, D, Src><<<dim3(M, (nh * D + 1023) / 1024), 256, 0, st>>>(w.pml, w.po, src, w.chunk, w.maxch, nh, out, w.out_mtt);
+  attn_merge_kernel<DT, D, Src><<<dim3(M, (nh * D + 1023) / 1024), 256, 0, st>>>(w.pml, w.po, src, w.maxch, nh, out, w.out_mtt);
 }
 template <int DT, int D>
 static void launch_attn(const void* q, const void* kc, const void* vc, const AttnWork& w, int M, int nh, int Smax, void* out,
                         hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
-  if (w.rows && M * w.maxch <= 1024) {
-    launch_attn<DT, D>(q, kc, vc, w, RowList{*w.rows, M}, M * w.maxch, M, nh, Smax, out, st, ev0, ev1);
-    return;
-  }
-  if (w.rows) attn_items_kernel<<<1, kAttnRows, 0, st>>>(*w.rows, M, w.chunk, (int*)w.row_len, (int4*)w.items);
-  launch_attn<DT, D>(q, kc, vc, w, ItemList{w.items, w.row_len}, w.n_items, M, nh, Smax, out, st, ev0, ev1);
+  if (w.rows) launch_attn<DT, D>(q, kc, vc, w, RowList{*w.rows, M}, M, nh, Smax, out, st, ev0, ev1);
+  else launch_attn<DT, D>(q, kc, vc, w, ItemList{w.items, w.row_len}, M, nh, Smax, out, st, ev0, ev1);
 }
 
 hipError_t decode_attention(int dtype, int d, const void* q, const void* kc, const void* vc, const AttnWork& w, int M,
@@ -614,8 +611,8 @@ static void launch_prefill(const void* q, const void* kc, const void* vc, const 
   const float scale = 1.0f / sqrtf((float)D);
   if constexpr (DT == DT_F32) {
     attn_prefill_kernel<DT, D, kPrefillQB><<<dim3(w.n_blocks, nh / 4), 256, 0, st>>>(
-        q, kc, vc, w.blocks, w.row_slot, w.row_len, nh, Smax, w.chunk, w.maxch, scale, w.pml, w.po);
-    attn_merge_kernel<DT, D, ItemList><<<dim3(M, (nh * D + 1023) / 1024), 256, 0, st>>>(w.pml, w.po, ItemList{w.items, w.row_len}, w.chunk, w.maxch,
+        q, kc, vc, w.blocks, w.row_slot, w.row_len, nh, Smax, w.maxch, scale, w.pml, w.po);
+    attn_merge_kernel<DT, D, ItemList><<<dim3(M, (nh * D + 1023) / 1024), 256, 0, st>>>(w.pml, w.po, ItemList{w.items, w.row_len}, w.maxch,
                                                                                      nh, out, w.out_mtt);
   } else {
     const int nrb = (M + 63) / 64;

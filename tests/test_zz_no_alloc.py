@@ -1,6 +1,8 @@
 """flover_k_decode_attention_noalloc (the entry point for callers that cannot allocate) against
 flover_k_decode_attention on the same inputs, through the C ABI: same kernels, so the outputs must be equal bit for
 bit; two calls in a row on the library's one scratch array, the second with a smaller input."""
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
@@ -64,3 +66,48 @@ def test_noalloc_attention_limits_and_bad_arguments(fl):
     ref = fl.k_decode_attention(qd, kd, vd, slots, lens)
     got = fl.k_decode_attention_noalloc(qd, kd, vd, slots, lens, torch.empty_like(ref))
     assert torch.equal(got, ref)
+
+
+class _KernelNode(C.Structure):              # hipKernelNodeParams
+    _fields_ = [("block", C.c_uint32 * 3), ("extra", C.c_void_p), ("func", C.c_void_p), ("grid", C.c_uint32 * 3), ("params", C.c_void_p),
+                ("lds", C.c_uint32)]
+
+
+def _captured_grids(call):
+    """Grids of the kernels that `call` enqueues on the current stream, in order; any other node fails the test."""
+    path = next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64" in line)
+    hip = C.CDLL(path)
+    stream, graph, n = C.c_void_p(torch.cuda.current_stream().cuda_stream), C.c_void_p(), C.c_size_t()
+    assert hip.hipStreamBeginCapture(stream, 1) == 0
+    try:
+        call()
+    finally:
+        rc = hip.hipStreamEndCapture(stream, C.byref(graph))
+    assert rc == 0
+    assert hip.hipGraphGetNodes(graph, None, C.byref(n)) == 0
+    nodes = (C.c_void_p * n.value)()
+    assert hip.hipGraphGetNodes(graph, nodes, C.byref(n)) == 0
+    grids = []
+    for node in nodes:
+        p = _KernelNode()
+        assert hip.hipGraphKernelNodeGetParams(C.c_void_p(node), C.byref(p)) == 0
+        grids.append(tuple(p.grid))
+    assert hip.hipGraphDestroy(graph) == 0
+    return grids
+
+
+@pytest.mark.parametrize("M,hi", [(1, 256), (1, 700), (9, 256), (48, 700), (200, 1500)])
+def test_noalloc_attention_launches_one_block_row_per_chunk(fl, M, hi):
+    """The streaming kernel's grid holds the rows' chunks of 256 positions and nothing else, and where no row has a second
+    one it is the only launch: no block without work and no launch that only prepares another."""
+    nh, d = 8, 64
+    q, k, v, slots, lens = synth.attention_case(M, M, M, nh, d, hi, synth.DT_BF16, 1, hi)
+    qd, kd, vd = q.cuda(), k.cuda(), v.cuda()
+    out = torch.empty_like(qd)
+    ref = fl.k_decode_attention_noalloc(qd, kd, vd, slots, lens, out).clone()
+    with torch.cuda.stream(torch.cuda.Stream()):
+        grids = _captured_grids(lambda: fl.k_decode_attention_noalloc(qd, kd, vd, slots, lens, out))
+    chunks = int(((lens + 255) // 256).sum())
+    assert grids[0] == (chunks, nh // 4, 1)
+    assert len(grids) == (1 if chunks == M else 2)
+    assert torch.equal(fl.k_decode_attention_noalloc(qd, kd, vd, slots, lens, out), ref)
