@@ -587,6 +587,11 @@ int find_window(const int32_t* arr, int n, int* min_cost, int* non_zero) {
   return at;
 }
 
+// Whether the byte ranges [a, a + na) and [b, b + nb) have memory in common.
+bool overlap(const void* a, size_t na, const void* b, size_t nb) {
+  return (uintptr_t)a < (uintptr_t)b + nb && (uintptr_t)b < (uintptr_t)a + na;
+}
+
 int copy_in(flover_ctx* c, void* dst, const void* src, size_t bytes, const char* name) {
   if (!src) return fail(c, FLOVER_E_INVAL, std::string("missing weight: ") + name);
   HIPCHK(c, hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToDevice, c->st));
@@ -1512,8 +1517,11 @@ extern "C" int32_t flover_k_gemm(int32_t dtype, const void* x, const void* w_til
   const size_t stride = (size_t)M * p.ldc;
   if ((size_t)p.S * stride * 4 > workspace_bytes) return fail(nullptr, FLOVER_E_NOMEM, "gemm workspace too small");
   hipStream_t st = (hipStream_t)stream;
-  // one slice and 16-byte aligned rows: the contraction's own stores are the result
-  const bool direct = y && p.S == 1 && N % 4 == 0 && ((uintptr_t)y & 15) == 0;
+  // one slice and 16-byte aligned rows: the contraction's own stores are the result, unless they would fall on what its other
+  // blocks still read (y may share memory with x)
+  const size_t y_bytes = (size_t)M * N * 4;
+  const bool direct = y && p.S == 1 && N % 4 == 0 && ((uintptr_t)y & 15) == 0 && !overlap(y, y_bytes, x, (size_t)M * K * esize(dtype)) &&
+                      !overlap(y, y_bytes, w_tiled, flk::gemm_tiled_bytes(dtype, N, K));
   HIPCHK(nullptr, flk::gemm(dtype, x, w_tiled, M, p, direct ? y : (float*)workspace, stride, 0, st));
   if (y && !direct) {
     // grid.y is the row: at most 65535 of them per launch

@@ -108,6 +108,25 @@ def test_gemm_takes_rows_as_they_are(dtype, M, N):
         assert torch.equal(fl.k_gemm(other, tw), ref)
 
 
+@pytest.mark.parametrize("dtype,M,N,K", [(synth.DT_F32, 40, 256, 256), (synth.DT_F32, 7, 96, 1024), (synth.DT_BF16, 24, 40, 96),
+                                         (synth.DT_F16, 150, 8192, 32)])
+def test_gemm_result_may_share_memory_with_the_rows(dtype, M, N, K):
+    """y over the memory that x lies in, at shapes taken in one slice (elsewhere the sums go through the workspace anyway):
+    the same bits as into memory of its own."""
+    assert fl.binding.k_gemm_plan(dtype, N, K)[0] == 1
+    g = torch.Generator(device="cuda").manual_seed(M + N)
+    tw = fl.binding.TiledWeight(torch.randn((N, K), generator=g, device="cuda").to(TDT[dtype]))
+    x0 = torch.randn((M, K), generator=g, device="cuda").to(TDT[dtype])
+    ref = fl.k_gemm(x0, tw)
+    x_bytes, y_bytes = M * K * x0.element_size(), M * N * 4
+    room = torch.zeros(x_bytes + y_bytes, dtype=torch.uint8, device="cuda")
+    for x_at, y_at in ((0, 0), (0, x_bytes - 16), (y_bytes - 16, 0)):
+        x = room[x_at:x_at + x_bytes].view(TDT[dtype]).view(M, K)
+        x.copy_(x0)
+        y = room[y_at:y_at + y_bytes].view(torch.float32).view(M, N)
+        assert torch.equal(fl.k_gemm(x, tw, y), ref), (x_at, y_at)
+
+
 # ---------------------------------------------------------------- gated MLP input (contraction + activation, one launch)
 
 def _gated_reference(dtype, x, Wg, Wu):
