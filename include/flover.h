@@ -319,7 +319,7 @@ int32_t flover_k_gemm(int32_t dtype, const void* x, const void* w_tiled, int32_t
  * flover_k_gated_retile writes both matrices ([device][F][K] each) into w_tiled ([device],
  * flover_k_gemm_tiled_bytes(dtype, 2F, K) bytes) with gate and up columns interleaved in tiles of 16;
  * flover_k_gated_mlp streams that copy.  x [device][M][K] row-major, 16-byte aligned;
- * act [device][M][F] row-major, model dtype.
+ * act [device][M][F] row-major, model dtype, apart from x.
  * context_pass == 0, the fused iteration: a row's result depends on that row of x alone, not on M.  Up to 128 rows (64
  * when F > 16384) it is one launch; above that the two halves of K go through `workspace` as partial sums and the
  * activation is a second launch, with the same result bit for bit.

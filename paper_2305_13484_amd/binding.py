@@ -390,6 +390,12 @@ def _aligned_rows(x: torch.Tensor) -> torch.Tensor:
     return x if x.data_ptr() % 16 == 0 else x.clone()
 
 
+def _overlap(a: torch.Tensor, b: torch.Tensor) -> bool:
+    """Whether two contiguous tensors have memory in common."""
+    pa, pb = a.data_ptr(), b.data_ptr()
+    return pa < pb + b.numel() * b.element_size() and pb < pa + a.numel() * a.element_size()
+
+
 def k_gemm(x: torch.Tensor, W, out: Optional[torch.Tensor] = None, workspace: Optional[torch.Tensor] = None):
     """y[M][N] fp32 = x[M][K] . W[N][K]^T; W a device tensor or a TiledWeight."""
     tw = W if isinstance(W, TiledWeight) else TiledWeight(W)
@@ -431,6 +437,8 @@ def k_gated_mlp(x: torch.Tensor, gw: GatedWeight, out: Optional[torch.Tensor] = 
     xp = _aligned_rows(x)
     if out is None:
         out = torch.empty((M, gw.F), dtype=x.dtype, device=x.device)
+    elif _overlap(xp, out):
+        xp = xp.clone()        # the one launch writes activations while other blocks still read rows
     n = C.c_uint64()
     _check(load_library().flover_k_gated_workspace_bytes(gw.dtype, M, gw.F, K, C.byref(n)))
     ws = torch.empty(max(int(n.value), 16), dtype=torch.uint8, device="cuda")

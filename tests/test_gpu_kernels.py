@@ -129,6 +129,22 @@ def test_gemm_result_may_share_memory_with_the_rows(dtype, M, N, K):
 
 # ---------------------------------------------------------------- gated MLP input (contraction + activation, one launch)
 
+@pytest.mark.parametrize("M", [5, 40, 100, 200])
+def test_gated_mlp_result_may_share_memory_with_the_rows(M):
+    """The activations over the memory that x lies in give the same bits as into memory of their own."""
+    dtype, F, K = synth.DT_BF16, 512, 512
+    g = torch.Generator(device="cuda").manual_seed(M)
+    gw = fl.binding.GatedWeight(*[(torch.randn((F, K), generator=g, device="cuda") * 0.05).to(TDT[dtype]) for _ in range(2)])
+    x0 = torch.randn((M, K), generator=g, device="cuda").to(TDT[dtype])
+    for context in (False, True):
+        ref = fl.binding.k_gated_mlp(x0, gw, context_pass=context)
+        room = torch.zeros(M * K + 64, dtype=TDT[dtype], device="cuda")
+        x, out = room[:M * K].view(M, K), room[64:].view(M, F)
+        for o in (x, out):
+            x.copy_(x0)
+            assert torch.equal(fl.binding.k_gated_mlp(x, gw, o, context_pass=context), ref)
+
+
 def _gated_reference(dtype, x, Wg, Wu):
     """fp64 silu(g) * u before the final rounding, and a bound on what fp32 accumulation may move it by."""
     g, u = orc.gemm(dtype, x, Wg), orc.gemm(dtype, x, Wu)
