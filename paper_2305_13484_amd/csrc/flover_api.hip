@@ -1248,6 +1248,13 @@ int32_t flover_k_attention_workspace_bytes(int32_t M, int32_t nh, int32_t d, int
   return FLOVER_OK;
 }
 
+// Whether the output shares memory with what the call reads.
+static bool attn_out_overlaps(int dtype, const void* q, const void* kcache, const void* vcache, int M, int C, int nh, int d, int S,
+                              const void* out) {
+  const size_t rows = (size_t)M * nh * d * esize(dtype), cache = (size_t)C * nh * S * d * esize(dtype);
+  return overlap(out, rows, q, rows) || overlap(out, rows, kcache, cache) || overlap(out, rows, vcache, cache);
+}
+
 // Row descriptors for the kernels' argument; returns the number of chunks.
 static int attn_rows(const int32_t* slot, const int32_t* len, int M, flk::AttnRows* r) {
   int n_items = 0;
@@ -1303,6 +1310,7 @@ int32_t flover_k_decode_attention(int32_t dtype, const void* q, const void* kcac
     HIPCHK(nullptr, hipStreamSynchronize(st));
     aw.n_items = (int)items.size() / 4;
   }
+  aw.merge_last = attn_out_overlaps(dtype, q, kcache, vcache, M, C, nh, d, S, out);
   HIPCHK(nullptr, flk::decode_attention(dtype, d, q, kcache, vcache, aw, M, nh, S, out, st));
   return FLOVER_OK;
 }
@@ -1376,6 +1384,7 @@ int32_t flover_k_decode_attention_noalloc(int32_t dtype, const void* q, const vo
   flk::AttnWork aw{nullptr, nullptr, nullptr, (float*)(ws + o_pml), (float*)(ws + o_po), n_items,
                    (max_len + flk::kAttnChunk - 1) / flk::kAttnChunk};
   aw.rows = &rows;
+  aw.merge_last = attn_out_overlaps(dtype, q, kcache, vcache, M, C, nh, d, S, out);
   HIPCHK(nullptr, flk::decode_attention(dtype, d, q, kcache, vcache, aw, M, nh, S, out, (hipStream_t)stream));
   return FLOVER_OK;
 }

@@ -129,6 +129,7 @@ struct AttnWork {          // device pointers unless stated
   const int4* blocks = nullptr;   // pre-processing passes of fp32 models: (first row, rows <= kPrefillQB, chunk, -)
   int n_blocks = 0;
   const AttnRows* rows = nullptr;   // [host] set: the rows' descriptors (at most kAttnRows rows), instead of items and row_len
+  bool merge_last = false;        // the output shares memory with q or the caches: written by a launch of its own
   int out_mtt = 0;                // layout of the attention output: 0 row-major, else fragment order (see add_norm)
 };
 constexpr int kPrefillQB = 8;     // query rows one wave serves in a pre-processing pass of an fp32 model (an entry of blocks)

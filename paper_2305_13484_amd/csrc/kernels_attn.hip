@@ -574,7 +574,7 @@ static void launch_attn(const void* q, const void* kc, const void* vc, const Att
                         void* out, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
   const float scale = 1.0f / sqrtf((float)D);
   const dim3 grid(w.n_items, nh / 4);
-  if (w.n_items == M) {        // one chunk per row
+  if (w.n_items == M && !w.merge_last) {        // one chunk per row
     launch_timed(attn_partial_kernel<DT, D, 4, true, Src>, grid, dim3(256), st, ev0, ev1, q, kc, vc, src, nh, Smax, w.maxch,
                  scale, w.pml, w.po, out, w.out_mtt);
     return;

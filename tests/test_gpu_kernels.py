@@ -307,6 +307,23 @@ def test_attention_rows_by_argument_by_list_and_by_copy_give_the_same_bits(dtype
         assert torch.equal(part, full[lo:hi]), (lo, hi)
 
 
+@pytest.mark.parametrize("M,hi", [(6, 200), (6, 600), (300, 100)])
+def test_attention_output_may_share_memory_with_the_queries(M, hi):
+    """The output over q itself and over its neighbouring rows, with and without second chunks, by argument and by list."""
+    dtype, nh, d = synth.DT_BF16, 4, 128
+    q, k, v, slots, lens = synth.attention_case(M, M, M, nh, d, hi, dtype, 1, hi)
+    kd, vd = k.cuda(), v.cuda()
+    ref = fl.k_decode_attention(q.cuda(), kd, vd, slots, lens)
+    room = torch.zeros((M + 1, nh, d), dtype=TDT[dtype], device="cuda")
+    for q_at, out_at in ((0, 0), (0, 1), (1, 0)):
+        qd, out = room[q_at:q_at + M], room[out_at:out_at + M]
+        qd.copy_(q)
+        assert torch.equal(fl.k_decode_attention(qd, kd, vd, slots, lens, out), ref), (q_at, out_at)
+        if M <= 256:
+            qd.copy_(q)
+            assert torch.equal(fl.k_decode_attention_noalloc(qd, kd, vd, slots, lens, out), ref), (q_at, out_at)
+
+
 def test_attention_benchmark_shape_sampled_pairs():
     """Config 2's shape (256 live, 32 heads, head_dim 128, lengths U{1..4096}, bf16): sampled (row, head) outputs."""
     dtype, M, Cn, nh, d, S = synth.DT_BF16, 256, 256, 32, 128, 4096
