@@ -1477,8 +1477,9 @@ extern "C" int32_t flover_k_copy_probe(void* dst, const void* src, uint64_t byte
 }
 
 // y = sum of the split-K slices, in slice order (same order the step's consumers use).  grid = (ceil(N / 1024), M): four
-// consecutive columns per thread; the slices' rows are 16-byte aligned, those of y only when N is a multiple of 4.
+// consecutive columns per thread; the slices' rows are 16-byte aligned, those of y where VEC says so.
 namespace flk {
+template <bool VEC>
 __global__ __launch_bounds__(256) void slice_sum_kernel(const float* __restrict__ part, int S, size_t stride, int ldc, float* __restrict__ y,
                                                         int N) {
   const int n = (blockIdx.x * 256 + threadIdx.x) * 4;
@@ -1493,7 +1494,7 @@ __global__ __launch_bounds__(256) void slice_sum_kernel(const float* __restrict_
     v.w += w.w;
   }
   float* o = y + (size_t)blockIdx.y * N + n;
-  if ((N & 3) == 0) {
+  if constexpr (VEC) {
     *(float4*)o = v;
   } else {
     o[0] = v.x;
@@ -1529,15 +1530,16 @@ extern "C" int32_t flover_k_gemm(int32_t dtype, const void* x, const void* w_til
   // one slice and 16-byte aligned rows: the contraction's own stores are the result, unless they would fall on what its other
   // blocks still read (y may share memory with x)
   const size_t y_bytes = (size_t)M * N * 4;
-  const bool direct = y && p.S == 1 && N % 4 == 0 && ((uintptr_t)y & 15) == 0 && !overlap(y, y_bytes, x, (size_t)M * K * esize(dtype)) &&
+  const bool aligned = N % 4 == 0 && ((uintptr_t)y & 15) == 0;
+  const bool direct = y && p.S == 1 && aligned && !overlap(y, y_bytes, x, (size_t)M * K * esize(dtype)) &&
                       !overlap(y, y_bytes, w_tiled, flk::gemm_tiled_bytes(dtype, N, K));
   HIPCHK(nullptr, flk::gemm(dtype, x, w_tiled, M, p, direct ? y : (float*)workspace, stride, 0, st));
   if (y && !direct) {
     // grid.y is the row: at most 65535 of them per launch
     for (int m = 0; m < M; m += 65535) {
-      const int n = std::min(M - m, 65535);
-      flk::slice_sum_kernel<<<dim3((unsigned)((N + 1023) / 1024), (unsigned)n), 256, 0, st>>>((const float*)workspace + (size_t)m * p.ldc, p.S,
-                                                                                         stride, p.ldc, y + (size_t)m * N, N);
+      const dim3 grid((unsigned)((N + 1023) / 1024), (unsigned)std::min(M - m, 65535));
+      const auto kernel = aligned ? flk::slice_sum_kernel<true> : flk::slice_sum_kernel<false>;
+      kernel<<<grid, 256, 0, st>>>((const float*)workspace + (size_t)m * p.ldc, p.S, stride, p.ldc, y + (size_t)m * N, N);
     }
     HIPCHK(nullptr, hipGetLastError());
   }

@@ -108,6 +108,19 @@ def test_gemm_takes_rows_as_they_are(dtype, M, N):
         assert torch.equal(fl.k_gemm(other, tw), ref)
 
 
+@pytest.mark.parametrize("dtype,M,N,K", [(synth.DT_F32, 9, 96, 64), (synth.DT_BF16, 20, 512, 2048), (synth.DT_F16, 200, 1030, 512)])
+def test_gemm_result_at_any_float(dtype, M, N, K):
+    """Results that start off the 16-byte grid hold the same bits, and nothing beside them is written."""
+    g = torch.Generator(device="cuda").manual_seed(N)
+    tw = fl.binding.TiledWeight(torch.randn((N, K), generator=g, device="cuda").to(TDT[dtype]))
+    x = torch.randn((M, K), generator=g, device="cuda").to(TDT[dtype])
+    ref = fl.k_gemm(x, tw)
+    for at in (0, 1, 2, 3):
+        room = torch.full((M * N + 8,), 7.0, dtype=torch.float32, device="cuda")
+        assert torch.equal(fl.k_gemm(x, tw, room[at:at + M * N].view(M, N)), ref)
+        assert torch.all(room[:at] == 7.0) and torch.all(room[at + M * N:] == 7.0)
+
+
 @pytest.mark.parametrize("dtype,M,N,K", [(synth.DT_F32, 40, 256, 256), (synth.DT_F32, 7, 96, 1024), (synth.DT_BF16, 24, 40, 96),
                                          (synth.DT_F16, 150, 8192, 32)])
 def test_gemm_result_may_share_memory_with_the_rows(dtype, M, N, K):
