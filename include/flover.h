@@ -296,8 +296,8 @@ int32_t flover_k_compact(void* cache, int32_t L, int32_t C, int32_t n_head, int3
 
 /* Weight GEMM of the fused rows: y[M][N] (fp32) = x[M][K] . W[N][K]^T, fp32 accumulation (MFMA for the 16-bit
  * dtypes).  W is first re-tiled into `w_tiled` (flover_k_gemm_tiled_bytes bytes, [device]) by flover_k_gemm_retile;
- * flover_k_gemm then streams the tiled copy.  x [device][M][K], 16-byte aligned;
- * workspace holds the split-K partial sums.  K % 32 == 0.  y == NULL leaves the result as partial sums in the
+ * flover_k_gemm then streams the tiled copy.  x [device][M][K] (any alignment; fastest at 16 bytes); y may share memory
+ * with x; workspace holds the split-K partial sums.  K % 32 == 0.  y == NULL leaves the result as partial sums in the
  * workspace (timing the streaming kernel alone). */
 int32_t flover_k_gemm_tiled_bytes(int32_t dtype, int32_t N, int32_t K, uint64_t* out);
 /* [host only] K slicing of the weight GEMM: *slices partial sums, each over *k_blocks_per_slice blocks of 32 input
@@ -318,7 +318,7 @@ int32_t flover_k_gemm(int32_t dtype, const void* x, const void* w_tiled, int32_t
  * K % 512 == 0, INVAL otherwise (the step then uses flover_k_gemm's kernels and a separate activation).
  * flover_k_gated_retile writes both matrices ([device][F][K] each) into w_tiled ([device],
  * flover_k_gemm_tiled_bytes(dtype, 2F, K) bytes) with gate and up columns interleaved in tiles of 16;
- * flover_k_gated_mlp streams that copy.  x [device][M][K] row-major, 16-byte aligned;
+ * flover_k_gated_mlp streams that copy.  x [device][M][K] row-major (any alignment; fastest at 16 bytes);
  * act [device][M][F] row-major, model dtype, apart from x.
  * context_pass == 0, the fused iteration: a row's result depends on that row of x alone, not on M.  Up to 128 rows (64
  * when F > 16384) it is one launch; above that the two halves of K go through `workspace` as partial sums and the

@@ -23,6 +23,8 @@ typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
 typedef __attribute__((ext_vector_type(8))) _Float16 f16x8_t;
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 typedef __attribute__((ext_vector_type(4))) unsigned int u32x4_t;   // 16 bytes of storage
+typedef u32x4_t u32x4_any __attribute__((aligned(2)));               // ... of 16-bit rows, or
+typedef f32x4_t f32x4_any __attribute__((aligned(4)));               // fp32 rows, that a caller may start at any element
 
 template <int DT> struct Store;          // storage element of a model dtype
 template <> struct Store<DT_F32> { typedef float type; };

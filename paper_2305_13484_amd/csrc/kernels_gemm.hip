@@ -96,7 +96,7 @@ __global__ __launch_bounds__(256) void gemm16_direct_kernel(const uint16_t* __re
 #pragma unroll
     for (int t = 0; t < NT; ++t) bq[j][t] = __builtin_nontemporal_load(wp + ((size_t)kk * NT + t) * 64);
 #pragma unroll
-    for (int i = 0; i < MT; ++i) aq[j][i] = *(const u32x4_t*)(xp + i * tstride + kk * kstride);
+    for (int i = 0; i < MT; ++i) aq[j][i] = *(const u32x4_any*)(xp + i * tstride + kk * kstride);
     __builtin_amdgcn_sched_barrier(0);
   }
   // One turn of the ring.  The steady-state turns (TAIL = false: all PFW k-blocks exist) are free of branches, so the
@@ -118,7 +118,7 @@ __global__ __launch_bounds__(256) void gemm16_direct_kernel(const uint16_t* __re
         for (int t = 0; t < NT; ++t) bq[j][t] = __builtin_nontemporal_load(wp + ((size_t)kw * NT + t) * 64);
         const int ka = min(kb + j + PFA, kb1 - 1);
 #pragma unroll
-        for (int i = 0; i < MT; ++i) aq[j % PFA][i] = *(const u32x4_t*)(xp + i * tstride + ka * kstride);
+        for (int i = 0; i < MT; ++i) aq[j % PFA][i] = *(const u32x4_any*)(xp + i * tstride + ka * kstride);
         __builtin_amdgcn_sched_barrier(0);
       }
     }
@@ -202,7 +202,7 @@ __global__ __launch_bounds__(64 * GPB * (NT / NTW)) void gemm16_lds_kernel(const
     for (int j = 0; j < FPW; ++j) {
       const int kc = min(wave + NW * j, KC * MT - 1) / MT;
       const int kk = min(kb0 + chunk * KC + kc, kb1 - 1);
-      areg[j] = *(const u32x4_t*)(xp + xo[j] + kk * kstride);
+      areg[j] = *(const u32x4_any*)(xp + xo[j] + kk * kstride);
     }
   };
   auto store_a = [&](int buf) {      // surplus waves store the last fragment once more (same data, no branch)
@@ -320,7 +320,7 @@ __global__ __launch_bounds__(128 * GPB) void gated_lds_kernel(const uint16_t* __
 #pragma unroll
     for (int j = 0; j < FPW; ++j) {
       const int kc = min(gw + GPB * j, KC * MT - 1) / MT;
-      areg[j] = *(const u32x4_t*)(x + xo[j] + (kb0 + chunk * KC + kc) * kstride);
+      areg[j] = *(const u32x4_any*)(x + xo[j] + (kb0 + chunk * KC + kc) * kstride);
     }
   };
   auto store_a = [&](int buf) {      // surplus fragments store the last one once more (same data, no branch)
@@ -767,10 +767,10 @@ __global__ __launch_bounds__(256) void gemm32_kernel(const float* __restrict__ x
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int k = min(k0 + u * 256, K - 4);
-      a[u] = ld4(w0 + k);
-      b[u] = ld4(w1 + k);
+      a[u] = *(const f32x4_any*)(w0 + k);
+      b[u] = *(const f32x4_any*)(w1 + k);
 #pragma unroll
-      for (int r = 0; r < 8; ++r) v[u][r] = ld4(x + (size_t)min(m0 + r, M - 1) * K + k);
+      for (int r = 0; r < 8; ++r) v[u][r] = *(const f32x4_any*)(x + (size_t)min(m0 + r, M - 1) * K + k);
     }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -1045,12 +1045,17 @@ hipError_t gemm_act(int dtype, bool swiglu, const void* x, const void* wt, int M
   return swiglu ? finish<EPI_GATED>(dtype, x, wt, o, M, p, xmtt, st, ev0, ev1) : finish<EPI_GELU>(dtype, x, wt, o, M, p, xmtt, st, ev0, ev1);
 }
 
+// The copies to LDS move whole 16-byte pieces; operands of an operation-level call may start anywhere.
+static bool aligned16(const void* x, const void* wt) { return (((uintptr_t)x | (uintptr_t)wt) & 15) == 0; }
+
 template <int DT, int NT>
 static void dispatch16(const void* x, const void* wt, float* part, int M, const GemmPlan& p, size_t ss, int xmtt,
                        hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
+  // up to 128 rows, and rows or weights off the 16-byte grid: through registers, row blocks of at most 128 rows
+  const bool regs = M <= 128 || !aligned16(x, wt);
   if (M <= 16) launch_direct<DT, 1, NT, 8, 8>(x, wt, part, M, p, ss, xmtt, st, ev0, ev1);
   else if (M <= 32) launch_lds<DT, 2, NT, NT, 4, 4, (NT == 2 ? 4 : 2)>(x, wt, part, M, p, ss, xmtt, st, ev0, ev1);     // 4 waves, one per column group
-  else if (NT == 2 && !p.paired && M <= 128) {
+  else if (NT == 2 && !p.paired && regs) {
     // 32-column groups above 32 rows: two waves per group, one n-tile each (8 waves per 128-column block); measured
     // 0.6 us (33-64 rows) and 1.5 us (65-128 rows) faster per launch than one wave per group.  For these groups chunks
     // of 4 k-blocks (half the barriers) are 0.2-1.5 us faster per launch at every row count; for the 64-column ones not.
@@ -1064,7 +1069,7 @@ static void dispatch16(const void* x, const void* wt, float* part, int M, const 
       default: launch_lds<DT, 8, NT, 1, 4, 4, 4>(x, wt, part, M, p, ss, xmtt, st, ev0, ev1);
     }
   }
-  else if (M <= 128 && !(NT == 2 && p.paired)) {
+  else if (regs && !(NT == 2 && p.paired)) {
     switch ((M + 15) / 16) {                                                                  // 8 waves, two per column group
       case 3: launch_lds<DT, 3, NT, 2, 4>(x, wt, part, M, p, ss, xmtt, st, ev0, ev1); break;
       case 4: launch_lds<DT, 4, NT, 2, 4>(x, wt, part, M, p, ss, xmtt, st, ev0, ev1); break;
@@ -1075,7 +1080,7 @@ static void dispatch16(const void* x, const void* wt, float* part, int M, const 
     }
   }
   else if (M <= 64) launch_lds<DT, 4, NT, 2, 4>(x, wt, part, M, p, ss, xmtt, st, ev0, ev1);
-  else if (M <= 128) launch_lds<DT, 8, NT, 2, 4, 8>(x, wt, part, M, p, ss, xmtt, st, ev0, ev1);   // paired: 8 groups, 256 columns
+  else if (regs) launch_lds<DT, 8, NT, 2, 4, 8>(x, wt, part, M, p, ss, xmtt, st, ev0, ev1);   // paired: 8 groups, 256 columns
   else {                                                                             // context passes, very wide windows
     GemmPlan q = p;
     if (q.tile < 0) q.tile = best_tile(M, p);
@@ -1125,7 +1130,16 @@ hipError_t gemm_gated(int dtype, const void* x, const void* wt, int M, const Gem
                       size_t slice_stride, int xmtt, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
   if (M <= 0) return hipSuccess;
   if (!p.paired || dtype == DT_F32) return hipErrorInvalidValue;
-  if (gemm_finishes(dtype, p, M)) return gemm_act(dtype, true, x, wt, M, p, act, nullptr, xmtt, st, ev0, ev1);
+  if (gemm_finishes(dtype, p, M) && aligned16(x, wt)) return gemm_act(dtype, true, x, wt, M, p, act, nullptr, xmtt, st, ev0, ev1);
+  if (gemm_finishes(dtype, p, M)) {      // one slice, but rows that cannot be copied to LDS: the iteration's launches, which need no
+    const GemmPlan it = gemm_plan_gated(dtype, p.N / 2, p.K);                               // partial sums either
+    for (int m = 0; m < M; m += gated_fused_rows(it)) {
+      const hipError_t e = gemm_gated(dtype, (const uint16_t*)x + (size_t)m * p.K, wt, std::min(M - m, gated_fused_rows(it)), it,
+                                      (uint16_t*)act + (size_t)m * (p.N / 2), nullptr, 0, 0, st);
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+  }
   if (M > gated_fused_rows(p) || p.S != 2) {
     hipError_t e = gemm(dtype, x, wt, M, p, part, slice_stride, xmtt, st, ev0, nullptr);   // timed from the first launch's
     if (e != hipSuccess) return e;                                                       // start to the second's end

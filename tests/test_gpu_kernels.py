@@ -1,4 +1,6 @@
 """Parity of each HIP kernel, called through the C ABI, against the CPU oracle on the same seeded inputs."""
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
@@ -108,6 +110,35 @@ def test_gemm_takes_rows_as_they_are(dtype, M, N):
         assert torch.equal(fl.k_gemm(other, tw), ref)
 
 
+def _at_element(t, at):
+    """A copy of t that starts `at` elements behind a 16-byte boundary."""
+    room = torch.zeros(t.numel() + 8, dtype=t.dtype, device="cuda")
+    room[at:at + t.numel()].copy_(t.reshape(-1))
+    return room[at:at + t.numel()].view(t.shape)
+
+
+@pytest.mark.parametrize("dtype,M,N,K", [(synth.DT_F32, 5, 70, 96), (synth.DT_F32, 20, 260, 1056), (synth.DT_BF16, 9, 130, 160),
+                                         (synth.DT_F16, 30, 98, 96), (synth.DT_BF16, 77, 320, 512), (synth.DT_BF16, 300, 200, 1024),
+                                         (synth.DT_F16, 129, 24576, 256), (synth.DT_BF16, 260, 24576, 8192)])
+def test_gemm_c_entry_takes_rows_at_any_element(dtype, M, N, K):
+    """flover_k_gemm itself (the binding copies such rows) with x that starts off the 16-byte grid: the bits of aligned rows, at
+    both group widths and on either side of 128 rows."""
+    g = torch.Generator(device="cuda").manual_seed(M)
+    x = torch.randn((M, K), generator=g, device="cuda").to(TDT[dtype])
+    tw = fl.binding.TiledWeight((torch.randn((N, K), generator=g, device="cuda") * 0.05).to(TDT[dtype]))
+    ref = fl.k_gemm(x, tw)
+    n = C.c_uint64()
+    lib = fl.load_library()
+    assert lib.flover_k_gemm_workspace_bytes(dtype, M, N, K, C.byref(n)) == 0
+    ws = torch.empty(int(n.value), dtype=torch.uint8, device="cuda")
+    for at in (1, 2, 3):
+        xo, y = _at_element(x, at), torch.empty_like(ref)
+        assert xo.data_ptr() % 16
+        assert lib.flover_k_gemm(dtype, xo.data_ptr(), tw.buf.data_ptr(), M, N, K, y.data_ptr(), ws.data_ptr(), n.value,
+                                 torch.cuda.current_stream().cuda_stream) == 0
+        assert torch.equal(y, ref), at
+
+
 @pytest.mark.parametrize("dtype,M,N,K", [(synth.DT_F32, 9, 96, 64), (synth.DT_BF16, 20, 512, 2048), (synth.DT_F16, 200, 1030, 512)])
 def test_gemm_result_at_any_float(dtype, M, N, K):
     """Results that start off the 16-byte grid hold the same bits, and nothing beside them is written."""
@@ -141,6 +172,27 @@ def test_gemm_result_may_share_memory_with_the_rows(dtype, M, N, K):
 
 
 # ---------------------------------------------------------------- gated MLP input (contraction + activation, one launch)
+
+@pytest.mark.parametrize("M,F,K,context", [(7, 96, 512, 0), (100, 96, 512, 0), (200, 96, 512, 0), (200, 96, 4096, 1), (200, 1376, 512, 1), (300, 11008, 1024, 1)])
+def test_gated_c_entry_takes_rows_at_any_element(M, F, K, context):
+    """flover_k_gated_mlp itself with x off the 16-byte grid.  An iteration's rows give the bits of aligned rows, and so do a
+    context pass's with slices; with one slice they are the iteration's, which add up K in two halves."""
+    dtype = synth.DT_BF16
+    g = torch.Generator(device="cuda").manual_seed(M)
+    gw = fl.binding.GatedWeight(*[(torch.randn((F, K), generator=g, device="cuda") * 0.05).to(TDT[dtype]) for _ in range(2)])
+    x = torch.randn((M, K), generator=g, device="cuda").to(TDT[dtype])
+    halves = not context or fl.binding.k_gemm_plan(dtype, 2 * F, K, M)[0] == 1
+    ref = fl.binding.k_gated_mlp(x, gw, context_pass=not halves)
+    n = C.c_uint64()
+    lib = fl.load_library()
+    assert lib.flover_k_gated_workspace_bytes(dtype, M, F, K, C.byref(n)) == 0
+    ws = torch.empty(max(int(n.value), 16), dtype=torch.uint8, device="cuda")
+    for at in (1, 5):
+        xo, act = _at_element(x, at), torch.empty_like(ref)
+        assert lib.flover_k_gated_mlp(dtype, xo.data_ptr(), gw.buf.data_ptr(), M, F, K, context, act.data_ptr(), ws.data_ptr(), n.value,
+                                      torch.cuda.current_stream().cuda_stream) == 0
+        assert torch.equal(act, ref), at
+
 
 @pytest.mark.parametrize("M", [5, 40, 100, 200])
 def test_gated_mlp_result_may_share_memory_with_the_rows(M):
