@@ -560,6 +560,35 @@ def test_more_than_128_live_rows():
     ls.close()
 
 
+@pytest.mark.parametrize("make", [lambda **k: synth.tiny_llama(synth.DT_BF16, **k), lambda **k: synth.small_gpt16(synth.DT_F16, **k),
+                                  lambda **k: synth.small_llama16(synth.DT_F16, **k), lambda **k: synth.tiny_gpt(**k),
+                                  # rows longer than a norm block's first pass over them
+                                  lambda **k: dataclasses.replace(synth.small_llama16(synth.DT_BF16, **k), H=4608, nh=36, F=512),
+                                  lambda **k: dataclasses.replace(synth.small_gpt16(synth.DT_F16, **k), H=4608, nh=36, F=512)])
+def test_a_row_among_600_live_ones_is_the_row_alone(make):
+    """A request's logits are the same bits in a window of 600, of 130 and by itself: every kernel of the iteration, at every
+    choice that it makes by the number of live rows."""
+    import paper_2305_13484_amd as fl
+    cfg = make(C=600, S=40)
+    srv = fl.Flover(cfg, synth.make_weights(cfg, 41, "cuda"))
+    g = torch.Generator(device="cuda").manual_seed(42)
+    srv.kv_cache().normal_(generator=g)
+    rng = np.random.default_rng(43)
+    lens, toks = rng.integers(0, cfg.S - 2, size=600), rng.integers(0, cfg.V, size=600)
+
+    def logits(rows):
+        for i in rows:                                      # slots in order, so that slot i holds request i's cache
+            assert srv.add_request_cached(i, int(lens[i]), int(toks[i]), 1) == i
+        out = srv.step(want_logits=True).logits.clone()
+        srv.reorder_evict()
+        return out
+    full = logits(range(600))
+    assert torch.isfinite(full).all()
+    for n in (130, 17, 1):
+        assert torch.equal(logits(range(n)), full[:n]), n
+    srv.close()
+
+
 @pytest.mark.parametrize("mode", ["slots", "off", "by_length"])
 def test_randomised_scheduler_stress(mode):
     """Many requests through few slots with random arrivals, waiting, forced finishes at seeded indices and bursts:
