@@ -57,7 +57,8 @@ struct Lane {
   void *h = nullptr, *q = nullptr, *att = nullptr, *act = nullptr;
   float* part = nullptr;
   flk::Choice* choice = nullptr;   // [rows][parts]
-  int* d_stage = nullptr;   // tok | pos | slot | len | (2 host-only arrays) | items(4x) | context-pass blocks(4x)
+  int* d_stage = nullptr;   // tok | pos | slot | len | (2 host-only arrays) | items or context-pass blocks (4x)
+  size_t stage_ints = 0;
   float *pml = nullptr, *po = nullptr;
   // pinned host staging; a ring so that passes can be queued without waiting for the previous copy
   int* h_stage[kStageRing] = {nullptr, nullptr, nullptr, nullptr};
@@ -111,7 +112,6 @@ struct flover_ctx {
   Lane prep_lanes[kPrepLanes];
   int prep_next = 0;
   int4* d_moves;
-  size_t stage_ints;
   size_t part_floats = 0;      // capacity of a lane's split-K partial-sum buffer
   size_t act_off = 0;          // arena offset where the row buffers start
   struct InFlight {                  // an iteration submitted with flover_step_submit and not collected yet
@@ -230,7 +230,6 @@ size_t layout(flover_ctx* c, char* base) {
   c->max_items = R * chunks;
   size_t pw = 0;
   for (const flk::GemmPlan* p : {&c->p_qkv, &c->p_o, &c->p_1, &c->p_2, &c->p_lm}) pw = std::max(pw, (size_t)p->S * p->ldc);
-  c->stage_ints = (size_t)6 * R + (size_t)8 * c->max_items;   // row arrays, (row, chunk, slot, len) items, context-pass blocks
   c->act_off = align_up(b.off, 256);
   std::vector<Lane*> lanes{&c->step_lane};
   for (Lane& pl : c->prep_lanes) lanes.push_back(&pl);
@@ -243,10 +242,15 @@ size_t layout(flover_ctx* c, char* base) {
     ln->act = b.take((size_t)R * F * e);
     ln->part = (float*)b.take(pw * R * 4);
     c->part_floats = pw * R;
-    ln->choice = (flk::Choice*)b.take((size_t)R * flk::argmax_parts(V) * sizeof(flk::Choice));
-    ln->d_stage = (int*)b.take(c->stage_ints * 4);
-    ln->pml = (float*)b.take((size_t)c->max_items * f.n_head * 2 * 4);
-    ln->po = (float*)b.take((size_t)c->max_items * f.n_head * f.head_dim * 4);
+    // the attention of 16-bit context passes has no work list and no partial results, and only iterations choose tokens
+    const bool lists = ln == &c->step_lane || f.dtype == FLOVER_F32;
+    ln->stage_ints = (size_t)6 * R + (lists ? (size_t)4 * c->max_items : 0);   // row arrays, items of an iteration or blocks of a pass
+    ln->d_stage = (int*)b.take(ln->stage_ints * 4);
+    if (ln == &c->step_lane) ln->choice = (flk::Choice*)b.take((size_t)R * flk::argmax_parts(V) * sizeof(flk::Choice));
+    if (lists) {
+      ln->pml = (float*)b.take((size_t)c->max_items * f.n_head * 2 * 4);
+      ln->po = (float*)b.take((size_t)c->max_items * f.n_head * f.head_dim * 4);
+    }
   }
   c->d_moves = (int4*)b.take((size_t)C * sizeof(int4));
   return align_up(b.off, 256);
@@ -733,7 +737,7 @@ int32_t flover_init(const flover_config* cfg, const flover_weights* w, flover_ct
   c->step_lane.st = c->st;
   c->step_lane.ring = kStageRing;
   for (int i = 0; i < kStageRing; ++i) {
-    HIPTRY(hipHostMalloc((void**)&c->step_lane.h_stage[i], c->stage_ints * 4, hipHostMallocDefault));
+    HIPTRY(hipHostMalloc((void**)&c->step_lane.h_stage[i], c->step_lane.stage_ints * 4, hipHostMallocDefault));
     HIPTRY(hipEventCreateWithFlags(&c->step_lane.staged[i], hipEventDisableTiming));
     HIPTRY(hipEventCreateWithFlags(&c->step_lane.done[i], hipEventDisableTiming));
     HIPTRY(hipHostMalloc((void**)&c->h_moves_ring[i], (size_t)cfg->max_concurrency * sizeof(int4), hipHostMallocDefault));
@@ -746,7 +750,7 @@ int32_t flover_init(const flover_config* cfg, const flover_weights* w, flover_ct
       HIPTRY(hipStreamCreateWithFlags(&pl.st, hipStreamNonBlocking));   // default priority
       pl.ring = kStageRing;
       for (int i = 0; i < kStageRing; ++i) {
-        HIPTRY(hipHostMalloc((void**)&pl.h_stage[i], c->stage_ints * 4, hipHostMallocDefault));
+        HIPTRY(hipHostMalloc((void**)&pl.h_stage[i], pl.stage_ints * 4, hipHostMallocDefault));
         HIPTRY(hipEventCreateWithFlags(&pl.staged[i], hipEventDisableTiming));
       }
     }

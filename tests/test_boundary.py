@@ -47,6 +47,20 @@ def test_host_only_entry_point_and_argument_errors():
     assert lib.flover_query_arena_bytes(ctypes.byref(cfg), ctypes.byref(n)) == -1
 
 
+def test_context_lanes_of_16_bit_models_hold_nothing_per_sequence_length():
+    """What a pre-processing lane adds to the arena: row buffers and partial sums of its GEMMs.  The attention of its passes
+    leaves no partial results in memory, so the lanes do not grow with max_seq (as those of fp32 models do)."""
+    import dataclasses
+    import flover_synth as synth
+
+    def lanes(cfg, S):
+        cfg = dataclasses.replace(cfg, S=S)
+        return fl.arena_bytes(cfg, 2) - fl.arena_bytes(cfg, 0)
+    for cfg in (synth.llama_7b(L=2), synth.gpt_1p3b(L=2), synth.small_llama16()):
+        assert lanes(cfg, 4096) == lanes(cfg, 512), cfg.name
+    assert lanes(synth.tiny_gpt(), 4096) > lanes(synth.tiny_gpt(), 512)
+
+
 def test_host_window_search_matches_oracle():
     from oracle import oracle as orc
     import flover_synth as synth
