@@ -307,6 +307,11 @@ int32_t flover_k_gemm_tiled_bytes(int32_t dtype, int32_t N, int32_t K, uint64_t*
  * partial-sum buffer, sized for the iteration, holds fewer at that row count). */
 int32_t flover_k_gemm_plan(int32_t dtype, int32_t N, int32_t K, int32_t context_rows, int32_t* slices,
                            int32_t* k_blocks_per_slice);
+/* [host only] The kernel that serves a 16-bit weight GEMM of more than 128 rows (INVAL otherwise): columns of the weight
+ * layout's groups, rows and columns of a block's output tile.  context_pass == 0: rows of a fused iteration (the result
+ * does not depend on the block); != 0: of one request's pre-processing pass (its q|k|v takes 128 columns for 64). */
+int32_t flover_k_gemm_block(int32_t dtype, int32_t N, int32_t K, int32_t rows, int32_t context_pass,
+                            int32_t* group_columns, int32_t* block_rows, int32_t* block_columns);
 int32_t flover_k_gemm_workspace_bytes(int32_t dtype, int32_t M, int32_t N, int32_t K, uint64_t* out);
 int32_t flover_k_gemm_retile(int32_t dtype, const void* W, int32_t N, int32_t K, void* w_tiled, void* stream);
 int32_t flover_k_gemm(int32_t dtype, const void* x, const void* w_tiled, int32_t M, int32_t N, int32_t K, float* y,

@@ -18,7 +18,7 @@ _LIB_PATH = os.path.join(_HERE, "libflover.so")
 EXPORTED_SYMBOLS = [
     "flover_query_arena_bytes", "flover_init", "flover_destroy", "flover_last_error", "flover_add_request",
     "flover_step", "flover_reorder_evict", "flover_mark_finished", "flover_set_next_token", "flover_get_state",
-    "flover_get_kv_cache", "flover_last_step_launches", "flover_step_submit", "flover_step_collect", "flover_set_layer_weights", "flover_k_gemm_plan", "flover_set_profile", "flover_get_profile", "flover_k_find_window", "flover_k_attention_workspace_bytes",
+    "flover_get_kv_cache", "flover_last_step_launches", "flover_step_submit", "flover_step_collect", "flover_set_layer_weights", "flover_k_gemm_plan", "flover_k_gemm_block", "flover_set_profile", "flover_get_profile", "flover_k_find_window", "flover_k_attention_workspace_bytes",
     "flover_k_decode_attention", "flover_k_compact_workspace_bytes", "flover_k_compact", "flover_k_gemm_tiled_bytes",
     "flover_k_gemm_workspace_bytes", "flover_k_gemm_retile", "flover_k_gemm", "flover_add_request_cached",
     "flover_k_copy_probe", "flover_k_decode_attention_noalloc", "flover_k_gated_retile", "flover_k_gated_workspace_bytes", "flover_k_gated_mlp",
@@ -302,6 +302,13 @@ def k_gemm_plan(dtype: int, N: int, K: int, context_rows: int = 0) -> Tuple[int,
     s, kbs = C.c_int32(), C.c_int32()
     _check(load_library().flover_k_gemm_plan(dtype, N, K, context_rows, C.byref(s), C.byref(kbs)))
     return s.value, kbs.value
+
+
+def k_gemm_block(dtype: int, N: int, K: int, rows: int, context_pass: bool = False) -> Tuple[int, int, int]:
+    """(columns of a layout group, rows, columns of a block) of the kernel for more than 128 rows; host only."""
+    g, r, c = C.c_int32(), C.c_int32(), C.c_int32()
+    _check(load_library().flover_k_gemm_block(dtype, N, K, rows, 1 if context_pass else 0, C.byref(g), C.byref(r), C.byref(c)))
+    return g.value, r.value, c.value
 
 
 def arena_bytes(cfg, async_preprocess: int = 0) -> int:

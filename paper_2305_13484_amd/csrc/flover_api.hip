@@ -1521,6 +1521,18 @@ extern "C" int32_t flover_k_gemm_plan(int32_t dtype, int32_t N, int32_t K, int32
   return FLOVER_OK;
 }
 
+extern "C" int32_t flover_k_gemm_block(int32_t dtype, int32_t N, int32_t K, int32_t rows, int32_t context_pass, int32_t* group_columns,
+                                       int32_t* block_rows, int32_t* block_columns) {
+  if (dtype < FLOVER_F16 || dtype > FLOVER_BF16 || N < 1 || K < 32 || K % 32 || rows <= 128 || !group_columns || !block_rows ||
+      !block_columns)
+    return fail(nullptr, FLOVER_E_INVAL, "bad argument");
+  flk::GemmPlan p = flk::gemm_plan(dtype, N, K);
+  if (context_pass) p = flk::context_plan(p, dtype, rows, 16);
+  *group_columns = 16 * p.NT;
+  flk::gemm_block(rows, p, block_rows, block_columns);
+  return FLOVER_OK;
+}
+
 extern "C" int32_t flover_k_gemm(int32_t dtype, const void* x, const void* w_tiled, int32_t M, int32_t N, int32_t K,
                                  float* y, void* workspace, uint64_t workspace_bytes, void* stream) {
   if (dtype < FLOVER_F32 || dtype > FLOVER_BF16 || M < 0 || N < 1 || K < 32 || K % 32)

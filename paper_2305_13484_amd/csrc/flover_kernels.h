@@ -45,6 +45,8 @@ size_t gemm_tiled_bytes(int dtype, int N, int K);
 // Slicing for a context pass of M rows of one request (a function of the matrix shape and of that request's own row
 // count only): same tiling, its own number of K slices, at most max_slices (what the partial-sum buffer holds) and 16.
 GemmPlan context_plan(const GemmPlan& p, int dtype, int M, int max_slices);
+// Block of the kernel that gemm() takes for M > 128 rows (16-bit dtypes, operands on the 16-byte grid).
+void gemm_block(int M, const GemmPlan& p, int* rows, int* columns);
 // The contraction and what follows it in one launch: fp32 models always, 16-bit models in a context pass whose plan takes K in
 // one slice (gemm_finishes); otherwise the caller goes through gemm() and the row-wise kernel.  gemm_qkv: bias, rotary, q and
 // the cache rows (o: bias, rope, pos, slot, q, kc, vc, d, Smax).  gemm_add: res[M][N] += x . W^T + bias (bias may be null).

@@ -887,18 +887,23 @@ size_t gemm_tiled_bytes(int dtype, int N, int K) {
 struct TileKernel {
   int bm, bn, occ;      // rows and columns of a block, blocks a compute unit holds
   double start, step, busy, store;
+  double w_start, w_step, w_store;   // see best_tile
 };
 static constexpr TileKernel kTile[] = {
-    {256, 256, 1, 7.7, 0.628, 0.628, 4.3e6},    // TILE_ROWS
-    {128, 256, 1, 4.9, 0.411, 0.411, 4.0e6},    // TILE_128X256
-    {128, 128, 2, 3.7, 0.256, 0.238, 4.3e6},    // TILE_128X128
-    {64, 128, 3, 2.4, 0.205, 0.169, 4.9e6},     // TILE_64X128
-    {64, 64, 4, 2.15, 0.160, 0.107, 5.1e6},     // TILE_64X64
+    {256, 256, 1, 7.7, 0.628, 0.628, 4.3e6, 7.8, 0.79, 5.2e6},    // TILE_ROWS
+    {128, 256, 1, 4.9, 0.411, 0.411, 4.0e6, 4.7, 0.53, 5.6e6},    // TILE_128X256
+    {128, 128, 2, 3.7, 0.256, 0.238, 4.3e6, 3.8, 0.343, 5.6e6},   // TILE_128X128
+    {64, 128, 3, 2.4, 0.205, 0.169, 4.9e6, 3.5, 0.22, 7.4e6},     // TILE_64X128
+    {64, 64, 4, 2.15, 0.160, 0.107, 5.1e6, 3.4, 0.158, 8.7e6},    // TILE_64X64
 };
-static double tile_cost(int tile, int M, const GemmPlan& p, int S, int kbs) {
+static long tile_blocks(int tile, int M, const GemmPlan& p, int S) {
   const TileKernel& k = kTile[tile];
   const int ncols = tile == TILE_ROWS ? p.Npad : p.N;
-  const long blocks = (long)((M + k.bm - 1) / k.bm) * ((ncols + k.bn - 1) / k.bn) * S, per_cu = (blocks + 255) / 256;
+  return (long)((M + k.bm - 1) / k.bm) * ((ncols + k.bn - 1) / k.bn) * S;
+}
+static double tile_cost(int tile, int M, const GemmPlan& p, int S, int kbs) {
+  const TileKernel& k = kTile[tile];
+  const long blocks = tile_blocks(tile, M, p, S), per_cu = (blocks + 255) / 256;
   const long full = per_cu / k.occ, rest = per_cu % k.occ;
   const double steps = full * std::max(k.step, k.busy * k.occ) + (rest ? std::max(k.step, k.busy * rest) : 0.0);
   return k.start + kbs * (0.7 * steps + 0.3 * k.busy * blocks / 256) + (double)S * M * p.N * 4.0 / k.store;
@@ -929,12 +934,26 @@ GemmPlan context_plan(const GemmPlan& p, int dtype, int M, int max_slices) {
   }
   return q;
 }
-// The slicing is given (a fused iteration of more than 128 rows, whose slices depend on the matrix alone): only the kernel.
+// The slicing is given (a fused iteration of more than 128 rows, whose slices depend on the matrix alone): only the kernel, and
+// the results do not depend on it.  Every k-block costs w_step per round of blocks on the 256 compute units: fitted to 1365
+// launches of its own (21 matrix shapes from 1000 x 512 to 32000 x 6656 at the plan's slices, 129 to 1024 rows, cold weights;
+// 6-7 % rms), for the model above, which weighs rounds and throughput for passes that share the chip, picked kernels 3.3 % off
+// the best on average and up to 21 %, this one 0.9 % and 15 % (12288 x 4096 at 768 rows 131 -> 115 us, 6144 x 2048 at 384 rows
+// 25.0 -> 20.6).
 static int best_tile(int M, const GemmPlan& p) {
+  auto cost = [&](int tile) {
+    const TileKernel& k = kTile[tile];
+    return k.w_start + p.kbs * k.w_step * ((tile_blocks(tile, M, p, p.S) + 255) / 256) + (double)p.S * M * p.N * 4.0 / k.w_store;
+  };
   int at = TILE_ROWS;
   for (int tile = TILE_ROWS + 1; tile < TILE_KINDS; ++tile)
-    if (tile_cost(tile, M, p, p.S, p.kbs) < tile_cost(at, M, p, p.S, p.kbs)) at = tile;
+    if (cost(tile) < cost(at)) at = tile;
   return at;
+}
+void gemm_block(int M, const GemmPlan& p, int* rows, int* columns) {
+  const TileKernel& k = kTile[p.tile < 0 ? best_tile(M, p) : p.tile];
+  *rows = k.bm;
+  *columns = k.bn;
 }
 
 hipError_t retile(int dtype, const void* W, int N, int K, void* tiled, int n_off, int NT, hipStream_t st, int tile_step) {
