@@ -83,8 +83,9 @@ def test_gemm_full_size_sampled_columns(M):
 @pytest.mark.parametrize("M,N,K", [(129, 70, 32), (191, 130, 64), (257, 320, 96), (130, 4100, 160), (300, 2050, 512), (513, 8192, 288),
                                    (700, 8192, 1024), (900, 12288, 2048), (1024, 22016, 256)])
 def test_gemm_of_more_than_128_rows_every_block_shape(dtype, M, N, K):
-    """Row blocks of 64, 128 and 256 rows and their ragged last ones, slices shorter than the copy ring, columns past the
-    last full block; the bound is fp32 accumulation (4e-6 of the sum of magnitudes) against fp64."""
+    """Ragged last row blocks, slices shorter than the copy ring, columns past the last full block, at the shapes' own choice of
+    block (which blocks there are is pinned in the next test); the bound is fp32 accumulation (4e-6 of the sum of magnitudes)
+    against fp64."""
     g = torch.Generator(device="cuda").manual_seed(M + N + K)
     x = torch.randn((M, K), generator=g, device="cuda").to(TDT[dtype])
     W = (torch.randn((N, K), generator=g, device="cuda") * 0.05).to(TDT[dtype])
@@ -108,6 +109,22 @@ def test_gemm_takes_rows_as_they_are(dtype, M, N):
     flat[1:] = x.reshape(-1)
     for other in (wide[:, :K], flat[1:].view(M, K)):
         assert torch.equal(fl.k_gemm(other, tw), ref)
+
+
+@pytest.mark.parametrize("dtype", [synth.DT_BF16, synth.DT_F16])
+@pytest.mark.parametrize("group,block_rows,block_columns,M,N,K", [
+    (32, 64, 64, 191, 130, 64), (32, 64, 128, 150, 6000, 64), (32, 128, 128, 131, 1000, 2048), (32, 128, 256, 257, 10000, 512),
+    (32, 256, 256, 257, 2050, 8192), (64, 64, 128, 129, 33000, 288), (64, 128, 256, 257, 33000, 512), (64, 256, 256, 130, 50257, 1024)])
+def test_gemm_of_more_than_128_rows_each_block_and_group_width(dtype, group, block_rows, block_columns, M, N, K):
+    """One shape for every block and both widths of the layout's column groups, ragged in rows and columns; the shape's choice
+    is asserted, so that a new rule cannot leave one out unnoticed.  Bound as above."""
+    assert fl.binding.k_gemm_block(dtype, N, K, M) == (group, block_rows, block_columns)
+    g = torch.Generator(device="cuda").manual_seed(M + N + K)
+    x = torch.randn((M, K), generator=g, device="cuda").to(TDT[dtype])
+    W = (torch.randn((N, K), generator=g, device="cuda") * 0.05).to(TDT[dtype])
+    got = fl.k_gemm(x, W).double()
+    xd, Wd = x.double(), W.double()
+    assert torch.all((got - xd @ Wd.T).abs() <= 4e-6 * (xd.abs() @ Wd.abs().T) + 1e-30)
 
 
 def _at_element(t, at):

@@ -1,6 +1,8 @@
 """Parity of the fused decode stream (flover_add_request / flover_step / flover_reorder_evict through the C ABI)
 against the CPU oracle, step by step, on seeded synthetic request streams."""
 import dataclasses
+import importlib.util
+import os
 
 import numpy as np
 import pytest
@@ -12,6 +14,10 @@ from helpers import (Lockstep, LockstepPipelined, gpu_run_stream, gpu_run_stream
                      oracle_per_request, assert_matches_oracle_per_request)
 
 pytestmark = pytest.mark.gpu
+
+_spec = importlib.util.spec_from_file_location("perf_cases", os.path.join(os.path.dirname(__file__), os.pardir, "perf", "cases.py"))
+perf_cases = importlib.util.module_from_spec(_spec)
+_spec.loader.exec_module(perf_cases)
 
 
 @pytest.fixture(scope="module", autouse=True)
@@ -547,6 +553,46 @@ def test_context_passes_at_the_edges_of_their_blocks(make):
     ls.close()
 
 
+# context rows of one request, and the blocks that q|k|v, out, the MLP's input and its output take: rows x columns / slices
+# (one slice: the kernel finishes the job), with the layout's group width where it is not 32 (gate|up is paired in groups of 32)
+WIDE_CONTEXTS = [
+    ("llama_7b", "bf16", 299, "64x128/1, 128x128/2, 256x256/1, 128x256/5"),
+    ("llama_7b", "bf16", 645, "256x256/1, 128x128/1, 256x256/1, 256x256/5"),
+    ("llama_7b", "f16", 1003, "256x256/1, 128x128/1, 256x256/1, 128x256/2"),
+    ("llama_30b", "bf16", 403, "256x256/1 of 64, 128x128/1, 256x256/2, 256x256/4"),
+    ("llama_30b", "bf16", 779, "256x256/1 of 64, 128x256/1, 128x256/1, 256x256/2"),
+    ("gpt_1p3b", "f16", 301, "64x128/1, 64x64/1, 128x128/1, 64x128/3"),
+    ("gpt_1p3b", "bf16", 611, "128x128/1, 64x128/1, 128x256/1, 128x128/3"),
+    ("gpt_1p3b", "f16", 1001, "128x256/1, 64x128/1, 128x256/1, 128x128/2"),
+]
+
+
+@pytest.mark.parametrize("model,dtype,rows,blocks", WIDE_CONTEXTS)
+def test_context_pass_of_hundreds_of_rows_against_64_bits(model, dtype, rows, blocks):
+    """Keys and values that a pass of one prompt leaves in the cache, row by row, at the shapes and row counts that take the
+    wide blocks with their epilogues (rotary and append, residual add, both activations), ragged last blocks included.  The
+    bound is twice the whole cache's tolerance; a row or column written to the wrong place is off by its own size."""
+    import paper_2305_13484_amd as fl
+    case = {"kind": "context", "model": model, "dtype": dtype, "layers": 2, "rows": 1, "slots": 2, "max_seq": 1056, "len_lo": rows + 1,
+            "len_hi": rows + 1, "overlap": False}
+    arch, H, _, _, F, _, _ = perf_cases.MODELS[model]
+    matrices = [(3 * H, H), (H, H), (2 * F if arch == "llama" else F, H), (H, F)]
+    took = []
+    for N, K in matrices:
+        group, bm, bn = fl.binding.k_gemm_block(2, N, K, rows, True)
+        took.append("%dx%d/%d%s" % (bm, bn, fl.binding.k_gemm_plan(2, N, K, rows)[0], " of 64" if group == 64 and N != 2 * F else ""))
+    assert ", ".join(took) == blocks
+    state = perf_cases.prepare(case, 5)
+    got, = perf_cases.run(state)
+    torch.cuda.synchronize()
+    ref, = perf_cases.exact(case, 5)                      # [layer][k|v][head][row][d]
+    err = (got.double() - ref).norm(dim=(2, 4)) / ref.norm(dim=(2, 4))
+    print(model, dtype, rows, "largest error of a row", float(err.max()), "at the last row", float(err[:, :, -1].max()))
+    assert float(err.max()) <= 2 * perf_cases.tolerance(case)["rel"]
+    state["engine"].close()
+    torch.cuda.empty_cache()
+
+
 def test_more_than_128_live_rows():
     """max_concurrency above one GEMM row block: 150 requests live at once (two row blocks, XCD-mapped), against the
     oracle on a tiny model, and the window bookkeeping with a large burst."""
@@ -587,6 +633,55 @@ def test_a_row_among_600_live_ones_is_the_row_alone(make):
     for n in (130, 17, 1):
         assert torch.equal(logits(range(n)), full[:n]), n
     srv.close()
+
+
+CHOICES = {                                    # what the output projection's columns hold; V is their number
+    "a tie across parts": lambda v: v.index_fill_(0, torch.tensor([100, 1700, len(v) - 1]), 2.0),
+    "a tie at the edge of two parts": lambda v: v.index_fill_(0, torch.tensor([1667, 1668]), 2.0),
+    "the last column": lambda v: v.index_fill_(0, torch.tensor([len(v) - 1]), 2.0),
+    "a part of NaNs": lambda v: v[:1668].fill_(float("nan")),
+    "NaNs around one number": lambda v: v.fill_(float("nan")).index_fill_(0, torch.tensor([4000]), -3.0),
+    "NaNs only": lambda v: v.fill_(float("nan")),
+    "minus infinity only": lambda v: v.fill_(-float("inf")),
+    "minus infinity and NaN": lambda v: v.fill_(-float("inf")).index_fill_(0, torch.tensor([7, 2000]), float("nan")),
+    "one number above minus infinity": lambda v: v.fill_(-float("inf")).index_fill_(0, torch.tensor([3333]), -2.0),
+    "two plus infinities": lambda v: v.index_fill_(0, torch.tensor([2500, 4500]), float("inf")),
+}
+
+
+@pytest.mark.parametrize("V", [5000, 4999])
+@pytest.mark.parametrize("kind", CHOICES)
+def test_greedy_choice_over_the_parts_of_a_vocabulary(kind, V):
+    """The lowest column of the largest logit, no NaN ever, column 0 where there is none, with the vocabulary in three parts;
+    logits on and off the 16-byte grid, the token as the host returns it and as the next iteration takes it."""
+    import paper_2305_13484_amd as fl
+    cfg = dataclasses.replace(synth.small_llama16(synth.DT_BF16, C=4, S=24), V=V)
+    w = synth.make_weights(cfg, 51, "cuda")
+    w["wte"][:, 0] = 8.0                       # the first feature is positive in every row, and the only one that counts
+    v = torch.empty(V).uniform_(-1, 1, generator=torch.Generator().manual_seed(52))
+    CHOICES[kind](v)
+    w["wlm"].zero_()
+    w["wlm"][:, 0] = v.to(torch.bfloat16).cuda()
+    col = v.to(torch.bfloat16).float()
+    numbers = torch.where(torch.isnan(col), torch.full_like(col, -float("inf")), col)
+    best = int(torch.argmax((numbers == numbers.max()).int())) if numbers.max() > -float("inf") else 0
+    prompts = [np.asarray(p, np.int32) for p in ([1, 2, 3], [4], [5, 6])]
+    srv, piped = fl.Flover(cfg, w), fl.Flover(cfg, w)
+    for i, p in enumerate(prompts):
+        srv.add_request(i, p, 2)
+        piped.add_request(i, p, 2)
+    room = torch.empty(3 * V + 3, dtype=torch.float32, device="cuda")
+    for at in (0, 1):
+        out = srv.step(want_logits=True)
+        lg = room[at:at + 3 * V].view(3, V)
+        assert piped.step_submit(lg) == 3
+        torch.cuda.synchronize()
+        assert torch.equal(torch.isnan(out.logits[0].cpu()), torch.isnan(col))
+        assert torch.equal(lg.view(torch.int32), out.logits.view(torch.int32))
+        assert out.token.tolist() == [best] * 3
+    assert piped.step_collect().token.tolist() == [best] * 3 and piped.step_collect().token.tolist() == [best] * 3
+    srv.close()
+    piped.close()
 
 
 @pytest.mark.parametrize("mode", ["slots", "off", "by_length"])
