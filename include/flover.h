@@ -330,7 +330,7 @@ int32_t flover_k_gemm(int32_t dtype, const void* x, const void* w_tiled, int32_t
  * activation is a second launch, with the same result bit for bit.
  * context_pass != 0, the M rows of one request's pre-processing pass (Section V-B): K is sliced by M as well, as
  * flover_k_gemm_plan reports for context rows; with one slice and more than 128 rows the activation is the epilogue of
- * the 256-row-block kernel, otherwise partial sums and a second launch.
+ * the contraction, otherwise partial sums and a second launch.
  * workspace [device], flover_k_gated_workspace_bytes bytes (0 where one launch serves the fused iteration); NOMEM if
  * it is needed and smaller. */
 int32_t flover_k_gated_retile(int32_t dtype, const void* Wgate, const void* Wup, int32_t F, int32_t K, void* w_tiled,

@@ -168,19 +168,21 @@ __device__ __forceinline__ void copy_to_lds(const char* base, uint32_t off, u32x
                                            (__attribute__((address_space(3))) void*)l, 16, off, 0, 0, 0);
 }
 
-// ---- cross-lane: DPP within a row of 16 lanes, LDS-permute beyond.  Every step is a fixed butterfly,
+// ---- cross-lane: DPP within a row of 16 lanes, lane swaps beyond.  Every step is a fixed butterfly,
 // so a reduction's result does not depend on anything but the values reduced.
 template <int CTRL> __device__ __forceinline__ float dpp_f(float v) {
   return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, false));
 }
-// xor-butterfly partner of `v` at distance DIST (power of two < 64); valid when all lanes at smaller distances
+// xor-butterfly partner of `v` at distance DIST (1, 2, 4 or 8); valid when all lanes at smaller distances
 // already agree for DIST in {4, 8} (mirror forms), which is how the reductions below use it.
 template <int DIST> __device__ __forceinline__ float partner(float v) {
   if constexpr (DIST == 1) return dpp_f<0xB1>(v);        // quad_perm [1,0,3,2]
   else if constexpr (DIST == 2) return dpp_f<0x4E>(v);   // quad_perm [2,3,0,1]
   else if constexpr (DIST == 4) return dpp_f<0x141>(v);  // row_half_mirror
-  else if constexpr (DIST == 8) return dpp_f<0x140>(v);  // row_mirror
-  else return __shfl_xor(v, DIST, 64);
+  else {
+    static_assert(DIST == 8, "within a row of 16 lanes");
+    return dpp_f<0x140>(v);                              // row_mirror
+  }
 }
 // v + its partner, and the larger of the two; at distances 16 and 32 the lane swaps give both sides of the pair without a
 // round through LDS (sums are the same bits: a + b = b + a).

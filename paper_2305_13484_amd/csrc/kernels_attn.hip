@@ -401,7 +401,7 @@ __global__ __launch_bounds__(256) void attn_prefill_kernel(const void* __restric
 // next three steps are on their way to LDS by asynchronous copies (a ring of four steps), shared by the block's waves.
 //   scores   S^T[key][query] = K . Q^T   : A = K rows (a lane's 16 bytes are 8 consecutive d of one key; copied in that
 //                                          order), B = Q^T (8 consecutive d of one query);
-//   softmax  per query = per output column: 8 values in the lane, then the 4 lane groups (2 shuffles);
+//   softmax  per query = per output column: 8 values in the lane, then the 4 lane groups (2 lane swaps);
 //   output   O^T[d][query] += V^T . P^T  : B = P^T is what the lane already holds from S^T (keys 4g..4g+3 of both
 //            16-key tiles = its 8 k-slots), A = V^T by transposing LDS reads (ds_read_b64_tr_b16: 16 lanes give the
 //            addresses of 4 keys x 16 d and get 4 keys of one d each).  V rows lie in LDS with their 16-byte pieces

@@ -881,9 +881,9 @@ size_t gemm_tiled_bytes(int dtype, int N, int K) {
 // Fitted to 3000 measured launches (16 matrix shapes from 512 x 512 to 35840 x 6656, 132 to 1024 rows, 1 to 8 slices,
 // cold weights): 6-8 % rms per kernel, and the kernel and count it picks are on average 0.7 % slower than the best.
 // That is the time of a launch that has the chip to itself; two pre-processing streams share it, and there the work per
-// launch counts (blocks x steps over 256 compute units).  Weighed 7 : 3 (0, 3, 5, 8 and 10 tenths tried: prompts of 120 to
-// 440 tokens at the 1.3B shape one after the other 1.90 / 1.96 / 1.95 / 2.05 / 3.81 ms, two overlapped 7B prompts of 780
-// and 940 tokens 2.96 / 2.88 / 2.9-3.1 / 2.86 / 2.87 ms).
+// launch counts (blocks x steps over 256 compute units).  Weighed 7 : 3 in every mode: over 28 sets of 1 to 4 prompts of 130 to
+// 1025 tokens at the 7B, GPT-1.3B and 30B shapes, 10 : 0 takes 0.997 of its time one after the other and 1.005 overlapped,
+// 5 : 5 1.013 and 1.012.
 struct TileKernel {
   int bm, bn, occ;      // rows and columns of a block, blocks a compute unit holds
   double start, step, busy, store;
@@ -910,7 +910,9 @@ static double tile_cost(int tile, int M, const GemmPlan& p, int S, int kbs) {
 }
 
 // Kernel and slice count of a context pass's GEMM: the pair with the least time, counting what the result costs the next
-// kernel as well -- fp32 sums read back (4 TB/s) and a launch of its own, unless the kernel takes K in one slice and finishes the job in its epilogue.
+// kernel as well -- fp32 sums read back (4 TB/s) and a launch of its own, unless the kernel takes K in one slice and finishes the
+// job in its epilogue.  Priced as if every one-slice kernel did (an unpaired gate|up matrix does not), and with the blocks in
+// the table (q|k|v takes 128 columns where 64 are picked).
 GemmPlan context_plan(const GemmPlan& p, int dtype, int M, int max_slices) {
   GemmPlan q = p;
   if (dtype == DT_F32 || M <= 128) return q;
@@ -1143,7 +1145,7 @@ static void dispatch_gated(const void* x, const void* wt, void* act, int M, cons
 // halves as partial sums and the activation as its own launch -- the same two chains, added in the same order, rounded
 // once: bit-identical results.  (At 65-128 rows the x tile of a 128-column block weighs as much as its weights; the one
 // launch still measures 1.3 % faster per step there than the two: no partial sums, no second launch.)  A context
-// pass's plan: one slice -> the 256-row-block kernel with the activation as its epilogue; any other slice count ->
+// pass's plan: one slice -> the kernel that the plan names with the activation as its epilogue; any other slice count ->
 // gemm() and the activation launch.
 hipError_t gemm_gated(int dtype, const void* x, const void* wt, int M, const GemmPlan& p, void* act, float* part,
                       size_t slice_stride, int xmtt, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
