@@ -260,7 +260,7 @@ __global__ __launch_bounds__(256) void act_kernel(const float* __restrict__ part
     o = act_swiglu(g, u);
   } else {
     const f32x4_t t = psum4(part, S, stride, (size_t)m * ldp + j) + ldv4<DT>(bias, j);
-    o = act_gelu(t);
+    o = act_gelu<DT>(t);
   }
   stv4<DT>(a, xrow_index((int)m, j, F, mtt), o);
 }
