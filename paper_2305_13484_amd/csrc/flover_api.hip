@@ -193,9 +193,9 @@ size_t layout(flover_ctx* c, char* base) {
   const int e = esize(f.dtype), L = f.n_layer, H = f.hidden, F = f.ffn, V = f.vocab, C = f.max_concurrency, S = f.max_seq;
   const bool gpt = f.arch == FLOVER_ARCH_GPT;
   Bump b{base};
-  c->p_qkv = flk::gemm_plan(f.dtype, 3 * H, H);
+  c->p_qkv = flk::gemm_plan_finished(f.dtype, 3 * H, H);
   c->p_o = flk::gemm_plan(f.dtype, H, H);
-  c->p_1 = gpt ? flk::gemm_plan(f.dtype, F, H) : flk::gemm_plan_gated(f.dtype, F, H);
+  c->p_1 = gpt ? flk::gemm_plan_finished(f.dtype, F, H) : flk::gemm_plan_gated(f.dtype, F, H);
   c->p_2 = flk::gemm_plan(f.dtype, H, F);
   c->p_lm = flk::gemm_plan(f.dtype, V, H);
   c->lw.resize(L);
@@ -417,8 +417,8 @@ int run_rows(flover_ctx* c, Lane& ln, const Row* rows, int n, bool want_tokens, 
     char* kl = c->kv + (size_t)(2 * l) * c->plane_bytes;
     char* vl = kl + c->plane_bytes;
     const bool gs = gemm_iter && l == L / 2;
-    // a GEMM whose kernel finishes the job leaves nothing to the row-wise kernel behind it (in a fused iteration: fp32 models)
-    auto finishes = [&](const flk::GemmPlan& p) { return (context_pass || f.dtype == FLOVER_F32) && flk::gemm_finishes(f.dtype, p, n); };
+    // a GEMM whose kernel finishes the job leaves nothing to the row-wise kernel behind it
+    auto finishes = [&](const flk::GemmPlan& p) { return flk::gemm_finishes(f.dtype, p, n); };
     {
       const GemmTimer t(c, ln, FLOVER_PROF_GEMM_QKV, p_qkv, gs);
       if (finishes(p_qkv)) {
@@ -1597,7 +1597,7 @@ extern "C" int32_t flover_k_gated_mlp(int32_t dtype, const void* x, const void* 
   if (!x || !w_tiled || !act) return fail(nullptr, FLOVER_E_INVAL, "null argument");
   if (context_pass) p = flk::context_plan(p, dtype, M, 16);
   const size_t stride = (size_t)M * p.ldc;
-  const bool one_launch = (p.S == 2 && M <= flk::gated_fused_rows(p)) || (p.S == 1 && M > 128);
+  const bool one_launch = (p.whole && M <= flk::kWholeRows) || (!p.whole && p.S == 2 && M <= flk::gated_fused_rows(p)) || (p.S == 1 && M > 128);
   if (!one_launch && (!workspace || (size_t)p.S * stride * 4 > workspace_bytes))
     return fail(nullptr, FLOVER_E_NOMEM, "gated workspace too small");
   HIPCHK(nullptr, flk::gemm_gated(dtype, x, w_tiled, M, p, act, (float*)workspace, stride, 0, (hipStream_t)stream));

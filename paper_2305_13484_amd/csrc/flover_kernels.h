@@ -17,12 +17,17 @@ struct GemmPlan {
   int ldc;    // row length of the partial-sum slices (N rounded up to 4)
   int tile = -1;    // more than 128 rows: which kernel (TILE_*), -1 = left to gemm()
   int paired = 0;   // gate|up of a gated MLP in paired 32-column groups (see gemm_plan_gated)
+  int whole = 0;    // up to kWholeRows rows one block takes all of K and finishes the job (see gemm_plan_finished)
 };
+constexpr int kWholeRows = 128;
 // kernels of more than 128 rows, by block shape: TILE_ROWS holds the weights in registers, the others copy both operands
 // to LDS (gemm16_rows_kernel, gemm16_tile_kernel)
 enum { TILE_ROWS = 0, TILE_128X256 = 1, TILE_128X128 = 2, TILE_64X128 = 3, TILE_64X64 = 4, TILE_KINDS = 5 };
 inline int part_ld(int N) { return (N + 3) / 4 * 4; }
 GemmPlan gemm_plan(int dtype, int N, int K);
+// The same for a matrix whose result a row-wise kernel would only finish (q|k|v, the input of an ungated MLP), which the GEMM does
+// itself up to kWholeRows rows where the shape makes that the shorter way.
+GemmPlan gemm_plan_finished(int dtype, int N, int K);
 // Where a GEMM that finishes the job leaves its result (the members its kind of epilogue uses).
 struct TileOut {
   float* part = nullptr;          // partial sums; or the residual stream [M][ldc] the result is added to
@@ -38,7 +43,7 @@ struct TileOut {
 };
 // gate|up of a gated MLP with F columns each.  paired = 1: group j of the layout holds gate columns 16j..16j+15 then up
 // columns 16j..16j+15 (re-tile gate with n_off = 0 and up with n_off = 16, both with tile_step = 2), K is cut in two
-// halves, gemm_gated() serves the fused iterations, and gemm() writes its partial sums in that column order (gate column
+// halves (or as gemm_plan_finished does), gemm_gated() serves the fused iterations, and gemm() writes its partial sums in that column order (gate column
 // j at (j/16)*32 + j%16, up column j 16 further).  paired = 0 (fp32, or a shape the fused kernels do not take): gemm_plan(2F, K), up after gate.
 GemmPlan gemm_plan_gated(int dtype, int F, int K);
 size_t gemm_tiled_bytes(int dtype, int N, int K);
@@ -47,8 +52,8 @@ size_t gemm_tiled_bytes(int dtype, int N, int K);
 GemmPlan context_plan(const GemmPlan& p, int dtype, int M, int max_slices);
 // Block of the kernel that gemm() takes for M > 128 rows (16-bit dtypes, operands on the 16-byte grid).
 void gemm_block(int M, const GemmPlan& p, int* rows, int* columns);
-// The contraction and what follows it in one launch: fp32 models always, 16-bit models in a context pass whose plan takes K in
-// one slice (gemm_finishes); otherwise the caller goes through gemm() and the row-wise kernel.  gemm_qkv: bias, rotary, q and
+// The contraction and what follows it in one launch: fp32 models always, 16-bit models up to kWholeRows rows where the plan says so
+// and in a context pass whose plan takes K in one slice (gemm_finishes); otherwise the caller goes through gemm() and the row-wise kernel.  gemm_qkv: bias, rotary, q and
 // the cache rows (o: bias, rope, pos, slot, q, kc, vc, d, Smax).  gemm_add: res[M][N] += x . W^T + bias (bias may be null).
 // gemm_act: GELU of x . W^T + bias, or SwiGLU (16-bit: paired layout; fp32: up after gate).  x is read and the activation written
 // in the layout xmtt says.
@@ -78,7 +83,7 @@ hipError_t gemm(int dtype, const void* x, const void* w_tiled, int M, const Gemm
 // two launches (same result, bit for bit).
 // rows up to which gemm_gated() is one launch for this plan: 128, or 64 for a matrix whose 128-column blocks outnumber the
 // compute units (it takes 16-wave blocks, whose hand-over space in LDS ends at four row tiles)
-inline int gated_fused_rows(const GemmPlan& p) { return (p.N / 2 / 16 + 3) / 4 > 256 ? 64 : 128; }
+inline int gated_fused_rows(const GemmPlan& p) { return p.whole ? kWholeRows : (p.N / 2 / 16 + 3) / 4 > 256 ? 64 : 128; }
 hipError_t gemm_gated(int dtype, const void* x, const void* w_tiled, int M, const GemmPlan& p, void* act, float* part,
                       size_t slice_stride, int xmtt, hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 

@@ -516,6 +516,134 @@ __device__ __forceinline__ void tile_epilogue(f32x4_t (&acc)[A][B], const TileOu
   }
 }
 
+// ---- up to 128 rows, K of moderate length: a block per column group (32 columns), all of K in one block, its S slices in the block's
+// S waves, what follows the contraction as the epilogue -- no partial sums in memory and no launch that adds them up.  A wave is
+// the direct kernel's: weights and rows' operand straight to registers, PF k-blocks ahead, no barrier before the hand-over of the
+// sums through LDS.  They are added in slice order, so a row's bits are those of gemm() and the row-wise kernel behind it.
+template <int DT, int MT, int S, int PF, int EPI>
+__global__ __launch_bounds__(64 * S) void gemm16_whole_kernel(const uint16_t* __restrict__ x, const u32x4_t* __restrict__ wt, TileOut o, int M,
+                                                              int N, int KB, int kbs, int xmtt) {
+  __shared__ f32x4_t red[S][MT][2][64];
+  const int lane = threadIdx.x & 63, s = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int kb0 = s * kbs, kb1 = min(KB, kb0 + kbs), c4 = (lane >> 4) * 4;
+  // the block's two n-tiles: a group of the layout (gate and up of the same columns where it is paired), or for a rotary epilogue
+  // the partners (i, i + d/2) of a head
+  int t0 = blockIdx.x * 2, t1 = t0 + 1;
+  if (EPI == EPI_QKV && o.rope) {
+    const int h = o.d >> 5;                      // n-tiles of half a head
+    t0 = (int)blockIdx.x / h * 2 * h + (int)blockIdx.x % h;
+    t1 = t0 + h;
+  }
+  const u32x4_t* w0 = wt + ((size_t)(t0 >> 1) * KB * 2 + (t0 & 1)) * 64 + lane;      // + kb * 128
+  const u32x4_t* w1 = wt + ((size_t)(t1 >> 1) * KB * 2 + (t1 & 1)) * 64 + lane;
+  // rows' operand: row-major (xmtt == 0; rows past M repeat the last one) or fragment order with xmtt row tiles per k-block
+  const size_t kstride = xmtt ? (size_t)xmtt * 512 : 32;
+  uint32_t xo[MT];
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+    xo[i] = xmtt ? (uint32_t)(i * 512 + lane * 8) : (uint32_t)min(i * 16 + (lane & 15), M - 1) * KB * 32 + (lane >> 4) * 8;
+  u32x4_t bq[PF][2], aq[PF][MT];
+  auto load = [&](int j, int kb) {
+    const int kk = min(kb, kb1 - 1);             // past the slice: its last block once more (in bounds, unused)
+    bq[j][0] = __builtin_nontemporal_load(w0 + (size_t)kk * 128);
+    bq[j][1] = __builtin_nontemporal_load(w1 + (size_t)kk * 128);
+#pragma unroll
+    for (int i = 0; i < MT; ++i) aq[j][i] = *(const u32x4_any*)(x + xo[i] + kk * kstride);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+#pragma unroll
+  for (int j = 0; j < PF; ++j) load(j, kb0 + j);
+  f32x4_t acc[MT][2];
+#pragma unroll
+  for (int i = 0; i < MT; ++i) acc[i][0] = acc[i][1] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  auto multiply = [&](int j) {
+#pragma unroll
+    for (int i = 0; i < MT; ++i) {
+      acc[i][0] = mfma16<DT>(bq[j][0], aq[j][i], acc[i][0]);
+      acc[i][1] = mfma16<DT>(bq[j][1], aq[j][i], acc[i][1]);
+    }
+  };
+  int kb = kb0;
+  for (; kb + PF <= kb1; kb += PF)
+#pragma unroll
+    for (int j = 0; j < PF; ++j) {
+      multiply(j);
+      load(j, kb + j + PF);
+    }
+#pragma unroll
+  for (int j = 0; j < PF - 1; ++j)
+    if (kb + j < kb1) multiply(j);
+  // what the epilogue reads, under way during the hand-over
+  constexpr int OWN = (MT + S - 1) / S;          // row tiles a wave finishes: s, s + S, ...
+  const int n0 = t0 * 16 + c4, n1 = t1 * 16 + c4, half = o.d >> 1;
+  f32x4_t b0 = {0.f, 0.f, 0.f, 0.f}, b1 = b0;
+  if (EPI != EPI_GATED && o.bias) {
+    b0 = ldv4<DT>(o.bias, n0);
+    b1 = ldv4<DT>(o.bias, n1);
+  }
+  int pos[OWN], slot[OWN];
+  f32x4_t r0[OWN], r1[OWN];                      // (cos, sin) of four consecutive pairs
+  if constexpr (EPI == EPI_QKV) {
+#pragma unroll
+    for (int q = 0; q < OWN; ++q) {
+      const int m = min((s + q * S) * 16 + (lane & 15), M - 1);
+      pos[q] = o.pos[m];
+      slot[q] = o.slot[m];
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < MT; ++i) {
+    red[s][i][0][lane] = acc[i][0];
+    red[s][i][1][lane] = acc[i][1];
+  }
+  if (EPI == EPI_QKV && o.rope) {
+#pragma unroll
+    for (int q = 0; q < OWN; ++q) {
+      const float* tab = o.rope + ((size_t)pos[q] * half + (n0 & (o.d - 1))) * 2;
+      r0[q] = ld4(tab);
+      r1[q] = ld4(tab + 4);
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < OWN; ++q) {
+    const int i = s + q * S, m = i * 16 + (lane & 15);
+    if (i >= MT) break;
+    f32x4_t v[S][2];
+#pragma unroll
+    for (int p = 0; p < S; ++p) {
+      v[p][0] = red[p][i][0][lane];
+      v[p][1] = red[p][i][1][lane];
+    }
+    f32x4_t a0 = v[0][0], a1 = v[0][1];
+#pragma unroll
+    for (int p = 1; p < S; ++p) {
+      a0 += v[p][0];
+      a1 += v[p][1];
+    }
+    if (EPI != EPI_GATED && o.bias) {
+      a0 += b0;
+      a1 += b1;
+    }
+    if (m >= M) continue;
+    if constexpr (EPI == EPI_GATED) {
+      stv4<DT>(o.act, xrow_index(m, blockIdx.x * 16 + c4, o.F, o.mtt), act_swiglu(a0, a1));
+    } else if constexpr (EPI == EPI_GELU) {
+      stv4<DT>(o.act, xrow_index(m, n0, o.F, o.mtt), act_gelu<DT>(a0));
+      stv4<DT>(o.act, xrow_index(m, n1, o.F, o.mtt), act_gelu<DT>(a1));
+    } else {
+      const int H = N / 3, which = n0 / H, c = n0 - which * H;       // both tiles lie in the same third and head
+      if (o.rope && which < 2)
+        rope_rotate(a0, a1, f32x4_t{r0[q][0], r0[q][2], r1[q][0], r1[q][2]}, f32x4_t{r0[q][1], r0[q][3], r1[q][1], r1[q][3]});
+      const int hd = c / o.d, e = c - hd * o.d;
+      void* dst = which == 0 ? o.q : which == 1 ? o.kc : o.vc;
+      const size_t at = which == 0 ? (size_t)m * H + c : (((size_t)slot[q] * (H / o.d) + hd) * o.Smax + pos[q]) * o.d + e;
+      stv4<DT>(dst, at, a0);
+      stv4<DT>(dst, at + (n1 - n0), a1);
+    }
+  }
+}
+
 // The rows' operand of a block as 1 KiB fragments: row tile mt0 + f of k-block kb0 + t is at base + t * step + offset(f).
 // Row-major (xmtt == 0) or fragment order with xmtt row tiles per k-block; rows and row tiles past the last repeat it.
 struct RowTiles {
@@ -912,7 +1040,28 @@ GemmPlan gemm_plan(int dtype, int N, int K) {
   return p;
 }
 
-// gate|up of a gated MLP (N = 2F): paired 32-column groups, no K slices (the fused kernels split K in two inside),
+// A block per 32 columns with all of K in it (gemm16_whole_kernel) is the shorter way while all blocks run at once and a block's
+// bytes (its columns and all rows, over K) stay few: every block reads all rows, at the 110 bytes per nanosecond that a compute
+// unit gets.  Measured with the launch that it saves, us at 6 / 23 / 64 / 101 rows, two launches -> one: q|k|v of 2048 columns (192
+// blocks) 9.3 / 10.8 / 13.5 / 17.2 -> 7.2 / 8.5 / 10.5 / 14.0, of 2560 (240) 11.1 / 13.0 / 16.2 / 20.9 -> 8.9 / 10.5 / 12.8 / 17.6, of
+// 3072 (288) 14.1 / 15.2 / 18.6 / 23.3 -> 16.0 / 18.6 / 23.8 / 32.6; 8192 x 2048 with GELU (256) 10.7 / 12.1 / 15.3 / 19.4 -> 8.5 / 9.6 /
+// 11.0 / 15.1, 10240 x 2560 (320) 13.0 / 14.9 / 19.1 / 23.6 -> 14.4 / 17.0 / 20.9 / 28.7, 4096 x 4096 (128 blocks, long K) 10.2 / 12.2 /
+// 15.2 / 19.5 -> 10.9 / 12.9 / 16.5 / 22.6.  Four slices: with two, 48 rows and more are 10 to 40 % slower.
+static bool whole_shape(int dtype, int N, int K) { return dtype != DT_F32 && N % 32 == 0 && N / 32 <= 256 && K >= 512; }
+static constexpr int kWholeSlices = 4;
+static void take_whole(GemmPlan& p) {
+  p.NT = 2;
+  p.S = kWholeSlices;
+  p.kbs = (p.KB + kWholeSlices - 1) / kWholeSlices;      // 16 k-blocks at least: the last slice is not empty
+  p.whole = 1;
+}
+GemmPlan gemm_plan_finished(int dtype, int N, int K) {
+  GemmPlan p = gemm_plan(dtype, N, K);
+  if (whole_shape(dtype, N, K) && K <= 2560) take_whole(p);
+  return p;
+}
+
+// gate|up of a gated MLP (N = 2F): paired 32-column groups, no K slices in memory (the fused kernels split K inside),
 // when the shape allows it; otherwise the plain plan of a 2F-column matrix with gate and up side by side.
 GemmPlan gemm_plan_gated(int dtype, int F, int K) {
   GemmPlan p = gemm_plan(dtype, 2 * F, K);
@@ -921,6 +1070,9 @@ GemmPlan gemm_plan_gated(int dtype, int F, int K) {
   p.S = 2;               // the two halves of K: partial sums of gemm(), the two in-kernel chains of the fused kernels
   p.kbs = p.KB / 2;
   p.paired = 1;
+  // at any K: gated_lds_kernel has a quarter of the blocks there (F x K, us at 6 / 64 / 101 rows: 1376 x 512 4.9 / 7.9 / 10.2 -> 3.7 /
+  // 4.6 / 6.4, 4096 x 1536 10.2 / 14.5 / 18.0 -> 6.4 / 8.6 / 11.8, 1024 x 6656 34.2 / 45.0 / 55.2 -> 14.0 / 22.7 / 31.9)
+  if (whole_shape(dtype, 2 * F, K)) take_whole(p);
   return p;
 }
 
@@ -1082,6 +1234,29 @@ static void dispatch_tile(int tile, const void* x, const void* wt, const TileOut
   else if (tile == TILE_64X128 || EPI == EPI_QKV) launch_tile<DT, 2, 4, 2, 2, 4, EPI>(x, wt, o, M, p, xmtt, st, ev0, ev1);
   else if constexpr (EPI != EPI_QKV) launch_tile<DT, 2, 2, 2, 2, 4, EPI>(x, wt, o, M, p, xmtt, st, ev0, ev1);
 }
+// The whole-K kernel per count of row tiles; four k-blocks ahead, two where the rows' operand would take too many registers (eight
+// were 3 to 25 % slower: a longer way to the first product).
+template <int DT, int EPI, int MT>
+static void launch_whole(const void* x, const void* wt, const TileOut& o, int M, const GemmPlan& p, int xmtt, hipStream_t st,
+                         hipEvent_t ev0, hipEvent_t ev1) {
+  launch_timed(gemm16_whole_kernel<DT, MT, kWholeSlices, MT <= 3 ? 4 : 2, EPI>, dim3(p.N / 32), dim3(64 * kWholeSlices), st, ev0, ev1,
+               (const uint16_t*)x, (const u32x4_t*)wt, o, M, p.N, p.KB, p.kbs, xmtt);
+}
+template <int DT, int EPI>
+static void dispatch_whole(const void* x, const void* wt, const TileOut& o, int M, const GemmPlan& p, int xmtt, hipStream_t st,
+                           hipEvent_t ev0, hipEvent_t ev1) {
+  switch ((M + 15) / 16) {
+    case 1: launch_whole<DT, EPI, 1>(x, wt, o, M, p, xmtt, st, ev0, ev1); break;
+    case 2: launch_whole<DT, EPI, 2>(x, wt, o, M, p, xmtt, st, ev0, ev1); break;
+    case 3: launch_whole<DT, EPI, 3>(x, wt, o, M, p, xmtt, st, ev0, ev1); break;
+    case 4: launch_whole<DT, EPI, 4>(x, wt, o, M, p, xmtt, st, ev0, ev1); break;
+    case 5: launch_whole<DT, EPI, 5>(x, wt, o, M, p, xmtt, st, ev0, ev1); break;
+    case 6: launch_whole<DT, EPI, 6>(x, wt, o, M, p, xmtt, st, ev0, ev1); break;
+    case 7: launch_whole<DT, EPI, 7>(x, wt, o, M, p, xmtt, st, ev0, ev1); break;
+    default: launch_whole<DT, EPI, 8>(x, wt, o, M, p, xmtt, st, ev0, ev1);
+  }
+}
+static bool takes_whole(const GemmPlan& p, int M) { return p.whole && M <= kWholeRows; }
 template <int EPI>
 static hipError_t finish(int dtype, const void* x, const void* wt, const TileOut& o, int M, const GemmPlan& p, int xmtt, hipStream_t st,
                          hipEvent_t ev0, hipEvent_t ev1) {
@@ -1090,14 +1265,22 @@ static hipError_t finish(int dtype, const void* x, const void* wt, const TileOut
     const dim3 grid((pairs + 3) / 4, (M + 7) / 8);
     if (p.K <= 256) launch_timed(gemm32_kernel<EPI, 1>, grid, dim3(256), st, ev0, ev1, (const float*)x, (const float*)wt, o, M, p.N, p.K);
     else launch_timed(gemm32_kernel<EPI, 4>, grid, dim3(256), st, ev0, ev1, (const float*)x, (const float*)wt, o, M, p.N, p.K);
-  } else if (dtype == DT_BF16) {
-    dispatch_tile<DT_BF16, EPI>(p.tile, x, wt, o, M, p, xmtt, st, ev0, ev1);
-  } else {
-    dispatch_tile<DT_F16, EPI>(p.tile, x, wt, o, M, p, xmtt, st, ev0, ev1);
+    return hipGetLastError();
   }
+  if constexpr (EPI == EPI_QKV || EPI == EPI_GATED || EPI == EPI_GELU) {
+    if (takes_whole(p, M)) {
+      if (dtype == DT_BF16) dispatch_whole<DT_BF16, EPI>(x, wt, o, M, p, xmtt, st, ev0, ev1);
+      else dispatch_whole<DT_F16, EPI>(x, wt, o, M, p, xmtt, st, ev0, ev1);
+      return hipGetLastError();
+    }
+  }
+  if (dtype == DT_BF16) dispatch_tile<DT_BF16, EPI>(p.tile, x, wt, o, M, p, xmtt, st, ev0, ev1);
+  else dispatch_tile<DT_F16, EPI>(p.tile, x, wt, o, M, p, xmtt, st, ev0, ev1);
   return hipGetLastError();
 }
-bool gemm_finishes(int dtype, const GemmPlan& p, int M) { return dtype == DT_F32 || (M > 128 && p.S == 1 && p.tile >= 0); }
+bool gemm_finishes(int dtype, const GemmPlan& p, int M) {
+  return dtype == DT_F32 || takes_whole(p, M) || (M > 128 && p.S == 1 && p.tile >= 0);
+}
 
 hipError_t gemm_qkv(int dtype, const void* x, const void* wt, int M, const GemmPlan& p, const TileOut& o, int xmtt, hipStream_t st,
                     hipEvent_t ev0, hipEvent_t ev1) {
@@ -1196,9 +1379,8 @@ static void dispatch_gated(const void* x, const void* wt, void* act, int M, cons
   }
 }
 
-// The iteration's plan (two K halves): up to gated_fused_rows(p) rows one launch; above that gemm() with the two K
-// halves as partial sums and the activation as its own launch -- the same two chains, added in the same order, rounded
-// once: bit-identical results.  (At 65-128 rows the x tile of a 128-column block weighs as much as its weights; the one
+// The iteration's plan: up to gated_fused_rows(p) rows one launch; above that gemm() with the plan's K slices as partial sums
+// and the activation as its own launch -- the same chains, added in the same order, rounded once: bit-identical results.  (At 65-128 rows the x tile of a 128-column block weighs as much as its weights; the one
 // launch still measures 1.3 % faster per step there than the two: no partial sums, no second launch.)  A context
 // pass's plan: one slice -> the kernel that the plan names with the activation as its epilogue; any other slice count ->
 // gemm() and the activation launch.
@@ -1206,7 +1388,7 @@ hipError_t gemm_gated(int dtype, const void* x, const void* wt, int M, const Gem
                       size_t slice_stride, int xmtt, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
   if (M <= 0) return hipSuccess;
   if (!p.paired || dtype == DT_F32) return hipErrorInvalidValue;
-  if (gemm_finishes(dtype, p, M) && aligned16(x, wt)) return gemm_act(dtype, true, x, wt, M, p, act, nullptr, xmtt, st, ev0, ev1);
+  if (takes_whole(p, M) || (gemm_finishes(dtype, p, M) && aligned16(x, wt))) return gemm_act(dtype, true, x, wt, M, p, act, nullptr, xmtt, st, ev0, ev1);
   if (gemm_finishes(dtype, p, M)) {      // one slice, but rows that cannot be copied to LDS: the iteration's launches, which need no
     const GemmPlan it = gemm_plan_gated(dtype, p.N / 2, p.K);                               // partial sums either
     for (int m = 0; m < M; m += gated_fused_rows(it)) {
@@ -1216,7 +1398,7 @@ hipError_t gemm_gated(int dtype, const void* x, const void* wt, int M, const Gem
     }
     return hipSuccess;
   }
-  if (M > gated_fused_rows(p) || p.S != 2) {
+  if (p.whole || M > gated_fused_rows(p) || p.S != 2) {
     hipError_t e = gemm(dtype, x, wt, M, p, part, slice_stride, xmtt, st, ev0, nullptr);   // timed from the first launch's
     if (e != hipSuccess) return e;                                                       // start to the second's end
     return activation(dtype, true, part, p.S, slice_stride, p.ldc, nullptr, act, M, p.N / 2, xmtt, st, true, ev1);

@@ -635,6 +635,32 @@ def test_a_row_among_600_live_ones_is_the_row_alone(make):
     srv.close()
 
 
+@pytest.mark.parametrize("make", [lambda **k: synth.small_gpt16(synth.DT_F16, **k), lambda **k: synth.small_llama16(synth.DT_BF16, **k),
+                                  # heads of 64; slices of six and ten k-blocks, which the four loaded ahead do not divide; the
+                                  # first width whose q|k|v is two launches again
+                                  lambda **k: dataclasses.replace(synth.small_llama16(synth.DT_F16, **k), H=768, nh=12, d=64, F=512),
+                                  lambda **k: dataclasses.replace(synth.small_gpt16(synth.DT_BF16, **k), H=1280, nh=20, d=64, F=672),
+                                  lambda **k: dataclasses.replace(synth.small_gpt16(synth.DT_F16, **k), H=2816, nh=44, d=64, F=512)])
+def test_a_row_is_the_same_at_every_count_of_row_tiles(make):
+    """q|k|v with the rotation and the append, and the MLP's input with its activation, are one launch up to 128 rows (one variant per
+    count of 16-row tiles) and two above: the same bits on either side of every edge."""
+    import paper_2305_13484_amd as fl
+    cfg = make(C=140, S=40)
+    srv = fl.Flover(cfg, synth.make_weights(cfg, 51, "cuda"))
+    srv.kv_cache().normal_(generator=torch.Generator(device="cuda").manual_seed(52))
+    rng = np.random.default_rng(53)
+    lens, toks = rng.integers(0, cfg.S - 2, size=140), rng.integers(0, cfg.V, size=140)
+    full = None
+    for n in (140, 1, 15, 16, 17, 32, 33, 48, 49, 64, 65, 80, 81, 96, 97, 112, 113, 127, 128, 129):
+        for i in range(n):
+            assert srv.add_request_cached(i, int(lens[i]), int(toks[i]), 1) == i
+        out = srv.step(want_logits=True).logits.clone()
+        srv.reorder_evict()
+        full = out if full is None else full
+        assert torch.isfinite(out).all() and torch.equal(out, full[:n]), n
+    srv.close()
+
+
 CHOICES = {                                    # what the output projection's columns hold; V is their number
     "a tie across parts": lambda v: v.index_fill_(0, torch.tensor([100, 1700, len(v) - 1]), 2.0),
     "a tie at the edge of two parts": lambda v: v.index_fill_(0, torch.tensor([1667, 1668]), 2.0),
