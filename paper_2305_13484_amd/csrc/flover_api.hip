@@ -57,12 +57,11 @@ struct Lane {
   void *h = nullptr, *q = nullptr, *att = nullptr, *act = nullptr;
   float* part = nullptr;
   flk::Choice* choice = nullptr;   // [rows][parts]
-  int* d_stage = nullptr;   // tok | pos | slot | len | (2 host-only arrays) | items or context-pass blocks (4x)
-  size_t stage_ints = 0;
+  flk::RowOut rows{};       // row descriptors on the device, and the list of an iteration's attention or of an fp32 context pass's
   float *pml = nullptr, *po = nullptr;
-  // pinned host staging; a ring so that passes can be queued without waiting for the previous copy
-  int* h_stage[kStageRing] = {nullptr, nullptr, nullptr, nullptr};
-  hipEvent_t staged[kStageRing] = {nullptr, nullptr, nullptr, nullptr};   // copy of h_stage[i] has been consumed
+  // a pass's rows in pinned memory, where its first kernel reads them; a ring so that passes can be queued without waiting
+  flk::RowIn* h_rows[kStageRing] = {nullptr, nullptr, nullptr, nullptr};
+  hipEvent_t staged[kStageRing] = {nullptr, nullptr, nullptr, nullptr};   // h_rows[i] has been read
   bool staged_busy[kStageRing] = {false, false, false, false};
   int ring = 1, next = 0;
   int tok_next = 0;         // ring of token buffers: advanced only by passes that return tokens
@@ -244,8 +243,11 @@ size_t layout(flover_ctx* c, char* base) {
     c->part_floats = pw * R;
     // the attention of 16-bit context passes has no work list and no partial results, and only iterations choose tokens
     const bool lists = ln == &c->step_lane || f.dtype == FLOVER_F32;
-    ln->stage_ints = (size_t)6 * R + (lists ? (size_t)4 * c->max_items : 0);   // row arrays, items of an iteration or blocks of a pass
-    ln->d_stage = (int*)b.take(ln->stage_ints * 4);
+    int* rows = (int*)b.take((size_t)3 * R * 4);
+    ln->rows.pos = rows;
+    ln->rows.slot = rows + R;
+    ln->rows.len = rows + 2 * R;
+    ln->rows.list = lists ? (int4*)b.take((size_t)c->max_items * sizeof(int4)) : nullptr;
     if (ln == &c->step_lane) ln->choice = (flk::Choice*)b.take((size_t)R * flk::argmax_parts(V) * sizeof(flk::Choice));
     if (lists) {
       ln->pml = (float*)b.take((size_t)c->max_items * f.n_head * 2 * 4);
@@ -324,65 +326,34 @@ int run_rows(flover_ctx* c, Lane& ln, const Row* rows, int n, bool want_tokens, 
   const bool gpt = f.arch == FLOVER_ARCH_GPT;
   hipStream_t st = ln.st;
   if (n <= 0) return FLOVER_OK;
-  // row descriptors and the attention work list, one host-to-device copy from the next staging buffer of the ring
+  // row descriptors in the next buffer of the ring; the pass's first kernel reads them there and enters the attention's work list
   const int ri = ln.next;
   ln.next = (ln.next + 1) % ln.ring;
   if (ln.staged_busy[ri]) {
     HIPCHK(c, hipEventSynchronize(ln.staged[ri]));
     ln.staged_busy[ri] = false;
   }
-  int* hs = ln.h_stage[ri];
-  int *tok = hs, *pos = hs + R, *slot = hs + 2 * R, *len = hs + 3 * R, *nchunk = hs + 5 * R;   // nchunk: host use only
-  int* items = hs + 6 * R;
-  int n_items = 0;
+  flk::RowIn* hr = ln.h_rows[ri];
+  // the attention of a 16-bit context pass takes the rows as they are; an fp32 model's serves runs of consecutive positions of one
+  // slot, several query rows per wave (a pass holds rows of one request, in order)
+  flk::RowOut ro = ln.rows;
+  ro.block_rows = context_pass ? flk::kPrefillQB : 0;
+  int n_list = 0;
   int64_t attn_bytes = 0;   // K and V rows [0,len) of every row, all heads: what one attention launch has to read
   for (int i = 0; i < n; ++i) {
     attn_bytes += (int64_t)(rows[i].pos + 1) * 2 * H * esize(f.dtype);
-    tok[i] = rows[i].tok;
-    pos[i] = rows[i].pos;
-    slot[i] = rows[i].slot;
-    len[i] = rows[i].pos + 1;
-    const int nc = (len[i] + flk::kAttnChunk - 1) / flk::kAttnChunk;
-    nchunk[i] = nc;
-    if (context_pass) continue;         // its attention takes the rows as they are, or (fp32) the blocks below
-    for (int ch = 0; ch < nc; ++ch) {
-      items[4 * n_items] = i;
-      items[4 * n_items + 1] = ch;
-      items[4 * n_items + 2] = rows[i].slot;
-      items[4 * n_items + 3] = len[i];
-      ++n_items;
+    const bool enters = !context_pass || (f.dtype == FLOVER_F32 && i % flk::kPrefillQB == 0);
+    hr[i] = flk::RowIn{rows[i].tok, rows[i].pos, rows[i].slot, enters ? n_list : -1};
+    if (enters) {
+      const int last = context_pass ? std::min(i + flk::kPrefillQB, n) - 1 : i;
+      n_list += (rows[last].pos + flk::kAttnChunk) / flk::kAttnChunk;
     }
   }
-  // context pass of an fp32 model: runs of consecutive positions of one slot are served several query rows per wave
-  int n_blocks = 0;
-  int* blk = items + 4 * n_items;
-  if (context_pass && f.dtype == FLOVER_F32) {
-    for (int i = 0; i < n;) {
-      int nr = 1;
-      while (nr < flk::kPrefillQB && i + nr < n && rows[i + nr].slot == rows[i].slot && rows[i + nr].pos == rows[i].pos + nr)
-        ++nr;
-      for (int ch = 0; ch < nchunk[i + nr - 1]; ++ch) {
-        blk[4 * n_blocks] = i;
-        blk[4 * n_blocks + 1] = nr;
-        blk[4 * n_blocks + 2] = ch;
-        blk[4 * n_blocks + 3] = 0;
-        ++n_blocks;
-      }
-      i += nr;
-    }
-  }
-  HIPCHK(c, hipMemcpyAsync(ln.d_stage, hs, ((size_t)6 * R + (size_t)4 * n_items + (size_t)4 * n_blocks) * 4,
-                           hipMemcpyHostToDevice, st));
-  if (!wait) {
-    HIPCHK(c, hipEventRecord(ln.staged[ri], st));
-    ln.staged_busy[ri] = true;
-  }
-  int* ds = ln.d_stage;
-  const int *d_tok = ds, *d_pos = ds + R, *d_slot = ds + 2 * R, *d_len = ds + 3 * R;
-  flk::AttnWork aw{(const int4*)(ds + 6 * R), d_slot, d_len, ln.pml, ln.po, n_items,
-                   (f.max_seq + flk::kAttnChunk - 1) / flk::kAttnChunk};
-  aw.blocks = (const int4*)(ds + 6 * R + 4 * n_items);
-  aw.n_blocks = n_blocks;
+  const int n_items = context_pass ? 0 : n_list;
+  const int *d_pos = ro.pos, *d_slot = ro.slot;
+  flk::AttnWork aw{ro.list, d_slot, ro.len, ln.pml, ln.po, n_items, (f.max_seq + flk::kAttnChunk - 1) / flk::kAttnChunk};
+  aw.blocks = ro.list;
+  aw.n_blocks = context_pass ? n_list : 0;
   // what feeds a GEMM (norm output, attention output, MLP activation) is written in the order the GEMM's MFMA reads
   // it: 16-bit models only, tiles of 16 rows, mtt of them per k-block
   const int mtt = f.dtype == FLOVER_F32 ? 0 : (n + 15) / 16;
@@ -406,8 +377,12 @@ int run_rows(flover_ctx* c, Lane& ln, const Row* rows, int n, bool want_tokens, 
   const size_t ss_qkv = (size_t)n * p_qkv.ldc, ss_h = (size_t)n * p_o.ldc, ss_1 = (size_t)n * p_1.ldc,
                ss_v = (size_t)n * c->p_lm.ldc;
   const int parts = flk::argmax_parts(V);
-  HIPCHK(c, flk::embed_norm(f.dtype, !gpt, c->wte, c->wpe, d_tok, d_pos, ln.choice, parts, ln.x, c->lw[0].ln1_g, c->lw[0].ln1_b, ln.h, n, H,
+  HIPCHK(c, flk::embed_norm(f.dtype, !gpt, c->wte, c->wpe, hr, ro, ln.choice, parts, ln.x, c->lw[0].ln1_g, c->lw[0].ln1_b, ln.h, n, H,
                             f.norm_eps, mtt, st));
+  if (!wait) {
+    HIPCHK(c, hipEventRecord(ln.staged[ri], st));
+    ln.staged_busy[ri] = true;
+  }
   bool added = true;      // the residual stream already holds what the GEMM before the norm computed
   for (int l = 0; l < L; ++l) {
     const LayerW& w = c->lw[l];
@@ -488,12 +463,10 @@ int run_rows(flover_ctx* c, Lane& ln, const Row* rows, int n, bool want_tokens, 
                             c->lnf_g, c->lnf_b, ln.h, n, H, f.norm_eps, mtt, st));
     const GemmTimer t(c, ln, FLOVER_PROF_GEMM_LM, c->p_lm, gemm_iter);
     HIPCHK(c, flk::gemm(f.dtype, ln.h, c->wlm, n, c->p_lm, ln.part, ss_v, mtt, st, t.ev0, t.ev1));
-    HIPCHK(c, flk::logits_argmax(ln.part, c->p_lm.S, ss_v, c->p_lm.ldc, logits_out, ln.choice, n, V, st));
     const int ti = ln.tok_next;       // at most kStageRing - 1 iterations are outstanding, so this entry is free
     ln.tok_next = (ln.tok_next + 1) % kStageRing;
     if (ring_used) *ring_used = ti;
-    HIPCHK(c, hipMemcpyAsync(ln.h_choice + (size_t)ti * R * parts, ln.choice, (size_t)n * parts * sizeof(flk::Choice), hipMemcpyDeviceToHost,
-                             st));
+    HIPCHK(c, flk::logits_argmax(ln.part, c->p_lm.S, ss_v, c->p_lm.ldc, logits_out, ln.choice, ln.h_choice + (size_t)ti * R * parts, n, V, st));
     if (!wait) HIPCHK(c, hipEventRecord(ln.done[ti], st));
     launches += 3;
   }
@@ -653,7 +626,7 @@ void release(flover_ctx* c) {
   for (Lane& pl : c->prep_lanes) lanes.push_back(&pl);
   for (Lane* ln : lanes) {
     for (int i = 0; i < kStageRing; ++i) {
-      if (ln->h_stage[i]) (void)hipHostFree(ln->h_stage[i]);
+      if (ln->h_rows[i]) (void)hipHostFree(ln->h_rows[i]);
       if (ln->staged[i]) (void)hipEventDestroy(ln->staged[i]);
       if (ln->done[i]) (void)hipEventDestroy(ln->done[i]);
     }
@@ -737,7 +710,7 @@ int32_t flover_init(const flover_config* cfg, const flover_weights* w, flover_ct
   c->step_lane.st = c->st;
   c->step_lane.ring = kStageRing;
   for (int i = 0; i < kStageRing; ++i) {
-    HIPTRY(hipHostMalloc((void**)&c->step_lane.h_stage[i], c->step_lane.stage_ints * 4, hipHostMallocDefault));
+    HIPTRY(hipHostMalloc((void**)&c->step_lane.h_rows[i], c->rows_cap * sizeof(flk::RowIn), hipHostMallocDefault));
     HIPTRY(hipEventCreateWithFlags(&c->step_lane.staged[i], hipEventDisableTiming));
     HIPTRY(hipEventCreateWithFlags(&c->step_lane.done[i], hipEventDisableTiming));
     HIPTRY(hipHostMalloc((void**)&c->h_moves_ring[i], (size_t)cfg->max_concurrency * sizeof(int4), hipHostMallocDefault));
@@ -750,7 +723,7 @@ int32_t flover_init(const flover_config* cfg, const flover_weights* w, flover_ct
       HIPTRY(hipStreamCreateWithFlags(&pl.st, hipStreamNonBlocking));   // default priority
       pl.ring = kStageRing;
       for (int i = 0; i < kStageRing; ++i) {
-        HIPTRY(hipHostMalloc((void**)&pl.h_stage[i], pl.stage_ints * 4, hipHostMallocDefault));
+        HIPTRY(hipHostMalloc((void**)&pl.h_rows[i], c->rows_cap * sizeof(flk::RowIn), hipHostMallocDefault));
         HIPTRY(hipEventCreateWithFlags(&pl.staged[i], hipEventDisableTiming));
       }
     }

@@ -102,10 +102,22 @@ __host__ __device__ inline int best_choice(const Choice* c, int parts) {
   return b.token == kNoToken ? 0 : b.token;
 }
 int argmax_parts(int V);
-// x = embedding of the rows (wpe: learned positions, may be null), h = the norm of it.  tok[m] < 0: the token is the best of
-// the previous iteration's choices for its row -1 - tok[m].
-hipError_t embed_norm(int dtype, bool rms, const void* wte, const void* wpe, const int* tok, const int* pos, const Choice* prev, int parts,
-                      float* x, const void* g, const void* b, void* h, int M, int H, float eps, int mtt, hipStream_t st);
+// A pass's rows as the host leaves them in pinned memory.  The first kernel of a pass reads them there and lays out on the device
+// what the others want.
+struct alignas(16) RowIn {
+  int32_t tok, pos, slot;
+  int32_t first;           // number of the row's first entry in `list`, -1: none
+};
+struct RowOut {            // device memory
+  int *pos, *slot, *len;   // [rows]; len = pos + 1, the rows of cache attended to
+  int4* list;              // one entry per chunk of kAttnChunk positions: (row, chunk, slot, len), or where block_rows > 0 (row, rows
+                           // of the block, chunk, -) for each block of consecutive positions, entered by its first row
+  int block_rows;
+};
+// x = embedding of the rows (wpe: learned positions, may be null), h = the norm of it.  tok < 0: the token is the best of
+// the previous iteration's choices for its row -1 - tok.
+hipError_t embed_norm(int dtype, bool rms, const void* wte, const void* wpe, const RowIn* rows, const RowOut& out, const Choice* prev,
+                      int parts, float* x, const void* g, const void* b, void* h, int M, int H, float eps, int mtt, hipStream_t st);
 // `part` is the preceding GEMM's split-K output: S slices, `stride` floats apart, rows of `ldp` floats (ldp % 4 == 0).
 // h (and the outputs of activation and of the attention calls below) feed a GEMM: with mtt = ceil(M/16) they are
 // written in fragment order (16-bit dtypes; see gemm), with mtt == 0 row-major.
@@ -117,7 +129,9 @@ hipError_t qkv_post(int dtype, const float* part, int S, size_t stride, int ldp,
 // paired: gate and up columns of `part` interleaved in tiles of 16 (see gemm_plan_gated); gated activation only.
 hipError_t activation(int dtype, bool swiglu, const float* part, int S, size_t stride, int ldp, const void* bias, void* a,
                       int M, int F, int mtt, hipStream_t st, bool paired = false, hipEvent_t ev1 = nullptr);
-hipError_t logits_argmax(const float* part, int S, size_t stride, int ldp, float* logits, Choice* choice, int M, int V, hipStream_t st);
+// choice: device memory, for the next iteration; choice_host: the same in pinned memory, for the host.
+hipError_t logits_argmax(const float* part, int S, size_t stride, int ldp, float* logits, Choice* choice, Choice* choice_host, int M, int V,
+                         hipStream_t st);
 
 // ---- ragged decode attention
 constexpr int kAttnChunk = 256;   // most positions of a wave task; fixed, so chunking depends on a request's own length only

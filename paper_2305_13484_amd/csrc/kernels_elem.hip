@@ -155,17 +155,34 @@ __global__ __launch_bounds__(1024 / VW) void add_norm_kernel(float* __restrict__
 // ---------------------------------------------------------------- embedding + first norm
 // x[m][i] = wte[tok[m]][i] (+ wpe[pos[m]][i]), then the norm above of that row: one launch for both (the embedding alone
 // took 4 to 5 us of every pass, nearly all of it the launch and one round trip to memory).
-// tok[m] < 0 feeds the token the previous iteration chose for its row -1 - tok[m]: the best of that row's `parts` choices.
+// The row comes from the host's pinned memory (one 16-byte read per block, in place of a copy to the device ahead of the pass: an
+// engine of its own that the stream waits for), and what later kernels read of it is written out here.
+// tok < 0 feeds the token the previous iteration chose for its row -1 - tok: the best of that row's `parts` choices.
 template <int DT, int RMS, int VW>
 __global__ __launch_bounds__(1024 / VW) void embed_norm_kernel(const void* __restrict__ wte, const void* __restrict__ wpe,
-                                                               const int* __restrict__ tok, const int* __restrict__ pos,
+                                                               const RowIn* __restrict__ rows, RowOut out,
                                                                const Choice* __restrict__ prev, int parts, float* __restrict__ x,
                                                                const void* __restrict__ g, const void* __restrict__ b,
                                                                void* __restrict__ h, int H, float eps, int mtt) {
-  const int m = blockIdx.x;
-  int tk = tok[m];
-  if (tk < 0) tk = best_choice(prev + (size_t)(-1 - tk) * parts, parts);
-  const size_t t = (size_t)tk * H, p = wpe ? (size_t)pos[m] * H : 0;
+  __shared__ RowIn row;
+  const int m = blockIdx.x, tid = threadIdx.x;
+  if (tid == 0) {
+    RowIn r = rows[m];
+    out.pos[m] = r.pos;
+    out.slot[m] = r.slot;
+    out.len[m] = r.pos + 1;
+    if (r.tok < 0) r.tok = best_choice(prev + (size_t)(-1 - r.tok) * parts, parts);
+    row = r;
+  }
+  __syncthreads();
+  const int tk = row.tok, pos = row.pos, first = row.first;
+  if (first >= 0) {
+    const int nr = out.block_rows > 0 ? min(out.block_rows, (int)gridDim.x - m) : 1, len = pos + nr;
+    const int chunks = (len + kAttnChunk - 1) / kAttnChunk;
+    for (int c = tid; c < chunks; c += 1024 / VW)
+      out.list[first + c] = out.block_rows > 0 ? make_int4(m, nr, c, 0) : make_int4(m, c, row.slot, len);
+  }
+  const size_t t = (size_t)tk * H, p = wpe ? (size_t)pos * H : 0;
   norm_row<DT, RMS, VW>([&](int i) {
     f32x4_t v = ldv4<DT>(wte, t + i);
     if (wpe) v += ldv4<DT>(wpe, p + i);
@@ -273,7 +290,8 @@ __global__ __launch_bounds__(256) void act_kernel(const float* __restrict__ part
 // VEC: rows of logits are 16-byte aligned; otherwise lanes take single columns side by side.
 template <bool VEC>
 __global__ __launch_bounds__(512) void argmax_kernel(const float* __restrict__ part, int S, size_t stride, int ldp,
-                                                     float* __restrict__ logits, Choice* __restrict__ choice, int V, int per) {
+                                                     float* __restrict__ logits, Choice* __restrict__ choice, Choice* __restrict__ choice_host,
+                                                     int V, int per) {
   __shared__ float bv[8];
   __shared__ int bi[8];
   const int m = blockIdx.x, first = blockIdx.y * per, last = min(V, first + per);
@@ -325,7 +343,9 @@ __global__ __launch_bounds__(512) void argmax_kernel(const float* __restrict__ p
   if (threadIdx.x == 0) {
     for (int w = 1; w < 8; ++w)
       if (bv[w] > best || (bv[w] == best && bi[w] < arg)) { best = bv[w]; arg = bi[w]; }
-    choice[(size_t)m * gridDim.y + blockIdx.y] = Choice{best, arg};
+    const size_t at = (size_t)m * gridDim.y + blockIdx.y;
+    choice[at] = Choice{best, arg};
+    choice_host[at] = Choice{best, arg};         // 8 bytes over the bus per part instead of a copy behind the iteration
   }
 }
 
@@ -338,11 +358,11 @@ __global__ __launch_bounds__(512) void argmax_kernel(const float* __restrict__ p
     default: { constexpr int DT = DT_BF16; CALL; } break;     \
   }
 
-hipError_t embed_norm(int dtype, bool rms, const void* wte, const void* wpe, const int* tok, const int* pos, const Choice* prev, int parts,
-                      float* x, const void* g, const void* b, void* h, int M, int H, float eps, int mtt, hipStream_t st) {
+hipError_t embed_norm(int dtype, bool rms, const void* wte, const void* wpe, const RowIn* rows, const RowOut& out, const Choice* prev,
+                      int parts, float* x, const void* g, const void* b, void* h, int M, int H, float eps, int mtt, hipStream_t st) {
   if (M <= 0) return hipSuccess;
 #define FLK_EMBED(RMS, VW) \
-  FLK_DT_SWITCH(dtype, (embed_norm_kernel<DT, RMS, VW><<<M, 1024 / VW, 0, st>>>(wte, wpe, tok, pos, prev, parts, x, g, b, h, H, eps, mtt)))
+  FLK_DT_SWITCH(dtype, (embed_norm_kernel<DT, RMS, VW><<<M, 1024 / VW, 0, st>>>(wte, wpe, rows, out, prev, parts, x, g, b, h, H, eps, mtt)))
   if (M > 512) {         // as for add_norm
     if (rms) FLK_EMBED(1, 4) else FLK_EMBED(0, 4)
   } else {
@@ -393,12 +413,13 @@ hipError_t activation(int dtype, bool swiglu, const float* part, int S, size_t s
 // as many blocks per row as 2048 columns each, at most 8
 int argmax_parts(int V) { return std::max(1, std::min(8, (V + 2047) / 2048)); }
 
-hipError_t logits_argmax(const float* part, int S, size_t stride, int ldp, float* logits, Choice* choice, int M, int V, hipStream_t st) {
+hipError_t logits_argmax(const float* part, int S, size_t stride, int ldp, float* logits, Choice* choice, Choice* choice_host, int M, int V,
+                         hipStream_t st) {
   if (M <= 0) return hipSuccess;
   const int parts = argmax_parts(V), per = ((V + parts - 1) / parts + 3) / 4 * 4;
   const dim3 grid(M, parts);
-  if (V % 4 == 0 && ((uintptr_t)logits & 15) == 0) argmax_kernel<true><<<grid, 512, 0, st>>>(part, S, stride, ldp, logits, choice, V, per);
-  else argmax_kernel<false><<<grid, 512, 0, st>>>(part, S, stride, ldp, logits, choice, V, per);
+  if (V % 4 == 0 && ((uintptr_t)logits & 15) == 0) argmax_kernel<true><<<grid, 512, 0, st>>>(part, S, stride, ldp, logits, choice, choice_host, V, per);
+  else argmax_kernel<false><<<grid, 512, 0, st>>>(part, S, stride, ldp, logits, choice, choice_host, V, per);
   return hipGetLastError();
 }
 

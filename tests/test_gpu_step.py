@@ -536,6 +536,12 @@ def test_long_prompts_through_the_context_pass(make):
     ls.close()
 
 
+def test_long_fp32_prompts_enter_their_attention_blocks():
+    """The first kernel of a pass enters the attention's work list: an fp32 prompt of two passes, the second behind 1024 cached
+    rows (five chunks per block of eight rows, ragged last block), and iterations whose rows have one to six chunks each."""
+    test_long_prompts_through_the_context_pass(lambda: synth.tiny_gpt(C=4, S=1300))
+
+
 @pytest.mark.parametrize("make", [lambda: synth.tiny_llama(synth.DT_BF16, C=11, S=320), lambda: synth.small_llama16(synth.DT_BF16, C=11, S=320),
                                   lambda: synth.small_gpt16(synth.DT_F16, C=11, S=320)])
 def test_context_passes_at_the_edges_of_their_blocks(make):
