@@ -1512,22 +1512,24 @@ extern "C" int32_t flover_k_gemm(int32_t dtype, const void* x, const void* w_til
     return fail(nullptr, FLOVER_E_INVAL, "bad argument");
   if (M == 0) return FLOVER_OK;
   if (!x || !w_tiled || !workspace) return fail(nullptr, FLOVER_E_INVAL, "null argument");
-  const flk::GemmPlan p = flk::gemm_plan(dtype, N, K);
+  const flk::GemmPlan p = flk::gemm_plan_summed(dtype, N, K);
   const size_t stride = (size_t)M * p.ldc;
   if ((size_t)p.S * stride * 4 > workspace_bytes) return fail(nullptr, FLOVER_E_NOMEM, "gemm workspace too small");
   hipStream_t st = (hipStream_t)stream;
-  // one slice and 16-byte aligned rows: the contraction's own stores are the result, unless they would fall on what its other
-  // blocks still read (y may share memory with x)
-  const size_t y_bytes = (size_t)M * N * 4;
-  const bool aligned = N % 4 == 0 && ((uintptr_t)y & 15) == 0;
-  const bool direct = y && p.S == 1 && aligned && !overlap(y, y_bytes, x, (size_t)M * K * esize(dtype)) &&
-                      !overlap(y, y_bytes, w_tiled, flk::gemm_tiled_bytes(dtype, N, K));
-  HIPCHK(nullptr, flk::gemm(dtype, x, w_tiled, M, p, direct ? y : (float*)workspace, stride, 0, st));
-  if (y && !direct) {
+  // one launch, whose own stores are the result, unless they would fall on what its other blocks still read (y may share memory
+  // with x)
+  const bool direct = y && flk::gemm_adds_up(dtype, p, M) && !overlap(y, (size_t)M * N * 4, x, (size_t)M * K * esize(dtype)) &&
+                      !overlap(y, (size_t)M * N * 4, w_tiled, flk::gemm_tiled_bytes(dtype, N, K));
+  if (direct) {
+    HIPCHK(nullptr, flk::gemm_sum(dtype, x, w_tiled, M, p, y, N, st));
+    return FLOVER_OK;
+  }
+  HIPCHK(nullptr, flk::gemm(dtype, x, w_tiled, M, p, (float*)workspace, stride, 0, st));
+  if (y) {
+    const auto kernel = N % 4 == 0 && ((uintptr_t)y & 15) == 0 ? flk::slice_sum_kernel<true> : flk::slice_sum_kernel<false>;
     // grid.y is the row: at most 65535 of them per launch
     for (int m = 0; m < M; m += 65535) {
       const dim3 grid((unsigned)((N + 1023) / 1024), (unsigned)std::min(M - m, 65535));
-      const auto kernel = aligned ? flk::slice_sum_kernel<true> : flk::slice_sum_kernel<false>;
       kernel<<<grid, 256, 0, st>>>((const float*)workspace + (size_t)m * p.ldc, p.S, stride, p.ldc, y + (size_t)m * N, N);
     }
     HIPCHK(nullptr, hipGetLastError());

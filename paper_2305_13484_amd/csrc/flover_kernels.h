@@ -28,6 +28,7 @@ GemmPlan gemm_plan(int dtype, int N, int K);
 // The same for a matrix whose result a row-wise kernel would only finish (q|k|v, the input of an ungated MLP), which the GEMM does
 // itself up to kWholeRows rows where the shape makes that the shorter way.
 GemmPlan gemm_plan_finished(int dtype, int N, int K);
+GemmPlan gemm_plan_summed(int dtype, int N, int K);    // gemm_plan for a caller who wants the sum (gemm_sum)
 // Where a GEMM that finishes the job leaves its result (the members its kind of epilogue uses).
 struct TileOut {
   float* part = nullptr;          // partial sums; or the residual stream [M][ldc] the result is added to
@@ -77,6 +78,10 @@ hipError_t zero_fill(void* p, size_t bytes, hipStream_t st);
 // ev0 / ev1 (optional, here and below): take the start / end time stamps of the call's first / last dispatch.
 hipError_t gemm(int dtype, const void* x, const void* w_tiled, int M, const GemmPlan& p, float* part,
                 size_t slice_stride, int xmtt, hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+// y[M][ldy] = x . W^T, rows row-major and y at any float, where one launch leaves the whole sum (gemm_adds_up): one slice, or a
+// gemm_plan_summed that says so; the bits of gemm()'s slices added in order.
+bool gemm_adds_up(int dtype, const GemmPlan& p, int M);
+hipError_t gemm_sum(int dtype, const void* x, const void* w_tiled, int M, const GemmPlan& p, float* y, int ldy, hipStream_t st);
 // act[M][F] = silu(x . Wgate^T) * (x . Wup^T) rounded to the model dtype, for a paired plan (16-bit dtypes); x and act
 // are both row-major (xmtt == 0) or both in fragment order with xmtt row tiles per k-block; reads the rows gemm() reads.
 // part / slice_stride as for gemm(): used above gated_fused_rows(p) rows, where the contraction and the activation are

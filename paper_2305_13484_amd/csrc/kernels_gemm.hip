@@ -58,6 +58,17 @@ __global__ void retile16_kernel(const uint16_t* __restrict__ W, u32x4_t* __restr
 
 // ---------------------------------------------------------------- 16-bit MFMA kernel
 
+// Columns n .. n+3 of a row of ldc fp32 results: partial sums (rows padded to whole fours), or a caller's rows, which may have any
+// length and start at any element.
+__device__ __forceinline__ void store_sums(float* row, int n, int ldc, const f32x4_t& v) {
+  if (n + 4 <= ldc) *(f32x4_any*)(row + n) = v;
+  else {
+#pragma unroll
+    for (int e = 0; e < 3; ++e)
+      if (n + e < ldc) row[n + e] = v[e];
+  }
+}
+
 // ---- direct variant: 4 independent waves per block, no LDS, no barriers; the rows' operand comes straight from L2/L1.
 // grid = (ceil(ngroups/4), S, row blocks), block = 256; a wave owns NT n-tiles (16*NT columns) x one K slice x 16*MT rows.
 // W is prefetched PFW k-blocks ahead, x PFA k-blocks ahead (PFW % PFA == 0).
@@ -132,7 +143,7 @@ __global__ __launch_bounds__(256) void gemm16_direct_kernel(const uint16_t* __re
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
       const int n = (g * NT + t) * 16 + (lane >> 4) * 4, m = m0 + i * 16 + (lane & 15);
-      if (m < M && n < ldc) *(f32x4_t*)(out + (size_t)m * ldc + n) = acc[i][t];
+      if (m < M) store_sums(out + (size_t)m * ldc, n, ldc, acc[i][t]);
     }
 }
 
@@ -263,7 +274,7 @@ __global__ __launch_bounds__(64 * GPB * (NT / NTW)) void gemm16_lds_kernel(const
 #pragma unroll
     for (int t = 0; t < NTW; ++t) {
       const int n = (g * NT + sub * NTW + t) * 16 + (lane >> 4) * 4, m = m0 + i * 16 + (lane & 15);
-      if (m < M && n < ldc) *(f32x4_t*)(out + (size_t)m * ldc + n) = acc[i][t];
+      if (m < M) store_sums(out + (size_t)m * ldc, n, ldc, acc[i][t]);
     }
 }
 
@@ -427,7 +438,7 @@ __device__ __forceinline__ void tile_epilogue(f32x4_t (&acc)[A][B], const TileOu
       float* out = o.part + (size_t)s * o.slice_stride + (size_t)m * o.ldc;
 #pragma unroll
       for (int u = 0; u < B; ++u)
-        if (column(u) < o.ldc) *(f32x4_t*)(out + column(u)) = acc[i][u];
+        store_sums(out, column(u), o.ldc, acc[i][u]);
     }
   } else if constexpr (EPI == EPI_GATED) {      // n-tiles alternate gate and up of the same 16 MLP columns
 #pragma unroll
@@ -577,7 +588,7 @@ __global__ __launch_bounds__(64 * S) void gemm16_whole_kernel(const uint16_t* __
   constexpr int OWN = (MT + S - 1) / S;          // row tiles a wave finishes: s, s + S, ...
   const int n0 = t0 * 16 + c4, n1 = t1 * 16 + c4, half = o.d >> 1;
   f32x4_t b0 = {0.f, 0.f, 0.f, 0.f}, b1 = b0;
-  if (EPI != EPI_GATED && o.bias) {
+  if ((EPI == EPI_QKV || EPI == EPI_GELU) && o.bias) {
     b0 = ldv4<DT>(o.bias, n0);
     b1 = ldv4<DT>(o.bias, n1);
   }
@@ -621,12 +632,15 @@ __global__ __launch_bounds__(64 * S) void gemm16_whole_kernel(const uint16_t* __
       a0 += v[p][0];
       a1 += v[p][1];
     }
-    if (EPI != EPI_GATED && o.bias) {
+    if ((EPI == EPI_QKV || EPI == EPI_GELU) && o.bias) {
       a0 += b0;
       a1 += b1;
     }
     if (m >= M) continue;
-    if constexpr (EPI == EPI_GATED) {
+    if constexpr (EPI == EPI_PART) {
+      store_sums(o.part + (size_t)m * o.ldc, n0, o.ldc, a0);
+      store_sums(o.part + (size_t)m * o.ldc, n1, o.ldc, a1);
+    } else if constexpr (EPI == EPI_GATED) {
       stv4<DT>(o.act, xrow_index(m, blockIdx.x * 16 + c4, o.F, o.mtt), act_swiglu(a0, a1));
     } else if constexpr (EPI == EPI_GELU) {
       stv4<DT>(o.act, xrow_index(m, n0, o.F, o.mtt), act_gelu<DT>(a0));
@@ -1047,7 +1061,7 @@ GemmPlan gemm_plan(int dtype, int N, int K) {
 // 3072 (288) 14.1 / 15.2 / 18.6 / 23.3 -> 16.0 / 18.6 / 23.8 / 32.6; 8192 x 2048 with GELU (256) 10.7 / 12.1 / 15.3 / 19.4 -> 8.5 / 9.6 /
 // 11.0 / 15.1, 10240 x 2560 (320) 13.0 / 14.9 / 19.1 / 23.6 -> 14.4 / 17.0 / 20.9 / 28.7, 4096 x 4096 (128 blocks, long K) 10.2 / 12.2 /
 // 15.2 / 19.5 -> 10.9 / 12.9 / 16.5 / 22.6.  Four slices: with two, 48 rows and more are 10 to 40 % slower.
-static bool whole_shape(int dtype, int N, int K) { return dtype != DT_F32 && N % 32 == 0 && N / 32 <= 256 && K >= 512; }
+static bool whole_shape(int dtype, int N, int K) { return dtype != DT_F32 && (N + 31) / 32 <= 256 && K >= 512; }
 static constexpr int kWholeSlices = 4;
 static void take_whole(GemmPlan& p) {
   p.NT = 2;
@@ -1057,7 +1071,13 @@ static void take_whole(GemmPlan& p) {
 }
 GemmPlan gemm_plan_finished(int dtype, int N, int K) {
   GemmPlan p = gemm_plan(dtype, N, K);
-  if (whole_shape(dtype, N, K) && K <= 2560) take_whole(p);
+  if (whole_shape(dtype, N, K) && N % 32 == 0 && K <= 2560) take_whole(p);
+  return p;
+}
+// Only where the plan has these very slices, so that nothing changes above kWholeRows rows.
+GemmPlan gemm_plan_summed(int dtype, int N, int K) {
+  GemmPlan p = gemm_plan(dtype, N, K);
+  p.whole = whole_shape(dtype, N, K) && K <= 2560 && p.S == kWholeSlices && p.NT == 2;
   return p;
 }
 
@@ -1239,7 +1259,7 @@ static void dispatch_tile(int tile, const void* x, const void* wt, const TileOut
 template <int DT, int EPI, int MT>
 static void launch_whole(const void* x, const void* wt, const TileOut& o, int M, const GemmPlan& p, int xmtt, hipStream_t st,
                          hipEvent_t ev0, hipEvent_t ev1) {
-  launch_timed(gemm16_whole_kernel<DT, MT, kWholeSlices, MT <= 3 ? 4 : 2, EPI>, dim3(p.N / 32), dim3(64 * kWholeSlices), st, ev0, ev1,
+  launch_timed(gemm16_whole_kernel<DT, MT, kWholeSlices, MT <= 3 ? 4 : 2, EPI>, dim3((p.N + 31) / 32), dim3(64 * kWholeSlices), st, ev0, ev1,
                (const uint16_t*)x, (const u32x4_t*)wt, o, M, p.N, p.KB, p.kbs, xmtt);
 }
 template <int DT, int EPI>
@@ -1267,7 +1287,7 @@ static hipError_t finish(int dtype, const void* x, const void* wt, const TileOut
     else launch_timed(gemm32_kernel<EPI, 4>, grid, dim3(256), st, ev0, ev1, (const float*)x, (const float*)wt, o, M, p.N, p.K);
     return hipGetLastError();
   }
-  if constexpr (EPI == EPI_QKV || EPI == EPI_GATED || EPI == EPI_GELU) {
+  if constexpr (EPI != EPI_ADD) {
     if (takes_whole(p, M)) {
       if (dtype == DT_BF16) dispatch_whole<DT_BF16, EPI>(x, wt, o, M, p, xmtt, st, ev0, ev1);
       else dispatch_whole<DT_F16, EPI>(x, wt, o, M, p, xmtt, st, ev0, ev1);
@@ -1406,6 +1426,22 @@ hipError_t gemm_gated(int dtype, const void* x, const void* wt, int M, const Gem
   if (dtype == DT_BF16) dispatch_gated<DT_BF16>(x, wt, act, M, p, xmtt, st, ev0, ev1);
   else dispatch_gated<DT_F16>(x, wt, act, M, p, xmtt, st, ev0, ev1);
   return hipGetLastError();
+}
+
+// Row-major rows are read 64 bytes at a time: above 64 rows, where every block of 32 columns reads them all, two launches are shorter
+// (us per call, two launches -> one: 1536 x 512 at 23 rows 24.1 -> 21.8, 3071 x 1024 at 60 rows 26.4 -> 26.0, 4607 x 1536 at 101 rows
+// 32.3 -> 33.8).
+bool gemm_adds_up(int dtype, const GemmPlan& p, int M) { return p.S == 1 || (dtype != DT_F32 && p.whole && M <= 64); }
+hipError_t gemm_sum(int dtype, const void* x, const void* wt, int M, const GemmPlan& p, float* y, int ldy, hipStream_t st) {
+  if (M <= 0) return hipSuccess;
+  if (!gemm_adds_up(dtype, p, M)) return hipErrorInvalidValue;
+  TileOut o;
+  o.part = y;
+  o.ldc = ldy;
+  if (p.S > 1) return finish<EPI_PART>(dtype, x, wt, o, M, p, 0, st, nullptr, nullptr);
+  GemmPlan q = p;
+  q.ldc = ldy;
+  return gemm(dtype, x, wt, M, q, y, 0, 0, st);
 }
 
 hipError_t gemm(int dtype, const void* x, const void* wt, int M, const GemmPlan& p, float* part, size_t slice_stride,
