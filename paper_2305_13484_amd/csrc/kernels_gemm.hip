@@ -147,6 +147,50 @@ __global__ __launch_bounds__(256) void gemm16_direct_kernel(const uint16_t* __re
     }
 }
 
+// The rows' operand of a chunk (KC k-blocks x MT row tiles) on its way to LDS: KC * MT pieces of 1 KiB, one wave load each, shared
+// out to NW waves, up to FPW of them per wave (surplus ones repeat the last: same data, no branch).  Fragment order: a piece is a
+// fragment.  Row-major: a piece is the chunk's 64 * KC bytes of 16 / KC rows, whole cache lines, which the store spreads over KC
+// fragments -- sixteen rows' 64 bytes at a time, as the MFMA wants them, meet in the same cache channel where the row length is
+// a power of two (call with SwiGLU, 11008 x 4096 at 40 / 70 / 101 / 128 rows: 54.9 / 60.7 / 67.6 / 75.5 -> 51.2 / 54.2 / 58.7 / 61.3 us;
+// 50257 x 2048 at 100 rows 74.7 -> 57.8, the second launch counted).  In LDS a fragment's rows are permuted by an exclusive or (place()), so that neither the spread
+// stores nor the reads collide.
+template <int KC, int MT, int NW>
+struct ChunkRows {
+  static constexpr int FPW = (KC * MT + NW - 1) / NW, PIECES = 4 * KC;    // PIECES: 16-byte pieces of a row in a chunk
+  const uint16_t* x;
+  uint32_t step, limit;                          // elements per k-block, and the last offset a load may take
+  uint32_t from[FPW], ahead[FPW], to[FPW];       // row (tile) in x, element within the chunk, place in the LDS buffer
+  static __device__ int place(int kc, int quad, int row) { return quad * 16 + (row ^ ((kc & 1) * 4 + quad)); }   // row < 16
+  // rows: how many there are (those past the last repeat it); K: their length; kend: end of the slice in k-blocks, past which its
+  // last block is loaded again
+  __device__ ChunkRows(const uint16_t* x_, int rows, int K, int kend, int xmtt, int w, int lane) : x(x_) {
+    step = xmtt ? (uint32_t)xmtt * 512 : 32;
+    limit = xmtt ? (uint32_t)(kend - 1) * step : (uint32_t)kend * 32 - 8;
+#pragma unroll
+    for (int j = 0; j < FPW; ++j) {
+      const int f = min(w + NW * j, KC * MT - 1);
+      if (xmtt) {
+        from[j] = (f % MT) * 512 + lane * 8;
+        ahead[j] = (f / MT) * step;
+        to[j] = f * 64 + place(f / MT, lane >> 4, lane & 15);
+      } else {
+        const int row = f * (16 / KC) + lane / PIECES, p = lane % PIECES;
+        from[j] = (uint32_t)min(row, rows - 1) * K;
+        ahead[j] = p * 8;
+        to[j] = ((p >> 2) * MT + (row >> 4)) * 64 + place(p >> 2, p & 3, row & 15);
+      }
+    }
+  }
+  __device__ void load(u32x4_t (&r)[FPW], int kb) const {      // the chunk that starts at k-block kb
+#pragma unroll
+    for (int j = 0; j < FPW; ++j) r[j] = *(const u32x4_any*)(x + (from[j] + min(kb * step + ahead[j], limit)));
+  }
+  __device__ void store(u32x4_t* buf, const u32x4_t (&r)[FPW]) const {
+#pragma unroll
+    for (int j = 0; j < FPW; ++j) buf[to[j]] = r[j];
+  }
+};
+
 // ---- larger M (17..128 rows per block): the rows' operand is staged through LDS once per block and shared by its
 // waves; a block covers GPB = 4 column groups (256 columns; 128 for matrices laid out in 32-column groups), each group
 // by NT/NTW waves that own NTW of its n-tiles and stream their W tiles from HBM into registers, PF k-blocks ahead.
@@ -166,7 +210,7 @@ __global__ __launch_bounds__(64 * GPB * (NT / NTW)) void gemm16_lds_kernel(const
   constexpr int WPG = NT / NTW;                  // waves that share one column group, each taking NTW of its n-tiles
   constexpr int NW = GPB * WPG;                  // waves per block: GPB column groups (256 columns)
   __shared__ u32x4_t lds[2][KC * MT * 64];
-  constexpr int FPW = (KC * MT + NW - 1) / NW;   // fragments each wave stages per chunk (surplus ones are skipped)
+  typedef ChunkRows<KC, MT, NW> Rows;
   constexpr int CPR = PF / KC;                   // chunks per turn of the W ring
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   // 1-D grid, XCD-aware: workgroup ids go round-robin over the 8 XCDs (each with its own L2), so the row blocks of one
@@ -190,36 +234,19 @@ __global__ __launch_bounds__(64 * GPB * (NT / NTW)) void gemm16_lds_kernel(const
     for (int t = 0; t < NTW; ++t) acc[i][t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
   const u32x4_t* wp = wt + (((size_t)gl * KB) * NT + sub * NTW) * 64 + lane;     // + (kb*NT + t)*64
-  // rows' operand: row-major [M][K] (xmtt == 0; rows past M repeat the last one) or fragment order with xmtt row tiles per
-  // k-block; xo: where the wave's j-th fragment of a chunk is, relative to the block's rows
-  const size_t kstride = xmtt ? (size_t)xmtt * 512 : 32;
-  const uint16_t* xp = x + (xmtt ? (size_t)(m0 >> 4) * 512 : (size_t)m0 * K);
-  uint32_t xo[FPW];
+  const Rows rows(x + (xmtt ? (size_t)(m0 >> 4) * 512 : (size_t)m0 * K), M - m0, K, kb1, xmtt, wave, lane);
+  int at[2];                                     // where a lane finds its part of a fragment, even and odd k-blocks of a chunk
 #pragma unroll
-  for (int j = 0; j < FPW; ++j) {
-    const int i = min(wave + NW * j, KC * MT - 1) % MT;
-    xo[j] = xmtt ? (uint32_t)(i * 512 + lane * 8) : (uint32_t)min(i * 16 + (lane & 15), M - 1 - m0) * K + (lane >> 4) * 8;
-  }
-
-  u32x4_t bq[PF][NTW], areg[FPW];
+  for (int kc = 0; kc < 2; ++kc) at[kc] = Rows::place(kc, lane >> 4, lane & 15);
+  u32x4_t bq[PF][NTW], areg[Rows::FPW];
 #pragma unroll
   for (int j = 0; j < PF; ++j) {
     const int kk = min(kb0 + j, kb1 - 1);
 #pragma unroll
     for (int t = 0; t < NTW; ++t) bq[j][t] = __builtin_nontemporal_load(wp + ((size_t)kk * NT + t) * 64);
   }
-  auto load_a = [&](int chunk) {      // one fragment = 16 rows x 64 B per wave load
-#pragma unroll
-    for (int j = 0; j < FPW; ++j) {
-      const int kc = min(wave + NW * j, KC * MT - 1) / MT;
-      const int kk = min(kb0 + chunk * KC + kc, kb1 - 1);
-      areg[j] = *(const u32x4_any*)(xp + xo[j] + kk * kstride);
-    }
-  };
-  auto store_a = [&](int buf) {      // surplus waves store the last fragment once more (same data, no branch)
-#pragma unroll
-    for (int j = 0; j < FPW; ++j) lds[buf][min(wave + NW * j, KC * MT - 1) * 64 + lane] = areg[j];
-  };
+  auto load_a = [&](int chunk) { rows.load(areg, kb0 + chunk * KC); };
+  auto store_a = [&](int buf) { rows.store(lds[buf], areg); };
   load_a(0);
   store_a(0);
   __syncthreads();
@@ -240,7 +267,7 @@ __global__ __launch_bounds__(64 * GPB * (NT / NTW)) void gemm16_lds_kernel(const
       if (!tail || kb < kb1) {
         u32x4_t af[MT];
 #pragma unroll
-        for (int i = 0; i < MT; ++i) af[i] = la[(kc * MT + i) * 64 + lane];
+        for (int i = 0; i < MT; ++i) af[i] = la[(kc * MT + i) * 64 + at[kc & 1]];
 #pragma unroll
         for (int i = 0; i < MT; ++i)
 #pragma unroll
@@ -297,7 +324,7 @@ __global__ __launch_bounds__(128 * GPB) void gated_lds_kernel(const uint16_t* __
   static_assert(PF % KC == 0 && KC >= 2, "ring shape; the hand-over below reuses the x tiles' LDS");
   // GPB column groups per block (32 columns each) = waves that stage one half's x tile
   __shared__ u32x4_t lds[2][2][KC * MT * 64];    // [half][buffer]
-  constexpr int FPW = (KC * MT + GPB - 1) / GPB;
+  typedef ChunkRows<KC, MT, GPB> Rows;
   constexpr int CPR = PF / KC;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int half = wave / GPB, gw = wave % GPB;
@@ -314,30 +341,17 @@ __global__ __launch_bounds__(128 * GPB) void gated_lds_kernel(const uint16_t* __
     for (int t = 0; t < 2; ++t) acc[i][t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
   const u32x4_t* wp = wt + ((size_t)gl * KB) * 2 * 64 + lane;                    // + (kb*2 + t)*64
-  const size_t kstride = xmtt ? (size_t)xmtt * 512 : 32;
-  uint32_t xo[FPW];                              // where the wave's j-th fragment of a chunk is; row-major rows past M repeat the last one
+  const Rows rows(x, M, K, kb1, xmtt, gw, lane);
+  int at[2];                                     // see gemm16_lds_kernel
 #pragma unroll
-  for (int j = 0; j < FPW; ++j) {
-    const int i = min(gw + GPB * j, KC * MT - 1) % MT;
-    xo[j] = xmtt ? (uint32_t)(i * 512 + lane * 8) : (uint32_t)min(i * 16 + (lane & 15), M - 1) * K + (lane >> 4) * 8;
-  }
-
-  u32x4_t bq[PF][2], areg[FPW];
+  for (int kc = 0; kc < 2; ++kc) at[kc] = Rows::place(kc, lane >> 4, lane & 15);
+  u32x4_t bq[PF][2], areg[Rows::FPW];
 #pragma unroll
   for (int j = 0; j < PF; ++j)
 #pragma unroll
     for (int t = 0; t < 2; ++t) bq[j][t] = __builtin_nontemporal_load(wp + ((size_t)(kb0 + j) * 2 + t) * 64);
-  auto load_a = [&](int chunk) {
-#pragma unroll
-    for (int j = 0; j < FPW; ++j) {
-      const int kc = min(gw + GPB * j, KC * MT - 1) / MT;
-      areg[j] = *(const u32x4_any*)(x + xo[j] + (kb0 + chunk * KC + kc) * kstride);
-    }
-  };
-  auto store_a = [&](int buf) {      // surplus fragments store the last one once more (same data, no branch)
-#pragma unroll
-    for (int j = 0; j < FPW; ++j) lds[half][buf][min(gw + GPB * j, KC * MT - 1) * 64 + lane] = areg[j];
-  };
+  auto load_a = [&](int chunk) { rows.load(areg, kb0 + chunk * KC); };
+  auto store_a = [&](int buf) { rows.store(lds[half][buf], areg); };
   load_a(0);
   store_a(0);
   __syncthreads();
@@ -354,7 +368,7 @@ __global__ __launch_bounds__(128 * GPB) void gated_lds_kernel(const uint16_t* __
       const int kb = kb0 + c * KC + kc;
       u32x4_t af[MT];
 #pragma unroll
-      for (int i = 0; i < MT; ++i) af[i] = la[(kc * MT + i) * 64 + lane];
+      for (int i = 0; i < MT; ++i) af[i] = la[(kc * MT + i) * 64 + at[kc & 1]];
 #pragma unroll
       for (int i = 0; i < MT; ++i)
 #pragma unroll
