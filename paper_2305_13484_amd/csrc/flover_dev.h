@@ -120,6 +120,19 @@ template <int DT> __device__ __forceinline__ void stv4(void* p, size_t i, f32x4_
 // ---- row-wise epilogue arithmetic shared by the stand-alone kernels and the GEMM kernels that fuse them
 // Floating-point contraction is switched off inside, so that the same inputs give the same bits wherever the function
 // is inlined (a request's result must not depend on which variant served it).
+// Norm of a row: sums of four consecutive elements, and the normalised elements (layer norm, or RMS where mean and b are not used).
+__device__ __forceinline__ float sum4(const f32x4_t& t) { return (t[0] + t[1]) + (t[2] + t[3]); }
+__device__ __forceinline__ float square_sum4(const f32x4_t& t) {
+#pragma clang fp contract(off)
+  return fmaf(t[0], t[0], t[1] * t[1]) + fmaf(t[2], t[2], t[3] * t[3]);
+}
+template <bool RMS> __device__ __forceinline__ f32x4_t norm_value(const f32x4_t& v, float mean, float inv, const f32x4_t& g, const f32x4_t& b) {
+#pragma clang fp contract(off)
+  f32x4_t o;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) o[e] = RMS ? v[e] * inv * g[e] : fmaf((v[e] - mean) * inv, g[e], b[e]);
+  return o;
+}
 // Rotary pair (a0, a1) = elements (i, i + d/2) of a head, (cs, sn) = cos/sin of pos * theta^(-2i/d).
 __device__ __forceinline__ void rope_rotate(f32x4_t& a0, f32x4_t& a1, const f32x4_t& cs, const f32x4_t& sn) {
 #pragma clang fp contract(off)

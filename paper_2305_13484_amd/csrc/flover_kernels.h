@@ -29,6 +29,13 @@ GemmPlan gemm_plan(int dtype, int N, int K);
 // itself up to kWholeRows rows where the shape makes that the shorter way.
 GemmPlan gemm_plan_finished(int dtype, int N, int K);
 GemmPlan gemm_plan_summed(int dtype, int N, int K);    // gemm_plan for a caller who wants the sum (gemm_sum)
+// The norm of the rows ahead of an fp32 contraction, taken in the GEMM's own launch (gemm_norms): x is then the residual stream.
+struct NormIn {
+  const void *g = nullptr, *b = nullptr;   // [K]; no g: the rows as they are.  b: layer norm only
+  bool rms = false;
+  float eps = 0.f;
+};
+bool gemm_norms(int dtype, int M, int K);
 // Where a GEMM that finishes the job leaves its result (the members its kind of epilogue uses).
 struct TileOut {
   float* part = nullptr;          // partial sums; or the residual stream [M][ldc] the result is added to
@@ -41,6 +48,7 @@ struct TileOut {
   const int *pos = nullptr, *slot = nullptr;
   void *q = nullptr, *kc = nullptr, *vc = nullptr;
   int d = 0, Smax = 0;
+  NormIn norm;
 };
 // gate|up of a gated MLP with F columns each.  paired = 1: group j of the layout holds gate columns 16j..16j+15 then up
 // columns 16j..16j+15 (re-tile gate with n_off = 0 and up with n_off = 16, both with tile_step = 2), K is cut in two
@@ -64,7 +72,7 @@ hipError_t gemm_qkv(int dtype, const void* x, const void* w_tiled, int M, const 
 hipError_t gemm_add(int dtype, const void* x, const void* w_tiled, int M, const GemmPlan& p, float* res, const void* bias, int xmtt,
                     hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 hipError_t gemm_act(int dtype, bool swiglu, const void* x, const void* w_tiled, int M, const GemmPlan& p, void* act, const void* bias, int xmtt,
-                    hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+                    hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr, const NormIn& norm = NormIn());
 // Re-tile W [N][K] into `tiled` starting at output column n_off (multiple of 16) of a possibly larger matrix whose
 // plan uses NT n-tiles per column group.
 // Tile t of W lands at tile position n_off/16 + t * tile_step of the layout.
@@ -77,7 +85,8 @@ hipError_t zero_fill(void* p, size_t bytes, hipStream_t st);
 // rounded up to 16, 32, 64, 128 or a multiple of 256 rows (row tiles past the last may be read).
 // ev0 / ev1 (optional, here and below): take the start / end time stamps of the call's first / last dispatch.
 hipError_t gemm(int dtype, const void* x, const void* w_tiled, int M, const GemmPlan& p, float* part,
-                size_t slice_stride, int xmtt, hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+                size_t slice_stride, int xmtt, hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr,
+                const NormIn& norm = NormIn());
 // y[M][ldy] = x . W^T, rows row-major and y at any float, where one launch leaves the whole sum (gemm_adds_up): one slice, or a
 // gemm_plan_summed that says so; the bits of gemm()'s slices added in order.
 bool gemm_adds_up(int dtype, const GemmPlan& p, int M);

@@ -98,7 +98,7 @@ __device__ __forceinline__ void norm_row(Update update, int m, const void* __res
         if (!RMS) bv[w][c] = ldv4<DT>(b, i);
         const f32x4_t t = update(i);
         v[w][c] = t;
-        sum[w] += RMS ? (t[0] * t[0] + t[1] * t[1]) + (t[2] * t[2] + t[3] * t[3]) : (t[0] + t[1]) + (t[2] + t[3]);
+        sum[w] += RMS ? square_sum4(t) : sum4(t);
       }
     }
   }
@@ -114,10 +114,7 @@ __device__ __forceinline__ void norm_row(Update update, int m, const void* __res
       sq[w] = 0.f;
 #pragma unroll
       for (int c = 0; c < PER; ++c)
-        if (column(w, c) < H) {
-          const f32x4_t dlt = v[w][c] - mean;
-          sq[w] += (dlt[0] * dlt[0] + dlt[1] * dlt[1]) + (dlt[2] * dlt[2] + dlt[3] * dlt[3]);
-        }
+        if (column(w, c) < H) sq[w] += square_sum4(v[w][c] - mean);
     }
     inv = 1.0f / sqrtf(row_sum(sq, red[1]) / (float)H + eps);
   }
@@ -126,11 +123,7 @@ __device__ __forceinline__ void norm_row(Update update, int m, const void* __res
 #pragma unroll
     for (int c = 0; c < PER; ++c) {
       const int i = column(w, c);
-      if (i < H) {
-        f32x4_t o = (v[w][c] - mean) * inv * gv[w][c];
-        if (!RMS) o += bv[w][c];
-        stv4<DT>(h, xrow_index(m, i, H, mtt), o);
-      }
+      if (i < H) stv4<DT>(h, xrow_index(m, i, H, mtt), norm_value<RMS != 0>(v[w][c], mean, inv, gv[w][c], bv[w][c]));
     }
 }
 

@@ -950,7 +950,9 @@ __device__ __forceinline__ float wave_sums16(float (&v)[16], int lane) {
 // load: 5.2 on average, up to 10.5; the time is the launch and the round trips).  The second column is the next one, or the one that
 // the epilogue needs beside it: the rotary partner, or up beside gate.  Every model of this type finishes in the epilogue
 // (see tile_epilogue): tiny models are bound by their count of launches.
-template <int EPI, int U>
+// NORM (1: layer norm, 2: RMS; K <= 256 U): x is the residual stream and every wave takes the norm of its rows while its weights are
+// under way, in the order of norm_row, so that the bits are those of the norm in a launch of its own.
+template <int EPI, int U, int NORM>
 __global__ __launch_bounds__(256) void gemm32_kernel(const float* __restrict__ x, const float* __restrict__ W, TileOut o, int M, int N,
                                                      int K) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -973,7 +975,7 @@ __global__ __launch_bounds__(256) void gemm32_kernel(const float* __restrict__ x
 #pragma unroll
   for (int i = 0; i < 16; ++i) acc[i] = 0.f;
   const float *w0 = W + (size_t)c0 * K, *w1 = W + (size_t)min(c1, N - 1) * K;
-  for (int k0 = lane * 4; k0 < K; k0 += U * 256) {             // U rounds of loads in flight; those past K count as zero
+  for (int k0 = lane * 4; NORM || k0 < K; k0 += U * 256) {     // U rounds of loads in flight; those past K count as zero
     f32x4_t a[U], b[U], v[U][8];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -983,7 +985,40 @@ __global__ __launch_bounds__(256) void gemm32_kernel(const float* __restrict__ x
 #pragma unroll
       for (int r = 0; r < 8; ++r) v[u][r] = *(const f32x4_any*)(x + (size_t)min(m0 + r, M - 1) * K + k);
     }
+    f32x4_t g[U], bt[U];
+    if constexpr (NORM != 0) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int k = min(k0 + u * 256, K - 4);
+        g[u] = ld4((const float*)o.norm.g + k);
+        if (NORM == 1) bt[u] = ld4((const float*)o.norm.b + k);
+      }
+    }
     __builtin_amdgcn_sched_barrier(0);
+    if constexpr (NORM != 0) {
+#pragma unroll
+      for (int r = 0; r < 8; ++r) {
+        auto row_sum = [&](auto of) {
+          float t = 0.f;
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            const float w = group_sum<64>(k0 + u * 256 < K ? of(v[u][r]) : 0.f);
+            t = u == 0 ? w : t + w;
+          }
+          return t;
+        };
+        float mean = 0.f, total;
+        if constexpr (NORM == 2) {
+          total = row_sum([](const f32x4_t& t) { return square_sum4(t); });
+        } else {
+          mean = row_sum([](const f32x4_t& t) { return sum4(t); }) / (float)K;
+          total = row_sum([&](const f32x4_t& t) { return square_sum4(t - mean); });
+        }
+        const float inv = 1.0f / sqrtf(total / (float)K + o.norm.eps);
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u][r] = norm_value<NORM == 2>(v[u][r], mean, inv, g[u], NORM == 1 ? bt[u] : g[u]);
+      }
+    }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       if (k0 + u * 256 >= K) continue;
@@ -995,6 +1030,7 @@ __global__ __launch_bounds__(256) void gemm32_kernel(const float* __restrict__ x
           acc[2 * r + 1] = fmaf(v[u][r][e], b[u][e], acc[2 * r + 1]);
         }
     }
+    if (NORM) break;                             // one round holds the row
   }
   const float sum = wave_sums16(acc, lane) + (EPI == EPI_PART || EPI == EPI_GATED ? 0.f : bias), other = __shfl_xor(sum, 4, 64);
   if (m >= M || (lane & 3)) return;
@@ -1297,8 +1333,17 @@ static hipError_t finish(int dtype, const void* x, const void* wt, const TileOut
   if (dtype == DT_F32) {
     const int pairs = EPI == EPI_GATED ? o.F : (p.N + 1) / 2;
     const dim3 grid((pairs + 3) / 4, (M + 7) / 8);
-    if (p.K <= 256) launch_timed(gemm32_kernel<EPI, 1>, grid, dim3(256), st, ev0, ev1, (const float*)x, (const float*)wt, o, M, p.N, p.K);
-    else launch_timed(gemm32_kernel<EPI, 4>, grid, dim3(256), st, ev0, ev1, (const float*)x, (const float*)wt, o, M, p.N, p.K);
+    auto launch = [&](void (*kernel)(const float*, const float*, TileOut, int, int, int)) {
+      launch_timed(kernel, grid, dim3(256), st, ev0, ev1, (const float*)x, (const float*)wt, o, M, p.N, p.K);
+    };
+    const bool one = p.K <= 256;
+    if (!o.norm.g) {
+      launch(one ? gemm32_kernel<EPI, 1, 0> : gemm32_kernel<EPI, 4, 0>);
+    } else if constexpr (EPI != EPI_ADD) {
+      if (!gemm_norms(dtype, M, p.K)) return hipErrorInvalidValue;
+      if (o.norm.rms) launch(one ? gemm32_kernel<EPI, 1, 2> : gemm32_kernel<EPI, 4, 2>);
+      else launch(one ? gemm32_kernel<EPI, 1, 1> : gemm32_kernel<EPI, 4, 1>);
+    }
     return hipGetLastError();
   }
   if constexpr (EPI != EPI_ADD) {
@@ -1312,6 +1357,10 @@ static hipError_t finish(int dtype, const void* x, const void* wt, const TileOut
   else dispatch_tile<DT_F16, EPI>(p.tile, x, wt, o, M, p, xmtt, st, ev0, ev1);
   return hipGetLastError();
 }
+// Every wave repeats the norm of its eight rows, so few rows gain (a launch of the small chain, 4 to 5 us) and many lose: two layers of
+// 256 columns, us per pass, norm apart -> inside: 16 rows 86 -> 73, 20 rows 126 -> 105, 70 rows 131 -> 146,
+// 155 rows 173 -> 202.
+bool gemm_norms(int dtype, int M, int K) { return dtype == DT_F32 && K <= 1024 && M <= 32; }
 bool gemm_finishes(int dtype, const GemmPlan& p, int M) {
   return dtype == DT_F32 || takes_whole(p, M) || (M > 128 && p.S == 1 && p.tile >= 0);
 }
@@ -1329,8 +1378,9 @@ hipError_t gemm_add(int dtype, const void* x, const void* wt, int M, const GemmP
   return finish<EPI_ADD>(dtype, x, wt, o, M, p, xmtt, st, ev0, ev1);
 }
 hipError_t gemm_act(int dtype, bool swiglu, const void* x, const void* wt, int M, const GemmPlan& p, void* act, const void* bias, int xmtt,
-                    hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
+                    hipStream_t st, hipEvent_t ev0, hipEvent_t ev1, const NormIn& norm) {
   TileOut o;
+  o.norm = norm;
   o.act = act;
   o.bias = bias;
   o.F = swiglu ? p.N / 2 : p.N;
@@ -1459,11 +1509,12 @@ hipError_t gemm_sum(int dtype, const void* x, const void* wt, int M, const GemmP
 }
 
 hipError_t gemm(int dtype, const void* x, const void* wt, int M, const GemmPlan& p, float* part, size_t slice_stride,
-                int xmtt, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
+                int xmtt, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1, const NormIn& norm) {
   if (M <= 0) return hipSuccess;
   if (dtype == DT_F32) {
     if (xmtt) return hipErrorInvalidValue;   // fp32 rows are always row-major
     TileOut o;
+    o.norm = norm;
     o.part = part;
     o.ldc = p.ldc;
     return finish<EPI_PART>(dtype, x, wt, o, M, p, 0, st, ev0, ev1);

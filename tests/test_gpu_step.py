@@ -667,6 +667,31 @@ def test_a_row_is_the_same_at_every_count_of_row_tiles(make):
     srv.close()
 
 
+@pytest.mark.parametrize("make", [lambda **k: synth.tiny_gpt(**k), lambda **k: synth.tiny_llama(synth.DT_F32, **k),
+                                  # rows of several rounds of loads, the last one ragged; too long for the norm inside the GEMM
+                                  lambda **k: dataclasses.replace(synth.tiny_gpt(**k), H=768, nh=12, F=512),
+                                  lambda **k: dataclasses.replace(synth.tiny_llama(synth.DT_F32, **k), H=1024, nh=16, F=512),
+                                  lambda **k: dataclasses.replace(synth.tiny_llama(synth.DT_F32, **k), H=1280, nh=20, F=512)])
+def test_fp32_norm_inside_the_gemm_has_the_bits_of_the_launch_of_its_own(make):
+    """Up to 32 rows an fp32 iteration takes its norms inside the GEMMs, above that in launches of their own: the same bits on either
+    side and at every edge of the GEMM's eight rows; against 64 bits in the parity tests."""
+    import paper_2305_13484_amd as fl
+    cfg = make(C=40, S=40)
+    srv = fl.Flover(cfg, synth.make_weights(cfg, 61, "cuda"))
+    srv.kv_cache().normal_(generator=torch.Generator(device="cuda").manual_seed(62))
+    rng = np.random.default_rng(63)
+    lens, toks = rng.integers(0, cfg.S - 2, size=40), rng.integers(0, cfg.V, size=40)
+    full = None
+    for n in (40, 33, 32, 31, 9, 8, 7, 1):
+        for i in range(n):
+            assert srv.add_request_cached(i, int(lens[i]), int(toks[i]), 1) == i
+        out = srv.step(want_logits=True).logits.clone()
+        srv.reorder_evict()
+        full = out if full is None else full
+        assert torch.isfinite(out).all() and torch.equal(out, full[:n]), n
+    srv.close()
+
+
 CHOICES = {                                    # what the output projection's columns hold; V is their number
     "a tie across parts": lambda v: v.index_fill_(0, torch.tensor([100, 1700, len(v) - 1]), 2.0),
     "a tie at the edge of two parts": lambda v: v.index_fill_(0, torch.tensor([1667, 1668]), 2.0),
