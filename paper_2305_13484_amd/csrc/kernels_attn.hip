@@ -14,6 +14,8 @@
 //     request's own length only, and a second tiny kernel merges a row's chunks in chunk order (results never depend
 //     on other rows); where every row of a launch has one chunk, the first kernel writes the output itself.
 // Context passes of 16-bit models take the matrix cores instead (attn_context_kernel).
+#include <type_traits>
+
 #include "flover_dev.h"
 #include "flover_kernels.h"
 
@@ -411,7 +413,10 @@ __global__ __launch_bounds__(256) void attn_prefill_kernel(const void* __restric
 // What bounds it: the chain of a step (LDS read, product, softmax, LDS read, product) at the few wavefronts a pass offers,
 // hence 16 queries per wave: 32 halve the LDS reads per multiplication but also the blocks (943 rows x 32 heads: 75 us
 // against 43; key chunks per wave with a merge launch, V through 2-byte LDS reads: 38 + 15).  290 rows x 16 heads: 16.4 us
-// and a merge of 5.2 -> 11.9 us.
+// and a merge of 5.2 -> 11.9 us.  KP = 2: the block's keys are shared out, step by step, to two sets of waves, whose results are put
+// together through LDS at the end; for passes whose blocks do not fill the chip (us, one part -> two, 16 heads of 128: 138 rows 10.6 ->
+// 9.8, 287 16.1 -> 13.6, 436 22.8 -> 17.9; 32 heads: 500 rows (256 blocks) 25.5 -> 20.0, 943 (480 blocks) 47.8 -> 47.5; 52 heads, 400
+// rows (364 blocks) 24.5 -> 26.2; 4 heads, 15 rows 5.1 -> 5.8; four parts: no faster than two).
 template <int DT> __device__ __forceinline__ uint32_t pack2(float a, float b) {
   if constexpr (DT == DT_BF16) return (uint32_t)f32_to_bf16(a) | ((uint32_t)f32_to_bf16(b) << 16);
   else return (uint32_t)f32_to_f16(a) | ((uint32_t)f32_to_f16(b) << 16);
@@ -436,18 +441,19 @@ template <int HI> __device__ __forceinline__ void read_transposed4(const uint32_
 // permutation of a V row's 16-byte pieces (pairs stay together): 8 consecutive keys put the same pair in 8 places
 template <int D> __device__ __forceinline__ int swizzle(int key) { return D == 128 ? (key & 7) * 2 : ((key >> 1) & 3) * 2; }
 
-template <int DT, int D>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void attn_context_kernel(
+template <int DT, int D, int KP>
+__global__ __launch_bounds__(256 * KP) __attribute__((amdgpu_waves_per_eu(2))) void attn_context_kernel(
     const uint16_t* __restrict__ q, const char* __restrict__ kc, const char* __restrict__ vc, const int* __restrict__ row_slot,
     const int* __restrict__ row_len, int M, int nh, int Smax, int nrb, float scale, void* __restrict__ out, int mtt) {
   static_assert(DT != DT_F32, "16-bit models only");
   constexpr int KS = D / 32;                // MFMA steps over the head dimension
   constexpr int DTL = D / 16;               // output tiles over the head dimension
   constexpr int SEG = D / 8;                // 16-byte pieces of a row
-  constexpr int RING = 4, F = D / 32;       // copies per wave and step: 2 * KS fragments of K and as many KiB of V by 4 waves
-  __shared__ __attribute__((aligned(1024))) u32x4_t lds[RING][2][32 * SEG];   // [step][K fragments | V rows]
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int g = lane >> 4, n = lane & 15;
+  constexpr int RING = KP == 1 ? 4 : 3;
+  constexpr int F = D / 32;                 // copies per wave and step: 2 * KS fragments of K and as many KiB of V by a part's 4 waves
+  __shared__ __attribute__((aligned(1024))) u32x4_t lds[RING][KP][2][32 * SEG];   // [step][part][K fragments | V rows]
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((threadIdx.x >> 6) & 3);
+  const int part = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8), g = lane >> 4, n = lane & 15;
   // heads go round the XCDs, so that a head's K and V stay in one L2; the blocks with the most keys start first
   const int qq = blockIdx.x >> 3, hd = (qq / nrb) * 8 + (blockIdx.x & 7), rb = nrb - 1 - qq % nrb;
   if (hd >= nh) return;
@@ -455,29 +461,30 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
   const int first = rb * 64 + wave * 16;                   // the wave's rows
   const int klen = len0 + min(M, (rb + 1) * 64) - 1;   // keys of the block's last row
   const int wlen = first < M ? len0 + min(M, first + 16) - 1 : 0;   // of the wave's last row
-  const int T = (klen + 31) >> 5;
+  const int T = (klen + 32 * KP - 1) / (32 * KP);
   const size_t head_off = ((size_t)slot * nh + hd) * Smax * D * 2;
   const char *kb = kc + head_off, *vb = vc + head_off;
 
   auto issue = [&](int t) {                                 // rows past the last key repeat it (masked below)
-    u32x4_t(*buf)[32 * SEG] = lds[t % RING];
+    u32x4_t(*buf)[32 * SEG] = lds[t % RING][part];
+    const int k0 = (t * KP + part) * 32;
 #pragma unroll
     for (int j = 0; j < F / 2; ++j) {
       const int f = wave + 4 * j;                           // K fragment: 16 keys x 32 d
-      const int key = min(t * 32 + (f / KS) * 16 + n, klen - 1);
+      const int key = min(k0 + (f / KS) * 16 + n, klen - 1);
       copy_to_lds(kb, (uint32_t)key * D * 2 + (f % KS) * 64 + g * 16, buf[0] + f * 64);
     }
 #pragma unroll
     for (int j = 0; j < F / 2; ++j) {
       const int u = (wave + 4 * j) * 64 + lane, kr = u / SEG;   // V piece: key kr of the step, place u % SEG
       const int seg = (u % SEG) ^ swizzle<D>(kr);
-      copy_to_lds(vb, (uint32_t)min(t * 32 + kr, klen - 1) * D * 2 + seg * 16, buf[1] + (wave + 4 * j) * 64);
+      copy_to_lds(vb, (uint32_t)min(k0 + kr, klen - 1) * D * 2 + seg * 16, buf[1] + (wave + 4 * j) * 64);
     }
   };
   // the 8 bytes of V this lane addresses for the first operand: key 4g + n/4, d 4 * (n % 4); 16 d further is a flip of the
   // piece's bits above bit 0 (the places of a row's pieces are permuted by an exclusive or as well)
   const int vk = 4 * g + (n >> 2);
-  const uint32_t vaddr = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds[0][1] +
+  const uint32_t vaddr = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds[0][part][1] +
                          (uint32_t)((vk * SEG + (((n & 3) >> 1) ^ swizzle<D>(vk))) * 16 + (n & 1) * 8);
   u32x4_t qf[KS];
   const uint16_t* qr = q + ((size_t)min(first + n, M - 1) * nh + hd) * D + g * 8;
@@ -494,9 +501,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
   for (int t = 0; t < T; ++t) {
     copies_barrier<F * (RING - 2)>(t + RING - 2 >= T);      // step t has landed; every wave is done with step t - 1
     if (t + RING - 1 < T) issue(t + RING - 1);
-    const int jb = t * 32;
+    const int jb = (t * KP + part) * 32;
     if (jb >= wlen) continue;                               // wave-uniform: none of its rows sees these keys
-    const u32x4_t* kl = lds[t % RING][0] + lane;
+    const u32x4_t* kl = lds[t % RING][part][0] + lane;
     u32x4_t kf[2][KS];
 #pragma unroll
     for (int kt = 0; kt < 2; ++kt)
@@ -559,6 +566,40 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
       }
     }
   }
+  // The parts' results of a query, put together by the first part's wave in the order of the parts
+  if constexpr (KP > 1) {
+    f32x4_t* room = (f32x4_t*)&lds[0][0][0][0];              // [part - 1][wave][DTL + 1][lane]
+    static_assert(sizeof(lds) >= (size_t)(KP - 1) * 4 * (DTL + 1) * 64 * sizeof(f32x4_t), "hand-over space");
+    copies_barrier<0>(true);
+    f32x4_t* mine = room + (size_t)((part - 1) * 4 + wave) * (DTL + 1) * 64 + lane;
+    if (part > 0) {
+#pragma unroll
+      for (int dt = 0; dt < DTL; ++dt) mine[dt * 64] = oacc[dt];
+      mine[DTL * 64] = f32x4_t{m, l, 0.f, 0.f};
+    }
+    __syncthreads();
+    if (part > 0) return;
+    f32x4_t ml[KP];
+    ml[0] = f32x4_t{m, l, 0.f, 0.f};
+    float mt = m;
+#pragma unroll
+    for (int p = 1; p < KP; ++p) {
+      ml[p] = room[(size_t)((p - 1) * 4 + wave) * (DTL + 1) * 64 + DTL * 64 + lane];
+      mt = fmaxf(mt, ml[p][0]);
+    }
+    const float ms = mt == -INFINITY ? 0.f : mt;             // rows past the last: nothing is stored
+    const float w0 = __expf(m - ms);
+    l *= w0;
+#pragma unroll
+    for (int dt = 0; dt < DTL; ++dt) oacc[dt] *= w0;
+#pragma unroll
+    for (int p = 1; p < KP; ++p) {
+      const float w = __expf(ml[p][0] - ms);                 // a part without a key for this row: 0
+      l += w * ml[p][1];
+#pragma unroll
+      for (int dt = 0; dt < DTL; ++dt) oacc[dt] += w * room[(size_t)((p - 1) * 4 + wave) * (DTL + 1) * 64 + dt * 64 + lane];
+    }
+  }
   // lane (n, g) owns O[query n][d = dt*16 + 4g .. +3]
   l = sum_partner<32>(sum_partner<16>(l));
   if (first + n < M) {
@@ -605,6 +646,8 @@ hipError_t decode_attention(int dtype, int d, const void* q, const void* kc, con
   return hipGetLastError();
 }
 
+// Two parts of the keys per block while every block gets a compute unit to itself and there are keys to share (see the kernel).
+static int context_parts(int M, int blocks) { return M > 64 && blocks <= 256 ? 2 : 1; }
 template <int DT, int D>
 static void launch_prefill(const void* q, const void* kc, const void* vc, const AttnWork& w, int M, int nh, int Smax,
                            void* out, hipStream_t st) {
@@ -615,9 +658,14 @@ static void launch_prefill(const void* q, const void* kc, const void* vc, const 
     attn_merge_kernel<DT, D, ItemList><<<dim3(M, (nh * D + 1023) / 1024), 256, 0, st>>>(w.pml, w.po, ItemList{w.items, w.row_len}, w.maxch,
                                                                                      nh, out, w.out_mtt);
   } else {
-    const int nrb = (M + 63) / 64;
-    attn_context_kernel<DT, D><<<(nh + 7) / 8 * 8 * nrb, 256, 0, st>>>((const uint16_t*)q, (const char*)kc, (const char*)vc, w.row_slot,
-                                                                      w.row_len, M, nh, Smax, nrb, scale, out, w.out_mtt);
+    const int nrb = (M + 63) / 64, blocks = (nh + 7) / 8 * 8 * nrb;
+    auto launch = [&](auto parts_) {
+      constexpr int parts = decltype(parts_)::value;
+      attn_context_kernel<DT, D, parts><<<blocks, 256 * parts, 0, st>>>((const uint16_t*)q, (const char*)kc, (const char*)vc, w.row_slot,
+                                                                       w.row_len, M, nh, Smax, nrb, scale, out, w.out_mtt);
+    };
+    if (context_parts(M, nh * nrb) == 2) launch(std::integral_constant<int, 2>{});
+    else launch(std::integral_constant<int, 1>{});
   }
 }
 
