@@ -78,8 +78,10 @@ __device__ __forceinline__ void norm_row(Update update, int m, const void* __res
     }
     __syncthreads();
     float t = r[0];
+    const int n = blockDim.x / 64 * VW;
 #pragma unroll
-    for (int i = 1; i < 16; ++i) t += r[i];
+    for (int i = 1; i < 16; ++i)
+      if (i < n) t += r[i];
     return t;
   };
   f32x4_t v[VW][PER], gv[VW][PER], bv[VW][PER];
@@ -172,7 +174,7 @@ __global__ __launch_bounds__(1024 / VW) void embed_norm_kernel(const void* __res
   if (first >= 0) {
     const int nr = out.block_rows > 0 ? min(out.block_rows, (int)gridDim.x - m) : 1, len = pos + nr;
     const int chunks = (len + kAttnChunk - 1) / kAttnChunk;
-    for (int c = tid; c < chunks; c += 1024 / VW)
+    for (int c = tid; c < chunks; c += blockDim.x)
       out.list[first + c] = out.block_rows > 0 ? make_int4(m, nr, c, 0) : make_int4(m, c, row.slot, len);
   }
   const size_t t = (size_t)tk * H, p = wpe ? (size_t)pos * H : 0;
@@ -351,11 +353,16 @@ __global__ __launch_bounds__(512) void argmax_kernel(const float* __restrict__ p
     default: { constexpr int DT = DT_BF16; CALL; } break;     \
   }
 
+// Threads of a norm block: a row of fewer than 4096 columns leaves the later waves nothing but the barriers (their sums are zero), and
+// without them more rows fit a compute unit (three prompts of 138 / 287 / 436 rows of 2048 columns, six layers: 1676 -> 1658 us; a few
+// rows take the same time).
+static int norm_threads(int H, int VW) { return VW > 1 ? 1024 / VW : std::min(1024, (H + 255) / 256 * 64); }
+
 hipError_t embed_norm(int dtype, bool rms, const void* wte, const void* wpe, const RowIn* rows, const RowOut& out, const Choice* prev,
                       int parts, float* x, const void* g, const void* b, void* h, int M, int H, float eps, int mtt, hipStream_t st) {
   if (M <= 0) return hipSuccess;
 #define FLK_EMBED(RMS, VW) \
-  FLK_DT_SWITCH(dtype, (embed_norm_kernel<DT, RMS, VW><<<M, 1024 / VW, 0, st>>>(wte, wpe, rows, out, prev, parts, x, g, b, h, H, eps, mtt)))
+  FLK_DT_SWITCH(dtype, (embed_norm_kernel<DT, RMS, VW><<<M, norm_threads(H, VW), 0, st>>>(wte, wpe, rows, out, prev, parts, x, g, b, h, H, eps, mtt)))
   if (M > 512) {         // as for add_norm
     if (rms) FLK_EMBED(1, 4) else FLK_EMBED(0, 4)
   } else {
@@ -369,7 +376,7 @@ hipError_t add_norm(int dtype, bool rms, float* x, const float* part, int S, siz
                     const void* g, const void* b, void* h, int M, int H, float eps, int mtt, hipStream_t st) {
   if (M <= 0) return hipSuccess;
 #define FLK_NORM(RMS, VW) \
-  FLK_DT_SWITCH(dtype, (add_norm_kernel<DT, RMS, VW><<<M, 1024 / VW, 0, st>>>(x, part, S, stride, ldp, bias, g, b, h, H, eps, mtt)))
+  FLK_DT_SWITCH(dtype, (add_norm_kernel<DT, RMS, VW><<<M, norm_threads(H, VW), 0, st>>>(x, part, S, stride, ldp, bias, g, b, h, H, eps, mtt)))
   if (M > 512) {         // more rows than 1024-thread blocks fit the chip at once
     if (rms) FLK_NORM(1, 4) else FLK_NORM(0, 4)
   } else {
