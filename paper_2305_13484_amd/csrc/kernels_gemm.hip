@@ -771,7 +771,7 @@ __global__ __launch_bounds__(512) void gemm16_rows_kernel(const uint16_t* __rest
   copies_barrier<(F + B) * L - F>(false);        // the copies of k-block 0 have landed
   int slot = 0;                                  // of the k-block being multiplied
   // One k-block.  ROWS8 = all eight row tiles live (no branches); otherwise dead row tiles are skipped (wave-uniform).
-  auto kblock = [&](auto j_, auto rows8_, int t) {
+  auto kblock = [&](auto j_, auto rows8_, auto last_, int t) {
     constexpr int j = decltype(j_)::value;
     constexpr bool rows8 = decltype(rows8_)::value;
     const int nslot = slot + 1 == D ? 0 : slot + 1, cslot = slot == 0 ? D - 1 : slot - 1;
@@ -779,8 +779,9 @@ __global__ __launch_bounds__(512) void gemm16_rows_kernel(const uint16_t* __rest
 #pragma unroll
     for (int i = 0; i < A; ++i) {
       if (i == A / 2) {
-        // the copies of k-block t + 1 have landed; every wave has read k-block t - 1, whose slot is refilled
-        copies_barrier<(F + B) * (L - 1) - F>(false);
+        // the copies of k-block t + 1 have landed; every wave has read k-block t - 1, whose slot is refilled.  In the last turn the W
+        // loads feed nothing and are not made, so fewer loads follow those copies than the count says: wait for all.
+        copies_barrier<(F + B) * (L - 1) - F>(decltype(last_)::value);
         copy_rows(t + L, cslot);
         __builtin_amdgcn_sched_barrier(0);
       }
@@ -806,14 +807,14 @@ __global__ __launch_bounds__(512) void gemm16_rows_kernel(const uint16_t* __rest
     }
     int t = 0;
     for (; t + PF <= T; t += PF) {
-      kblock(std::integral_constant<int, 0>{}, rows8_, t);
-      kblock(std::integral_constant<int, 1>{}, rows8_, t + 1);
-      kblock(std::integral_constant<int, 2>{}, rows8_, t + 2);
-      kblock(std::integral_constant<int, 3>{}, rows8_, t + 3);
+      kblock(std::integral_constant<int, 0>{}, rows8_, std::false_type{}, t);
+      kblock(std::integral_constant<int, 1>{}, rows8_, std::false_type{}, t + 1);
+      kblock(std::integral_constant<int, 2>{}, rows8_, std::false_type{}, t + 2);
+      kblock(std::integral_constant<int, 3>{}, rows8_, std::false_type{}, t + 3);
     }
-    if (t < T) kblock(std::integral_constant<int, 0>{}, rows8_, t);
-    if (t + 1 < T) kblock(std::integral_constant<int, 1>{}, rows8_, t + 1);
-    if (t + 2 < T) kblock(std::integral_constant<int, 2>{}, rows8_, t + 2);
+    if (t < T) kblock(std::integral_constant<int, 0>{}, rows8_, std::true_type{}, t);
+    if (t + 1 < T) kblock(std::integral_constant<int, 1>{}, rows8_, std::true_type{}, t + 1);
+    if (t + 2 < T) kblock(std::integral_constant<int, 2>{}, rows8_, std::true_type{}, t + 2);
   };
   // Two copies of the loop, chosen per wave (both pass the same barriers).
   if (live == A) loop(std::true_type{});

@@ -127,6 +127,20 @@ def test_gemm_of_more_than_128_rows_each_block_and_group_width(dtype, group, blo
     assert torch.all((got - xd @ Wd.T).abs() <= 4e-6 * (xd.abs() @ Wd.abs().T) + 1e-30)
 
 
+@pytest.mark.parametrize("dtype", [synth.DT_BF16, synth.DT_F16])
+def test_gemm_of_256_row_blocks_with_three_k_blocks_in_the_last_turn(dtype):
+    """The weight ring turns four k-blocks at a time; slices of 4n + 3 read row copies in the last turn that only that turn's own
+    waits cover.  Bound as above."""
+    M, N, K = 513, 4096, 2336
+    assert fl.binding.k_gemm_block(dtype, N, K, M)[1:] == (256, 256) and fl.binding.k_gemm_plan(dtype, N, K)[1] % 4 == 3
+    g = torch.Generator(device="cuda").manual_seed(4)
+    x = torch.randn((M, K), generator=g, device="cuda").to(TDT[dtype])
+    tw = fl.binding.TiledWeight((torch.randn((N, K), generator=g, device="cuda") * 0.05).to(TDT[dtype]))
+    part = fl.k_gemm(x[:100].contiguous(), tw)
+    got = fl.k_gemm(x, tw)
+    assert torch.equal(got[:100], part)
+
+
 def _at_element(t, at):
     """A copy of t that starts `at` elements behind a 16-byte boundary."""
     room = torch.zeros(t.numel() + 8, dtype=t.dtype, device="cuda")
