@@ -923,6 +923,162 @@ __global__ __launch_bounds__(64 * WR * WC) __attribute__((amdgpu_waves_per_eu(2)
   tile_epilogue<DT, A, B, WR, WC, EPI>(acc, o, M, N, mt0 + wr * A, nt0, wc, s, lane);
 }
 
+// ---- context passes, the blocks of up to 128 x 256: K in WK parts inside the block.  A block is WC x WK = 8 waves; a wave owns A
+// row tiles x B n-tiles over one part of the slice's k-blocks, so that the weights go straight to registers without any two
+// waves loading the same ones (PF k-blocks ahead), and only the rows' operand, which the WC waves of a part share, goes through
+// LDS (asynchronous copies, L k-blocks ahead).  A step is one k-block of every part.  With both operands through LDS its 128 bytes per
+// cycle are the bound (64 x 128 blocks 0.165 us per k-block, here 0.11; 64 x 64 0.128 and 0.066; 128 x 256 0.40 and 0.36), which
+// leaves the 110 bytes per nanosecond that reach a compute unit; the hand-over at the end costs 1 to 2 us.
+template <int DT, int A, int B, int WC, int WK, int PF, int L, int EPI>
+__global__ __launch_bounds__(64 * WC * WK) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm16_parts_kernel(
+    const uint16_t* __restrict__ x, const u32x4_t* __restrict__ wt, TileOut o, int M, int N, int K, int ntiles, int NTL, int KB, int kbs,
+    int ncb, int nrb, int tasks, int per, int xmtt) {
+  constexpr int NW = WC * WK, F = A * WK / NW, D = L + 1;      // F: copies per wave and step
+  constexpr int OWN = A / WK;                                  // row tiles a wave finishes
+  static_assert(NW == 8 && A * WK % NW == 0 && A % WK == 0 && B % 2 == 0, "fragments divide among the waves");
+  static_assert(PF >= L - 1 && (F + B) * (L - 1) - F < 64, "wait counts");
+  constexpr int RT = OWN > 1 && (WK - 1) * B * NW * OWN > 96 ? OWN / 2 : OWN;   // row tiles per round of the hand-over
+  constexpr int XF = D * WK * A, RF = (WK - 1) * B * NW * RT;
+  __shared__ u32x4_t lds[(XF > RF ? XF : RF) * 64];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wk = wave / WC, wc = wave % WC;
+  const int task = (blockIdx.x & 7) * per + (blockIdx.x >> 3);  // see gemm16_tile_kernel
+  if ((int)(blockIdx.x >> 3) >= per || task >= tasks) return;
+  const int rb = task % nrb, cs = task / nrb, cb = cs % ncb, s = cs / ncb;
+  const int kb0 = s * kbs, T = min(KB, kb0 + kbs) - kb0;
+  const int mt0 = rb * A, nt0 = cb * B * WC;
+  // part p: k-blocks first(p) .. first(p + 1) - 1 of the slice; every part has one at least (the host sees to it)
+  auto first = [&](int p) { return p * (T / WK) + min(p, T % WK); };
+  const int steps = (T + WK - 1) / WK, k0 = kb0 + first(wk), Tp = first(wk + 1) - first(wk);
+
+  const RowTiles rows(x, M, K, mt0, 0, xmtt);
+  uint32_t src[F];
+  const char* from[F];
+  int left[F];                                   // k-blocks of the part that are still to be copied behind the next one
+#pragma unroll
+  for (int j = 0; j < F; ++j) {
+    const int f = wave + NW * j, p = f / A;
+    src[j] = rows.offset(f % A, lane);
+    from[j] = rows.base + (size_t)(kb0 + first(p)) * rows.step;
+    left[j] = first(p + 1) - first(p) - 1;
+  }
+  // Copies and W loads past a part repeat its last k-block (in bounds, unused): every step issues the same number of loads and
+  // the wait counts are constants.
+  auto copy_rows = [&](int slot) {
+#pragma unroll
+    for (int j = 0; j < F; ++j) {
+      copy_to_lds(from[j], src[j], lds + (slot * WK * A + wave + NW * j) * 64);
+      from[j] += left[j] > 0 ? rows.step : 0;
+      left[j] -= 1;
+    }
+  };
+  const u32x4_t* wp[B / 2];                      // pairs of n-tiles lie side by side
+#pragma unroll
+  for (int u = 0; u < B; u += 2) {
+    const int nt = min(nt0 + tile_of<B, WC, EPI>(wc, u, o.d), ntiles - 2);
+    wp[u / 2] = wt + (((size_t)(nt / NTL) * KB + k0) * NTL + nt % NTL) * 64 + lane;
+  }
+  u32x4_t bq[PF][B], af[4];
+  auto load_w = [&](auto j_, int t) {
+    constexpr int j = decltype(j_)::value;
+    const uint32_t at = (uint32_t)min(t, Tp - 1) * NTL * 64;
+#pragma unroll
+    for (int u = 0; u < B; ++u) bq[j][u] = wp[u / 2][at + (u & 1) * 64];
+  };
+  f32x4_t acc[A][B];
+#pragma unroll
+  for (int i = 0; i < A; ++i)
+#pragma unroll
+    for (int u = 0; u < B; ++u) acc[i][u] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int t = 0; t < L; ++t) copy_rows(t);
+  __builtin_amdgcn_sched_barrier(0);
+  auto prologue = [&](auto self, auto j_) -> void {
+    constexpr int j = decltype(j_)::value;
+    load_w(j_, j);
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (j + 1 < PF) self(self, std::integral_constant<int, j + 1>{});
+  };
+  prologue(prologue, std::integral_constant<int, 0>{});
+  copies_barrier<(L - 1) * F + PF * B>(false);   // the copies of step 0 have landed
+  int slot = 0;
+  af[0] = lds[(wk * A) * 64 + lane];
+  af[1] = lds[(wk * A + 1) * 64 + lane];
+  auto step = [&](auto j_, auto all_, int t) {
+    constexpr int j = decltype(j_)::value;
+    constexpr bool all = decltype(all_)::value;  // every part has a k-block left
+    const int nslot = slot + 1 == D ? 0 : slot + 1, cslot = slot == 0 ? D - 1 : slot - 1;
+    const u32x4_t *lw = lds + (slot * WK + wk) * A * 64 + lane, *ln = lds + (nslot * WK + wk) * A * 64 + lane;
+#pragma unroll
+    for (int i = 0; i < A; ++i) {
+      if (i == A / 2) {
+        // the copies of step t + 1 have landed; every wave has read step t - 1, whose slot is refilled; in the last turn wait for all
+        // (see gemm16_rows_kernel)
+        copies_barrier<(F + B) * (L - 1) - F>(!all);
+        copy_rows(cslot);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      af[(i + 2) % 4] = i + 2 < A ? lw[(i + 2) * 64] : ln[(i + 2 - A) * 64];
+      if (all || t < Tp) {
+#pragma unroll
+        for (int u = 0; u < B; ++u) acc[i][u] = mfma16<DT>(bq[j][u], af[i % 4], acc[i][u]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    load_w(j_, t + PF);
+    __builtin_amdgcn_sched_barrier(0);
+    slot = nslot;
+  };
+  auto turn = [&](auto self, auto j_, auto all_, int t, int n) -> void {      // steps t .. of one turn of the W ring, n of them
+    constexpr int j = decltype(j_)::value;
+    if (decltype(all_)::value || j < n) {
+      step(j_, all_, t + j);
+      if constexpr (j + 1 < PF) self(self, std::integral_constant<int, j + 1>{}, all_, t, n);
+    }
+  };
+  int t = 0;
+  for (; t + PF < steps; t += PF) turn(turn, std::integral_constant<int, 0>{}, std::true_type{}, t, PF);
+  turn(turn, std::integral_constant<int, 0>{}, std::false_type{}, t, steps - t);
+  // The parts' sums: a wave finishes OWN of its row tiles and hands the others to the waves of the same columns, RT per owner and
+  // round; added in the order of the parts.
+  f32x4_t own[OWN][B];
+  f32x4_t* red = (f32x4_t*)lds;
+#pragma unroll
+  for (int r = 0; r < OWN; r += RT) {
+    if (r == 0) copies_barrier<0>(true);         // no copy may still be under way when its place is written
+    else copies_barrier<0>(false);
+#pragma unroll
+    for (int p = 0; p < WK; ++p) {               // what part p finishes
+      const int at = ((p * (WK - 1) + wk - (wk > p)) * WC + wc) * RT * B;
+      if (p == wk) {
+#pragma unroll
+        for (int i = 0; i < RT; ++i)
+#pragma unroll
+          for (int u = 0; u < B; ++u) own[r + i][u] = acc[p * OWN + r + i][u];
+      } else {
+#pragma unroll
+        for (int i = 0; i < RT; ++i)
+#pragma unroll
+          for (int u = 0; u < B; ++u) red[(at + i * B + u) * 64 + lane] = acc[p * OWN + r + i][u];
+      }
+    }
+    copies_barrier<0>(false);
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+#pragma unroll
+      for (int u = 0; u < B; ++u) {
+        f32x4_t v[WK];
+#pragma unroll
+        for (int p = 0; p < WK; ++p)             // the slot of part wk itself: any, replaced
+          v[p] = red[(((wk * (WK - 1) + min(p - (p > wk), WK - 2)) * WC + wc) * RT * B + i * B + u) * 64 + lane];
+        f32x4_t sum = wk == 0 ? own[r + i][u] : v[0];
+#pragma unroll
+        for (int p = 1; p < WK; ++p) sum += p == wk ? own[r + i][u] : v[p];
+        own[r + i][u] = sum;
+      }
+  }
+  tile_epilogue<DT, OWN, B, 1, WC, EPI>(own, o, M, N, mt0 + wk * OWN, nt0, wc, s, lane);
+}
+
 // ---------------------------------------------------------------- fp32 FMA kernel (tiny models)
 
 // Lane l ends with the sum over the wave of v[l >> 2]: halves of the values are exchanged at distances 32, 16, 8 and 4 (15
@@ -1289,7 +1445,24 @@ static void launch_tile(const void* x, const void* wt, const TileOut& o, int M, 
   launch_timed(gemm16_tile_kernel<DT, A, B, WR, WC, D, EPI>, dim3(per * 8), dim3(64 * WR * WC), st, ev0, ev1, (const uint16_t*)x,
                (const char*)wt, o, M, p.N, p.K, p.Npad / 16, p.NT, p.KB, p.kbs, ncb, nrb, tasks, per, xmtt);
 }
+template <int DT, int A, int B, int WC, int WK, int PF, int L, int EPI>
+static void launch_parts(const void* x, const void* wt, const TileOut& o, int M, const GemmPlan& p, int xmtt, hipStream_t st,
+                         hipEvent_t ev0, hipEvent_t ev1) {
+  const int nrb = (M + 16 * A - 1) / (16 * A), ncb = (p.N + 16 * B * WC - 1) / (16 * B * WC);
+  const int tasks = nrb * ncb * p.S, per = (tasks + 7) / 8;
+  launch_timed(gemm16_parts_kernel<DT, A, B, WC, WK, PF, L, EPI>, dim3(per * 8), dim3(64 * WC * WK), st, ev0, ev1, (const uint16_t*)x,
+               (const u32x4_t*)wt, o, M, p.N, p.K, p.Npad / 16, p.NT, p.KB, p.kbs, ncb, nrb, tasks, per, xmtt);
+}
 // 64-column blocks do not hold the rotary partners of a 128-wide head: that epilogue takes 128 columns instead
+// Whether a context pass's GEMM takes K in parts inside the block; the windows' slices are single chains, so they never do.
+// us per launch, cold weights, both operands through LDS -> in parts: 64 x 64 blocks 2048 x 2048 at 287 / 436 rows (160 / 224 blocks) 11.3 /
+// 11.5 -> 8.0 / 8.5, 4096 x 4096 at 138 (192) 28.6 -> 16.6, 2048 x 2048 at 943 (480 blocks, which share the compute units) 15.1 -> 17.4;
+// 64 x 128 6144 x 2048 at 287 (240) 18.4 -> 16.4, at 436 (336) 26.3 -> 31.0; slices of 16 k-blocks 6.4 -> 7.4; 128 x 256 12288 x 4096 at 138 /
+// 780 (192 / 336) 56.0 / 112 -> 52.9 / 104; 128 x 128 gains nothing (6144 x 2048 at 436 22.7 -> 22.4) and loses on short slices.
+static bool parts_pay(int tile, int M, const GemmPlan& p) {
+  if (p.tile < 0 || tile == TILE_128X128 || p.KB - (p.S - 1) * p.kbs < 32) return false;
+  return tile == TILE_128X256 || tile_blocks(tile, M, p, p.S) <= 256;
+}
 template <int DT, int EPI>
 static void dispatch_tile(int tile, const void* x, const void* wt, const TileOut& o, int M, const GemmPlan& p, int xmtt, hipStream_t st,
                           hipEvent_t ev0, hipEvent_t ev1) {
@@ -1299,6 +1472,11 @@ static void dispatch_tile(int tile, const void* x, const void* wt, const TileOut
     } else {
       launch_rows<DT, 2, EPI>(x, wt, o, M, p, xmtt, st, ev0, ev1);
     }
+  }
+  else if (parts_pay(tile, M, p)) {
+    if (tile == TILE_128X256) launch_parts<DT, 8, 4, 4, 2, 4, 4, EPI>(x, wt, o, M, p, xmtt, st, ev0, ev1);
+    else if (tile == TILE_64X128 || EPI == EPI_QKV) launch_parts<DT, 4, 4, 2, 4, 4, 4, EPI>(x, wt, o, M, p, xmtt, st, ev0, ev1);
+    else if constexpr (EPI != EPI_QKV) launch_parts<DT, 4, 2, 2, 4, 4, 3, EPI>(x, wt, o, M, p, xmtt, st, ev0, ev1);
   }
   else if (tile == TILE_128X256) launch_tile<DT, 4, 4, 2, 4, 4, EPI>(x, wt, o, M, p, xmtt, st, ev0, ev1);
   else if (tile == TILE_128X128) launch_tile<DT, 2, 4, 4, 2, 4, EPI>(x, wt, o, M, p, xmtt, st, ev0, ev1);
@@ -1426,13 +1604,11 @@ static void dispatch16(const void* x, const void* wt, float* part, int M, const 
   else if (M <= 64) launch_lds<DT, 4, NT, 2, 4>(x, wt, part, M, p, ss, xmtt, st, ev0, ev1);
   else if (regs) launch_lds<DT, 8, NT, 2, 4, 8>(x, wt, part, M, p, ss, xmtt, st, ev0, ev1);   // paired: 8 groups, 256 columns
   else {                                                                             // context passes, very wide windows
-    GemmPlan q = p;
-    if (q.tile < 0) q.tile = best_tile(M, p);
     TileOut o;
     o.part = part;
     o.slice_stride = ss;
     o.ldc = p.ldc;
-    dispatch_tile<DT, EPI_PART>(q.tile, x, wt, o, M, q, xmtt, st, ev0, ev1);
+    dispatch_tile<DT, EPI_PART>(p.tile < 0 ? best_tile(M, p) : p.tile, x, wt, o, M, p, xmtt, st, ev0, ev1);
   }
 }
 

@@ -599,6 +599,23 @@ def test_context_pass_of_hundreds_of_rows_against_64_bits(model, dtype, rows, bl
     torch.cuda.empty_cache()
 
 
+@pytest.mark.parametrize("model,dtype,rows", [("gpt_1p3b", "f16", 138), ("gpt_1p3b", "bf16", 287), ("gpt_1p3b", "f16", 436),
+                                              ("llama_7b", "bf16", 130), ("llama_7b", "f16", 200)])
+def test_context_pass_with_k_in_parts_against_64_bits(model, dtype, rows):
+    """The blocks that cut K among their waves, each with the epilogues it serves (q|k|v, residual add with and without bias, GELU, SwiGLU,
+    slices), at row counts whose blocks all run at once; row by row, bound as above."""
+    case = {"kind": "context", "model": model, "dtype": dtype, "layers": 2, "rows": 1, "slots": 2, "max_seq": 512, "len_lo": rows + 1,
+            "len_hi": rows + 1, "overlap": False}
+    state = perf_cases.prepare(case, 6)
+    got, = perf_cases.run(state)
+    torch.cuda.synchronize()
+    ref, = perf_cases.exact(case, 6)
+    err = (got.double() - ref).norm(dim=(2, 4)) / ref.norm(dim=(2, 4))
+    assert float(err.max()) <= 2 * perf_cases.tolerance(case)["rel"]
+    state["engine"].close()
+    torch.cuda.empty_cache()
+
+
 def test_more_than_128_live_rows():
     """max_concurrency above one GEMM row block: 150 requests live at once (two row blocks, XCD-mapped), against the
     oracle on a tiny model, and the window bookkeeping with a large burst."""
