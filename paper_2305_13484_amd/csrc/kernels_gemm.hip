@@ -11,9 +11,13 @@
 //     a row block is the unit of work; up to 16 rows one wave takes it and reads the rows' operand straight from L2/L1
 //     (no LDS, no barriers); above that the rows' operand is staged through LDS once per block of 4 column groups and
 //     shared by the block's 4 or 8 waves.
+//   * matrices whose result a row-wise kernel would only finish (q|k|v, GELU input) and narrow gate|up matrices, K of moderate length,
+//     up to 128 rows: a block per 32 columns with all of K in it, the slices in its waves, the job finished by it
+//     (gemm16_whole_kernel).
 //   * more than 128 rows (context passes, very wide windows): the contraction turns MFMA- and operand-bound.  A wave keeps
 //     a 128 x 64 output tile and a block covers 256 rows x 256 columns (gemm16_rows_kernel), or, where such blocks would
-//     leave the chip idle, smaller blocks with both operands in LDS (gemm16_tile_kernel); context_plan picks by a cost
+//     leave the chip idle, smaller blocks, either with both operands in LDS (gemm16_tile_kernel) or, in context passes of few blocks,
+//     with K in parts and the weights straight to registers (gemm16_parts_kernel); context_plan picks the block by a cost
 //     model.  Taken in one slice, the kernel finishes the job itself: residual add, activation, or rotary and append.
 //     Row blocks of one (column block, K slice) get workgroup ids that land on the same XCD, so the weight tiles cross HBM
 //     once and are L2 hits for the others.
@@ -24,9 +28,9 @@
 //     of rows, where the fp32 partial sums would outweigh the weights, more for short prompts.
 //   * MFMA v_mfma_f32_16x16x32_{bf16,f16}: A = 16 columns of W, B = 16 rows of x, 32-deep: the accumulator tile is
 //     y^T, so a lane holds 4 consecutive output columns of one row and stores them as one 16-byte write.
-//   * gate|up of a gated MLP, up to 128 fused rows: no partial sums at all -- the two K halves are the two wave sets of
-//     a block and the activation is the kernel's epilogue (gated_lds_kernel), with gate and up columns interleaved in
-//     the layout so that a lane holds both; above 128 rows the same halves go through memory as two slices.
+//   * gate|up of a gated MLP, up to 128 fused rows: no partial sums at all -- the two K halves (or the whole kernel's four slices)
+//     are wave sets of a block and the activation is the kernel's epilogue (gated_lds_kernel), with gate and up columns
+//     interleaved in the layout so that a lane holds both; above 128 rows the same slices go through memory.
 // fp32 models (tiny configurations only) use a plain FMA kernel on the untiled matrix, with what follows the contraction as
 // its epilogue.
 #include <algorithm>
