@@ -48,6 +48,7 @@ struct TileOut {
   const int *pos = nullptr, *slot = nullptr;
   void *q = nullptr, *kc = nullptr, *vc = nullptr;
   int d = 0, Smax = 0;
+  int H = 0, third = 0;           // columns of q, of k and of v; which of them the matrix starts with (1: k|v alone)
   NormIn norm;
 };
 // gate|up of a gated MLP with F columns each.  paired = 1: group j of the layout holds gate columns 16j..16j+15 then up
@@ -63,7 +64,7 @@ GemmPlan context_plan(const GemmPlan& p, int dtype, int M, int max_slices);
 void gemm_block(int M, const GemmPlan& p, int* rows, int* columns);
 // The contraction and what follows it in one launch: fp32 models always, 16-bit models up to kWholeRows rows where the plan says so
 // and in a context pass whose plan takes K in one slice (gemm_finishes); otherwise the caller goes through gemm() and the row-wise kernel.  gemm_qkv: bias, rotary, q and
-// the cache rows (o: bias, rope, pos, slot, q, kc, vc, d, Smax).  gemm_add: res[M][N] += x . W^T + bias (bias may be null).
+// the cache rows (o: bias, rope, pos, slot, q, kc, vc, d, Smax, H, third).  gemm_add: res[M][N] += x . W^T + bias (bias may be null).
 // gemm_act: GELU of x . W^T + bias, or SwiGLU (16-bit: paired layout; fp32: up after gate).  x is read and the activation written
 // in the layout xmtt says.
 bool gemm_finishes(int dtype, const GemmPlan& p, int M);

@@ -498,7 +498,7 @@ __device__ __forceinline__ void tile_epilogue(f32x4_t (&acc)[A][B], const TileOu
         }
     }
   } else {                                       // q | k | v columns of one head, rotary partners u and u + B/2
-    const int H = N / 3, half = o.d >> 1;
+    const int H = o.H, half = o.d >> 1;
     int pos[A], slot[A];
 #pragma unroll
     for (int i = 0; i < A; ++i) {
@@ -529,7 +529,7 @@ __device__ __forceinline__ void tile_epilogue(f32x4_t (&acc)[A][B], const TileOu
         for (int u = 0; u < B / 2; ++u) {
           const int n = column(u);
           if (n >= N) continue;
-          const int which = n / H, r = n - which * H, hd = r / o.d, e = r - hd * o.d;
+          const int t = n / H, which = o.third + t, r = n - t * H, hd = r / o.d, e = r - hd * o.d;
           f32x4_t a0 = acc[i0 + i][u], a1 = acc[i0 + i][u + B / 2];
           if (o.bias) { a0 += bias[u]; a1 += bias[u + B / 2]; }
           if (o.rope && which < 2)
@@ -664,7 +664,7 @@ __global__ __launch_bounds__(64 * S) void gemm16_whole_kernel(const uint16_t* __
       stv4<DT>(o.act, xrow_index(m, n0, o.F, o.mtt), act_gelu<DT>(a0));
       stv4<DT>(o.act, xrow_index(m, n1, o.F, o.mtt), act_gelu<DT>(a1));
     } else {
-      const int H = N / 3, which = n0 / H, c = n0 - which * H;       // both tiles lie in the same third and head
+      const int H = o.H, t = n0 / H, which = o.third + t, c = n0 - t * H;      // both tiles lie in the same third and head
       if (o.rope && which < 2)
         rope_rotate(a0, a1, f32x4_t{r0[q][0], r0[q][2], r1[q][0], r1[q][2]}, f32x4_t{r0[q][1], r0[q][3], r1[q][1], r1[q][3]});
       const int hd = c / o.d, e = c - hd * o.d;
@@ -1197,7 +1197,7 @@ __global__ __launch_bounds__(256) void gemm32_kernel(const float* __restrict__ x
   if (m >= M || (lane & 3)) return;
   if constexpr (EPI == EPI_QKV) {
     if (lane & 4) return;
-    const int H = N / 3, which = c0 / H, r = c0 - which * H, hd = r / o.d, e = r - hd * o.d;
+    const int H = o.H, t = c0 / H, which = o.third + t, r = c0 - t * H, hd = r / o.d, e = r - hd * o.d;
     f32x4_t a0 = {sum, 0.f, 0.f, 0.f}, a1 = {other, 0.f, 0.f, 0.f};
     if (o.rope && which < 2) {
       const float* tab = o.rope + ((size_t)pos * half + e) * 2;
