@@ -59,7 +59,8 @@ struct Lane {
   flk::Choice* choice = nullptr;   // [rows][parts]
   flk::RowOut rows{};       // row descriptors on the device, and the list of an iteration's attention or of an fp32 context pass's
   float *pml = nullptr, *po = nullptr;
-  // a pass's rows in pinned memory, where its first kernel reads them; a ring so that passes can be queued without waiting
+  // a pass's rows in pinned memory (coherent: no cache of the GPU keeps what a ring entry held before), where its first kernel reads
+  // them; a ring so that passes can be queued without waiting
   flk::RowIn* h_rows[kStageRing] = {nullptr, nullptr, nullptr, nullptr};
   hipEvent_t staged[kStageRing] = {nullptr, nullptr, nullptr, nullptr};   // h_rows[i] has been read
   bool staged_busy[kStageRing] = {false, false, false, false};
@@ -734,20 +735,20 @@ int32_t flover_init(const flover_config* cfg, const flover_weights* w, flover_ct
   c->step_lane.st = c->st;
   c->step_lane.ring = kStageRing;
   for (int i = 0; i < kStageRing; ++i) {
-    HIPTRY(hipHostMalloc((void**)&c->step_lane.h_rows[i], c->rows_cap * sizeof(flk::RowIn), hipHostMallocDefault));
+    HIPTRY(hipHostMalloc((void**)&c->step_lane.h_rows[i], c->rows_cap * sizeof(flk::RowIn), hipHostMallocCoherent));
     HIPTRY(hipEventCreateWithFlags(&c->step_lane.staged[i], hipEventDisableTiming));
     HIPTRY(hipEventCreateWithFlags(&c->step_lane.done[i], hipEventDisableTiming));
     HIPTRY(hipHostMalloc((void**)&c->h_moves_ring[i], (size_t)cfg->max_concurrency * sizeof(int4), hipHostMallocDefault));
     HIPTRY(hipEventCreateWithFlags(&c->moves_ev[i], hipEventDisableTiming));
   }
   HIPTRY(hipHostMalloc((void**)&c->step_lane.h_choice,
-                       (size_t)kStageRing * c->rows_cap * flk::argmax_parts(cfg->vocab) * sizeof(flk::Choice), hipHostMallocDefault));
+                       (size_t)kStageRing * c->rows_cap * flk::argmax_parts(cfg->vocab) * sizeof(flk::Choice), hipHostMallocCoherent));
   if (cfg->async_preprocess) {
     for (Lane& pl : c->prep_lanes) {
       HIPTRY(hipStreamCreateWithFlags(&pl.st, hipStreamNonBlocking));   // default priority
       pl.ring = kStageRing;
       for (int i = 0; i < kStageRing; ++i) {
-        HIPTRY(hipHostMalloc((void**)&pl.h_rows[i], c->rows_cap * sizeof(flk::RowIn), hipHostMallocDefault));
+        HIPTRY(hipHostMalloc((void**)&pl.h_rows[i], c->rows_cap * sizeof(flk::RowIn), hipHostMallocCoherent));
         HIPTRY(hipEventCreateWithFlags(&pl.staged[i], hipEventDisableTiming));
       }
     }
