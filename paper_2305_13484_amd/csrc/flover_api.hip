@@ -390,27 +390,27 @@ int run_rows(flover_ctx* c, Lane& ln, const Row* rows, int n, bool want_tokens, 
     HIPCHK(c, hipEventRecord(ln.staged[ri], st));
     ln.staged_busy[ri] = true;
   }
-  const bool norms = flk::gemm_norms(f.dtype, n, H);
+  // fp32 models: the norm in the launch of the GEMM that reads it, which then reads the residual stream
+  auto normed = [&](const flk::GemmPlan& p, const void* g, const void* b) {
+    flk::NormIn in;
+    if (flk::gemm_norms(f.dtype, n, p)) in = flk::NormIn{g, b, !gpt, f.norm_eps};
+    return in;
+  };
+  // a GEMM whose kernel finishes the job leaves nothing to the row-wise kernel behind it
+  auto finishes = [&](const flk::GemmPlan& p) { return flk::gemm_finishes(f.dtype, p, n); };
   bool added = true;      // the residual stream already holds what the GEMM before the norm computed
   for (int l = 0; l < L; ++l) {
     const LayerW& w = c->lw[l];
-    // fp32 models: the norm in the GEMM's own launch, which reads the residual stream
-    auto normed = [&](const void* g, const void* b) {
-      flk::NormIn in;
-      if (norms) in = flk::NormIn{g, b, !gpt, f.norm_eps};
-      return in;
-    };
-    if (l > 0 && !norms)
+    const bool kv_only = context_pass && l == L - 1 && finishes(p_kv);
+    const flk::NormIn norm1 = l > 0 ? normed(kv_only ? p_kv : p_qkv, w.ln1_g, w.ln1_b) : flk::NormIn();
+    if (l > 0 && !norm1.g)
       HIPCHK(c, flk::add_norm(f.dtype, !gpt, ln.x, added ? nullptr : ln.part, p_2.S, ss_h, p_2.ldc, added ? nullptr : c->lw[l - 1].b2,
                               w.ln1_g, w.ln1_b, ln.h, n, H, f.norm_eps, mtt, st));
     char* kl = c->kv + (size_t)(2 * l) * c->plane_bytes;
     char* vl = kl + c->plane_bytes;
     const bool gs = gemm_iter && l == L / 2;
-    // a GEMM whose kernel finishes the job leaves nothing to the row-wise kernel behind it
-    auto finishes = [&](const flk::GemmPlan& p) { return flk::gemm_finishes(f.dtype, p, n); };
     {
       const GemmTimer t(c, ln, FLOVER_PROF_GEMM_QKV, p_qkv, gs);
-      const bool kv_only = context_pass && l == L - 1 && finishes(p_kv);
       if (kv_only || finishes(p_qkv)) {
         flk::TileOut qo;
         qo.H = H;
@@ -424,8 +424,8 @@ int run_rows(flover_ctx* c, Lane& ln, const Row* rows, int n, bool want_tokens, 
         qo.vc = vl;
         qo.d = d;
         qo.Smax = f.max_seq;
-        if (l > 0) qo.norm = normed(w.ln1_g, w.ln1_b);
-        HIPCHK(c, flk::gemm_qkv(f.dtype, qo.norm.g ? (const void*)ln.x : ln.h, kv_only ? (char*)w.wqkv + flk::gemm_tiled_bytes(f.dtype, H, H) : w.wqkv,
+        qo.norm = norm1;
+        HIPCHK(c, flk::gemm_qkv(f.dtype, norm1.g ? (const void*)ln.x : ln.h, kv_only ? (char*)w.wqkv + flk::gemm_tiled_bytes(f.dtype, H, H) : w.wqkv,
                                 n, kv_only ? p_kv : p_qkv, qo, mtt, st, t.ev0, t.ev1));
         launches -= 1;
       } else {
@@ -434,7 +434,7 @@ int run_rows(flover_ctx* c, Lane& ln, const Row* rows, int n, bool want_tokens, 
                                 f.max_seq, st));
       }
     }
-    if (norms && l > 0) launches -= 1;
+    if (norm1.g) launches -= 1;
     if (context_pass && l == L - 1) {
       launches += 3;
       break;   // the pass exists to fill the cache: the last layer's K and V rows are written, nothing reads the rest
@@ -454,7 +454,8 @@ int run_rows(flover_ctx* c, Lane& ln, const Row* rows, int n, bool want_tokens, 
       HIPCHK(c, added ? flk::gemm_add(f.dtype, ln.att, w.wo, n, p_o, ln.x, w.bo, mtt, st, t.ev0, t.ev1)
                       : flk::gemm(f.dtype, ln.att, w.wo, n, p_o, ln.part, ss_h, mtt, st, t.ev0, t.ev1));
     }
-    if (!norms)
+    const flk::NormIn norm2 = normed(p_1, w.ln2_g, w.ln2_b);
+    if (!norm2.g)
       HIPCHK(c, flk::add_norm(f.dtype, !gpt, ln.x, added ? nullptr : ln.part, p_o.S, ss_h, p_o.ldc, added ? nullptr : w.bo, w.ln2_g, w.ln2_b,
                               ln.h, n, H, f.norm_eps, mtt, st));
     {
@@ -464,8 +465,8 @@ int run_rows(flover_ctx* c, Lane& ln, const Row* rows, int n, bool want_tokens, 
         HIPCHK(c, flk::gemm_gated(f.dtype, ln.h, w.w1, n, p_1, ln.act, ln.part, ss_1, mtt, st, t.ev0, t.ev1));
         if (!context_pass && n <= flk::gated_fused_rows(p_1)) launches -= 1;
       } else if (finishes(p_1) && (gpt || f.dtype == FLOVER_F32)) {     // an unpaired 16-bit gated layout has up far from gate
-        HIPCHK(c, flk::gemm_act(f.dtype, !gpt, norms ? (const void*)ln.x : ln.h, w.w1, n, p_1, ln.act, w.b1, mtt, st, t.ev0, t.ev1,
-                                normed(w.ln2_g, w.ln2_b)));
+        HIPCHK(c, flk::gemm_act(f.dtype, !gpt, norm2.g ? (const void*)ln.x : ln.h, w.w1, n, p_1, ln.act, w.b1, mtt, st, t.ev0, t.ev1,
+                                norm2));
         launches -= 1;
       } else {
         HIPCHK(c, flk::gemm(f.dtype, ln.h, w.w1, n, p_1, ln.part, ss_1, mtt, st, t.ev0, t.ev1));
@@ -478,22 +479,21 @@ int run_rows(flover_ctx* c, Lane& ln, const Row* rows, int n, bool want_tokens, 
       HIPCHK(c, added ? flk::gemm_add(f.dtype, ln.act, w.w2, n, p_2, ln.x, w.b2, mtt, st, t.ev0, t.ev1)
                       : flk::gemm(f.dtype, ln.act, w.w2, n, p_2, ln.part, ss_h, mtt, st, t.ev0, t.ev1));
     }
-    launches += 10 - (norms ? 1 : 0) - (!context_pass && n_items == n ? 1 : 0);     // one chunk per row: nothing to merge
+    launches += 10 - (norm2.g ? 1 : 0) - (!context_pass && n_items == n ? 1 : 0);     // one chunk per row: nothing to merge
   }
   if (want_tokens) {
-    flk::NormIn last;
-    if (norms) last = flk::NormIn{c->lnf_g, c->lnf_b, !gpt, f.norm_eps};
-    else
+    const flk::NormIn last = normed(c->p_lm, c->lnf_g, c->lnf_b);
+    if (!last.g)
       HIPCHK(c, flk::add_norm(f.dtype, !gpt, ln.x, added ? nullptr : ln.part, c->p_2.S, ss_h, c->p_2.ldc, added ? nullptr : c->lw[L - 1].b2,
                               c->lnf_g, c->lnf_b, ln.h, n, H, f.norm_eps, mtt, st));
     const GemmTimer t(c, ln, FLOVER_PROF_GEMM_LM, c->p_lm, gemm_iter);
-    HIPCHK(c, flk::gemm(f.dtype, norms ? (const void*)ln.x : ln.h, c->wlm, n, c->p_lm, ln.part, ss_v, mtt, st, t.ev0, t.ev1, last));
+    HIPCHK(c, flk::gemm(f.dtype, last.g ? (const void*)ln.x : ln.h, c->wlm, n, c->p_lm, ln.part, ss_v, mtt, st, t.ev0, t.ev1, last));
     const int ti = ln.tok_next;       // at most kStageRing - 1 iterations are outstanding, so this entry is free
     ln.tok_next = (ln.tok_next + 1) % kStageRing;
     if (ring_used) *ring_used = ti;
     HIPCHK(c, flk::logits_argmax(ln.part, c->p_lm.S, ss_v, c->p_lm.ldc, logits_out, ln.choice, ln.h_choice + (size_t)ti * R * parts, n, V, st));
     if (!wait) HIPCHK(c, hipEventRecord(ln.done[ti], st));
-    launches += norms ? 2 : 3;
+    launches += last.g ? 2 : 3;
   }
   if (wait) {
     HIPCHK(c, hipStreamSynchronize(st));

@@ -35,7 +35,7 @@ struct NormIn {
   bool rms = false;
   float eps = 0.f;
 };
-bool gemm_norms(int dtype, int M, int K);
+bool gemm_norms(int dtype, int M, const GemmPlan& p);
 // Where a GEMM that finishes the job leaves its result (the members its kind of epilogue uses).
 struct TileOut {
   float* part = nullptr;          // partial sums; or the residual stream [M][ldc] the result is added to

@@ -1523,7 +1523,7 @@ static hipError_t finish(int dtype, const void* x, const void* wt, const TileOut
     if (!o.norm.g) {
       launch(one ? gemm32_kernel<EPI, 1, 0> : gemm32_kernel<EPI, 4, 0>);
     } else if constexpr (EPI != EPI_ADD) {
-      if (!gemm_norms(dtype, M, p.K)) return hipErrorInvalidValue;
+      if (p.K > 1024) return hipErrorInvalidValue;
       if (o.norm.rms) launch(one ? gemm32_kernel<EPI, 1, 2> : gemm32_kernel<EPI, 4, 2>);
       else launch(one ? gemm32_kernel<EPI, 1, 1> : gemm32_kernel<EPI, 4, 1>);
     }
@@ -1540,10 +1540,15 @@ static hipError_t finish(int dtype, const void* x, const void* wt, const TileOut
   else dispatch_tile<DT_F16, EPI>(p.tile, x, wt, o, M, p, xmtt, st, ev0, ev1);
   return hipGetLastError();
 }
-// Every wave repeats the norm of its eight rows, so few rows gain (a launch of the small chain, 4 to 5 us) and many lose: two layers of
-// 256 columns, us per pass, norm apart -> inside: 16 rows 86 -> 73, 20 rows 126 -> 105, 70 rows 131 -> 146,
-// 155 rows 173 -> 202.
-bool gemm_norms(int dtype, int M, int K) { return dtype == DT_F32 && K <= 1024 && M <= 32; }
+// Every wave repeats the norm of its eight rows, and where a SIMD takes several waves their norms follow each other: inside pays while
+// that is less than the launch saved (3 us and the gap before it, 4 to 5 us of a chain).  us per launch, norm apart -> inside, by
+// blocks of four waves: rows of 256 columns (one 16-byte piece per lane), layer norm 256 blocks 3.4 -> 4.9, 512 3.7 -> 6.6, 768 4.0 ->
+// 8.2, 1000 4.0 -> 9.8, 6283 (an output projection of 50257) 11.6 -> 42.8, RMS 3.3 -> 4.2, 3.7 -> 5.6, 4.0 -> 7.0, 4.0 -> 7.6, 11.6 -> 32.9;
+// of 512 to 1024 columns, layer norm 256 blocks 4.7 -> 8.4, 384 6.1 -> 14.8, 1024 9.2 -> 27.2, RMS 4.6 -> 7.2, 6.0 -> 10.7, 9.8 -> 17.2.
+bool gemm_norms(int dtype, int M, const GemmPlan& p) {
+  const long blocks = (long)(((p.N + 1) / 2 + 3) / 4) * ((M + 7) / 8);      // of gemm32_kernel
+  return dtype == DT_F32 && p.K <= 1024 && M <= 32 && blocks <= (p.K <= 256 ? 512 : 256);
+}
 bool gemm_finishes(int dtype, const GemmPlan& p, int M) {
   return dtype == DT_F32 || takes_whole(p, M) || (M > 128 && p.S == 1 && p.tile >= 0);
 }

@@ -684,14 +684,42 @@ def test_a_row_is_the_same_at_every_count_of_row_tiles(make):
     srv.close()
 
 
+@pytest.mark.parametrize("make,inside", [
+    # launches of q|k|v (second layer), the MLP's input (both layers) and the output projection that take the norm, by rows
+    (lambda **k: dataclasses.replace(synth.tiny_gpt(**k), V=12288), {1: 3, 8: 3, 9: 3, 32: 3, 40: 0}),
+    (lambda **k: dataclasses.replace(synth.tiny_llama(synth.DT_F32, **k), F=4096), {1: 2, 8: 2, 32: 2, 40: 0}),
+    (lambda **k: dataclasses.replace(synth.tiny_gpt(**k), H=512, nh=8, F=2048, V=4096), {8: 3, 9: 0, 16: 0, 40: 0}),
+    (lambda **k: dataclasses.replace(synth.tiny_llama(synth.DT_F32, **k), H=1024, nh=16, F=512, V=1000), {8: 3, 16: 3, 17: 0, 32: 0, 40: 0})])
+def test_fp32_norm_inside_the_gemm_only_where_it_saves_time(make, inside):
+    """The norm is repeated by every wave of the GEMM that takes it, so matrices of many columns, or many rows, keep its launch (with it
+    inside, an output projection of 50257 x 768 took 316 us instead of 72 + 3); the same bits either way."""
+    import paper_2305_13484_amd as fl
+    cfg = make(C=40, S=40)
+    srv = fl.Flover(cfg, synth.make_weights(cfg, 61, "cuda"))
+    srv.kv_cache().normal_(generator=torch.Generator(device="cuda").manual_seed(62))
+    rng = np.random.default_rng(63)
+    lens, toks = rng.integers(0, cfg.S - 2, size=40), rng.integers(0, cfg.V, size=40)
+    full = apart = None
+    for n in sorted(inside, reverse=True):
+        for i in range(n):
+            assert srv.add_request_cached(i, int(lens[i]), int(toks[i]), 1) == i
+        out = srv.step(want_logits=True).logits.clone()
+        launches = srv.last_step_launches()
+        srv.reorder_evict()
+        full, apart = (out, launches) if full is None else (full, apart)
+        assert apart - launches == inside[n], (n, apart, launches)
+        assert torch.equal(out, full[:n]), n
+    srv.close()
+
+
 @pytest.mark.parametrize("make", [lambda **k: synth.tiny_gpt(**k), lambda **k: synth.tiny_llama(synth.DT_F32, **k),
                                   # rows of several rounds of loads, the last one ragged; too long for the norm inside the GEMM
                                   lambda **k: dataclasses.replace(synth.tiny_gpt(**k), H=768, nh=12, F=512),
                                   lambda **k: dataclasses.replace(synth.tiny_llama(synth.DT_F32, **k), H=1024, nh=16, F=512),
                                   lambda **k: dataclasses.replace(synth.tiny_llama(synth.DT_F32, **k), H=1280, nh=20, F=512)])
 def test_fp32_norm_inside_the_gemm_has_the_bits_of_the_launch_of_its_own(make):
-    """Up to 32 rows an fp32 iteration takes its norms inside the GEMMs, above that in launches of their own: the same bits on either
-    side and at every edge of the GEMM's eight rows; against 64 bits in the parity tests."""
+    """Up to 32 rows an fp32 iteration takes the norms ahead of narrow matrices inside the GEMMs, above that in launches of their own: the
+    same bits on either side and at every edge of the GEMM's eight rows; against 64 bits in the parity tests."""
     import paper_2305_13484_amd as fl
     cfg = make(C=40, S=40)
     srv = fl.Flover(cfg, synth.make_weights(cfg, 61, "cuda"))
