@@ -326,8 +326,10 @@ int32_t flover_k_gemm(int32_t dtype, const void* x, const void* w_tiled, int32_t
  * flover_k_gated_mlp streams that copy.  x [device][M][K] row-major (any alignment; fastest at 16 bytes);
  * act [device][M][F] row-major, model dtype, apart from x.
  * context_pass == 0, the fused iteration: a row's result depends on that row of x alone, not on M.  Up to 128 rows (64
- * when F > 16384) it is one launch; above that its two halves of K (four slices where F <= 4096) go through `workspace` as
- * partial sums and the activation is a second launch, with the same result bit for bit.
+ * when F > 16384) it is one launch; above that its two halves of K go through `workspace` as partial sums and the
+ * activation is a second launch, with the same result bit for bit.  Where F <= 4096 K is cut in four and one launch serves
+ * more rows too; `workspace` then takes the rows in another order, or the four slices where that is shorter (with less
+ * than flover_k_gated_workspace_bytes, but room for two slices, a slower way is taken).
  * context_pass != 0, the M rows of one request's pre-processing pass (Section V-B): K is sliced by M as well, as
  * flover_k_gemm_plan reports for context rows; with one slice and more than 128 rows the activation is the epilogue of
  * the contraction, otherwise partial sums and a second launch.

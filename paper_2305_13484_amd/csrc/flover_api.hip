@@ -229,7 +229,11 @@ size_t layout(flover_ctx* c, char* base) {
   const int chunks = (S + flk::kAttnChunk - 1) / flk::kAttnChunk;
   c->max_items = R * chunks;
   size_t pw = 0;
-  for (const flk::GemmPlan* p : {&c->p_qkv, &c->p_o, &c->p_1, &c->p_2, &c->p_lm}) pw = std::max(pw, (size_t)p->S * p->ldc);
+  for (const flk::GemmPlan* p : {&c->p_qkv, &c->p_o, &c->p_1, &c->p_2, &c->p_lm}) {
+    // the slices of a whole plan stay inside the GEMM; its context passes get the room of a plan that leaves them in memory
+    const int slices = !p->whole ? p->S : p->paired ? 2 : flk::gemm_plan(f.dtype, p->N, p->K).S;
+    pw = std::max(pw, (size_t)slices * p->ldc);
+  }
   c->act_off = align_up(b.off, 256);
   std::vector<Lane*> lanes{&c->step_lane};
   for (Lane& pl : c->prep_lanes) lanes.push_back(&pl);
@@ -463,7 +467,7 @@ int run_rows(flover_ctx* c, Lane& ln, const Row* rows, int n, bool want_tokens, 
       if (p_1.paired) {
         // gated 16-bit model: the activation is the epilogue of the gate|up contraction wherever that is one launch
         HIPCHK(c, flk::gemm_gated(f.dtype, ln.h, w.w1, n, p_1, ln.act, ln.part, ss_1, mtt, st, t.ev0, t.ev1));
-        if (!context_pass && n <= flk::gated_fused_rows(p_1)) launches -= 1;
+        if (!context_pass && (p_1.whole || n <= flk::gated_fused_rows(p_1))) launches -= 1;
       } else if (finishes(p_1) && (gpt || f.dtype == FLOVER_F32)) {     // an unpaired 16-bit gated layout has up far from gate
         HIPCHK(c, flk::gemm_act(f.dtype, !gpt, norm2.g ? (const void*)ln.x : ln.h, w.w1, n, p_1, ln.act, w.b1, mtt, st, t.ev0, t.ev1,
                                 norm2));
@@ -1597,9 +1601,12 @@ extern "C" int32_t flover_k_gated_mlp(int32_t dtype, const void* x, const void* 
   if (!x || !w_tiled || !act) return fail(nullptr, FLOVER_E_INVAL, "null argument");
   if (context_pass) p = flk::context_plan(p, dtype, M, 16);
   const size_t stride = (size_t)M * p.ldc;
-  const bool one_launch = (p.whole && M <= flk::kWholeRows) || (!p.whole && p.S == 2 && M <= flk::gated_fused_rows(p)) || (p.S == 1 && M > 128);
-  if (!one_launch && (!workspace || (size_t)p.S * stride * 4 > workspace_bytes))
+  // a whole plan's iteration can do without room, if slowly; above 128 rows two slices' are asked for, as for the other iterations
+  const bool whole = p.whole && p.tile < 0;
+  const bool one_launch = M <= flk::gated_fused_rows(p) ? whole || p.S == 2 : p.S == 1 && M > 128;
+  if (!one_launch && (!workspace || (size_t)(whole ? 2 : p.S) * stride * 4 > workspace_bytes))
     return fail(nullptr, FLOVER_E_NOMEM, "gated workspace too small");
-  HIPCHK(nullptr, flk::gemm_gated(dtype, x, w_tiled, M, p, act, (float*)workspace, stride, 0, (hipStream_t)stream));
+  HIPCHK(nullptr, flk::gemm_gated(dtype, x, w_tiled, M, p, act, (float*)workspace, stride, 0, (hipStream_t)stream, nullptr, nullptr,
+                                  workspace_bytes));
   return FLOVER_OK;
 }

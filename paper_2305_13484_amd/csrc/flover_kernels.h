@@ -17,7 +17,7 @@ struct GemmPlan {
   int ldc;    // row length of the partial-sum slices (N rounded up to 4)
   int tile = -1;    // more than 128 rows: which kernel (TILE_*), -1 = left to gemm()
   int paired = 0;   // gate|up of a gated MLP in paired 32-column groups (see gemm_plan_gated)
-  int whole = 0;    // up to kWholeRows rows one block takes all of K and finishes the job (see gemm_plan_finished)
+  int whole = 0;    // in a fused iteration one block takes all of K and finishes the job (see gemm_plan_finished)
 };
 constexpr int kWholeRows = 128;
 // kernels of more than 128 rows, by block shape: TILE_ROWS holds the weights in registers, the others copy both operands
@@ -26,7 +26,7 @@ enum { TILE_ROWS = 0, TILE_128X256 = 1, TILE_128X128 = 2, TILE_64X128 = 3, TILE_
 inline int part_ld(int N) { return (N + 3) / 4 * 4; }
 GemmPlan gemm_plan(int dtype, int N, int K);
 // The same for a matrix whose result a row-wise kernel would only finish (q|k|v, the input of an ungated MLP), which the GEMM does
-// itself up to kWholeRows rows where the shape makes that the shorter way.
+// itself in a fused iteration, and in a context pass of up to kWholeRows rows, where the shape makes that the shorter way.
 GemmPlan gemm_plan_finished(int dtype, int N, int K);
 GemmPlan gemm_plan_summed(int dtype, int N, int K);    // gemm_plan for a caller who wants the sum (gemm_sum)
 // The norm of the rows ahead of an fp32 contraction, taken in the GEMM's own launch (gemm_norms): x is then the residual stream.
@@ -62,7 +62,7 @@ size_t gemm_tiled_bytes(int dtype, int N, int K);
 GemmPlan context_plan(const GemmPlan& p, int dtype, int M, int max_slices);
 // Block of the kernel that gemm() takes for M > 128 rows (16-bit dtypes, operands on the 16-byte grid).
 void gemm_block(int M, const GemmPlan& p, int* rows, int* columns);
-// The contraction and what follows it in one launch: fp32 models always, 16-bit models up to kWholeRows rows where the plan says so
+// The contraction and what follows it in one launch: fp32 models always, 16-bit models in a fused iteration whose plan says so (whole)
 // and in a context pass whose plan takes K in one slice (gemm_finishes); otherwise the caller goes through gemm() and the row-wise kernel.  gemm_qkv: bias, rotary, q and
 // the cache rows (o: bias, rope, pos, slot, q, kc, vc, d, Smax, H, third).  gemm_add: res[M][N] += x . W^T + bias (bias may be null).
 // gemm_act: GELU of x . W^T + bias, or SwiGLU (16-bit: paired layout; fp32: up after gate).  x is read and the activation written
@@ -99,8 +99,9 @@ hipError_t gemm_sum(int dtype, const void* x, const void* w_tiled, int M, const 
 // rows up to which gemm_gated() is one launch for this plan: 128, or 64 for a matrix whose 128-column blocks outnumber the
 // compute units (it takes 16-wave blocks, whose hand-over space in LDS ends at four row tiles)
 inline int gated_fused_rows(const GemmPlan& p) { return p.whole ? kWholeRows : (p.N / 2 / 16 + 3) / 4 > 256 ? 64 : 128; }
+// A whole plan is one launch at any row count (see the definition for row-major rows); part then is scratch of `room` bytes.
 hipError_t gemm_gated(int dtype, const void* x, const void* w_tiled, int M, const GemmPlan& p, void* act, float* part,
-                      size_t slice_stride, int xmtt, hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+                      size_t slice_stride, int xmtt, hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr, size_t room = 0);
 
 // ---- row-wise kernels
 // A row's greedy choice is left in parts: the best logit of each part of the vocabulary and its column (kNoToken: none, a part

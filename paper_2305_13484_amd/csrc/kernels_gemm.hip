@@ -11,9 +11,9 @@
 //     a row block is the unit of work; up to 16 rows one wave takes it and reads the rows' operand straight from L2/L1
 //     (no LDS, no barriers); above that the rows' operand is staged through LDS once per block of 4 column groups and
 //     shared by the block's 4 or 8 waves.
-//   * matrices whose result a row-wise kernel would only finish (q|k|v, GELU input) and narrow gate|up matrices, K of moderate length,
-//     up to 128 rows: a block per 32 columns with all of K in it, the slices in its waves, the job finished by it
-//     (gemm16_whole_kernel).
+//   * matrices whose result a row-wise kernel would only finish (q|k|v, GELU input) and narrow gate|up matrices, K of moderate length:
+//     all of K in a block, the slices in its waves, the job finished by it; a block per 32 columns up to 128 rows
+//     (gemm16_whole_kernel), above that gemm16_parts_kernel.
 //   * more than 128 rows (context passes, very wide windows): the contraction turns MFMA- and operand-bound.  A wave keeps
 //     a 128 x 64 output tile and a block covers 256 rows x 256 columns (gemm16_rows_kernel), or, where such blocks would
 //     leave the chip idle, smaller blocks, either with both operands in LDS (gemm16_tile_kernel) or, in context passes of few blocks,
@@ -545,7 +545,7 @@ __device__ __forceinline__ void tile_epilogue(f32x4_t (&acc)[A][B], const TileOu
   }
 }
 
-// ---- up to 128 rows, K of moderate length: a block per column group (32 columns), all of K in one block, its S slices in the block's
+// ---- up to 128 rows, K of moderate length (more rows: gemm16_parts_kernel): a block per column group (32 columns), all of K in one block, its S slices in the block's
 // S waves, what follows the contraction as the epilogue -- no partial sums in memory and no launch that adds them up.  A wave is
 // the direct kernel's: weights and rows' operand straight to registers, PF k-blocks ahead, no barrier before the hand-over of the
 // sums through LDS.  They are added in slice order, so a row's bits are those of gemm() and the row-wise kernel behind it.
@@ -1282,10 +1282,10 @@ static void take_whole(GemmPlan& p) {
 }
 GemmPlan gemm_plan_finished(int dtype, int N, int K) {
   GemmPlan p = gemm_plan(dtype, N, K);
-  if (whole_shape(dtype, N, K) && N % 32 == 0 && K <= 2560) take_whole(p);
+  if (whole_shape(dtype, N, K) && N % 32 == 0 && K <= 2560 && p.KB % kWholeSlices == 0) take_whole(p);
   return p;
 }
-// Only where the plan has these very slices, so that nothing changes above kWholeRows rows.
+// Only where the plan has these very slices, so that nothing changes where gemm_adds_up() is false.
 GemmPlan gemm_plan_summed(int dtype, int N, int K) {
   GemmPlan p = gemm_plan(dtype, N, K);
   p.whole = whole_shape(dtype, N, K) && K <= 2560 && p.S == kWholeSlices && p.NT == 2;
@@ -1510,6 +1510,27 @@ static void dispatch_whole(const void* x, const void* wt, const TileOut& o, int 
   }
 }
 static bool takes_whole(const GemmPlan& p, int M) { return p.whole && M <= kWholeRows; }
+// Above kWholeRows rows of a fused iteration a block still takes all of K and finishes the job: gemm16_parts_kernel, whose four parts are
+// then the plan's slices (K is a multiple of four k-blocks), so that a row's bits are those of gemm16_whole_kernel.  The smallest block
+// whose blocks all run at once, else 128 x 128.  us, 64 x 64 / 64 x 128 / 128 x 128 and in brackets the two launches with two or three
+// slices in memory: 4096 x 2048 with SwiGLU at 160 rows (192 / 96 / 64 blocks) 10.6 / 15.6 / 20.6 [18.0], at 384 (384 / 192 / 96) 20.5 / 16.2 /
+// 22.1 [23.5], at 1000 42.3 / 32.6 / 24.2 [36.5]; 8192 x 2048 with GELU at 160 (384 / 192 / 128) 23.8 / 19.5 / 25.8 [26.6], at 512 48.2 /
+// 37.6 / 28.1 [44.0], at 1000 95.0 / 74.2 / 55.2 [77.8]; 6144 x 2048 q|k|v at 256 - / 19.0 / 25.6 [25.9], at 384 - / 29.0 / 25.3 [28.1], at 700 (288
+// blocks of 128 x 128, the one size found where it is not ahead) - / 45.7 / 42.4 [42.0], with the rotation 45.1 / 43.8 [41.4].
+static bool whole_window(const GemmPlan& p, int M) { return p.whole && M > kWholeRows && p.tile < 0; }
+static bool one_round(int tile, int M, const GemmPlan& p) { return tile_blocks(tile, M, p, 1) <= 256; }
+template <int DT, int EPI>
+static void dispatch_whole_window(const void* x, const void* wt, const TileOut& o, int M, const GemmPlan& p, int xmtt, hipStream_t st,
+                                  hipEvent_t ev0, hipEvent_t ev1) {
+  GemmPlan q = p;
+  q.S = 1;
+  q.kbs = q.KB;
+  if constexpr (EPI != EPI_QKV) {                // whose 128 columns hold the rotary partners
+    if (one_round(TILE_64X64, M, p)) return launch_parts<DT, 4, 2, 2, kWholeSlices, 4, 3, EPI>(x, wt, o, M, q, xmtt, st, ev0, ev1);
+  }
+  if (one_round(TILE_64X128, M, p)) launch_parts<DT, 4, 4, 2, kWholeSlices, 4, 4, EPI>(x, wt, o, M, q, xmtt, st, ev0, ev1);
+  else launch_parts<DT, 8, 4, 2, kWholeSlices, 4, 3, EPI>(x, wt, o, M, q, xmtt, st, ev0, ev1);
+}
 template <int EPI>
 static hipError_t finish(int dtype, const void* x, const void* wt, const TileOut& o, int M, const GemmPlan& p, int xmtt, hipStream_t st,
                          hipEvent_t ev0, hipEvent_t ev1) {
@@ -1535,6 +1556,14 @@ static hipError_t finish(int dtype, const void* x, const void* wt, const TileOut
       else dispatch_whole<DT_F16, EPI>(x, wt, o, M, p, xmtt, st, ev0, ev1);
       return hipGetLastError();
     }
+    if constexpr (EPI != EPI_PART) {
+      if (whole_window(p, M)) {
+        if (p.KB % kWholeSlices) return hipErrorInvalidValue;
+        if (dtype == DT_BF16) dispatch_whole_window<DT_BF16, EPI>(x, wt, o, M, p, xmtt, st, ev0, ev1);
+        else dispatch_whole_window<DT_F16, EPI>(x, wt, o, M, p, xmtt, st, ev0, ev1);
+        return hipGetLastError();
+      }
+    }
   }
   if (dtype == DT_BF16) dispatch_tile<DT_BF16, EPI>(p.tile, x, wt, o, M, p, xmtt, st, ev0, ev1);
   else dispatch_tile<DT_F16, EPI>(p.tile, x, wt, o, M, p, xmtt, st, ev0, ev1);
@@ -1550,7 +1579,7 @@ bool gemm_norms(int dtype, int M, const GemmPlan& p) {
   return dtype == DT_F32 && p.K <= 1024 && M <= 32 && blocks <= (p.K <= 256 ? 512 : 256);
 }
 bool gemm_finishes(int dtype, const GemmPlan& p, int M) {
-  return dtype == DT_F32 || takes_whole(p, M) || (M > 128 && p.S == 1 && p.tile >= 0);
+  return dtype == DT_F32 || takes_whole(p, M) || whole_window(p, M) || (M > 128 && p.S == 1 && p.tile >= 0);
 }
 
 hipError_t gemm_qkv(int dtype, const void* x, const void* wt, int M, const GemmPlan& p, const TileOut& o, int xmtt, hipStream_t st,
@@ -1649,18 +1678,46 @@ static void dispatch_gated(const void* x, const void* wt, void* act, int M, cons
   }
 }
 
-// The iteration's plan: up to gated_fused_rows(p) rows one launch; above that gemm() with the plan's K slices as partial sums
-// and the activation as its own launch -- the same chains, added in the same order, rounded once: bit-identical results.  (At 65-128 rows the x tile of a 128-column block weighs as much as its weights; the one
-// launch still measures 1.3 % faster per step there than the two: no partial sums, no second launch.)  A context
-// pass's plan: one slice -> the kernel that the plan names with the activation as its epilogue; any other slice count ->
+// Rows in fragment order (see xrow_index) from row-major ones that start at any element; rows past the last repeat it.  A block: a row
+// tile, four k-blocks.
+__global__ __launch_bounds__(256) void lay_rows_kernel(const uint16_t* __restrict__ x, u32x4_t* __restrict__ to, int M, int K, int KB, int mtt) {
+  const int lane = threadIdx.x & 63, mt = blockIdx.x, kb = blockIdx.y * 4 + (threadIdx.x >> 6);
+  if (kb >= KB) return;
+  const int m = min(mt * 16 + (lane & 15), M - 1);
+  to[((size_t)kb * mtt + mt) * 64 + lane] = *(const u32x4_any*)(x + (size_t)m * K + kb * 32 + (lane >> 4) * 8);
+}
+
+// The iteration's plan, up to gated_fused_rows(p) rows: one launch.  Above that gemm() with the plan's K slices as partial sums and the
+// activation as its own launch -- the same chains, added in the same order, rounded once: bit-identical results (at 65-128 rows the x
+// tile of a 128-column block weighs as much as its weights; the one launch still measures 1.3 % faster per step there than the two).
+// A whole plan is one launch there too; rows of an operation-level call, which are row-major, make its copies slow (half a cache line
+// each, and none at all off the 16-byte grid), so with room for it
+//   * where the blocks are one round and K is long the two launches stay (us, two -> one: 2048 x 6656 at 129 / 512 / 1000 rows 17 / 29 / 40
+//     -> 34 / 36 / 48, 8192 x 4096 at 160 30.8 -> 32.7);
+//   * where they are more, and off the grid, the rows are laid out in fragment order first (8192 x 4096 at 512 / 1000 rows, two launches /
+//     one / laid out first 59 / 56 / 43 and 108 / 102 / 78; 8192 x 1536 at 1000 71 / 50 / 43; off the grid, two launches -> laid out: 2048 x
+//     6656 at 129 rows 38 -> 25, 2752 x 512 at 160 16 -> 11.5).
+// A context pass's plan: one slice -> the kernel that the plan names with the activation as its epilogue; any other slice count ->
 // gemm() and the activation launch.
 hipError_t gemm_gated(int dtype, const void* x, const void* wt, int M, const GemmPlan& p, void* act, float* part,
-                      size_t slice_stride, int xmtt, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
+                      size_t slice_stride, int xmtt, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1, size_t room) {
   if (M <= 0) return hipSuccess;
   if (!p.paired || dtype == DT_F32) return hipErrorInvalidValue;
-  if (takes_whole(p, M) || (gemm_finishes(dtype, p, M) && aligned16(x, wt))) return gemm_act(dtype, true, x, wt, M, p, act, nullptr, xmtt, st, ev0, ev1);
-  if (gemm_finishes(dtype, p, M)) {      // one slice, but rows that cannot be copied to LDS: the iteration's launches, which need no
-    const GemmPlan it = gemm_plan_gated(dtype, p.N / 2, p.K);                               // partial sums either
+  const bool grid16 = aligned16(x, wt), window = whole_window(p, M) && xmtt == 0, fits = part && room >= (size_t)p.S * slice_stride * 4;
+  const bool rounds = window && !one_round(TILE_64X128, M, p);
+  const int mtt = (M + 15) / 16;
+  if (window && (rounds || !grid16) && aligned16(part, wt) && part && room >= (size_t)mtt * 1024 * p.KB) {
+    lay_rows_kernel<<<dim3(mtt, (p.KB + 3) / 4), 256, 0, st>>>((const uint16_t*)x, (u32x4_t*)part, M, p.K, p.KB, mtt);
+    TileOut o;
+    o.act = act;
+    o.F = p.N / 2;
+    return finish<EPI_GATED>(dtype, part, wt, o, M, p, mtt, st, ev0, ev1);
+  }
+  const bool apart = window && fits && (!grid16 || (p.K > 2560 && !rounds));
+  if (!apart && (takes_whole(p, M) || (gemm_finishes(dtype, p, M) && grid16)))
+    return gemm_act(dtype, true, x, wt, M, p, act, nullptr, xmtt, st, ev0, ev1);
+  if (!apart && gemm_finishes(dtype, p, M)) {      // rows that cannot be copied to LDS: the iteration's launches, which need no
+    const GemmPlan it = gemm_plan_gated(dtype, p.N / 2, p.K);                                         // partial sums either
     for (int m = 0; m < M; m += gated_fused_rows(it)) {
       const hipError_t e = gemm_gated(dtype, (const uint16_t*)x + (size_t)m * p.K, wt, std::min(M - m, gated_fused_rows(it)), it,
                                       (uint16_t*)act + (size_t)m * (p.N / 2), nullptr, 0, 0, st);
@@ -1668,7 +1725,7 @@ hipError_t gemm_gated(int dtype, const void* x, const void* wt, int M, const Gem
     }
     return hipSuccess;
   }
-  if (p.whole || M > gated_fused_rows(p) || p.S != 2) {
+  if (M > gated_fused_rows(p) || p.S != 2) {
     hipError_t e = gemm(dtype, x, wt, M, p, part, slice_stride, xmtt, st, ev0, nullptr);   // timed from the first launch's
     if (e != hipSuccess) return e;                                                       // start to the second's end
     return activation(dtype, true, part, p.S, slice_stride, p.ldc, nullptr, act, M, p.N / 2, xmtt, st, true, ev1);

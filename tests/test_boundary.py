@@ -2,6 +2,7 @@
 import ctypes
 import os
 import re
+import types
 
 import numpy as np
 import pytest
@@ -134,6 +135,18 @@ def test_gated_mlp_workspace_sizes_host_only():
     assert lib.flover_k_gated_workspace_bytes(2, 65, 17920, 6656, ctypes.byref(n)) == 0 and n.value >= 2 * 65 * 35840 * 4
     assert lib.flover_k_gated_workspace_bytes(2, 8, 48, 512, ctypes.byref(n)) == -1      # F not a multiple of 32
     assert lib.flover_k_gated_workspace_bytes(0, 8, 64, 512, ctypes.byref(n)) == -1      # fp32
+
+
+@pytest.mark.parametrize("arch,H,nh,d,F", [(1, 1536, 12, 128, 4096), (1, 512, 4, 128, 1376), (0, 2048, 16, 128, 8192)])
+def test_arena_room_of_the_partial_sums(arch, H, nh, d, F):
+    """The arena holds the partial sums of flover_k_gemm's plans, and two slices of a paired gate|up matrix: where an iteration finishes a
+    matrix in one launch its four slices stay inside the launch and take no room."""
+    cfg = types.SimpleNamespace(arch=arch, dtype=2, L=1, H=H, nh=nh, d=d, F=F, V=64, S=64, C=4, eos_id=-1, ln_eps=1e-5, rope_theta=1e4)
+    sums = max([fl.binding.k_gemm_plan(2, N, K)[0] * N for N, K in ((3 * H, H), (H, H), (H, F), (64, H))] +
+               [2 * 2 * F if arch else fl.binding.k_gemm_plan(2, F, H)[0] * F])
+    weights = 2 * (4 * H * H + (3 if arch else 2) * H * F + (2 if arch else 3) * 64 * H)
+    rows = 1024 * (4 * H + 3 * 2 * H + 2 * F + 4 * sums + nh * (d + 2) * 4) + 2 * 2 * 4 * nh * 64 * d
+    assert 0 <= fl.arena_bytes(cfg) - weights - rows <= 1 << 20
 
 
 def test_bench_refuses_more_than_one_gpu():

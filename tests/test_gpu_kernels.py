@@ -531,3 +531,36 @@ def test_copy_probe_copies():
     fl.k_copy_probe(dst, src)
     torch.cuda.synchronize()
     assert torch.equal(dst, src)
+
+
+@pytest.mark.parametrize("dtype,M,F,K", [(synth.DT_BF16, 129, 1376, 512), (synth.DT_F16, 515, 1376, 512), (synth.DT_BF16, 1000, 1376, 512),
+                                         (synth.DT_F16, 260, 4096, 1536), (synth.DT_BF16, 300, 320, 3072), (synth.DT_F16, 530, 4064, 3072)])
+def test_gated_windows_of_more_than_128_rows(dtype, M, F, K):
+    """Rows of a fused iteration with narrow gate|up matrices: every block above 128 rows, rows on and off the 16-byte grid, with the room
+    that flover_k_gated_workspace_bytes names, the room of two slices and no less; the bits of calls of at most 128 rows."""
+    import paper_2305_13484_amd as fl
+    lib = fl.load_library()
+    g = torch.Generator(device="cuda").manual_seed(M + F)
+    x = torch.randn((M, K), generator=g, device="cuda").to(TDT[dtype])
+    w = [(torch.randn((F, K), generator=g, device="cuda") * 0.05).to(TDT[dtype]) for _ in range(2)]
+    gw = fl.binding.GatedWeight(*w)
+    ref = torch.cat([fl.binding.k_gated_mlp(x[m:m + 100].contiguous(), gw) for m in range(0, M, 100)])
+    xd = x.double()
+    exact = torch.nn.functional.silu(xd @ w[0].double().T) * (xd @ w[1].double().T)
+    assert float((ref.double() - exact).norm() / exact.norm()) <= (6e-3 if dtype == synth.DT_BF16 else 8e-4)
+    n = C.c_uint64()
+    assert lib.flover_k_gated_workspace_bytes(dtype, M, F, K, C.byref(n)) == 0
+    two = 2 * M * 2 * F * 4
+    assert n.value >= two
+    for at in (0, 1):
+        rows = _at_element(x, at)
+        for room in (int(n.value), two, two - 1):
+            ws = torch.full((int(n.value) + 256,), 7, dtype=torch.uint8, device="cuda")
+            out = torch.full((M * F + 64,), 3.0, dtype=x.dtype, device="cuda")
+            rc = lib.flover_k_gated_mlp(dtype, rows.data_ptr(), gw.buf.data_ptr(), M, F, K, 0, out.data_ptr(), ws.data_ptr(), room,
+                                        torch.cuda.current_stream().cuda_stream)
+            assert rc == (0 if room >= two else -3)
+            torch.cuda.synchronize()
+            if rc == 0:
+                assert torch.equal(out[:M * F].view(M, F), ref), (at, room)
+                assert bool((ws[room:] == 7).all()) and bool((out[M * F:] == 3.0).all())

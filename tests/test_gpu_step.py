@@ -633,7 +633,10 @@ def test_more_than_128_live_rows():
                                   lambda **k: synth.small_llama16(synth.DT_F16, **k), lambda **k: synth.tiny_gpt(**k),
                                   # rows longer than a norm block's first pass over them
                                   lambda **k: dataclasses.replace(synth.small_llama16(synth.DT_BF16, **k), H=4608, nh=36, F=512),
-                                  lambda **k: dataclasses.replace(synth.small_gpt16(synth.DT_F16, **k), H=4608, nh=36, F=512)])
+                                  lambda **k: dataclasses.replace(synth.small_gpt16(synth.DT_F16, **k), H=4608, nh=36, F=512),
+                                  # q|k|v and the MLP's input in one launch at every row count: each of the blocks above 128 rows, both heads
+                                  lambda **k: dataclasses.replace(synth.small_llama16(synth.DT_BF16, **k), H=1536, nh=12, F=1024),
+                                  lambda **k: dataclasses.replace(synth.small_gpt16(synth.DT_F16, **k), H=1536, nh=24, d=64, F=6144)])
 def test_a_row_among_600_live_ones_is_the_row_alone(make):
     """A request's logits are the same bits in a window of 600, of 130 and by itself: every kernel of the iteration, at every
     choice that it makes by the number of live rows."""
@@ -665,8 +668,8 @@ def test_a_row_among_600_live_ones_is_the_row_alone(make):
                                   lambda **k: dataclasses.replace(synth.small_gpt16(synth.DT_BF16, **k), H=1280, nh=20, d=64, F=672),
                                   lambda **k: dataclasses.replace(synth.small_gpt16(synth.DT_F16, **k), H=2816, nh=44, d=64, F=512)])
 def test_a_row_is_the_same_at_every_count_of_row_tiles(make):
-    """q|k|v with the rotation and the append, and the MLP's input with its activation, are one launch up to 128 rows (one variant per
-    count of 16-row tiles) and two above: the same bits on either side of every edge."""
+    """q|k|v with the rotation and the append, and the MLP's input with its activation, are one launch of one kernel up to 128 rows (one
+    variant per count of 16-row tiles) and of another above: the same bits on either side of every edge."""
     import paper_2305_13484_amd as fl
     cfg = make(C=140, S=40)
     srv = fl.Flover(cfg, synth.make_weights(cfg, 51, "cuda"))
