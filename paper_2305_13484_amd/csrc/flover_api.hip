@@ -1547,7 +1547,7 @@ extern "C" int32_t flover_k_gemm(int32_t dtype, const void* x, const void* w_til
   hipStream_t st = (hipStream_t)stream;
   // one launch, whose own stores are the result, unless they would fall on what its other blocks still read (y may share memory
   // with x)
-  const bool direct = y && flk::gemm_adds_up(dtype, p, M) && !overlap(y, (size_t)M * N * 4, x, (size_t)M * K * esize(dtype)) &&
+  const bool direct = y && flk::gemm_adds_up(dtype, p, M, x) && !overlap(y, (size_t)M * N * 4, x, (size_t)M * K * esize(dtype)) &&
                       !overlap(y, (size_t)M * N * 4, w_tiled, flk::gemm_tiled_bytes(dtype, N, K));
   if (direct) {
     HIPCHK(nullptr, flk::gemm_sum(dtype, x, w_tiled, M, p, y, N, st));

@@ -90,7 +90,7 @@ hipError_t gemm(int dtype, const void* x, const void* w_tiled, int M, const Gemm
                 const NormIn& norm = NormIn());
 // y[M][ldy] = x . W^T, rows row-major and y at any float, where one launch leaves the whole sum (gemm_adds_up): one slice, or a
 // gemm_plan_summed that says so; the bits of gemm()'s slices added in order.
-bool gemm_adds_up(int dtype, const GemmPlan& p, int M);
+bool gemm_adds_up(int dtype, const GemmPlan& p, int M, const void* x);
 hipError_t gemm_sum(int dtype, const void* x, const void* w_tiled, int M, const GemmPlan& p, float* y, int ldy, hipStream_t st);
 // act[M][F] = silu(x . Wgate^T) * (x . Wup^T) rounded to the model dtype, for a paired plan (16-bit dtypes); x and act
 // are both row-major (xmtt == 0) or both in fragment order with xmtt row tiles per k-block; reads the rows gemm() reads.

@@ -1495,18 +1495,23 @@ static void launch_whole(const void* x, const void* wt, const TileOut& o, int M,
   launch_timed(gemm16_whole_kernel<DT, MT, kWholeSlices, MT <= 3 ? 4 : 2, EPI>, dim3((p.N + 31) / 32), dim3(64 * kWholeSlices), st, ev0, ev1,
                (const uint16_t*)x, (const u32x4_t*)wt, o, M, p.N, p.KB, p.kbs, xmtt);
 }
+constexpr int kSumRows = 64;
 template <int DT, int EPI>
 static void dispatch_whole(const void* x, const void* wt, const TileOut& o, int M, const GemmPlan& p, int xmtt, hipStream_t st,
                            hipEvent_t ev0, hipEvent_t ev1) {
   switch ((M + 15) / 16) {
-    case 1: launch_whole<DT, EPI, 1>(x, wt, o, M, p, xmtt, st, ev0, ev1); break;
-    case 2: launch_whole<DT, EPI, 2>(x, wt, o, M, p, xmtt, st, ev0, ev1); break;
-    case 3: launch_whole<DT, EPI, 3>(x, wt, o, M, p, xmtt, st, ev0, ev1); break;
-    case 4: launch_whole<DT, EPI, 4>(x, wt, o, M, p, xmtt, st, ev0, ev1); break;
-    case 5: launch_whole<DT, EPI, 5>(x, wt, o, M, p, xmtt, st, ev0, ev1); break;
-    case 6: launch_whole<DT, EPI, 6>(x, wt, o, M, p, xmtt, st, ev0, ev1); break;
-    case 7: launch_whole<DT, EPI, 7>(x, wt, o, M, p, xmtt, st, ev0, ev1); break;
-    default: launch_whole<DT, EPI, 8>(x, wt, o, M, p, xmtt, st, ev0, ev1);
+    case 1: return launch_whole<DT, EPI, 1>(x, wt, o, M, p, xmtt, st, ev0, ev1);
+    case 2: return launch_whole<DT, EPI, 2>(x, wt, o, M, p, xmtt, st, ev0, ev1);
+    case 3: return launch_whole<DT, EPI, 3>(x, wt, o, M, p, xmtt, st, ev0, ev1);
+    case 4: return launch_whole<DT, EPI, 4>(x, wt, o, M, p, xmtt, st, ev0, ev1);
+  }
+  if constexpr (EPI != EPI_PART) {               // sums: up to kSumRows rows
+    switch ((M + 15) / 16) {
+      case 5: return launch_whole<DT, EPI, 5>(x, wt, o, M, p, xmtt, st, ev0, ev1);
+      case 6: return launch_whole<DT, EPI, 6>(x, wt, o, M, p, xmtt, st, ev0, ev1);
+      case 7: return launch_whole<DT, EPI, 7>(x, wt, o, M, p, xmtt, st, ev0, ev1);
+      default: return launch_whole<DT, EPI, 8>(x, wt, o, M, p, xmtt, st, ev0, ev1);
+    }
   }
 }
 static bool takes_whole(const GemmPlan& p, int M) { return p.whole && M <= kWholeRows; }
@@ -1735,13 +1740,17 @@ hipError_t gemm_gated(int dtype, const void* x, const void* wt, int M, const Gem
   return hipGetLastError();
 }
 
-// Row-major rows are read 64 bytes at a time: above 64 rows, where every block of 32 columns reads them all, two launches are shorter
-// (us per call, two launches -> one: 1536 x 512 at 23 rows 24.1 -> 21.8, 3071 x 1024 at 60 rows 26.4 -> 26.0, 4607 x 1536 at 101 rows
-// 32.3 -> 33.8).
-bool gemm_adds_up(int dtype, const GemmPlan& p, int M) { return p.S == 1 || (dtype != DT_F32 && p.whole && M <= 64); }
+// Every block of 32 columns reads all rows, row-major, 64 bytes at a time: one launch while the rows are few (us per call, two launches ->
+// one, at 17 / 32 / 64 rows: 1536 x 512 10.7 -> 7.4 / 7.5 / 7.6, 4224 x 1024 10.9 / 10.6 / 10.6 -> 7.4 / 7.4 / 9.2, 4480 x 1536 10.7 / 10.8 / 11.7 ->
+// 7.4 / 8.7 / 12.5, 4864 x 2048 10.8 / 10.8 / 12.9 -> 7.9 / 10.6 / 14.1, 4160 x 2560 10.8 / 11.1 / 14.0 -> 9.7 / 13.1 / 19.1).  Rows off the 16-byte
+// grid take several times as long to load: up to 16 rows 10 to 17 -> 8 to 15, at 17 rows 10.8 -> 14.6 (4864 x 2048).
+bool gemm_adds_up(int dtype, const GemmPlan& p, int M, const void* x) {
+  const bool few = M <= 16 || (M <= kSumRows && (long)M * p.K <= 60000 && ((uintptr_t)x & 15) == 0);
+  return p.S == 1 || (dtype != DT_F32 && p.whole && few);
+}
 hipError_t gemm_sum(int dtype, const void* x, const void* wt, int M, const GemmPlan& p, float* y, int ldy, hipStream_t st) {
   if (M <= 0) return hipSuccess;
-  if (!gemm_adds_up(dtype, p, M)) return hipErrorInvalidValue;
+  if (!gemm_adds_up(dtype, p, M, x)) return hipErrorInvalidValue;
   TileOut o;
   o.part = y;
   o.ldc = ldy;

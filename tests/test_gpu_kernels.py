@@ -564,3 +564,34 @@ def test_gated_windows_of_more_than_128_rows(dtype, M, F, K):
             if rc == 0:
                 assert torch.equal(out[:M * F].view(M, F), ref), (at, room)
                 assert bool((ws[room:] == 7).all()) and bool((out[M * F:] == 3.0).all())
+
+
+@pytest.mark.parametrize("dtype", [synth.DT_BF16, synth.DT_F16])
+@pytest.mark.parametrize("N,K", [(1617, 608), (3071, 1024), (7000, 2560), (64, 512)])
+def test_gemm_sums_in_one_launch_have_the_bits_of_two(dtype, N, K):
+    """Four slices of K, the last one shorter at 608, rows that end inside a group of four columns: one launch up to the row counts where it
+    is the shorter way and two above, rows on and off the 16-byte grid, y at any float.  A row's bits do not depend on the call; the bound
+    is that of the other GEMM tests."""
+    import paper_2305_13484_amd as fl
+    lib = fl.load_library()
+    assert fl.binding.k_gemm_plan(dtype, N, K)[0] == 4
+    g = torch.Generator(device="cuda").manual_seed(N)
+    x = torch.randn((65, K), generator=g, device="cuda").to(TDT[dtype])
+    W = (torch.randn((N, K), generator=g, device="cuda") * 0.05).to(TDT[dtype])
+    tw = fl.binding.TiledWeight(W)
+    full = fl.k_gemm(x, tw)
+    xd, Wd = x.double(), W.double()
+    assert torch.all((full.double() - xd @ Wd.T).abs() <= 4e-6 * (xd.abs() @ Wd.abs().T) + 1e-30)
+    n = C.c_uint64()
+    assert lib.flover_k_gemm_workspace_bytes(dtype, 65, N, K, C.byref(n)) == 0
+    ws = torch.empty(int(n.value), dtype=torch.uint8, device="cuda")
+    for M in sorted({1, 16, 17, 33, 60000 // K, 60000 // K + 1, 64} & set(range(1, 65))):
+        for at in (0, 1):
+            rows = _at_element(x[:M], at)
+            for y_at in range(4):
+                y = torch.full((M * N + 8,), 3.0, device="cuda")
+                assert lib.flover_k_gemm(dtype, rows.data_ptr(), tw.buf.data_ptr(), M, N, K, y[y_at:].data_ptr(), ws.data_ptr(), ws.numel(),
+                                         torch.cuda.current_stream().cuda_stream) == 0
+                torch.cuda.synchronize()
+                assert torch.equal(y[y_at:y_at + M * N].view(M, N), full[:M]), (M, at, y_at)
+                assert bool((y[:y_at] == 3.0).all()) and bool((y[y_at + M * N:] == 3.0).all())
