@@ -130,15 +130,18 @@ def test_gemm_of_more_than_128_rows_each_block_and_group_width(dtype, group, blo
 @pytest.mark.parametrize("dtype", [synth.DT_BF16, synth.DT_F16])
 def test_gemm_of_256_row_blocks_with_three_k_blocks_in_the_last_turn(dtype):
     """The weight ring turns four k-blocks at a time; slices of 4n + 3 read row copies in the last turn that only that turn's own
-    waits cover.  Bound as above."""
+    waits cover.  Every row of the three row blocks, the last one of a single live row tile: the bits of calls of at most 128 rows,
+    which another kernel serves, and the bound as above."""
     M, N, K = 513, 4096, 2336
     assert fl.binding.k_gemm_block(dtype, N, K, M)[1:] == (256, 256) and fl.binding.k_gemm_plan(dtype, N, K)[1] % 4 == 3
     g = torch.Generator(device="cuda").manual_seed(4)
     x = torch.randn((M, K), generator=g, device="cuda").to(TDT[dtype])
-    tw = fl.binding.TiledWeight((torch.randn((N, K), generator=g, device="cuda") * 0.05).to(TDT[dtype]))
-    part = fl.k_gemm(x[:100].contiguous(), tw)
+    W = (torch.randn((N, K), generator=g, device="cuda") * 0.05).to(TDT[dtype])
+    tw = fl.binding.TiledWeight(W)
     got = fl.k_gemm(x, tw)
-    assert torch.equal(got[:100], part)
+    assert torch.equal(got, torch.cat([fl.k_gemm(x[m:m + 128].contiguous(), tw) for m in range(0, M, 128)]))
+    xd, Wd = x.double(), W.double()
+    assert torch.all((got.double() - xd @ Wd.T).abs() <= 4e-6 * (xd.abs() @ Wd.abs().T) + 1e-30)
 
 
 def _at_element(t, at):
