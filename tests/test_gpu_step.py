@@ -599,12 +599,42 @@ def test_context_pass_of_hundreds_of_rows_against_64_bits(model, dtype, rows, bl
     torch.cuda.empty_cache()
 
 
-@pytest.mark.parametrize("model,dtype,rows", [("gpt_1p3b", "f16", 138), ("gpt_1p3b", "bf16", 287), ("gpt_1p3b", "f16", 436),
-                                              ("llama_7b", "bf16", 130), ("llama_7b", "f16", 200)])
-def test_context_pass_with_k_in_parts_against_64_bits(model, dtype, rows):
+# as above, for q|k|v, its k|v columns alone (the last layer's), out, the MLP's input and its output; * where K goes in parts: every block but
+# 128 x 128 and 256 x 256 whose slices have 32 k-blocks or more, the narrower ones while they are at most 256 blocks
+PARTS_CONTEXTS = [
+    (("gpt_1p3b",), "f16", 138, "64x128/1*, 64x64/1*, 64x64/4, 64x128/1*, 64x128/5*"),
+    (("gpt_1p3b",), "bf16", 287, "64x128/1*, 64x128/1*, 64x64/1*, 128x128/1, 64x128/3*"),
+    (("gpt_1p3b",), "f16", 436, "128x128/1, 64x128/1*, 64x64/1*, 128x128/1, 128x128/4"),
+    (("llama_7b",), "bf16", 130, "128x128/1, 128x128/2, 128x128/4, 128x256/1*, 128x128/4"),
+    (("llama_7b",), "f16", 200, "128x128/1, 128x128/2, 64x128/2*, 128x256/1*, 128x128/4"),
+    # gate|up in the narrower blocks; slices of 35 k-blocks in four parts, and of 57 in two
+    (("llama", 1024, 8, 128, 1280, 512, 1e-6), "bf16", 129, "64x64/1*, 64x64/1*, 64x64/4, 64x64/1*, 64x64/4"),
+    (("llama", 1024, 16, 64, 3520, 512, 1e-6), "f16", 129, "64x64/1*, 64x64/1*, 64x64/4, 64x128/1*, 64x64/5"),
+    (("gpt", 512, 8, 64, 1120, 512, 1e-5), "bf16", 500, "64x64/1, 64x64/1, 64x64/1, 64x64/1, 64x64/1*"),
+    (("gpt", 2816, 44, 64, 9120, 512, 1e-5), "f16", 500, "128x256/1*, 128x128/1, 64x128/1*, 128x256/1*, 128x256/5*"),
+]
+
+
+@pytest.mark.parametrize("model,dtype,rows,blocks", PARTS_CONTEXTS)
+def test_context_pass_with_k_in_parts_against_64_bits(model, dtype, rows, blocks, monkeypatch):
     """The blocks that cut K among their waves, each with the epilogues it serves (q|k|v, residual add with and without bias, GELU, SwiGLU,
-    slices), at row counts whose blocks all run at once; row by row, bound as above."""
-    case = {"kind": "context", "model": model, "dtype": dtype, "layers": 2, "rows": 1, "slots": 2, "max_seq": 512, "len_lo": rows + 1,
+    slices); the blocks and slices that a shape takes are asserted, so that a new rule cannot leave one out unnoticed.  Row by row, bound
+    as above."""
+    import paper_2305_13484_amd as fl
+    name = model[0]
+    if len(model) > 1:
+        name = "shape"
+        monkeypatch.setitem(perf_cases.MODELS, name, model)
+    arch, H, _, _, F, _, _ = perf_cases.MODELS[name]
+    took = []
+    for N, K in [(3 * H, H), (2 * H, H), (H, H), (2 * F if arch == "llama" else F, H), (H, F)]:
+        _, bm, bn = fl.binding.k_gemm_block(2, N, K, rows, True)
+        slices, per = fl.binding.k_gemm_plan(2, N, K, rows)
+        launched = -(-rows // bm) * -(-N // bn) * slices
+        parts = (bm, bn) not in ((128, 128), (256, 256)) and K // 32 - (slices - 1) * per >= 32 and (bn == 256 or launched <= 256)
+        took.append("%dx%d/%d%s" % (bm, bn, slices, "*" if parts else ""))
+    assert ", ".join(took) == blocks
+    case = {"kind": "context", "model": name, "dtype": dtype, "layers": 2, "rows": 1, "slots": 2, "max_seq": 512, "len_lo": rows + 1,
             "len_hi": rows + 1, "overlap": False}
     state = perf_cases.prepare(case, 6)
     got, = perf_cases.run(state)
