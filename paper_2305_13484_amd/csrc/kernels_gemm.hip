@@ -1350,7 +1350,8 @@ static double tile_cost(int tile, int M, const GemmPlan& p, int S, int kbs) {
 // Kernel and slice count of a context pass's GEMM: the pair with the least time, counting what the result costs the next
 // kernel as well -- fp32 sums read back (4 TB/s) and a launch of its own, unless the kernel takes K in one slice and finishes the
 // job in its epilogue.  Priced as if every one-slice kernel did (an unpaired gate|up matrix does not), and with the blocks in
-// the table (q|k|v takes 128 columns where 64 are picked).
+// the table (q|k|v takes 128 columns where 64 are picked).  The table's figures are those of both operands through LDS; what
+// parts_pay() launches in parts takes less than its price, so another block or more slices may be picked where it would be shorter.
 GemmPlan context_plan(const GemmPlan& p, int dtype, int M, int max_slices) {
   GemmPlan q = p;
   if (dtype == DT_F32 || M <= 128) return q;
@@ -1457,7 +1458,6 @@ static void launch_parts(const void* x, const void* wt, const TileOut& o, int M,
   launch_timed(gemm16_parts_kernel<DT, A, B, WC, WK, PF, L, EPI>, dim3(per * 8), dim3(64 * WC * WK), st, ev0, ev1, (const uint16_t*)x,
                (const u32x4_t*)wt, o, M, p.N, p.K, p.Npad / 16, p.NT, p.KB, p.kbs, ncb, nrb, tasks, per, xmtt);
 }
-// 64-column blocks do not hold the rotary partners of a 128-wide head: that epilogue takes 128 columns instead
 // Whether a context pass's GEMM takes K in parts inside the block; the windows' slices are single chains, so they never do.
 // us per launch, cold weights, both operands through LDS -> in parts: 64 x 64 blocks 2048 x 2048 at 287 / 436 rows (160 / 224 blocks) 11.3 /
 // 11.5 -> 8.0 / 8.5, 4096 x 4096 at 138 (192) 28.6 -> 16.6, 2048 x 2048 at 943 (480 blocks, which share the compute units) 15.1 -> 17.4;
@@ -1467,9 +1467,11 @@ static bool parts_pay(int tile, int M, const GemmPlan& p) {
   if (p.tile < 0 || tile == TILE_128X128 || p.KB - (p.S - 1) * p.kbs < 32) return false;
   return tile == TILE_128X256 || tile_blocks(tile, M, p, p.S) <= 256;
 }
+// 64-column blocks do not hold the rotary partners of a 128-wide head: that epilogue takes 128 columns instead
 template <int DT, int EPI>
 static void dispatch_tile(int tile, const void* x, const void* wt, const TileOut& o, int M, const GemmPlan& p, int xmtt, hipStream_t st,
                           hipEvent_t ev0, hipEvent_t ev1) {
+  if (EPI == EPI_QKV && tile == TILE_64X64) tile = TILE_64X128;
   if (tile == TILE_ROWS) {
     if (p.NT == 4) {
       if constexpr (EPI != EPI_GATED) launch_rows<DT, 4, EPI>(x, wt, o, M, p, xmtt, st, ev0, ev1);   // paired layouts have NT = 2
@@ -1479,12 +1481,12 @@ static void dispatch_tile(int tile, const void* x, const void* wt, const TileOut
   }
   else if (parts_pay(tile, M, p)) {
     if (tile == TILE_128X256) launch_parts<DT, 8, 4, 4, 2, 4, 4, EPI>(x, wt, o, M, p, xmtt, st, ev0, ev1);
-    else if (tile == TILE_64X128 || EPI == EPI_QKV) launch_parts<DT, 4, 4, 2, 4, 4, 4, EPI>(x, wt, o, M, p, xmtt, st, ev0, ev1);
+    else if (tile == TILE_64X128) launch_parts<DT, 4, 4, 2, 4, 4, 4, EPI>(x, wt, o, M, p, xmtt, st, ev0, ev1);
     else if constexpr (EPI != EPI_QKV) launch_parts<DT, 4, 2, 2, 4, 4, 3, EPI>(x, wt, o, M, p, xmtt, st, ev0, ev1);
   }
   else if (tile == TILE_128X256) launch_tile<DT, 4, 4, 2, 4, 4, EPI>(x, wt, o, M, p, xmtt, st, ev0, ev1);
   else if (tile == TILE_128X128) launch_tile<DT, 2, 4, 4, 2, 4, EPI>(x, wt, o, M, p, xmtt, st, ev0, ev1);
-  else if (tile == TILE_64X128 || EPI == EPI_QKV) launch_tile<DT, 2, 4, 2, 2, 4, EPI>(x, wt, o, M, p, xmtt, st, ev0, ev1);
+  else if (tile == TILE_64X128) launch_tile<DT, 2, 4, 2, 2, 4, EPI>(x, wt, o, M, p, xmtt, st, ev0, ev1);
   else if constexpr (EPI != EPI_QKV) launch_tile<DT, 2, 2, 2, 2, 4, EPI>(x, wt, o, M, p, xmtt, st, ev0, ev1);
 }
 // The whole-K kernel per count of row tiles; four k-blocks ahead, two where the rows' operand would take too many registers (eight
