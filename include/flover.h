@@ -300,15 +300,16 @@ int32_t flover_k_compact(void* cache, int32_t L, int32_t C, int32_t n_head, int3
  * with x; workspace holds the split-K partial sums.  K % 32 == 0.  y == NULL leaves the result as partial sums in the
  * workspace (timing the streaming kernel alone). */
 int32_t flover_k_gemm_tiled_bytes(int32_t dtype, int32_t N, int32_t K, uint64_t* out);
-/* [host only] K slicing of the weight GEMM: *slices partial sums, each over *k_blocks_per_slice blocks of 32 input
- * features (the last slice may be shorter).  context_rows == 0: the fused iteration's slicing, a function of (dtype, N,
- * K) alone, so that a row's result cannot depend on how many rows are live; context_rows > 0: the slicing of a
- * pre-processing pass of that many rows of one request (at most 16 slices; a context may use fewer when its
- * partial-sum buffer, sized for the iteration, holds fewer at that row count). */
+/* [host only] K slicing of flover_k_gemm: *slices partial sums, each over *k_blocks_per_slice blocks of 32 input
+ * features (the last slice may be shorter).  context_rows == 0: rows of a fused iteration, a function of (dtype, N,
+ * K) alone, so that a row's result cannot depend on how many rows are live (q|k|v and the input of an ungated MLP of a
+ * 16-bit model, with hidden sizes of 512 to 2560 and at most 8192 columns, take four slices inside one launch instead);
+ * context_rows > 0: the slicing of a pre-processing pass of that many rows of one request (at most 16 slices; a context
+ * may use fewer when its partial-sum buffer, sized for the iteration, holds fewer at that row count). */
 int32_t flover_k_gemm_plan(int32_t dtype, int32_t N, int32_t K, int32_t context_rows, int32_t* slices,
                            int32_t* k_blocks_per_slice);
 /* [host only] The kernel that serves a 16-bit weight GEMM of more than 128 rows (INVAL otherwise): columns of the weight
- * layout's groups, rows and columns of a block's output tile.  context_pass == 0: rows of a fused iteration (the result
+ * layout's groups, rows and columns of a block's output tile.  context_pass == 0: rows of flover_k_gemm (the result
  * does not depend on the block); != 0: of one request's pre-processing pass (its q|k|v takes 128 columns for 64). */
 int32_t flover_k_gemm_block(int32_t dtype, int32_t N, int32_t K, int32_t rows, int32_t context_pass,
                             int32_t* group_columns, int32_t* block_rows, int32_t* block_columns);
@@ -330,9 +331,9 @@ int32_t flover_k_gemm(int32_t dtype, const void* x, const void* w_tiled, int32_t
  * activation is a second launch, with the same result bit for bit.  Where F <= 4096 K is cut in four and one launch serves
  * more rows too; `workspace` then takes the rows in another order, or the four slices where that is shorter (with less
  * than flover_k_gated_workspace_bytes, but room for two slices, a slower way is taken).
- * context_pass != 0, the M rows of one request's pre-processing pass (Section V-B): K is sliced by M as well, as
- * flover_k_gemm_plan reports for context rows; with one slice and more than 128 rows the activation is the epilogue of
- * the contraction, otherwise partial sums and a second launch.
+ * context_pass != 0, the M rows of one request's pre-processing pass (Section V-B): up to 128 rows as in the iteration;
+ * above that K is sliced by M as well, as flover_k_gemm_plan reports for context rows, and with one slice the activation
+ * is the epilogue of the contraction, otherwise partial sums and a second launch.
  * workspace [device], flover_k_gated_workspace_bytes bytes (0 where one launch serves the fused iteration); NOMEM if
  * it is needed and smaller. */
 int32_t flover_k_gated_retile(int32_t dtype, const void* Wgate, const void* Wup, int32_t F, int32_t K, void* w_tiled,
