@@ -1465,8 +1465,14 @@ static void launch_parts(const void* x, const void* wt, const TileOut& o, int M,
 // 780 (192 / 336) 56.0 / 112 -> 52.9 / 104; 128 x 128 gains nothing (6144 x 2048 at 436 22.7 -> 22.4) and loses on short slices.
 // Two overlapped passes share the compute units: with at most 240 blocks in parts two of 200 and 230 rows, GPT-1.3B shape, six layers, take 566
 // us instead of 627 (7B shape, four layers, 932 for 943), but one after the other 1011 instead of 952; weighed as in context_plan, level.
-static bool parts_pay(int tile, int M, const GemmPlan& p) {
-  if (p.tile < 0 || tile == TILE_128X128 || p.KB - (p.S - 1) * p.kbs < 32) return false;
+// Row-major rows of an operation-level call come half a cache line at a time and every part fetches its own: gate|up, F x K at rows, LDS -> parts,
+// us per call: 64 x 64 blocks 640 x 6656 at 287 35.3 -> 38.2, 1280 x 1024 at 200 26.2 -> 28.0; 64 x 128 3520 x 1024 at 129 28.6 -> 30.7; 128 x 256
+// 14400 x 2048 at 256 62.3 -> 66.1, 4800 x 3584 at 640 69.2 -> 71.6, 11200 x 5632 at 200 111 -> 114, but long chains gain from 256 rows on:
+// 11200 x 4608 at 256 111 -> 108, 14400 x 4608 at 640 267 -> 256, 17920 x 6656 at 300 254 -> 244.
+static bool parts_pay(int tile, int M, const GemmPlan& p, bool row_major) {
+  const int last = p.KB - (p.S - 1) * p.kbs;
+  if (p.tile < 0 || tile == TILE_128X128 || last < 32) return false;
+  if (row_major) return tile == TILE_128X256 && M >= 256 && last >= 144;
   return tile == TILE_128X256 || tile_blocks(tile, M, p, p.S) <= 256;
 }
 // 64-column blocks do not hold the rotary partners of a 128-wide head: that epilogue takes 128 columns instead
@@ -1481,7 +1487,7 @@ static void dispatch_tile(int tile, const void* x, const void* wt, const TileOut
       launch_rows<DT, 2, EPI>(x, wt, o, M, p, xmtt, st, ev0, ev1);
     }
   }
-  else if (parts_pay(tile, M, p)) {
+  else if (parts_pay(tile, M, p, xmtt == 0)) {
     if (tile == TILE_128X256) launch_parts<DT, 8, 4, 4, 2, 4, 4, EPI>(x, wt, o, M, p, xmtt, st, ev0, ev1);
     else if (tile == TILE_64X128) launch_parts<DT, 4, 4, 2, 4, 4, 4, EPI>(x, wt, o, M, p, xmtt, st, ev0, ev1);
     else if constexpr (EPI != EPI_QKV) launch_parts<DT, 4, 2, 2, 4, 4, 3, EPI>(x, wt, o, M, p, xmtt, st, ev0, ev1);
