@@ -305,7 +305,7 @@ def run_c2(a):
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None, "dtype": "bf16", "data": "synthetic",
         "config": {"workload": "c2: decode-attention + reorder micro-benchmark, 256 live, 32 heads, head_dim 128, KV length "
                                "U{1..4096}, 10% finish per step at seeded indices, refilled to 256", "seed": a.seed},
-        "roofline": {"bound": "hbm", "kernel": "attn_partial_kernel", "achieved": round(ach, 1), "peak": HBM_PEAK_GBS,
+        "roofline": {"bound": "hbm", "kernel": "attn_row_kernel", "achieved": round(ach, 1), "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": round(ach / HBM_PEAK_GBS, 4), "traffic": None, "launches": att["launches"],
                      "avg_launch_us": round(1e3 * att["ms"] / att["launches"], 2),
                      "avg_bytes_per_launch": att["bytes"] // att["launches"]},
@@ -460,12 +460,12 @@ def main():
     att = prof["attention"]
     roof = None
     # the committed byte counters were taken on this workload (first 200 steps, see profiles/); not on the others
-    traffic = committed_traffic("attn_partial_kernel") if (a.workload == "c4" and not a.layers and not a.requests) else None
+    traffic = committed_traffic("attn_row_kernel") if (a.workload == "c4" and not a.layers and not a.requests) else None
     # the counters' bytes per launch belong beside `achieved` only when this run covers the window they were taken on
     same_window = bool(traffic) and a.cached_context and a.steps == 200 and a.warmup == 0
     if att["launches"]:
         ach = att["bytes"] / (att["ms"] * 1e-3) / 1e9
-        roof = {"bound": "hbm", "kernel": "attn_partial_kernel (ragged decode attention, one launch per layer)",
+        roof = {"bound": "hbm", "kernel": "attn_row_kernel (ragged decode attention, one launch per layer)",
                 "achieved": round(ach, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(ach / HBM_PEAK_GBS, 4),
                 "traffic": traffic["bytes_per_launch"] if same_window else None,
                 "traffic_ratio": (traffic or {}).get("ratio"), "traffic_window": (traffic or {}).get("window"),

@@ -64,6 +64,7 @@ struct Lane {
   flk::RowIn* h_rows[kStageRing] = {nullptr, nullptr, nullptr, nullptr};
   hipEvent_t staged[kStageRing] = {nullptr, nullptr, nullptr, nullptr};   // h_rows[i] has been read
   bool staged_busy[kStageRing] = {false, false, false, false};
+  std::vector<int> len;     // lengths of an iteration's rows, and their places in `list`
   int ring = 1, next = 0;
   int tok_next = 0;         // ring of token buffers: advanced only by passes that return tokens
   flk::Choice* h_choice = nullptr;   // [kStageRing][rows_cap][parts]
@@ -344,11 +345,15 @@ int run_rows(flover_ctx* c, Lane& ln, const Row* rows, int n, bool want_tokens, 
   flk::RowOut ro = ln.rows;
   ro.block_rows = context_pass ? flk::kPrefillQB : 0;
   int n_list = 0;
+  int most = 0;             // chunks of the longest row
+  ln.len.resize((size_t)2 * n);
   int64_t attn_bytes = 0;   // K and V rows [0,len) of every row, all heads: what one attention launch has to read
   for (int i = 0; i < n; ++i) {
     attn_bytes += (int64_t)(rows[i].pos + 1) * 2 * H * esize(f.dtype);
+    most = std::max(most, (rows[i].pos + flk::kAttnChunk) / flk::kAttnChunk);
     const bool enters = !context_pass || (f.dtype == FLOVER_F32 && i % flk::kPrefillQB == 0);
     hr[i] = flk::RowIn{rows[i].tok, rows[i].pos, rows[i].slot, enters ? n_list : -1};
+    ln.len[i] = rows[i].pos + 1;
     if (enters) {
       const int last = context_pass ? std::min(i + flk::kPrefillQB, n) - 1 : i;
       n_list += (rows[last].pos + flk::kAttnChunk) / flk::kAttnChunk;
@@ -356,7 +361,13 @@ int run_rows(flover_ctx* c, Lane& ln, const Row* rows, int n, bool want_tokens, 
   }
   const int n_items = context_pass ? 0 : n_list;
   const int *d_pos = ro.pos, *d_slot = ro.slot;
-  flk::AttnWork aw{ro.list, d_slot, ro.len, ln.pml, ln.po, n_items, (f.max_seq + flk::kAttnChunk - 1) / flk::kAttnChunk};
+  flk::AttnWork aw{ro.list, d_slot, ro.len, ln.pml, ln.po, n_items, (f.max_seq + flk::kAttnChunk - 1) / flk::kAttnChunk, most};
+  aw.by_rows = !context_pass && flk::attention_by_rows(f.dtype, d, aw, n, nh);
+  if (aw.by_rows) {
+    flk::longest_first(ln.len.data(), n, ln.len.data() + n);
+    for (int i = 0; i < n; ++i) hr[i].first = ln.len[n + i];
+    ro.block_rows = flk::kEntryPerRow;
+  }
   aw.blocks = ro.list;
   aw.n_blocks = context_pass ? n_list : 0;
   // what feeds a GEMM (norm output, attention output, MLP activation) is written in the order the GEMM's MFMA reads
@@ -483,7 +494,7 @@ int run_rows(flover_ctx* c, Lane& ln, const Row* rows, int n, bool want_tokens, 
       HIPCHK(c, added ? flk::gemm_add(f.dtype, ln.act, w.w2, n, p_2, ln.x, w.b2, mtt, st, t.ev0, t.ev1)
                       : flk::gemm(f.dtype, ln.act, w.w2, n, p_2, ln.part, ss_h, mtt, st, t.ev0, t.ev1));
     }
-    launches += 10 - (norm2.g ? 1 : 0) - (!context_pass && n_items == n ? 1 : 0);     // one chunk per row: nothing to merge
+    launches += 10 - (norm2.g ? 1 : 0) - (!context_pass && !flk::attention_merges(aw, n) ? 1 : 0);
   }
   if (want_tokens) {
     const flk::NormIn last = normed(c->p_lm, c->lnf_g, c->lnf_b);
@@ -1292,18 +1303,22 @@ int32_t flover_k_decode_attention(int32_t dtype, const void* q, const void* kcac
   char* ws = (char*)workspace;
   const int maxch = (max_len + flk::kAttnChunk - 1) / flk::kAttnChunk;
   flk::AttnWork aw{(const int4*)(ws + o_items), (const int*)ws, (const int*)ws + M, (float*)(ws + o_pml), (float*)(ws + o_po), 0,
-                   maxch};
+                   maxch, maxch};
+  aw.merge_last = attn_out_overlaps(dtype, q, kcache, vcache, M, C, nh, d, S, out);
   flk::AttnRows rows;
   std::vector<int> hs, items;
   if (M <= flk::kAttnRows) {
     aw.n_items = attn_rows(slot, len, M, &rows);
     aw.rows = &rows;
+    aw.by_rows = flk::attention_by_rows(dtype, d, aw, M, nh);
   } else {                                  // slot[M] | len[M] and the (row, chunk, slot, len) work list
+    for (int i = 0; i < M; ++i) aw.n_items += (len[i] + flk::kAttnChunk - 1) / flk::kAttnChunk;
+    aw.by_rows = flk::attention_by_rows(dtype, d, aw, M, nh);
     hs.resize((size_t)2 * M);
     for (int i = 0; i < M; ++i) {
       hs[i] = slot[i];
       hs[M + i] = len[i];
-      const int nc = (len[i] + flk::kAttnChunk - 1) / flk::kAttnChunk;
+      const int nc = aw.by_rows ? 0 : (len[i] + flk::kAttnChunk - 1) / flk::kAttnChunk;
       for (int ch = 0; ch < nc; ++ch) {
         items.push_back(i);
         items.push_back(ch);
@@ -1311,12 +1326,22 @@ int32_t flover_k_decode_attention(int32_t dtype, const void* q, const void* kcac
         items.push_back(len[i]);
       }
     }
+    if (aw.by_rows) {
+      std::vector<int> place((size_t)M);
+      flk::longest_first(len, M, place.data());
+      items.resize((size_t)4 * M);
+      for (int i = 0; i < M; ++i) {
+        int* e = &items[(size_t)4 * place[i]];
+        e[0] = i;
+        e[1] = 0;
+        e[2] = slot[i];
+        e[3] = len[i];
+      }
+    }
     HIPCHK(nullptr, hipMemcpyAsync(ws, hs.data(), (size_t)2 * M * 4, hipMemcpyHostToDevice, st));
     HIPCHK(nullptr, hipMemcpyAsync(ws + o_items, items.data(), items.size() * 4, hipMemcpyHostToDevice, st));
     HIPCHK(nullptr, hipStreamSynchronize(st));
-    aw.n_items = (int)items.size() / 4;
   }
-  aw.merge_last = attn_out_overlaps(dtype, q, kcache, vcache, M, C, nh, d, S, out);
   HIPCHK(nullptr, flk::decode_attention(dtype, d, q, kcache, vcache, aw, M, nh, S, out, st));
   return FLOVER_OK;
 }
@@ -1387,9 +1412,10 @@ int32_t flover_k_decode_attention_noalloc(int32_t dtype, const void* q, const vo
   if (rc != FLOVER_OK) return rc;
   char* ws = (char*)base;
   // every part of the scratch this call reads is written first by this call's own kernels: nothing has to start at zero
-  flk::AttnWork aw{nullptr, nullptr, nullptr, (float*)(ws + o_pml), (float*)(ws + o_po), n_items,
-                   (max_len + flk::kAttnChunk - 1) / flk::kAttnChunk};
+  const int most = (max_len + flk::kAttnChunk - 1) / flk::kAttnChunk;
+  flk::AttnWork aw{nullptr, nullptr, nullptr, (float*)(ws + o_pml), (float*)(ws + o_po), n_items, most, most};
   aw.rows = &rows;
+  aw.chunk_grid = true;        // and not by_rows: a caller that captures the call finds the launches that it always had
   aw.merge_last = attn_out_overlaps(dtype, q, kcache, vcache, M, C, nh, d, S, out);
   HIPCHK(nullptr, flk::decode_attention(dtype, d, q, kcache, vcache, aw, M, nh, S, out, (hipStream_t)stream));
   return FLOVER_OK;

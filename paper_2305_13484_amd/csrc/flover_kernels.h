@@ -127,9 +127,11 @@ struct alignas(16) RowIn {
 struct RowOut {            // device memory
   int *pos, *slot, *len;   // [rows]; len = pos + 1, the rows of cache attended to
   int4* list;              // one entry per chunk of kAttnChunk positions: (row, chunk, slot, len), or where block_rows > 0 (row, rows
-                           // of the block, chunk, -) for each block of consecutive positions, entered by its first row
+                           // of the block, chunk, -) for each block of consecutive positions, entered by its first row, or with
+                           // kEntryPerRow (row, 0, slot, len)
   int block_rows;
 };
+constexpr int kEntryPerRow = -1;
 // x = embedding of the rows (wpe: learned positions, may be null), h = the norm of it.  tok < 0: the token is the best of
 // the previous iteration's choices for its row -1 - tok.
 hipError_t embed_norm(int dtype, bool rms, const void* wte, const void* wpe, const RowIn* rows, const RowOut& out, const Choice* prev,
@@ -156,16 +158,19 @@ struct alignas(16) AttnRows {   // row descriptors of an operation-level call, p
   int32_t slot[kAttnRows], len[kAttnRows];
 };
 struct AttnWork {          // device pointers unless stated
-  const int4* items;       // [n_items] (row, chunk, slot of the row, cache rows of the row)
+  const int4* items;       // [n_items] (row, chunk, slot of the row, cache rows of the row); by_rows: [M] (row, 0, slot, cache rows)
   const int* row_slot;     // [M]
   const int* row_len;      // [M] rows of cache attended to (>= 1)
   float* pml;              // [M][maxch][nh][2]: (m, l) of chunk ch of row r at ((r * maxch + ch) * nh + head)
   float* po;               // [M][maxch][nh][d]
   int n_items;
   int maxch;               // chunk slots per row in pml / po: at least ceil(longest row / kAttnChunk)
+  int most;                // chunks of the longest row
   const int4* blocks = nullptr;   // pre-processing passes of fp32 models: (first row, rows <= kPrefillQB, chunk, -)
   int n_blocks = 0;
   const AttnRows* rows = nullptr;   // [host] set: the rows' descriptors (at most kAttnRows rows), instead of items and row_len
+  bool by_rows = false;           // a block takes a whole (row, head): what attention_by_rows() says of the rest of this struct
+  bool chunk_grid = false;        // blocks of four heads of a chunk, and the merge a launch of its own, whatever is shorter
   bool merge_last = false;        // the output shares memory with q or the caches: written by a launch of its own
   int out_mtt = 0;                // layout of the attention output: 0 row-major, else fragment order (see add_norm)
 };
@@ -174,6 +179,12 @@ constexpr int kPrefillQB = 8;     // query rows one wave serves in a pre-process
 hipError_t decode_attention(int dtype, int d, const void* q, const void* kc, const void* vc, const AttnWork& w, int M,
                             int nh, int Smax, void* out, hipStream_t st, hipEvent_t ev0 = nullptr,
                             hipEvent_t ev1 = nullptr);
+
+// Whether a block should take a whole (row, head) with all its chunks; then place[i] of longest_first() is where row i goes in `items`.
+bool attention_by_rows(int dtype, int d, const AttnWork& w, int M, int nh);
+void longest_first(const int* len, int M, int* place);
+// Whether decode_attention() launches a merge behind the streaming kernel.
+bool attention_merges(const AttnWork& w, int M);
 
 // Attention of a pre-processing pass: all M rows are consecutive positions of one slot (fp32: as listed in w.blocks, through
 // the partial results; 16-bit: w.items, blocks, pml and po are not used).

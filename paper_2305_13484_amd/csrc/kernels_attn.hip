@@ -11,9 +11,11 @@
 //   * work is flattened to (row, chunk) x head so a launch has thousands of similar wave tasks however ragged the
 //     lengths are: a row of len positions has ceil(len / CHUNK) chunks of equal length (no short remainder task, which
 //     would leave the memory system under-used while the full-length tasks finish); chunking depends on the
-//     request's own length only, and a second tiny kernel merges a row's chunks in chunk order (results never depend
-//     on other rows); where every row of a launch has one chunk, the first kernel writes the output itself.
+//     request's own length only, and a row's chunks are merged in chunk order (results never depend on other rows): by a
+//     second tiny kernel, or, where it is the shorter way, by the block that has taken all of them (attn_row_kernel);
+//     where every row of a launch has one chunk, the first kernel writes the output itself.
 // Context passes of 16-bit models take the matrix cores instead (attn_context_kernel).
+#include <algorithm>
 #include <type_traits>
 
 #include "flover_dev.h"
@@ -26,6 +28,124 @@ __device__ __forceinline__ float sum_over(float v, int d) { return d == 8 ? v + 
 __device__ __forceinline__ float max_over(float v, int d) { return d == 8 ? fmaxf(v, __shfl_xor(v, 8, 64)) : d == 16 ? max_partner<16>(v) : max_partner<32>(v); }
 
 __device__ __forceinline__ int chunks_of(int len) { return ((unsigned)len + kAttnChunk - 1) / kAttnChunk; }
+
+// A wave's share of one (row, head): cache rows [j0, j1), every cache row on LPR lanes, RPW rows per load, the lane groups merged at
+// the end.
+template <int DT, int D, int U>
+struct AttnWave {
+  static constexpr int EB = (DT == DT_F32) ? 4 : 2;
+  static constexpr int EPL = 16 / EB;          // elements per lane
+  static constexpr int LPR = D / EPL;          // lanes per row
+  static constexpr int RPW = 64 / LPR;         // rows per wave load
+  static constexpr int STEP = RPW * U;
+  const char *kb, *vb;                         // this lane's piece of cache row 0
+  int j1, grp;
+  float qf[EPL], m, l, o[EPL];
+
+  __device__ __forceinline__ void start(const void* kc, const void* vc, size_t head_off, int j1_, int lane) {
+    const size_t off = head_off + (size_t)(lane % LPR) * 16;
+    kb = (const char*)kc + off;
+    vb = (const char*)vc + off;
+    j1 = j1_;
+    grp = lane / LPR;
+    m = -INFINITY;
+    l = 0.f;
+#pragma unroll
+    for (int e = 0; e < EPL; ++e) o[e] = 0.f;
+  }
+  __device__ __forceinline__ void query(const u32x4_t& qr, float scale) {
+    unpack16<DT>(qr, qf);
+#pragma unroll
+    for (int e = 0; e < EPL; ++e) qf[e] *= scale;
+  }
+  __device__ __forceinline__ void load(u32x4_t* kr, u32x4_t* vr, int jb) const {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int r = min(jb + u * RPW + grp, j1 - 1);      // clamp: stays inside the request's valid rows
+      kr[u] = __builtin_nontemporal_load((const u32x4_t*)(kb + (size_t)r * D * EB));
+      vr[u] = __builtin_nontemporal_load((const u32x4_t*)(vb + (size_t)r * D * EB));
+    }
+  }
+  __device__ __forceinline__ void consume(const u32x4_t* kr, const u32x4_t* vr, int jb) {
+    float s[U];
+    float tmax = -INFINITY;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      float kf[EPL];
+      unpack16<DT>(kr[u], kf);
+      float d0 = 0.f;
+#pragma unroll
+      for (int e = 0; e < EPL; ++e) d0 = fmaf(qf[e], kf[e], d0);
+      d0 = group_sum<LPR>(d0);
+      s[u] = (jb + u * RPW + grp < j1) ? d0 : -INFINITY;
+      tmax = fmaxf(tmax, s[u]);
+    }
+    const float mn = fmaxf(m, tmax);
+    const float ms = (mn == -INFINITY) ? 0.f : mn;       // a group that has seen no valid row yet
+    const float alpha = __expf(m - ms);                  // m = -inf -> 0
+    l *= alpha;
+#pragma unroll
+    for (int e = 0; e < EPL; ++e) o[e] *= alpha;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const float p = __expf(s[u] - ms);
+      l += p;
+      float vf[EPL];
+      unpack16<DT>(vr[u], vf);
+#pragma unroll
+      for (int e = 0; e < EPL; ++e) o[e] = fmaf(p, vf[e], o[e]);
+    }
+    m = mn;
+  }
+  // Rows [j0, j1), whose first STEP are already under way in krA, vrA.  Two register buffers: the loads of the next rows are in flight
+  // while the current ones are consumed.  Steady state without branches (the compiler's wait counts for the in-order memory counter
+  // collapse to "wait for everything" around a branch, which would make consuming one buffer wait for the other's loads too); the
+  // loads past the chunk re-read its last row.
+  __device__ __forceinline__ void rows(u32x4_t (&krA)[U], u32x4_t (&vrA)[U], int j0) {
+    u32x4_t krB[U], vrB[U];
+    int jb = j0;
+    for (; jb + 2 * STEP <= j1; jb += 2 * STEP) {
+      load(krB, vrB, jb + STEP);
+      __builtin_amdgcn_sched_barrier(0);
+      consume(krA, vrA, jb);
+      load(krA, vrA, jb + 2 * STEP);
+      __builtin_amdgcn_sched_barrier(0);
+      consume(krB, vrB, jb + STEP);
+    }
+    if (jb < j1) {                                         // one or two steps left (wave-uniform)
+      const bool two = jb + STEP < j1;
+      if (two) load(krB, vrB, jb + STEP);
+      consume(krA, vrA, jb);
+      if (two) consume(krB, vrB, jb + STEP);
+    }
+  }
+  // merge the RPW lane groups (lanes with equal lane % LPR): butterfly over the group index bits
+  __device__ __forceinline__ void merge_groups() {
+    if constexpr (RPW > 1) {
+      float mt = m;
+#pragma unroll
+      for (int dlt = LPR; dlt < 64; dlt <<= 1) mt = max_over(mt, dlt);
+      const float w = (m == -INFINITY) ? 0.f : __expf(m - mt);
+      l *= w;
+#pragma unroll
+      for (int e = 0; e < EPL; ++e) o[e] *= w;
+#pragma unroll
+      for (int dlt = LPR; dlt < 64; dlt <<= 1) {
+        l = sum_over(l, dlt);
+#pragma unroll
+        for (int e = 0; e < EPL; ++e) o[e] = sum_over(o[e], dlt);
+      }
+      m = mt;
+    }
+  }
+};
+
+// A chunk's share of the merged row, w = exp(its maximum - the row's).
+__device__ __forceinline__ void add_chunk(float& l, f32x4_t& o, float w, float lc, const f32x4_t& oc) {
+  l = fmaf(w, lc, l);
+#pragma unroll
+  for (int e = 0; e < 4; ++e) o[e] = fmaf(w, oc[e], o[e]);
+}
 
 // Where a launch's work comes from, in either case row by row, one item per chunk: a list in device memory (the fused
 // iteration, and operation-level calls of more than 256 rows), or the rows' descriptors as a kernel argument (no copy to the
@@ -72,127 +192,48 @@ struct RowList {
   }
   __device__ int len(int row) const { return r.len[row]; }
 };
+struct RowOrder {             // rows as an argument, in the order of the blocks
+  AttnRows r;
+  int32_t row[kAttnRows];
+  __device__ int4 at(int b) const { return make_int4(row[b], 0, r.slot[b], r.len[b]); }
+};
 
-// grid = (items, n_head / 4), block = 256: wave w handles head blockIdx.y * 4 + w of item blockIdx.x = (row, chunk, slot,
-// len).  Writes the unnormalised partial (m, l, o[D]) of (row, chunk, head) at index (row * maxch + chunk) * n_head + head:
+// A wave takes one head of one item (row, chunk, slot, len).  side_by_side: grid = (n_head, items), block = 64, the heads of an item side by
+// side, so that every XCD gets its share of a long row and every compute unit of few waves; otherwise grid = (items, n_head / 4), block = 256,
+// wave w with head blockIdx.y * 4 + w (see wave_blocks).
+// Writes the unnormalised partial (m, l, o[D]) of (row, chunk, head) at index (row * maxch + chunk) * n_head + head:
 // the place depends on the row and the chunk alone, so the merge kernel finds a row's partials without looking anything up.
 // ONE: no row of the launch has a second chunk, so the wave normalises and writes the output itself (what the merge kernel
 // does with one chunk, bit for bit) and there is no merge launch.
 template <int DT, int D, int U, bool ONE, class Src>
 __global__ __launch_bounds__(256) void attn_partial_kernel(const void* __restrict__ q, const void* __restrict__ kc,
-                                                           const void* __restrict__ vc, Src src, int nh,
+                                                           const void* __restrict__ vc, Src src, int nh, int side_by_side,
                                                            int Smax, int maxch,
                                                            float scale, float* __restrict__ pml, float* __restrict__ po,
                                                            void* __restrict__ out, int mtt) {
-  constexpr int EB = (DT == DT_F32) ? 4 : 2;
-  constexpr int EPL = 16 / EB;          // elements per lane
-  constexpr int LPR = D / EPL;          // lanes per row
-  constexpr int RPW = 64 / LPR;         // rows per wave load
+  typedef AttnWave<DT, D, U> Wave;
+  constexpr int EPL = Wave::EPL, LPR = Wave::LPR;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int item = blockIdx.x;
-  const int hd = blockIdx.y * 4 + wave;
+  const int item = side_by_side ? blockIdx.y : blockIdx.x;
+  const int hd = side_by_side ? blockIdx.x : blockIdx.y * 4 + wave;
   const int4 it = src.at(item);         // one load: the cache addresses below depend on nothing else
   const int row = it.x, ch = it.y, slot = it.z, len = it.w;
   // the row's ceil(len / kAttnChunk) chunks are made equally long, so that no wave task of a row is a short remainder
   const int nch = chunks_of(len);
   const int cr = (len + nch - 1) / nch;
   const int j0 = ch * cr, j1 = min(len, j0 + cr);
-  const int grp = lane / LPR, li = lane % LPR;
+  const int li = lane % LPR;
 
-  float qf[EPL];
-  {
-    const u32x4_t qr = *(const u32x4_t*)((const char*)q + ((size_t)(row * nh + hd) * D + li * EPL) * EB);
-    unpack16<DT>(qr, qf);
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) qf[e] *= scale;
-  }
-  const size_t head_off = ((size_t)slot * nh + hd) * Smax * D * EB + (size_t)li * 16;
-  const char* kb = (const char*)kc + head_off;
-  const char* vb = (const char*)vc + head_off;
-
-  float m = -INFINITY, l = 0.f, o[EPL];
-#pragma unroll
-  for (int e = 0; e < EPL; ++e) o[e] = 0.f;
-
-  // Two register buffers: the loads of the next RPW*U rows are in flight while the current ones are consumed.
-  u32x4_t krA[U], vrA[U], krB[U], vrB[U];
-  auto load = [&](u32x4_t* kr, u32x4_t* vr, int jb) {
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int r = min(jb + u * RPW + grp, j1 - 1);      // clamp: stays inside the request's valid rows
-      kr[u] = __builtin_nontemporal_load((const u32x4_t*)(kb + (size_t)r * D * EB));
-      vr[u] = __builtin_nontemporal_load((const u32x4_t*)(vb + (size_t)r * D * EB));
-    }
-  };
-  auto consume = [&](const u32x4_t* kr, const u32x4_t* vr, int jb) {
-    float s[U];
-    float tmax = -INFINITY;
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      float kf[EPL];
-      unpack16<DT>(kr[u], kf);
-      float d0 = 0.f;
-#pragma unroll
-      for (int e = 0; e < EPL; ++e) d0 = fmaf(qf[e], kf[e], d0);
-      d0 = group_sum<LPR>(d0);
-      s[u] = (jb + u * RPW + grp < j1) ? d0 : -INFINITY;
-      tmax = fmaxf(tmax, s[u]);
-    }
-    const float mn = fmaxf(m, tmax);
-    const float ms = (mn == -INFINITY) ? 0.f : mn;       // a group that has seen no valid row yet
-    const float alpha = __expf(m - ms);                  // m = -inf -> 0
-    l *= alpha;
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) o[e] *= alpha;
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const float p = __expf(s[u] - ms);
-      l += p;
-      float vf[EPL];
-      unpack16<DT>(vr[u], vf);
-#pragma unroll
-      for (int e = 0; e < EPL; ++e) o[e] = fmaf(p, vf[e], o[e]);
-    }
-    m = mn;
-  };
-  constexpr int STEP = RPW * U;
-  load(krA, vrA, j0);
-  int jb = j0;
-  // Steady state without branches (the compiler's wait counts for the in-order memory counter collapse to "wait for
-  // everything" around a branch, which would make consuming one buffer wait for the other's loads too); the loads
-  // past the chunk re-read its last row.
-  for (; jb + 2 * STEP <= j1; jb += 2 * STEP) {
-    load(krB, vrB, jb + STEP);
-    __builtin_amdgcn_sched_barrier(0);
-    consume(krA, vrA, jb);
-    load(krA, vrA, jb + 2 * STEP);
-    __builtin_amdgcn_sched_barrier(0);
-    consume(krB, vrB, jb + STEP);
-  }
-  if (jb < j1) {                                           // one or two steps left (wave-uniform)
-    const bool two = jb + STEP < j1;
-    if (two) load(krB, vrB, jb + STEP);
-    consume(krA, vrA, jb);
-    if (two) consume(krB, vrB, jb + STEP);
-  }
-  // merge the RPW lane groups (lanes with equal li): butterfly over the group index bits
-  if constexpr (RPW > 1) {
-    float mt = m;
-#pragma unroll
-    for (int dlt = LPR; dlt < 64; dlt <<= 1) mt = max_over(mt, dlt);
-    const float w = (m == -INFINITY) ? 0.f : __expf(m - mt);
-    l *= w;
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) o[e] *= w;
-#pragma unroll
-    for (int dlt = LPR; dlt < 64; dlt <<= 1) {
-      l = sum_over(l, dlt);
-#pragma unroll
-      for (int e = 0; e < EPL; ++e) o[e] = sum_over(o[e], dlt);
-    }
-    m = mt;
-  }
-  if (grp != 0) return;
+  Wave w;
+  w.query(*(const u32x4_t*)((const char*)q + ((size_t)(row * nh + hd) * D + li * EPL) * Wave::EB), scale);
+  w.start(kc, vc, ((size_t)slot * nh + hd) * Smax * D * Wave::EB, j1, lane);
+  u32x4_t krA[U], vrA[U];
+  w.load(krA, vrA, j0);
+  w.rows(krA, vrA, j0);
+  w.merge_groups();
+  const float m = w.m, l = w.l;
+  const float(&o)[EPL] = w.o;
+  if (w.grp != 0) return;
   if constexpr (ONE) {
 #pragma unroll
     for (int e = 0; e < EPL; e += 4) {
@@ -209,6 +250,71 @@ __global__ __launch_bounds__(256) void attn_partial_kernel(const void* __restric
       pml[pi * 2 + 1] = l;
     }
   }
+}
+
+// A block per (row, head), a wave per chunk, the chunks merged through LDS: one launch, no partial results in memory.  grid = (n_head, M), a
+// row's heads side by side, block = 64 * the most chunks of a row, kRowWaves waves at most (a wave then takes every kRowWaves-th chunk);
+// waves without a chunk end at once, before the barrier, which waits for the others only.  blockIdx.y counts src,
+// the longest row first, so that the launch does not end with the long rows: rows of up to 1900 positions in any order -> that order, 32 heads,
+// bf16, us: 101 rows 240 -> 234 (caches of 2048 positions, whose heads lie 512 KB apart: 266 -> 243), 64 rows 157 -> 151, 24 rows 67 -> 62.
+// 256 rows of up to 4096 positions 1253 us (6.85 TB/s); 1386 in two launches.  Streaming and merging are those of the other two kernels, in the same order: the same bits.
+constexpr int kRowWaves = 8, kRowChunks = 16;
+template <int DT, int D, int U, class Src>
+__global__ __launch_bounds__(64 * kRowWaves) void attn_row_kernel(const void* __restrict__ q, const void* __restrict__ kc,
+                                                                  const void* __restrict__ vc, Src src, int nh, int Smax, float scale,
+                                                                  void* __restrict__ out, int mtt) {
+  typedef AttnWave<DT, D, U> Wave;
+  constexpr int EPL = Wave::EPL, LPR = Wave::LPR;
+  __shared__ __attribute__((aligned(16))) float part[kRowChunks][D + 4];       // [chunk]: o, m, l
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int hd = blockIdx.x, li = lane % LPR;
+  const int4 it = src.at(blockIdx.y);
+  const int row = it.x, slot = it.z, len = it.w;
+  const int nch = chunks_of(len);
+  if (wave >= nch) return;
+  const int cr = (len + nch - 1) / nch;                       // chunks of equal length, as in attn_partial_kernel
+  Wave w;
+  w.query(*(const u32x4_t*)((const char*)q + ((size_t)(row * nh + hd) * D + li * EPL) * Wave::EB), scale);
+  for (int c = wave; c < nch; c += kRowWaves) {
+    w.start(kc, vc, ((size_t)slot * nh + hd) * Smax * D * Wave::EB, min(len, (c + 1) * cr), lane);
+    u32x4_t krA[U], vrA[U];
+    w.load(krA, vrA, c * cr);
+    w.rows(krA, vrA, c * cr);
+    w.merge_groups();
+    if (nch == 1) break;
+    if (w.grp == 0) {
+#pragma unroll
+      for (int e = 0; e < EPL; ++e) part[c][li * EPL + e] = w.o[e];
+      if (li == 0) {
+        part[c][D] = w.m;
+        part[c][D + 1] = w.l;
+      }
+    }
+  }
+  if (nch == 1) {
+    if (w.grp != 0) return;
+#pragma unroll
+    for (int e = 0; e < EPL; e += 4) {
+      const f32x4_t v = f32x4_t{w.o[e], w.o[e + 1], w.o[e + 2], w.o[e + 3]} + 0.f;
+      stv4<DT>(out, xrow_index(row, hd * D + li * EPL + e, nh * D, mtt), v / w.l);
+    }
+    return;
+  }
+  __syncthreads();                                            // of the waves that have a chunk
+  if (wave > 0 || lane >= D / 4) return;
+  float m[kRowChunks];
+  float top = -INFINITY, l = 0.f;
+#pragma unroll
+  for (int c = 0; c < kRowChunks; ++c)
+    if (c < nch) {
+      m[c] = part[c][D];
+      top = fmaxf(top, m[c]);
+    }
+  f32x4_t o = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int c = 0; c < kRowChunks; ++c)
+    if (c < nch) add_chunk(l, o, __expf(m[c] - top), part[c][D + 1], ld4(&part[c][lane * 4]));
+  stv4<DT>(out, xrow_index(row, hd * D + lane * 4, nh * D, mtt), o / l);
 }
 
 // grid = (M, ceil(n_head / HPB)), block = 256: merges a row's chunks in chunk order, normalises, rounds to dtype.  A
@@ -247,9 +353,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const float* __restrict
 #pragma unroll
   for (int j = 0; j < FIRST; ++j)
     if (j < nc) {
-      const float w = __expf(mc[j] - red_m);
-      l += w * lc[j];
-      o += w * oc[j];
+      add_chunk(l, o, __expf(mc[j] - red_m), lc[j], oc[j]);
     }
   for (int c0 = FIRST; c0 < nc; c0 += 4) {      // longer rows: 4 chunks at a time, loads first, arithmetic in chunk order
     float m2[4], l2[4];
@@ -265,9 +369,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const float* __restrict
 #pragma unroll
     for (int j = 0; j < 4; ++j)
       if (c0 + j < nc) {
-        const float w = __expf(m2[j] - red_m);
-        l += w * l2[j];
-        o += w * o2[j];
+        add_chunk(l, o, __expf(m2[j] - red_m), l2[j], o2[j]);
       }
   }
   stv4<DT>(out, xrow_index(row, hd * D + i, nh * D, mtt), o / l);
@@ -610,25 +712,79 @@ __global__ __launch_bounds__(256 * KP) __attribute__((amdgpu_waves_per_eu(2))) v
 
 // ---------------------------------------------------------------- host side
 
+constexpr int kGridY = 65535;      // the most blocks of a grid in y
+
+// Blocks of one wave, or of four.  A compute unit streams about 40 bytes per ns whatever it holds, so while waves are few each should have a
+// unit to itself, and beyond one block of four per unit a second one lands on some (waves 1024 -> 1056, 12 rows x 32 heads: 19 -> 30 us).
+// Graphs of calls, cold caches, bf16 unless stated, us, four -> one: one chunk per row 9 x 16 heads (fp32, 128 wide) of up to 200 16.4 -> 12.7,
+// 6 x 32 of 200 10.9 -> 9.7, 70 x 32 of 200 28.6 -> 24.3, 256 x 32 of 200 72.5 -> 70.1; two launches 12 x 32 of 1000 (1056 waves) 30.4 -> 25.8,
+// 6 x 52 of 700 (624) 17.2 -> 15.9, 24 x 16 (fp32) of 700 29.6 -> 28.0, 101 x 32 of 300 52 -> 46; level above 2000 waves.  800 to 1024 waves
+// fill the units evenly as blocks of four: 9 x 32 of 1000 (800) 19.6 -> 20.2, 23 x 16 of 1000 (944) 21.1 -> 21.7.
+static bool wave_blocks(const AttnWork& w, int nh) {
+  const long waves = (long)w.n_items * nh;
+  return !w.chunk_grid && (waves < 800 || waves > 1024) && w.n_items <= kGridY;
+}
+// Whether a block takes a whole (row, head), which saves the merge launch and the partial results but ties a row's chunks to one compute unit
+// and holds the wave slots of the longest row.  us, two launches (the better of the two block shapes) -> one, bf16, d = 128 unless stated:
+//   * up to two chunks, always: 9 rows x 32 heads of up to 300 13.7 -> 11.4, 32 x 32 19.5 -> 18.2, 101 x 32 46.1 -> 45.6, 256 x 32 110 -> 104;
+//   * up to 256 blocks and three chunks (four of short rows, d = 64): 6 x 32 of 700 14.4 -> 13.4, 16 x 16 of 800 15.5 -> 14.1, d = 64 9 x 12 of 1000
+//     10.1 -> 9.6; four chunks 6 x 32 of 1000 15.3 -> 16.1, eight 23 -> 27.3; more blocks, three chunks: 9 x 32 of 700 16.1 -> 20.2;
+//   * from 1024 blocks, where the units are full anyway: 32 x 32 of 1000 50.6 -> 49.9, of 4000 195 -> 189, 64 x 32 of 1000 93.6 -> 86.5, of 4000
+//     372 -> 331, 80 x 32 of 2000 219 -> 207, 64 x 16 of 2000 91.0 -> 85.9, 40 x 52 of 2000 185 -> 174, 101 x 12 (d = 64) of 2000 55.3 -> 52.0, 101 x 16
+//     (fp32, d = 64) of 2000 136 -> 130; below, rows decide: 24 x 32 of 2000 69.8 -> 67.7, of 700 29.1 -> 29.3, 16 x 52 of 2000 73.5 -> 76.7.
+// With a row's heads apart in the grid (all of a row's blocks on one XCD where the rows are a multiple of eight) 128 x 32 of 2000 took 353 instead of 322.
+bool attention_by_rows(int dtype, int d, const AttnWork& w, int M, int nh) {
+  const long blocks = (long)M * nh;
+  if (w.n_items == M || w.merge_last || w.most > kRowChunks || M > kGridY) return false;
+  return w.most <= 2 || (w.most <= (d * (dtype == DT_F32 ? 4 : 2) <= 128 ? 4 : 3) && blocks <= 256) || blocks >= 1024;
+}
+bool attention_merges(const AttnWork& w, int M) { return w.merge_last || (w.n_items != M && !w.by_rows); }
+// By steps of 64 positions: one pass to count, one to place.
+void longest_first(const int* len, int M, int* place) {
+  constexpr int kSteps = kRowChunks * kAttnChunk / 64 + 1;
+  auto step = [](int n) { return kSteps - 1 - std::min(kSteps - 1, n / 64); };
+  int at[kSteps + 1] = {};
+  for (int i = 0; i < M; ++i) ++at[step(len[i]) + 1];
+  for (int k = 0; k < kSteps; ++k) at[k + 1] += at[k];
+  for (int i = 0; i < M; ++i) place[i] = at[step(len[i])]++;
+}
 template <int DT, int D, class Src>
 static void launch_attn(const void* q, const void* kc, const void* vc, const AttnWork& w, const Src& src, int M, int nh, int Smax,
                         void* out, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
   const float scale = 1.0f / sqrtf((float)D);
-  const dim3 grid(w.n_items, nh / 4);
-  if (w.n_items == M && !w.merge_last) {        // one chunk per row
-    launch_timed(attn_partial_kernel<DT, D, 4, true, Src>, grid, dim3(256), st, ev0, ev1, q, kc, vc, src, nh, Smax, w.maxch,
-                 scale, w.pml, w.po, out, w.out_mtt);
-    return;
-  }
-  launch_timed(attn_partial_kernel<DT, D, 4, false, Src>, grid, dim3(256), st, ev0, ev1, q, kc, vc, src, nh, Smax, w.maxch, scale,
-               w.pml, w.po, out, w.out_mtt);
+  const bool one_chunk = w.n_items == M && !w.merge_last, single = wave_blocks(w, nh);
+  launch_timed(one_chunk ? attn_partial_kernel<DT, D, 4, true, Src> : attn_partial_kernel<DT, D, 4, false, Src>,
+               single ? dim3(nh, w.n_items) : dim3(w.n_items, nh / 4), dim3(single ? 64 : 256), st, ev0, ev1, q, kc, vc, src, nh,
+               single ? 1 : 0, Smax, w.maxch, scale, w.pml, w.po, out, w.out_mtt);
+  if (one_chunk) return;
   attn_merge_kernel<DT, D, Src><<<dim3(M, (nh * D + 1023) / 1024), 256, 0, st>>>(w.pml, w.po, src, w.maxch, nh, out, w.out_mtt);
+}
+template <int DT, int D, class Src>
+static void launch_rows(const void* q, const void* kc, const void* vc, const AttnWork& w, const Src& src, int M, int nh, int Smax,
+                        void* out, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
+  launch_timed(attn_row_kernel<DT, D, 4, Src>, dim3(nh, M), dim3(64 * std::min(w.most, kRowWaves)), st, ev0, ev1, q, kc, vc, src, nh,
+               Smax, 1.0f / sqrtf((float)D), out, w.out_mtt);
 }
 template <int DT, int D>
 static void launch_attn(const void* q, const void* kc, const void* vc, const AttnWork& w, int M, int nh, int Smax, void* out,
                         hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
-  if (w.rows) launch_attn<DT, D>(q, kc, vc, w, RowList{*w.rows, M}, M, nh, Smax, out, st, ev0, ev1);
-  else launch_attn<DT, D>(q, kc, vc, w, ItemList{w.items, w.row_len}, M, nh, Smax, out, st, ev0, ev1);
+  if (w.by_rows && w.rows) {
+    RowOrder o;
+    int place[kAttnRows];
+    longest_first(w.rows->len, M, place);
+    for (int i = 0; i < M; ++i) {
+      o.row[place[i]] = i;
+      o.r.slot[place[i]] = w.rows->slot[i];
+      o.r.len[place[i]] = w.rows->len[i];
+    }
+    launch_rows<DT, D>(q, kc, vc, w, o, M, nh, Smax, out, st, ev0, ev1);
+  } else if (w.by_rows) {
+    launch_rows<DT, D>(q, kc, vc, w, ItemList{w.items, w.row_len}, M, nh, Smax, out, st, ev0, ev1);
+  } else if (w.rows) {
+    launch_attn<DT, D>(q, kc, vc, w, RowList{*w.rows, M}, M, nh, Smax, out, st, ev0, ev1);
+  } else {
+    launch_attn<DT, D>(q, kc, vc, w, ItemList{w.items, w.row_len}, M, nh, Smax, out, st, ev0, ev1);
+  }
 }
 
 hipError_t decode_attention(int dtype, int d, const void* q, const void* kc, const void* vc, const AttnWork& w, int M,

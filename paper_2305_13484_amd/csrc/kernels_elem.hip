@@ -173,7 +173,7 @@ __global__ __launch_bounds__(1024 / VW) void embed_norm_kernel(const void* __res
   const int tk = row.tok, pos = row.pos, first = row.first;
   if (first >= 0) {
     const int nr = out.block_rows > 0 ? min(out.block_rows, (int)gridDim.x - m) : 1, len = pos + nr;
-    const int chunks = (len + kAttnChunk - 1) / kAttnChunk;
+    const int chunks = out.block_rows == kEntryPerRow ? 1 : (len + kAttnChunk - 1) / kAttnChunk;
     for (int c = tid; c < chunks; c += blockDim.x)
       out.list[first + c] = out.block_rows > 0 ? make_int4(m, nr, c, 0) : make_int4(m, c, row.slot, len);
   }

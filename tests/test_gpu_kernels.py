@@ -406,6 +406,31 @@ def test_attention_rows_by_argument_by_list_and_by_copy_give_the_same_bits(dtype
         assert torch.equal(part, full[lo:hi]), (lo, hi)
 
 
+@pytest.mark.parametrize("dtype,d,nh,M,hi", [
+    (synth.DT_BF16, 128, 4, 1, 257), (synth.DT_BF16, 128, 4, 64, 768), (synth.DT_BF16, 128, 4, 65, 768),      # three chunks, 256 and 260 blocks
+    (synth.DT_BF16, 128, 4, 64, 769), (synth.DT_F16, 64, 4, 64, 1024), (synth.DT_F16, 64, 4, 64, 1025),       # four and five chunks of short rows
+    (synth.DT_F32, 128, 4, 3, 700), (synth.DT_F32, 64, 4, 200, 512),
+    (synth.DT_F16, 64, 4, 199, 256), (synth.DT_F16, 64, 4, 200, 256), (synth.DT_F16, 64, 4, 256, 256),        # one chunk, 796 to 1024 waves
+    (synth.DT_BF16, 64, 16, 63, 2048), (synth.DT_BF16, 64, 16, 64, 2048), (synth.DT_BF16, 64, 16, 64, 2305),     # 1008 and 1024 blocks; nine
+    (synth.DT_BF16, 64, 16, 64, 4096), (synth.DT_F16, 64, 20, 52, 4097), (synth.DT_BF16, 64, 4, 300, 600)])   # sixteen and seventeen; a list
+def test_attention_has_the_same_bits_in_blocks_of_rows_of_chunks_and_of_heads(dtype, d, nh, M, hi):
+    """A block takes a (row, head) with all its chunks, one head of a chunk, or four heads of it with the merge in a launch of its own (what
+    the call that cannot allocate always does): either side of every edge between them, against the last."""
+    Cn = min(M, 16)
+    q, k, v, slots, lens = synth.attention_case(M + hi, Cn, Cn, nh, d, hi, dtype, 1, hi, device="cuda", fill="all")
+    rng = np.random.default_rng(M)
+    qd = torch.randn(M, nh, d, generator=torch.Generator().manual_seed(5)).to(TDT[dtype]).cuda()
+    slots, lens = rng.integers(0, Cn, size=M).astype(np.int32), rng.integers(1, hi + 1, size=M).astype(np.int32)
+    lens[0] = hi
+    got = fl.k_decode_attention(qd, k, v, slots, lens)
+    part = 40                                  # its scratch does not hold the partial results of many long rows
+    assert torch.equal(got, fl.k_decode_attention(qd, k, v, slots, lens))
+    for lo in range(0, M, part):
+        ref = fl.k_decode_attention_noalloc(qd[lo:lo + part].contiguous(), k, v, slots[lo:lo + part], lens[lo:lo + part],
+                                            torch.empty_like(qd[lo:lo + part]))
+        assert torch.equal(got[lo:lo + part], ref), lo
+
+
 @pytest.mark.parametrize("M,hi", [(6, 200), (6, 600), (300, 100)])
 def test_attention_output_may_share_memory_with_the_queries(M, hi):
     """The output over q itself and over its neighbouring rows, with and without second chunks, by argument and by list."""
