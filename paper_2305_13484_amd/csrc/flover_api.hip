@@ -1612,7 +1612,7 @@ extern "C" int32_t flover_k_gated_workspace_bytes(int32_t dtype, int32_t M, int3
   if (!p.paired) return fail(nullptr, FLOVER_E_INVAL, "shape not served by the fused gated kernels");
   // enough for either use of M rows: the iteration's two halves, or the slices a context pass of M rows takes
   const int slices = std::max(p.S, flk::context_plan(p, dtype, M, 16).S);
-  *out = M > flk::gated_fused_rows(p) ? align_up((size_t)slices * M * p.ldc * 4, 256) : 0;
+  *out = M > flk::gated_roomless_rows(p) ? align_up((size_t)slices * M * p.ldc * 4, 256) : 0;
   return FLOVER_OK;
 }
 
@@ -1629,7 +1629,7 @@ extern "C" int32_t flover_k_gated_mlp(int32_t dtype, const void* x, const void* 
   const size_t stride = (size_t)M * p.ldc;
   // a whole plan's iteration can do without room, if slowly; above 128 rows two slices' are asked for, as for the other iterations
   const bool whole = p.whole && p.tile < 0;
-  const bool one_launch = M <= flk::gated_fused_rows(p) ? whole || p.S == 2 : p.S == 1 && M > 128;
+  const bool one_launch = M <= flk::gated_roomless_rows(p) ? whole || p.S == 2 : p.S == 1 && M > 128;
   if (!one_launch && (!workspace || (size_t)(whole ? 2 : p.S) * stride * 4 > workspace_bytes))
     return fail(nullptr, FLOVER_E_NOMEM, "gated workspace too small");
   HIPCHK(nullptr, flk::gemm_gated(dtype, x, w_tiled, M, p, act, (float*)workspace, stride, 0, (hipStream_t)stream, nullptr, nullptr,

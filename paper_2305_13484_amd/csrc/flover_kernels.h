@@ -96,9 +96,18 @@ hipError_t gemm_sum(int dtype, const void* x, const void* w_tiled, int M, const 
 // are both row-major (xmtt == 0) or both in fragment order with xmtt row tiles per k-block; reads the rows gemm() reads.
 // part / slice_stride as for gemm(): used above gated_fused_rows(p) rows, where the contraction and the activation are
 // two launches (same result, bit for bit).
-// rows up to which gemm_gated() is one launch for this plan: 128, or 64 for a matrix whose 128-column blocks outnumber the
-// compute units (it takes 16-wave blocks, whose hand-over space in LDS ends at four row tiles)
-inline int gated_fused_rows(const GemmPlan& p) { return p.whole ? kWholeRows : (p.N / 2 / 16 + 3) / 4 > 256 ? 64 : 128; }
+// Groups of 32 columns that a block of gemm_gated() takes: as few as leave one block per compute unit, two at least; every block stages
+// all rows, so narrower blocks in a second round lose (11008 x 4096, 688 groups, us at 6 / 40 / 101 rows: four groups, 172 blocks, 29.9 / 34.7 / 48.1,
+// three, 230, 29.0 / 31.8 / 43.0, two, 344, 37.0 / 43.8 / 56.8).  Call included, four -> now: 6400 x 4096 (two) at 100 rows 55 -> 47, 17920 x 6656 (five;
+// eight before) at 10 / 50 rows 98 / 107 -> 88 / 92.  Beyond five groups per unit: eight, whose sixteen waves leave registers for 64 rows.
+inline int gated_groups(const GemmPlan& p) {
+  const int per_unit = (p.N / 2 / 16 + 255) / 256;
+  return per_unit <= 2 ? 2 : per_unit <= 5 ? per_unit : 8;
+}
+// rows up to which gemm_gated() is one launch for this plan, and up to which a caller of the operation may come without room for its two
+// halves (F > 16384 took two launches above 64 rows once; the size that callers are told stays)
+inline int gated_fused_rows(const GemmPlan& p) { return p.whole ? kWholeRows : gated_groups(p) > 5 ? 64 : 128; }
+inline int gated_roomless_rows(const GemmPlan& p) { return p.whole ? kWholeRows : p.N / 2 > 16384 ? 64 : 128; }
 // A whole plan is one launch at any row count (see the definition for row-major rows); part then is scratch of `room` bytes.
 hipError_t gemm_gated(int dtype, const void* x, const void* w_tiled, int M, const GemmPlan& p, void* act, float* part,
                       size_t slice_stride, int xmtt, hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr, size_t room = 0);

@@ -309,6 +309,24 @@ __global__ __launch_bounds__(64 * GPB * (NT / NTW)) void gemm16_lds_kernel(const
     }
 }
 
+// A wave that does nothing but bring the rows' operand to LDS, a chunk ahead of the waves that multiply; barriers as theirs.  It stores
+// a chunk into the buffer whose last fragments the others have read before the barrier behind them.
+template <typename Rows>
+__device__ __forceinline__ void stage_rows(const Rows& rows, u32x4_t* even, u32x4_t* odd, int kb0, int KC, int nchunks) {
+  u32x4_t r[Rows::FPW];
+  rows.load(r, kb0);
+  rows.store(even, r);
+  if (nchunks > 1) rows.load(r, kb0 + KC);
+  __syncthreads();
+  for (int c = 0; c < nchunks; ++c) {
+    if (c + 1 < nchunks) {
+      rows.store(c & 1 ? even : odd, r);
+      if (c + 2 < nchunks) rows.load(r, kb0 + (c + 2) * KC);
+    }
+    __syncthreads();
+  }
+}
+
 // ---- gated MLP input (fused iterations of 16-bit gated models): the gate|up contraction with the activation as its
 // epilogue, so that neither partial sums nor the two projections reach memory and the activation needs no launch.
 // The matrix is laid out in "paired" groups of 32 columns -- group j = [gate columns 16j..16j+15 | up columns
@@ -321,22 +339,38 @@ __global__ __launch_bounds__(64 * GPB * (NT / NTW)) void gemm16_lds_kernel(const
 // bit, to gemm() with the halves as two K slices followed by the stand-alone activation.
 // Every chunk is full and the last ring turn is the only one whose chunks may lack a successor, so the steady state
 // is free of branches.  Requires KB % 16 == 0.
-template <int DT, int MT, int KC, int PF, int GPB = 4>
-__global__ __launch_bounds__(128 * GPB) void gated_lds_kernel(const uint16_t* __restrict__ x, const u32x4_t* __restrict__ wt,
+// P > 0: P further waves per half copy the rows' operand, so that the others wait for weights alone, in the order in which they asked for
+// them, and read a k-block's fragments from LDS while the one before it is multiplied (the barrier between two chunks comes ahead of the last
+// k-block's products); without, all waves read LDS, then all multiply, between the same two barriers.  11008 x 4096, bf16, blocks of three
+// groups, us without -> with copying waves -> and with fragments read ahead: 23 rows 30.6 -> 31.0 -> 30.4, 40 rows 32.0 -> 32.5 -> 30.7, 70 rows
+// 36.0 -> 34.4 -> 33.4, 101 rows 43.0 -> 42.2 -> 40.8, 120 rows 48.1 -> 46.9 -> 46.0.  The memory (29 us at 6 rows: 6.2 TB/s) and, from 65 rows on, the
+// products, 2.5 us per row tile, bound it; two rings as deep, or twice the copying waves, change nothing.  The same in gemm16_lds_kernel, whose
+// waves read a fragment for one or two products only, gained nothing (12288 x 4096 at 70 / 101 rows 22.1 / 25.9 -> 21.9 / 24.9, 50257 x 2048 39.9 -> 40.6).
+template <int DT, int MT, int KC, int PF, int GPB, int P>
+__global__ __launch_bounds__(128 * (GPB + P)) void gated_lds_kernel(const uint16_t* __restrict__ x, const u32x4_t* __restrict__ wt,
                                                         void* __restrict__ act, int M, int F, int ngroups, int KB,
                                                         int xmtt) {
-  static_assert(PF % KC == 0 && KC >= 2, "ring shape; the hand-over below reuses the x tiles' LDS");
-  // GPB column groups per block (32 columns each) = waves that stage one half's x tile
-  __shared__ u32x4_t lds[2][2][KC * MT * 64];    // [half][buffer]
-  typedef ChunkRows<KC, MT, GPB> Rows;
+  static_assert(PF % KC == 0, "ring shape");
+  // GPB column groups per block (32 columns each); without copying waves the GPB waves of a half stage its x tile
+  constexpr int TILE = KC * MT * 64;             // a half's x tile
+  __shared__ u32x4_t lds[4 * TILE > GPB * MT * 128 ? 4 * TILE : GPB * MT * 128];    // [half][buffer] tiles, then the hand-over
+  typedef ChunkRows<KC, MT, (P > 0 ? P : GPB)> Rows;
   constexpr int CPR = PF / KC;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int half = wave / GPB, gw = wave % GPB;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const bool stages = P > 0 && wave >= 2 * GPB;
+  const int half = stages ? (wave - 2 * GPB) / (P > 0 ? P : 1) : wave / GPB, gw = wave % GPB;
   const int g = blockIdx.x * GPB + gw;
   const int gl = min(g, ngroups - 1);            // surplus waves repeat the last group (they still serve the barriers)
   const int K = KB * 32;
   const int kb0 = half * (KB >> 1), kb1 = kb0 + (KB >> 1);
   const int nchunks = (kb1 - kb0) / KC;
+  if constexpr (P > 0) {
+    if (stages) {
+      stage_rows<Rows>(Rows(x, M, K, kb1, xmtt, (wave - 2 * GPB) % P, lane), lds + half * 2 * TILE, lds + half * 2 * TILE + TILE, kb0, KC, nchunks);
+      __syncthreads();                           // the hand-over
+      return;
+    }
+  }
 
   f32x4_t acc[MT][2];
 #pragma unroll
@@ -355,35 +389,49 @@ __global__ __launch_bounds__(128 * GPB) void gated_lds_kernel(const uint16_t* __
 #pragma unroll
     for (int t = 0; t < 2; ++t) bq[j][t] = __builtin_nontemporal_load(wp + ((size_t)(kb0 + j) * 2 + t) * 64);
   auto load_a = [&](int chunk) { rows.load(areg, kb0 + chunk * KC); };
-  auto store_a = [&](int buf) { rows.store(lds[half][buf], areg); };
-  load_a(0);
-  store_a(0);
+  auto store_a = [&](int buf) { rows.store(lds + (half * 2 + buf) * TILE, areg); };
+  if constexpr (P == 0) {
+    load_a(0);
+    store_a(0);
+  }
   __syncthreads();
+  u32x4_t af[P > 0 ? 2 : 1][MT];
+  auto fragments = [&](u32x4_t (&f)[MT], const u32x4_t* la, int kc) {
+#pragma unroll
+    for (int i = 0; i < MT; ++i) f[i] = la[(kc * MT + i) * 64 + at[kc & 1]];
+  };
+  if constexpr (P > 0) fragments(af[0], lds + half * 2 * TILE, 0);
   // One chunk: stage the next x tile, multiply this one, refill the W ring.
   auto chunk = [&](auto cc_, auto last_, int c) {
     constexpr int cc = decltype(cc_)::value;
     constexpr bool last = decltype(last_)::value;
-    const bool more = !last || c + 1 < nchunks;
+    const bool more = P == 0 && (!last || c + 1 < nchunks);
     if (more) load_a(c + 1);
     __builtin_amdgcn_sched_barrier(0);
-    const u32x4_t* la = lds[half][c & 1];
+    const u32x4_t* la = lds + (half * 2 + (c & 1)) * TILE;
 #pragma unroll
     for (int kc = 0; kc < KC; ++kc) {
-      const int kb = kb0 + c * KC + kc;
-      u32x4_t af[MT];
-#pragma unroll
-      for (int i = 0; i < MT; ++i) af[i] = la[(kc * MT + i) * 64 + at[kc & 1]];
+      const int kb = kb0 + c * KC + kc, now = P > 0 ? (cc * KC + kc) & 1 : 0;
+      if constexpr (P == 0) {
+        fragments(af[0], la, kc);
+      } else if (kc + 1 < KC) {
+        fragments(af[now ^ 1], la, kc + 1);
+      } else {
+        __syncthreads();
+        if (!last || c + 1 < nchunks) fragments(af[now ^ 1], lds + (half * 2 + ((c + 1) & 1)) * TILE, 0);
+      }
+      if constexpr (P > 0) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int i = 0; i < MT; ++i)
 #pragma unroll
-        for (int t = 0; t < 2; ++t) acc[i][t] = mfma16<DT>(bq[cc * KC + kc][t], af[i], acc[i][t]);
+        for (int t = 0; t < 2; ++t) acc[i][t] = mfma16<DT>(bq[cc * KC + kc][t], af[now][i], acc[i][t]);
       const int kk = min(kb + PF, kb1 - 1);      // the last turn re-reads the last block (in bounds, unused)
 #pragma unroll
       for (int t = 0; t < 2; ++t) bq[cc * KC + kc][t] = __builtin_nontemporal_load(wp + ((size_t)kk * 2 + t) * 64);
       __builtin_amdgcn_sched_barrier(0);
     }
     if (more) store_a((c + 1) & 1);
-    __syncthreads();
+    if constexpr (P == 0) __syncthreads();
   };
   auto ring_turn = [&](auto last_, int c) {
     static_assert(CPR <= 4, "chunks per ring turn");
@@ -396,8 +444,7 @@ __global__ __launch_bounds__(128 * GPB) void gated_lds_kernel(const uint16_t* __
   for (; c + CPR < nchunks; c += CPR) ring_turn(std::false_type{}, c);
   ring_turn(std::true_type{}, c);
   // second half -> first half through LDS (the x tiles are no longer read: every wave is past the last barrier)
-  f32x4_t* red = (f32x4_t*)&lds[0][0][0];
-  static_assert(sizeof(lds) >= (size_t)GPB * MT * 2 * 64 * sizeof(f32x4_t), "hand-over space");
+  f32x4_t* red = (f32x4_t*)lds;
   if (half == 1) {
 #pragma unroll
     for (int i = 0; i < MT; ++i)
@@ -1665,31 +1712,43 @@ static void dispatch16(const void* x, const void* wt, float* part, int M, const 
   }
 }
 
-template <int DT>
-static void dispatch_gated(const void* x, const void* wt, void* act, int M, const GemmPlan& p, int xmtt, hipStream_t st,
-                           hipEvent_t ev0, hipEvent_t ev1) {
-  const int F = p.N / 2, ngroups = F / 16, nx = (ngroups + 3) / 4;
-  const uint16_t* xx = (const uint16_t*)x;
-  const u32x4_t* ww = (const u32x4_t*)wt;
-  // chunks of 4 k-blocks at one row tile (half the barriers), of 2 above.  A matrix whose 128-column blocks outnumber
-  // the compute units (F > 16384; measured at the 30B shape, 280 blocks: 97 / 101 / 109 us at <= 16 / 17-32 / 33-64 rows
-  // against 86 / 87 / 101 for the wider blocks) takes 256-column blocks of 16 waves, half as many; at the 7B shape (172
-  // against 86 blocks) the 128-column blocks are 1.5x faster.
-  if (nx > 256) {
-    const dim3 g8((ngroups + 7) / 8), b16(1024);
-    if (M <= 16) launch_timed(gated_lds_kernel<DT, 1, 4, 8, 8>, g8, b16, st, ev0, ev1, xx, ww, act, M, F, ngroups, p.KB, xmtt);
-    else if (M <= 32) launch_timed(gated_lds_kernel<DT, 2, 4, 8, 8>, g8, b16, st, ev0, ev1, xx, ww, act, M, F, ngroups, p.KB, xmtt);
-    else launch_timed(gated_lds_kernel<DT, 4, 4, 4, 8>, g8, b16, st, ev0, ev1, xx, ww, act, M, F, ngroups, p.KB, xmtt);   // M <= 64
+template <int DT, int MT, int KC, int PF, int GPB, int P>
+static void launch_gated(const void* x, const void* wt, void* act, int M, const GemmPlan& p, int xmtt, hipStream_t st, hipEvent_t ev0,
+                         hipEvent_t ev1) {
+  const int F = p.N / 2, ngroups = F / 16;
+  launch_timed(gated_lds_kernel<DT, MT, KC, PF, GPB, P>, dim3((ngroups + GPB - 1) / GPB), dim3(128 * (GPB + P)), st, ev0, ev1, (const uint16_t*)x,
+               (const u32x4_t*)wt, act, M, F, ngroups, p.KB, xmtt);
+}
+// One variant per count of 16-row tiles; chunks of 4 k-blocks at one row tile (half the barriers), of 2 above.  P2: copying waves per half from two
+// tiles up, as many as fill the four SIMDs evenly; none where twelve waves leave too few registers for a second set of fragments (GPB 4 and 5 from
+// seven tiles up: 11008 x 4096 at 120 rows, GPB 4, 51 -> 72 us).  At GPB 5 the ring is 4 deep from three tiles on for the same reason.
+template <int DT, int GPB, int P2>
+static void dispatch_gated(const void* x, const void* wt, void* act, int M, const GemmPlan& p, int xmtt, hipStream_t st, hipEvent_t ev0,
+                           hipEvent_t ev1) {
+  constexpr int P7 = GPB <= 3 ? P2 : 0, RING = GPB <= 4 ? 8 : 4;
+  switch ((M + 15) / 16) {
+    case 1: return launch_gated<DT, 1, 4, 8, GPB, 0>(x, wt, act, M, p, xmtt, st, ev0, ev1);
+    case 2: return launch_gated<DT, 2, 2, 8, GPB, P2>(x, wt, act, M, p, xmtt, st, ev0, ev1);
+    case 3: return launch_gated<DT, 3, 2, RING, GPB, P2>(x, wt, act, M, p, xmtt, st, ev0, ev1);
+    case 4: return launch_gated<DT, 4, 2, RING, GPB, P2>(x, wt, act, M, p, xmtt, st, ev0, ev1);
+    case 5: return launch_gated<DT, 5, 2, 4, GPB, P2>(x, wt, act, M, p, xmtt, st, ev0, ev1);
+    case 6: return launch_gated<DT, 6, 2, 4, GPB, P2>(x, wt, act, M, p, xmtt, st, ev0, ev1);
+    case 7: return launch_gated<DT, 7, 2, 4, GPB, P7>(x, wt, act, M, p, xmtt, st, ev0, ev1);
+    default: return launch_gated<DT, 8, 2, 4, GPB, P7>(x, wt, act, M, p, xmtt, st, ev0, ev1);
   }
-  else if (M <= 16) launch_timed(gated_lds_kernel<DT, 1, 4, 8>, dim3(nx), dim3(512), st, ev0, ev1, xx, ww, act, M, F, ngroups, p.KB, xmtt);
-  else if (M <= 32) launch_timed(gated_lds_kernel<DT, 2, 2, 8>, dim3(nx), dim3(512), st, ev0, ev1, xx, ww, act, M, F, ngroups, p.KB, xmtt);
-  else switch ((M + 15) / 16) {     // M <= 128: one variant per count of 16-row tiles
-    case 3: launch_timed(gated_lds_kernel<DT, 3, 2, 8>, dim3(nx), dim3(512), st, ev0, ev1, xx, ww, act, M, F, ngroups, p.KB, xmtt); break;
-    case 4: launch_timed(gated_lds_kernel<DT, 4, 2, 8>, dim3(nx), dim3(512), st, ev0, ev1, xx, ww, act, M, F, ngroups, p.KB, xmtt); break;
-    case 5: launch_timed(gated_lds_kernel<DT, 5, 2, 4>, dim3(nx), dim3(512), st, ev0, ev1, xx, ww, act, M, F, ngroups, p.KB, xmtt); break;
-    case 6: launch_timed(gated_lds_kernel<DT, 6, 2, 4>, dim3(nx), dim3(512), st, ev0, ev1, xx, ww, act, M, F, ngroups, p.KB, xmtt); break;
-    case 7: launch_timed(gated_lds_kernel<DT, 7, 2, 4>, dim3(nx), dim3(512), st, ev0, ev1, xx, ww, act, M, F, ngroups, p.KB, xmtt); break;
-    default: launch_timed(gated_lds_kernel<DT, 8, 2, 4>, dim3(nx), dim3(512), st, ev0, ev1, xx, ww, act, M, F, ngroups, p.KB, xmtt);
+}
+template <int DT>
+static void dispatch_gated(const void* x, const void* wt, void* act, int M, const GemmPlan& p, int xmtt, hipStream_t st, hipEvent_t ev0,
+                           hipEvent_t ev1) {
+  switch (gated_groups(p)) {
+    case 2: return dispatch_gated<DT, 2, 2>(x, wt, act, M, p, xmtt, st, ev0, ev1);
+    case 3: return dispatch_gated<DT, 3, 1>(x, wt, act, M, p, xmtt, st, ev0, ev1);
+    case 4: return dispatch_gated<DT, 4, 2>(x, wt, act, M, p, xmtt, st, ev0, ev1);
+    case 5: return dispatch_gated<DT, 5, 1>(x, wt, act, M, p, xmtt, st, ev0, ev1);
+    default:                                     // M <= 64
+      if (M <= 16) return launch_gated<DT, 1, 4, 8, 8, 0>(x, wt, act, M, p, xmtt, st, ev0, ev1);
+      if (M <= 32) return launch_gated<DT, 2, 4, 8, 8, 0>(x, wt, act, M, p, xmtt, st, ev0, ev1);
+      return launch_gated<DT, 4, 4, 4, 8, 0>(x, wt, act, M, p, xmtt, st, ev0, ev1);
   }
 }
 
@@ -1703,8 +1762,8 @@ __global__ __launch_bounds__(256) void lay_rows_kernel(const uint16_t* __restric
 }
 
 // The iteration's plan, up to gated_fused_rows(p) rows: one launch.  Above that gemm() with the plan's K slices as partial sums and the
-// activation as its own launch -- the same chains, added in the same order, rounded once: bit-identical results (at 65-128 rows the x
-// tile of a 128-column block weighs as much as its weights; the one launch still measures 1.3 % faster per step there than the two).
+// activation as its own launch -- the same chains, added in the same order, rounded once: bit-identical results (the one
+// launch at 90 and 128 rows, call included: 17920 x 6656 139 -> 98 us, 17408 x 3072 93 -> 62).
 // A whole plan is one launch there too; rows of an operation-level call, which are row-major, make its copies slow (half a cache line
 // each, and none at all off the 16-byte grid), so with room for it
 //   * where the blocks are one round and K is long the two launches stay (us, two -> one: 2048 x 6656 at 129 / 512 / 1000 rows 17 / 29 / 40

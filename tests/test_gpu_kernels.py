@@ -328,9 +328,29 @@ def test_gated_mlp_full_size_sampled_columns(M, context):
     _gated_check(dtype, got[:, ci].cpu().double().numpy(), ref, slack)
 
 
+@pytest.mark.parametrize("dtype,F", [(synth.DT_BF16, 4128), (synth.DT_F16, 8192), (synth.DT_BF16, 8224), (synth.DT_F16, 12288), (synth.DT_BF16, 12320),
+                                     (synth.DT_F16, 16384), (synth.DT_BF16, 16416), (synth.DT_F16, 20480), (synth.DT_BF16, 20512)])
+def test_gated_mlp_blocks_of_every_width(dtype, F):
+    """First and last F of 2, 3, 4, 5 and 8 groups per block, the last block short or whole: sampled columns from the oracle, and at every
+    count of row tiles the bits of the two launches that 129 rows take."""
+    K = 512
+    g = torch.Generator(device="cuda").manual_seed(F)
+    x = torch.randn((129, K), generator=g, device="cuda").to(TDT[dtype])
+    Wg, Wu = [(torch.randn((F, K), generator=g, device="cuda") * 0.05).to(TDT[dtype]) for _ in range(2)]
+    gw = fl.binding.GatedWeight(Wg, Wu)
+    full = fl.k_gated_mlp(x, gw)
+    for M in (1, 16, 17, 33, 64, 65, 81, 97, 113, 128):
+        print("gated width", F, M, flush=True)
+        assert torch.equal(fl.k_gated_mlp(x[:M].contiguous(), gw), full[:M]), M
+    cols = np.concatenate([np.random.default_rng(F).choice(F, size=20, replace=False), [0, 16, F - 17, F - 1]])
+    ci = torch.as_tensor(cols, device="cuda").long()
+    ref, slack = _gated_reference(dtype, x[:48].cpu(), Wg[ci].cpu().contiguous(), Wu[ci].cpu().contiguous())
+    _gated_check(dtype, full[:48, ci].cpu().double().numpy(), ref, slack)
+
+
 def test_gated_mlp_at_the_30b_shape_sampled_columns_and_row_invariance():
-    """F = 17920, K = 6656: more 128-column blocks than compute units, so 33-64 rows take the 256-column blocks of 16
-    waves; sampled MLP columns from the oracle, and every row count gives the same bits for a row."""
+    """F = 17920, K = 6656, blocks of five groups: sampled MLP columns from the oracle, and every row count gives the same bits
+    for a row."""
     dtype, F, K = synth.DT_BF16, 17920, 6656
     g = torch.Generator(device="cuda").manual_seed(30)
     x = torch.randn((100, K), generator=g, device="cuda").to(TDT[dtype])
@@ -338,7 +358,7 @@ def test_gated_mlp_at_the_30b_shape_sampled_columns_and_row_invariance():
     Wu = (torch.randn((F, K), generator=g, device="cuda") * 0.02).to(TDT[dtype])
     gw = fl.binding.GatedWeight(Wg, Wu)
     full = fl.k_gated_mlp(x, gw)
-    for M in (8, 24, 48, 64, 65, 100):       # 65 and 100 rows: two launches at this shape
+    for M in (8, 24, 48, 64, 65, 100):
         print("gated 30b", M, flush=True)
         assert torch.equal(fl.k_gated_mlp(x[:M].contiguous(), gw), full[:M]), M
     cols = np.concatenate([np.random.default_rng(3).choice(F, size=20, replace=False), [0, 16, F - 1]])
