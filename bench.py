@@ -460,12 +460,12 @@ def main():
     att = prof["attention"]
     roof = None
     # the committed byte counters were taken on this workload (first 200 steps, see profiles/); not on the others
-    traffic = committed_traffic("attn_row_kernel") if (a.workload == "c4" and not a.layers and not a.requests) else None
+    traffic = committed_traffic("decode attention") if (a.workload == "c4" and not a.layers and not a.requests) else None
     # the counters' bytes per launch belong beside `achieved` only when this run covers the window they were taken on
     same_window = bool(traffic) and a.cached_context and a.steps == 200 and a.warmup == 0
     if att["launches"]:
         ach = att["bytes"] / (att["ms"] * 1e-3) / 1e9
-        roof = {"bound": "hbm", "kernel": "attn_row_kernel (ragged decode attention, one launch per layer)",
+        roof = {"bound": "hbm", "kernel": "attn_row_kernel or attn_partial_kernel (ragged decode attention, one streaming launch per layer)",
                 "achieved": round(ach, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(ach / HBM_PEAK_GBS, 4),
                 "traffic": traffic["bytes_per_launch"] if same_window else None,
                 "traffic_ratio": (traffic or {}).get("ratio"), "traffic_window": (traffic or {}).get("window"),

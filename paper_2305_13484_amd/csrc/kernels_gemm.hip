@@ -1348,7 +1348,7 @@ GemmPlan gemm_plan_gated(int dtype, int F, int K) {
   p.S = 2;               // the two halves of K: partial sums of gemm(), the two in-kernel chains of the fused kernels
   p.kbs = p.KB / 2;
   p.paired = 1;
-  // at any K: gated_lds_kernel has a quarter of the blocks there (F x K, us at 6 / 64 / 101 rows: 1376 x 512 4.9 / 7.9 / 10.2 -> 3.7 /
+  // at any K: gated_lds_kernel has half of the blocks there, a quarter when this was measured (F x K, us at 6 / 64 / 101 rows: 1376 x 512 4.9 / 7.9 / 10.2 -> 3.7 /
   // 4.6 / 6.4, 4096 x 1536 10.2 / 14.5 / 18.0 -> 6.4 / 8.6 / 11.8, 1024 x 6656 34.2 / 45.0 / 55.2 -> 14.0 / 22.7 / 31.9)
   if (whole_shape(dtype, 2 * F, K)) take_whole(p);
   return p;
