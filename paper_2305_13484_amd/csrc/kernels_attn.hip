@@ -732,11 +732,18 @@ static bool wave_blocks(const AttnWork& w, int nh) {
 //   * from 1024 blocks, where the units are full anyway: 32 x 32 of 1000 50.6 -> 49.9, of 4000 195 -> 189, 64 x 32 of 1000 93.6 -> 86.5, of 4000
 //     372 -> 331, 80 x 32 of 2000 219 -> 207, 64 x 16 of 2000 91.0 -> 85.9, 40 x 52 of 2000 185 -> 174, 101 x 12 (d = 64) of 2000 55.3 -> 52.0, 101 x 16
 //     (fp32, d = 64) of 2000 136 -> 130; below, rows decide: 24 x 32 of 2000 69.8 -> 67.7, of 700 29.1 -> 29.3, 16 x 52 of 2000 73.5 -> 76.7.
+//     There the longest row's blocks have to end with the rest: it has at most a unit's share of all chunks.  One row of 4096 among rows of up to
+//     100, 5.9 chunks a unit, 64 x 16 28.5 -> 46.1, (fp32) 70 x 16 41.1 -> 83.7, 64 x 32 (11.8) 44.8 -> 52.9; of up to 256, 40 x 32 (8.8) 43.8 -> 52.7;
+//     128 x 16, four of 4096 among 400 (15.0) 69.4 -> 75.3.  At the share and above: 40 x 32, one of 2048 among 700 (11.1 for 8) 53.9 -> 51.3, 64 x 32
+//     of 4096 (20.8 for 16) 102 -> 94, 128 x 32, four of 2048 among 400 (26) 103 -> 96; 250 x 32 (d = 64), one of 4096 among 100 (35) 41.7 -> 33.0.
+//     Of 160 length sets, uneven ones above all, the share loses most at 128 x 16, one of 4096 among 700 (16.5 for 16), 77.9 -> 82.0, and forgoes most
+//     at 40 x 32, four of 4096 among 400 (13.5), 71.6 -> 65.1.
 // With a row's heads apart in the grid (all of a row's blocks on one XCD where the rows are a multiple of eight) 128 x 32 of 2000 took 353 instead of 322.
 bool attention_by_rows(int dtype, int d, const AttnWork& w, int M, int nh) {
   const long blocks = (long)M * nh;
   if (w.n_items == M || w.merge_last || w.most > kRowChunks || M > kGridY) return false;
-  return w.most <= 2 || (w.most <= (d * (dtype == DT_F32 ? 4 : 2) <= 128 ? 4 : 3) && blocks <= 256) || blocks >= 1024;
+  if (w.most <= 2 || (w.most <= (d * (dtype == DT_F32 ? 4 : 2) <= 128 ? 4 : 3) && blocks <= 256)) return true;
+  return blocks >= 1024 && (long)w.n_items * nh >= (long)w.most * 256;
 }
 bool attention_merges(const AttnWork& w, int M) { return w.merge_last || (w.n_items != M && !w.by_rows); }
 // By steps of 64 positions: one pass to count, one to place.

@@ -111,3 +111,26 @@ def test_noalloc_attention_launches_one_block_row_per_chunk(fl, M, hi):
     assert grids[0] == (chunks, nh // 4, 1)
     assert len(grids) == (1 if chunks == M else 2)
     assert torch.equal(fl.k_decode_attention_noalloc(qd, kd, vd, slots, lens, out), ref)
+
+
+@pytest.mark.parametrize("M,nh,long,rest,one_launch", [
+    (64, 16, [4096], 100, False), (64, 16, [2048], 256, False),                  # 5.9 chunks a unit for 16, 4.9 for 8
+    (64, 16, [1024, 600], 256, True), (64, 16, [1152, 600], 256, False),         # 69 chunks, 4.3 a unit, for 4 and for 5
+    (64, 16, [769] * 64, 256, True), (128, 16, [2048], 100, True)])              # alike; 8.9 for 8
+def test_a_block_takes_a_whole_row_only_while_the_longest_ends_with_the_rest(fl, M, nh, long, rest, one_launch):
+    """1024 and more (row, head) blocks: one launch while the longest row has at most a compute unit's share of all chunks, else its chunks
+    go to units of their own and a merge follows; the same bits in both."""
+    d = 64
+    rng = np.random.default_rng(M + len(long))
+    q, k, v, slots, lens = synth.attention_case(M + len(long), M, M, nh, d, max(long), synth.DT_BF16, 1, rest, device="cuda", fill="all")
+    lens[rng.permutation(M)[:len(long)]] = long
+    out, ws = torch.empty_like(q), fl.binding.AttentionWorkspace(M, nh, d, max(long))
+    got = fl.k_decode_attention(q, k, v, slots, lens, out, ws).clone()
+    with torch.cuda.stream(torch.cuda.Stream()):
+        grids = _captured_grids(lambda: fl.k_decode_attention(q, k, v, slots, lens, out, ws))
+    assert (int(((lens + 255) // 256).sum()) * nh >= (max(long) + 255) // 256 * 256) == one_launch
+    assert len(grids) == (1 if one_launch else 2)
+    for lo in range(0, M, 32):                     # two launches, whatever the lengths
+        ref = fl.k_decode_attention_noalloc(q[lo:lo + 32].contiguous(), k, v, slots[lo:lo + 32], lens[lo:lo + 32],
+                                            torch.empty_like(q[lo:lo + 32]))
+        assert torch.equal(got[lo:lo + 32], ref), lo
