@@ -715,14 +715,21 @@ __global__ __launch_bounds__(256 * KP) __attribute__((amdgpu_waves_per_eu(2))) v
 constexpr int kGridY = 65535;      // the most blocks of a grid in y
 
 // Blocks of one wave, or of four.  A compute unit streams about 40 bytes per ns whatever it holds, so while waves are few each should have a
-// unit to itself, and beyond one block of four per unit a second one lands on some (waves 1024 -> 1056, 12 rows x 32 heads: 19 -> 30 us).
-// Graphs of calls, cold caches, bf16 unless stated, us, four -> one: one chunk per row 9 x 16 heads (fp32, 128 wide) of up to 200 16.4 -> 12.7,
-// 6 x 32 of 200 10.9 -> 9.7, 70 x 32 of 200 28.6 -> 24.3, 256 x 32 of 200 72.5 -> 70.1; two launches 12 x 32 of 1000 (1056 waves) 30.4 -> 25.8,
-// 6 x 52 of 700 (624) 17.2 -> 15.9, 24 x 16 (fp32) of 700 29.6 -> 28.0, 101 x 32 of 300 52 -> 46; level above 2000 waves.  800 to 1024 waves
-// fill the units evenly as blocks of four: 9 x 32 of 1000 (800) 19.6 -> 20.2, 23 x 16 of 1000 (944) 21.1 -> 21.7.
-static bool wave_blocks(const AttnWork& w, int nh) {
-  const long waves = (long)w.n_items * nh;
-  return !w.chunk_grid && (waves < 800 || waves > 1024) && w.n_items <= kGridY;
+// unit to itself, and a last round of blocks of four that is mostly empty leaves units idle beside full ones (waves 1024 -> 1056, 12 rows x 32
+// heads: 19 -> 30 us).  Where many rows of many chunks fill the units anyway, blocks of four lead (whether by their size or by the order of their
+// grid was not separated).  Graphs of calls, cold caches, rows of 1 to the stated positions, bf16, d = 128 unless stated, us, four -> one:
+//   * one chunk per row, always: 9 x 16 heads (fp32) of 200 16.4 -> 12.7, 6 x 32 10.9 -> 9.7, 28 x 32 (fp32) of 256 22.8 -> 17.5, 63 x 16 (fp32, d = 64)
+//     of 120 9.1 -> 8.2, 256 x 32 of 200 72.5 -> 70.1; level at 64 x 32 of 30 (fp32, d = 64 7.5 -> 8.0);
+//   * a last round (of 256 x 4 waves) that leaves the launch 1.3 times the places it needs, up to 787 waves for one: 9 x 32 of 700 (448 waves) 17.3 -> 15.9,
+//     6 x 52 of 700 (624) 17.2 -> 15.9, 23 x 16 of 1900 with short rows (592) 19.6 -> 18.5, 9 x 52 of 4096 (fp32, d = 64, 1248) 36.0 -> 31.5; loses most
+//     just inside, 3 x 52 of 1300 (fp32, d = 64, 780) 21.9 -> 23.9; fuller ones 9 x 32 of 1000 (800) 19.6 -> 20.2, 3 x 52 of 4096 (988) 30.5 -> 32.1;
+//   * more than one round and up to eight chunks, or rows of 512 bytes: 12 x 32 of 1000 (1056) 30.4 -> 25.8, 20 x 32 of 1900 (3424) 71.4 -> 68.9, 16 x 32
+//     (fp32) of 1000 54.8 -> 44.8, 100 x 32 (fp32), one of 6000 among 300, 161 -> 149; 6 x 52 of 1900 (1820) 38.5 -> 40.5.  With more chunks of shorter
+//     rows 16 x 32 (d = 64) of 8192 (8512) 100 -> 111, one of 8192 among 2000 51.1 -> 65.8, 30 x 52 (d = 64) of 8192 312 -> 339, 9 x 32 of 4096 68.0 -> 73.4.
+static bool wave_blocks(int row_bytes, const AttnWork& w, int M, int nh) {
+  if (w.chunk_grid || w.n_items > kGridY) return false;
+  const long waves = (long)w.n_items * nh, places = (waves + 1023) / 1024 * 1024;
+  return w.n_items == M || places * 10 >= waves * 13 || (waves > 1024 && (w.most <= 8 || row_bytes >= 512));
 }
 // Whether a block takes a whole (row, head), which saves the merge launch and the partial results but ties a row's chunks to one compute unit
 // and holds the wave slots of the longest row.  us, two launches (the better of the two block shapes) -> one, bf16, d = 128 unless stated:
@@ -736,8 +743,8 @@ static bool wave_blocks(const AttnWork& w, int nh) {
 //     100, 5.9 chunks a unit, 64 x 16 28.5 -> 46.1, (fp32) 70 x 16 41.1 -> 83.7, 64 x 32 (11.8) 44.8 -> 52.9; of up to 256, 40 x 32 (8.8) 43.8 -> 52.7;
 //     128 x 16, four of 4096 among 400 (15.0) 69.4 -> 75.3.  At the share and above: 40 x 32, one of 2048 among 700 (11.1 for 8) 53.9 -> 51.3, 64 x 32
 //     of 4096 (20.8 for 16) 102 -> 94, 128 x 32, four of 2048 among 400 (26) 103 -> 96; 250 x 32 (d = 64), one of 4096 among 100 (35) 41.7 -> 33.0.
-//     Of 160 length sets, uneven ones above all, the share loses most at 128 x 16, one of 4096 among 700 (16.5 for 16), 77.9 -> 82.0, and forgoes most
-//     at 40 x 32, four of 4096 among 400 (13.5), 71.6 -> 65.1.
+//     Of 300 length sets, uneven ones above all, the share loses most at 141 x 24, one of 3586 among 73 (15.8 for 15), 40.7 -> 45.6, and 128 x 16, one
+//     of 4096 among 700 (16.5 for 16), 77.9 -> 82.0, and forgoes most at 40 x 32, four of 4096 among 400 (13.5), 71.6 -> 65.1.
 // With a row's heads apart in the grid (all of a row's blocks on one XCD where the rows are a multiple of eight) 128 x 32 of 2000 took 353 instead of 322.
 bool attention_by_rows(int dtype, int d, const AttnWork& w, int M, int nh) {
   const long blocks = (long)M * nh;
@@ -759,7 +766,7 @@ template <int DT, int D, class Src>
 static void launch_attn(const void* q, const void* kc, const void* vc, const AttnWork& w, const Src& src, int M, int nh, int Smax,
                         void* out, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
   const float scale = 1.0f / sqrtf((float)D);
-  const bool one_chunk = w.n_items == M && !w.merge_last, single = wave_blocks(w, nh);
+  const bool one_chunk = w.n_items == M && !w.merge_last, single = wave_blocks(D * (DT == DT_F32 ? 4 : 2), w, M, nh);
   launch_timed(one_chunk ? attn_partial_kernel<DT, D, 4, true, Src> : attn_partial_kernel<DT, D, 4, false, Src>,
                single ? dim3(nh, w.n_items) : dim3(w.n_items, nh / 4), dim3(single ? 64 : 256), st, ev0, ev1, q, kc, vc, src, nh,
                single ? 1 : 0, Smax, w.maxch, scale, w.pml, w.po, out, w.out_mtt);

@@ -134,3 +134,32 @@ def test_a_block_takes_a_whole_row_only_while_the_longest_ends_with_the_rest(fl,
         ref = fl.k_decode_attention_noalloc(q[lo:lo + 32].contiguous(), k, v, slots[lo:lo + 32], lens[lo:lo + 32],
                                             torch.empty_like(q[lo:lo + 32]))
         assert torch.equal(got[lo:lo + 32], ref), lo
+
+
+@pytest.mark.parametrize("dtype,d,nh,chunks,one_wave", [
+    (synth.DT_F16, 64, 16, [1] * 60, True), (synth.DT_F32, 64, 4, [1] * 256, True),                             # one chunk per row: 960, 1024 waves
+    (synth.DT_F16, 64, 4, [4] * 47 + [8], True), (synth.DT_F16, 64, 4, [4] * 47 + [9], False),                  # 784 and 788 waves
+    (synth.DT_F16, 128, 16, [4] * 16, False), (synth.DT_F16, 128, 16, [4] * 15 + [5], True),                    # 1024 and 1040
+    (synth.DT_F16, 64, 16, [8] * 23, True), (synth.DT_F16, 64, 16, [8] * 22 + [9], False),                      # 2944 and 2960, of eight and of nine chunks
+    (synth.DT_F16, 64, 16, [9] * 16, True), (synth.DT_F16, 64, 12, [11] * 17 + [10], False),                    # 2304 and 2364: a last round of 1.3 times
+    (synth.DT_F32, 128, 4, [9] * 82, True), (synth.DT_BF16, 128, 4, [9] * 82, False),                           # 2952 waves, rows of 512 and of 256 bytes
+    (synth.DT_F16, 64, 8, [17] * 22, False)])
+def test_attention_blocks_of_one_wave_and_of_four_either_side_of_every_line(fl, dtype, d, nh, chunks, one_wave):
+    """The streaming kernel's grid is (heads, chunks) where a block is one wave, (chunks, heads / 4) where it has four; the same bits."""
+    M, most = len(chunks), max(chunks)
+    rng = np.random.default_rng(M)
+    Cn = min(M, 12)
+    q, k, v, _, _ = synth.attention_case(M + most, Cn, Cn, nh, d, 256 * most, dtype, 1, 1, device="cuda", fill="all")
+    q = torch.randn(M, nh, d, generator=torch.Generator().manual_seed(M)).to(q.dtype).cuda()
+    slots = rng.integers(0, Cn, size=M).astype(np.int32)
+    lens = (256 * np.array(chunks) - rng.integers(0, 256, size=M)).astype(np.int32)
+    out, ws = torch.empty_like(q), fl.binding.AttentionWorkspace(M, nh, d, 256 * most)
+    got = fl.k_decode_attention(q, k, v, slots, lens, out, ws).clone()
+    with torch.cuda.stream(torch.cuda.Stream()):
+        grids = _captured_grids(lambda: fl.k_decode_attention(q, k, v, slots, lens, out, ws))
+    assert grids[0] == ((nh, sum(chunks), 1) if one_wave else (sum(chunks), nh // 4, 1))
+    assert len(grids) == (1 if most == 1 else 2)
+    for lo in range(0, M, 20):                     # blocks of four, whatever the chunks
+        ref = fl.k_decode_attention_noalloc(q[lo:lo + 20].contiguous(), k, v, slots[lo:lo + 20], lens[lo:lo + 20],
+                                            torch.empty_like(q[lo:lo + 20]))
+        assert torch.equal(got[lo:lo + 20], ref), lo
