@@ -1311,13 +1311,10 @@ int32_t flover_k_decode_attention(int32_t dtype, const void* q, const void* kcac
     aw.n_items = attn_rows(slot, len, M, &rows);
     aw.rows = &rows;
     aw.by_rows = flk::attention_by_rows(dtype, d, aw, M, nh);
-  } else {                                  // slot[M] | len[M] and the (row, chunk, slot, len) work list
+  } else {                                  // the (row, chunk, slot, len) work list, and slot[M] | len[M] for the merge
     for (int i = 0; i < M; ++i) aw.n_items += (len[i] + flk::kAttnChunk - 1) / flk::kAttnChunk;
     aw.by_rows = flk::attention_by_rows(dtype, d, aw, M, nh);
-    hs.resize((size_t)2 * M);
     for (int i = 0; i < M; ++i) {
-      hs[i] = slot[i];
-      hs[M + i] = len[i];
       const int nc = aw.by_rows ? 0 : (len[i] + flk::kAttnChunk - 1) / flk::kAttnChunk;
       for (int ch = 0; ch < nc; ++ch) {
         items.push_back(i);
@@ -1338,7 +1335,11 @@ int32_t flover_k_decode_attention(int32_t dtype, const void* q, const void* kcac
         e[3] = len[i];
       }
     }
-    HIPCHK(nullptr, hipMemcpyAsync(ws, hs.data(), (size_t)2 * M * 4, hipMemcpyHostToDevice, st));
+    if (flk::attention_merges(aw, M)) {
+      hs.assign(slot, slot + M);
+      hs.insert(hs.end(), len, len + M);
+      HIPCHK(nullptr, hipMemcpyAsync(ws, hs.data(), (size_t)2 * M * 4, hipMemcpyHostToDevice, st));
+    }
     HIPCHK(nullptr, hipMemcpyAsync(ws + o_items, items.data(), items.size() * 4, hipMemcpyHostToDevice, st));
     HIPCHK(nullptr, hipStreamSynchronize(st));
   }

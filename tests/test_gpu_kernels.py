@@ -451,6 +451,24 @@ def test_attention_has_the_same_bits_in_blocks_of_rows_of_chunks_and_of_heads(dt
         assert torch.equal(got[lo:lo + part], ref), lo
 
 
+@pytest.mark.parametrize("hi,merges", [(200, False), (600, False), (4097, True)])
+def test_attention_of_a_list_copies_row_lengths_only_for_the_merge(hi, merges):
+    """More than 256 rows: slot | len go to the head of the workspace where a merge launch reads them, and nowhere else."""
+    M, nh, d = 300, 4, 64
+    q, k, v, _, _ = synth.attention_case(hi, 4, 4, nh, d, hi, synth.DT_BF16, 1, 1, device="cuda", fill="all")
+    q = torch.randn(M, nh, d, generator=torch.Generator().manual_seed(1)).to(torch.bfloat16).cuda()
+    rng = np.random.default_rng(hi)
+    slots, lens = rng.integers(0, 4, size=M).astype(np.int32), rng.integers(1, min(hi, 900) + 1, size=M).astype(np.int32)
+    lens[7] = hi
+    ws = fl.binding.AttentionWorkspace(M, nh, d, hi)
+    ws.buf.fill_(0x5a)
+    got = fl.k_decode_attention(q, k, v, slots, lens, workspace=ws)
+    head = ws.buf[:8 * M].cpu().numpy()
+    assert np.array_equal(head.view(np.int32), np.concatenate([slots, lens])) if merges else (head == 0x5a).all()
+    for lo in range(0, M, 60):
+        assert torch.equal(got[lo:lo + 60], fl.k_decode_attention(q[lo:lo + 60].contiguous(), k, v, slots[lo:lo + 60], lens[lo:lo + 60])), lo
+
+
 @pytest.mark.parametrize("M,hi", [(6, 200), (6, 600), (300, 100)])
 def test_attention_output_may_share_memory_with_the_queries(M, hi):
     """The output over q itself and over its neighbouring rows, with and without second chunks, by argument and by list."""
