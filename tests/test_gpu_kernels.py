@@ -328,12 +328,12 @@ def test_gated_mlp_full_size_sampled_columns(M, context):
     _gated_check(dtype, got[:, ci].cpu().double().numpy(), ref, slack)
 
 
-@pytest.mark.parametrize("dtype,F", [(synth.DT_BF16, 4128), (synth.DT_F16, 8192), (synth.DT_BF16, 8224), (synth.DT_F16, 12288), (synth.DT_BF16, 12320),
-                                     (synth.DT_F16, 16384), (synth.DT_BF16, 16416), (synth.DT_F16, 20480), (synth.DT_BF16, 20512)])
-def test_gated_mlp_blocks_of_every_width(dtype, F):
-    """First and last F of 2, 3, 4, 5 and 8 groups per block, the last block short or whole: sampled columns from the oracle, and at every
-    count of row tiles the bits of the two launches that 129 rows take."""
-    K = 512
+@pytest.mark.parametrize("dtype,F,K", [
+    (synth.DT_BF16, 4128, 2560), (synth.DT_F16, 8192, 512), (synth.DT_BF16, 8224, 1536), (synth.DT_F16, 12288, 512), (synth.DT_BF16, 12320, 2560),
+    (synth.DT_F16, 16384, 1536), (synth.DT_BF16, 16416, 2560), (synth.DT_F16, 20480, 512), (synth.DT_BF16, 20512, 1536)])
+def test_gated_mlp_blocks_of_every_width(dtype, F, K):
+    """First and last F of 2, 3, 4, 5 and 8 groups per block, the last block short or whole, K of one to five turns of the deepest weight
+    ring in a half: sampled columns from the oracle, and at every count of row tiles the bits of the two launches that 129 rows take."""
     g = torch.Generator(device="cuda").manual_seed(F)
     x = torch.randn((129, K), generator=g, device="cuda").to(TDT[dtype])
     Wg, Wu = [(torch.randn((F, K), generator=g, device="cuda") * 0.05).to(TDT[dtype]) for _ in range(2)]
