@@ -413,8 +413,8 @@ def test_attention_row_result_does_not_depend_on_other_rows():
 
 @pytest.mark.parametrize("dtype,d", [(synth.DT_BF16, 128), (synth.DT_F16, 64), (synth.DT_F32, 64)])
 def test_attention_rows_by_argument_by_list_and_by_copy_give_the_same_bits(dtype, d):
-    """300 rows take a work list copied from the host, 256 one built on the device, 20 come as a kernel argument, and rows
-    without a second chunk skip the merge: a row's result is the same in all of them."""
+    """300 rows come as a list copied from the host, 256 and fewer as a kernel argument; in both a block takes all chunks of a row.  20 rows
+    take a block per chunk and a merge, 16 without a second chunk no merge: a row's result is the same in all of them."""
     M, Cn, nh, S = 300, 301, 4, 1100
     q, k, v, slots, lens = synth.attention_case(31, M, Cn, nh, d, S, dtype, 1, S)
     lens[:4] = [1, 256, 257, S]
@@ -424,6 +424,24 @@ def test_attention_rows_by_argument_by_list_and_by_copy_give_the_same_bits(dtype
     for lo, hi in ((0, 256), (0, 20), (4, 20), (3, 4), (0, 1)):
         part = fl.k_decode_attention(qd[lo:hi].contiguous(), kd, vd, slots[lo:hi], lens[lo:hi])
         assert torch.equal(part, full[lo:hi]), (lo, hi)
+
+
+@pytest.mark.parametrize("dtype,d", [(synth.DT_BF16, 128), (synth.DT_F16, 64), (synth.DT_F32, 64)])
+def test_attention_chunks_by_argument_and_by_list_give_the_same_bits(dtype, d):
+    """A block per chunk and a merge: 256 rows of several chunks found by the argument's search (the call that cannot allocate), 300 from
+    a list copied from the host (one row is of 17 chunks), against a block that takes all chunks of a row."""
+    M, nh, S = 300, 4, 4400
+    q, k, v, _, _ = synth.attention_case(d, 8, 8, nh, d, S, dtype, 1, 1, device="cuda", fill="all")
+    q = torch.randn(M, nh, d, generator=torch.Generator().manual_seed(d)).to(TDT[dtype]).cuda()
+    rng = np.random.default_rng(d)
+    slots, lens = rng.integers(0, 8, size=M).astype(np.int32), rng.integers(1, 1101, size=M).astype(np.int32)
+    rows = fl.k_decode_attention(q, k, v, slots, lens)
+    lone = fl.k_decode_attention_noalloc(q[:256].contiguous(), k, v, slots[:256], lens[:256], torch.empty_like(q[:256]))
+    assert torch.equal(lone, rows[:256])
+    lens[290] = S
+    listed = fl.k_decode_attention(q, k, v, slots, lens)
+    assert torch.equal(listed[:290], rows[:290]) and torch.equal(listed[291:], rows[291:])
+    assert torch.equal(listed[290:291], fl.k_decode_attention(q[290:291].contiguous(), k, v, slots[290:291], lens[290:291]))
 
 
 @pytest.mark.parametrize("dtype,d,nh,M,hi", [
@@ -469,7 +487,7 @@ def test_attention_of_a_list_copies_row_lengths_only_for_the_merge(hi, merges):
         assert torch.equal(got[lo:lo + 60], fl.k_decode_attention(q[lo:lo + 60].contiguous(), k, v, slots[lo:lo + 60], lens[lo:lo + 60])), lo
 
 
-@pytest.mark.parametrize("M,hi", [(6, 200), (6, 600), (300, 100)])
+@pytest.mark.parametrize("M,hi", [(6, 200), (6, 600), (300, 100), (300, 600)])
 def test_attention_output_may_share_memory_with_the_queries(M, hi):
     """The output over q itself and over its neighbouring rows, with and without second chunks, by argument and by list."""
     dtype, nh, d = synth.DT_BF16, 4, 128
