@@ -327,15 +327,17 @@ int32_t flover_k_gemm(int32_t dtype, const void* x, const void* w_tiled, int32_t
  * flover_k_gated_mlp streams that copy.  x [device][M][K] row-major (any alignment; fastest at 16 bytes);
  * act [device][M][F] row-major, model dtype, apart from x.
  * context_pass == 0, the fused iteration: a row's result depends on that row of x alone, not on M.  Up to 128 rows (64
- * when F > 16384) it is one launch; above that its two halves of K go through `workspace` as partial sums and the
- * activation is a second launch, with the same result bit for bit.  Where F <= 4096 K is cut in four and one launch serves
- * more rows too; `workspace` then takes the rows in another order, or the four slices where that is shorter (with less
- * than flover_k_gated_workspace_bytes, but room for two slices, a slower way is taken).
+ * when F > 20480) it is one launch; above that its two halves of K go through `workspace` as partial sums and the
+ * activation is a second launch, with the same result bit for bit.  The room for them is asked for, and a call without it
+ * refused, above 64 rows from F > 16384 on: up to 128 rows and F = 20480 the one launch leaves it untouched.  Where
+ * F <= 4096 K is cut in four and one launch serves more rows too; `workspace` then takes the rows in another order, or the
+ * four slices where that is shorter (with less than flover_k_gated_workspace_bytes, but room for two slices, a slower way
+ * is taken).
  * context_pass != 0, the M rows of one request's pre-processing pass (Section V-B): up to 128 rows as in the iteration;
  * above that K is sliced by M as well, as flover_k_gemm_plan reports for context rows, and with one slice the activation
  * is the epilogue of the contraction, otherwise partial sums and a second launch.
- * workspace [device], flover_k_gated_workspace_bytes bytes (0 where one launch serves the fused iteration); NOMEM if
- * it is needed and smaller. */
+ * workspace [device], flover_k_gated_workspace_bytes bytes (0 up to 128 rows, up to 64 when F > 16384); NOMEM if it is
+ * asked for and smaller. */
 int32_t flover_k_gated_retile(int32_t dtype, const void* Wgate, const void* Wup, int32_t F, int32_t K, void* w_tiled,
                               void* stream);
 int32_t flover_k_gated_workspace_bytes(int32_t dtype, int32_t M, int32_t F, int32_t K, uint64_t* out);

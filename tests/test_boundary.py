@@ -123,8 +123,8 @@ def test_gemm_block_refuses_what_other_kernels_serve():
 
 
 def test_gated_mlp_workspace_sizes_host_only():
-    """Where the gated MLP input is one launch it needs no workspace: up to 128 rows, up to 64 where F > 16384; above
-    that the two K halves (or a context pass's slices) go through it."""
+    """The gated MLP input asks for no workspace up to 128 rows, up to 64 where F > 16384; above that for the two K halves (or a context
+    pass's slices), also where one launch of up to 128 rows leaves it untouched."""
     lib = fl.load_library()
     n = ctypes.c_uint64()
     for M in (1, 64, 128):
