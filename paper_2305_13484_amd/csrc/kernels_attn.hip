@@ -733,12 +733,15 @@ static bool wave_blocks(int row_bytes, const AttnWork& w, int M, int nh) {
 }
 // Whether a block takes a whole (row, head), which saves the merge launch and the partial results but ties a row's chunks to one compute unit
 // and holds the wave slots of the longest row.  us, two launches (the better of the two block shapes) -> one, bf16, d = 128 unless stated:
-//   * up to two chunks, always: 9 rows x 32 heads of up to 300 13.7 -> 11.4, 32 x 32 19.5 -> 18.2, 101 x 32 46.1 -> 45.6, 256 x 32 110 -> 104;
+//   * up to two chunks, always: 9 rows x 32 heads of up to 300 13.7 -> 11.4, 32 x 32 19.5 -> 18.2, 101 x 32 46.1 -> 45.6, 256 x 32 110 -> 104; 557 shapes,
+//     even and uneven, 0.86 of the time in the mean, 1.01 at most;
 //   * up to 256 blocks and three chunks (four of short rows, d = 64): 6 x 32 of 700 14.4 -> 13.4, 16 x 16 of 800 15.5 -> 14.1, d = 64 9 x 12 of 1000
 //     10.1 -> 9.6; four chunks 6 x 32 of 1000 15.3 -> 16.1, eight 23 -> 27.3; more blocks, three chunks: 9 x 32 of 700 16.1 -> 20.2;
+//     131 shapes of three chunks 0.88, at most 0.99, 32 of four chunks of short rows 0.89, at most 0.93, but 79 of four chunks of longer rows 1.03, up to 1.21;
 //   * from 1024 blocks, where the units are full anyway: 32 x 32 of 1000 50.6 -> 49.9, of 4000 195 -> 189, 64 x 32 of 1000 93.6 -> 86.5, of 4000
 //     372 -> 331, 80 x 32 of 2000 219 -> 207, 64 x 16 of 2000 91.0 -> 85.9, 40 x 52 of 2000 185 -> 174, 101 x 12 (d = 64) of 2000 55.3 -> 52.0, 101 x 16
-//     (fp32, d = 64) of 2000 136 -> 130; below, rows decide: 24 x 32 of 2000 69.8 -> 67.7, of 700 29.1 -> 29.3, 16 x 52 of 2000 73.5 -> 76.7.
+//     (fp32, d = 64) of 2000 136 -> 130; below, rows decide: 24 x 32 of 2000 69.8 -> 67.7, of 700 29.1 -> 29.3, 16 x 52 of 2000 73.5 -> 76.7
+//     (938 shapes of 257 to 1023 blocks 1.00, up to 1.79).
 //     There the longest row's blocks have to end with the rest: it has at most a unit's share of all chunks.  One row of 4096 among rows of up to
 //     100, 5.9 chunks a unit, 64 x 16 28.5 -> 46.1, (fp32) 70 x 16 41.1 -> 83.7, 64 x 32 (11.8) 44.8 -> 52.9; of up to 256, 40 x 32 (8.8) 43.8 -> 52.7;
 //     128 x 16, four of 4096 among 400 (15.0) 69.4 -> 75.3.  At the share and above: 40 x 32, one of 2048 among 700 (11.1 for 8) 53.9 -> 51.3, 64 x 32
