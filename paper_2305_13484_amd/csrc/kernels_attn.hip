@@ -742,7 +742,7 @@ static bool wave_blocks(int row_bytes, const AttnWork& w, int M, int nh) {
 //     372 -> 331, 80 x 32 of 2000 219 -> 207, 64 x 16 of 2000 91.0 -> 85.9, 40 x 52 of 2000 185 -> 174, 101 x 12 (d = 64) of 2000 55.3 -> 52.0, 101 x 16
 //     (fp32, d = 64) of 2000 136 -> 130; below, rows decide: 24 x 32 of 2000 69.8 -> 67.7, of 700 29.1 -> 29.3, 16 x 52 of 2000 73.5 -> 76.7
 //     (938 shapes of 257 to 1023 blocks 1.00, up to 1.79).
-//     There the longest row's blocks have to end with the rest: it has at most a unit's share of all chunks.  One row of 4096 among rows of up to
+//     From 1024 on the longest row has to end with the rest: at most a unit's share of all chunks.  One row of 4096 among rows of up to
 //     100, 5.9 chunks a unit, 64 x 16 28.5 -> 46.1, (fp32) 70 x 16 41.1 -> 83.7, 64 x 32 (11.8) 44.8 -> 52.9; of up to 256, 40 x 32 (8.8) 43.8 -> 52.7;
 //     128 x 16, four of 4096 among 400 (15.0) 69.4 -> 75.3.  At the share and above: 40 x 32, one of 2048 among 700 (11.1 for 8) 53.9 -> 51.3, 64 x 32
 //     of 4096 (20.8 for 16) 102 -> 94, 128 x 32, four of 2048 among 400 (26) 103 -> 96; 250 x 32 (d = 64), one of 4096 among 100 (35) 41.7 -> 33.0.
